@@ -200,6 +200,84 @@ int ray_batch(const porta_quad* q, const porta_options* o) {
 }
 
 // ---------------------------------------------------------------------------
+// How a plane step is cut into blocks
+// ---------------------------------------------------------------------------
+constexpr int kCus = 256;
+
+// Nodes per block of the plane kernels: the options' choice, else 256, fewer on planes
+// that fit in fewer wavefronts.
+int plane_block(const porta_grid* g, const porta_options* o) {
+  if (o && o->block > 0) return o->block;
+  const int64_t np = (int64_t)g->nx * g->ny;
+  return np >= 256 ? 256 : (int)((np + 63) / 64 * 64);
+}
+
+int64_t plane_tiles(const porta_grid* g, const porta_options* o) {
+  const int block = plane_block(g, o);
+  return ((int64_t)g->nx * g->ny + block - 1) / block;
+}
+
+// Frequency chunks of a launch of `blocks` blocks that would each hold every frequency.
+// Every chunk repeats the set-up of its nodes (kSetup updates' worth: 4 to 8 measured from
+// the cost of chunks on a full chip), so chunks pay only where CUs stay idle: the count
+// minimises (kSetup + frequencies per chunk) x blocks per CU, rounded up.  Time per plane
+// step with 1, 2, 3, 4, 6 chunks: FP64 16x16 nodes, 80 rays (80 blocks), 21 frequencies:
+// 22.5, 16.5, 15.8, 19.1, 18.3 us; FP32 32x32, 24 rays (96 blocks), 41 frequencies: 25.4,
+// 17.3, 19.2, 18.6, 19.5; FP64 32x32, 80 rays (320 blocks): 43.2, 43.0, 45.9, 51.7, 61.1;
+// FP64 64x64, 80 rays (1280 blocks): 213, 231, 250, 279, 319.
+int freq_chunks(int64_t blocks, int nfreq) {
+  constexpr int64_t kSetup = 6, kMaxChunks = 32;
+  int best = 1;
+  int64_t cost = 0;
+  for (int n = 1; n <= std::min<int64_t>(nfreq, kMaxChunks); ++n) {
+    const int64_t per = (nfreq + n - 1) / n;
+    if (n > 1 && per == (nfreq + n - 2) / (n - 1)) continue;   // no shorter chunk than n - 1
+    const int64_t c = (kSetup + per) * ((blocks * n + kCus - 1) / kCus);
+    if (n == 1 || c < cost) {
+      best = n;
+      cost = c;
+    }
+  }
+  return best;
+}
+
+// The cut of a sweep: whether the two hemispheres' batches share launches, and the
+// frequency chunks.  Sharing halves the number of dependent launches and fills each of
+// them; it takes the plane states of both batches, so it is for launches that leave
+// room on the chip (at most kShareBlocks blocks, about 8 per CU, from one hemisphere).
+struct SweepPlan {
+  int nrb;         // rays of a batch in one hemisphere
+  bool share;      // an upward and a downward batch per launch
+  int rows;        // rays whose states the workspace holds: nrb, or 2 nrb with share
+  size_t jrows;    // (ray, chunk) rows of partial sums the workspace holds
+};
+constexpr int64_t kShareBlocks = 2048;
+
+SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, const porta_options* o) {
+  SweepPlan P;
+  const int64_t tiles = plane_tiles(g, o);
+  // a launch is one row of at most 2^31 threads
+  P.nrb = (int)std::min<int64_t>(ray_batch(q, o), std::max<int64_t>(1, (1 << 23) / tiles));
+  P.share = tiles * P.nrb <= kShareBlocks;
+  P.rows = P.share ? 2 * P.nrb : P.nrb;
+  P.jrows = (size_t)P.rows * freq_chunks(tiles * P.rows, q->nfreq);
+  return P;
+}
+
+// The cut without sharing and chunks, which needs the least workspace.
+SweepPlan least_plan(const porta_grid* g, const porta_quad* q, const porta_options* o) {
+  const int nrb = sweep_plan(g, q, o).nrb;
+  return {nrb, false, nrb, (size_t)nrb};
+}
+
+// Chunks of a launch of `rays` rays (each chunk has a row of partial sums).
+int launch_chunks(const porta_grid* g, const porta_quad* q, const porta_options* o,
+                  const SweepPlan& P, int rays) {
+  const int n = freq_chunks(plane_tiles(g, o) * rays, q->nfreq);
+  return (int)std::max<size_t>(1, std::min<size_t>(n, P.jrows / std::max(rays, 1)));
+}
+
+// ---------------------------------------------------------------------------
 // Workspace layout (every region 256-byte aligned)
 // ---------------------------------------------------------------------------
 struct Layout {
@@ -238,18 +316,20 @@ Layout tables_layout(const porta_quad* q, int prec) {
   return L;
 }
 
-Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
+Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
+                    const SweepPlan& P) {
   Layout L = tables_layout(q, prec);
   const size_t np = (size_t)g->nx * g->ny;
-  const size_t nrb = (size_t)ray_batch(q, o);
-  const size_t state = nrb * q->nfreq * np * nstokes(o) * elem(prec);
+  const size_t nrb = (size_t)P.nrb;
+  const size_t state = (size_t)P.rows * q->nfreq * np * nstokes(o) * elem(prec);
   size_t off = L.end_tables;
   L.stateA = off;
   off = align_up(off + state);
   L.stateB = off;
   off = align_up(off + state);
   L.jpart = off;
-  off = align_up(off + 2 * nrb * 5 * np * sizeof(double));   // double-buffered partial sums
+  // double-buffered partial sums
+  off = align_up(off + 2 * P.jrows * (nstokes(o) + 1) * np * sizeof(double));
   if (faces_of(o)) {
     // per-chunk partial sums of the first-face kernel
     int lanes, fchunk;
@@ -372,6 +452,19 @@ int check_inputs(const porta_grid* g, const porta_fields* f, char* ws, const Lay
   return PORTA_OK;
 }
 
+int launch_jreduce(double* jkq, const double* jpart, const RayConsts* rays, int ray0, int nrb,
+                   int nchunk, int ns, int np, size_t N, size_t plane_off, double ibound,
+                   hipStream_t st) {
+  const dim3 grid(jblocks(np)), blk(256);
+  if (ns == 1)
+    hipLaunchKernelGGL(k_jreduce<1>, grid, blk, jlds_bytes(256), st, jkq, jpart, rays, ray0, nrb,
+                       nchunk, np, N, plane_off, ibound);
+  else
+    hipLaunchKernelGGL(k_jreduce<4>, grid, blk, jlds_bytes(256), st, jkq, jpart, rays, ray0, nrb,
+                       nchunk, np, N, plane_off, ibound);
+  return check_launch("jreduce");
+}
+
 // ---------------------------------------------------------------------------
 // Forward sweep with M and P on the first face crossed (options.faces = 1)
 // ---------------------------------------------------------------------------
@@ -391,7 +484,6 @@ int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_field
   double* jpart = reinterpret_cast<double*>(ws + L.jpart);
   double* jchunk = reinterpret_cast<double*>(ws + L.ck);
   const size_t lds = faces_lds_bytes<T>(q->nfreq, fchunk, lanes);
-  const dim3 rblk(256), rgrid((np + 255) / 256);
   // rays that meet an x face first read the fields with x and y exchanged
   T* tf = reinterpret_cast<T*>(ws + L.tf);
   {
@@ -416,9 +508,9 @@ int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_field
       const int ray0 = hemi * nh + r0;
       if (jkq) {
         // the boundary plane
-        hipLaunchKernelGGL(k_jreduce, rgrid, rblk, 0, st, jkq, (const double*)nullptr, rays,
-                           ray0, nrb, np, N, (size_t)kb * np, 1, (double)ibound);
-        if ((rc = check_launch("jreduce (boundary)"))) return rc;
+        if ((rc = launch_jreduce(jkq, nullptr, rays, ray0, nrb, 1, 4, np, N, (size_t)kb * np,
+                                 (double)ibound, st)))
+          return rc;
       }
       const T* prev = nullptr;
       for (int step = 1; step < nz; ++step) {
@@ -469,9 +561,9 @@ int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_field
                              (const double*)jchunk, rays, ray0, nchunk, nx, ny, nx / g->lx,
                              ny / g->ly);
           if ((rc = check_launch("sum_chunks"))) return rc;
-          hipLaunchKernelGGL(k_jreduce, rgrid, rblk, 0, st, jkq, (const double*)jpart, rays,
-                             ray0, nrb, np, N, (size_t)k * np, 0, 0.0);
-          if ((rc = check_launch("jreduce"))) return rc;
+          if ((rc = launch_jreduce(jkq, jpart, rays, ray0, nrb, 1, 4, np, N, (size_t)k * np, 0.0,
+                                   st)))
+            return rc;
         }
         prev = a.inext;
       }
@@ -483,107 +575,155 @@ int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_field
 // ---------------------------------------------------------------------------
 // Forward sweep
 // ---------------------------------------------------------------------------
+// The parts of a plane step's arguments that do not change from plane to plane.
+template <class T>
+PlaneArgs<T> plane_args(const porta_grid* g, const porta_quad* q, const porta_fields* f,
+                        const porta_options* o, char* ws, const Layout& L) {
+  PlaneArgs<T> a{};
+  a.kappa = static_cast<const T*>(f->kappa);
+  a.prop = static_cast<const T*>(f->propmat);
+  a.emis = static_cast<const T*>(f->emis);
+  a.rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
+  a.phi = reinterpret_cast<const T*>(ws + L.phiT);
+  a.wn = reinterpret_cast<const double*>(ws + L.wn);
+  a.nx = g->nx;
+  a.ny = g->ny;
+  a.np = g->nx * g->ny;
+  a.N = (size_t)a.np * g->nz;
+  a.nfreq = q->nfreq;
+  a.ntile = (int)plane_tiles(g, o);
+  a.inv_dx = g->nx / g->lx;
+  a.inv_dy = g->ny / g->ly;
+  a.xcd_remap = xcd_chunk(o);
+  a.parabolic = parabolic_of(o);
+  return a;
+}
+
+// Planes of O, M and P of a hemisphere's rays on their plane k (s = +-1 along the ray).
+template <class T>
+void set_plane(HemiArgs<T>& h, const porta_grid* g, int k, int s) {
+  const bool last = k + s < 0 || k + s >= g->nz;
+  h.kO = k;
+  h.kM = k - s;
+  h.kP = last ? -1 : k + s;
+  h.dzM = std::fabs(g->z[k] - g->z[k - s]);
+  h.dzP = last ? 0.0 : std::fabs(g->z[k + s] - g->z[k]);
+}
+
+template <class T>
+void set_chunks(PlaneArgs<T>& a, int nchunk, int rays) {
+  a.fchunk = (a.nfreq + nchunk - 1) / nchunk;
+  a.nchunk = (a.nfreq + a.fchunk - 1) / a.fchunk;
+  a.nstep = a.ntile * rays * a.nchunk;
+}
+
+template <class T>
+int launch_plane(const PlaneArgs<T>& a, int ns, int interp, int block, hipStream_t st) {
+  const size_t tab = (size_t)a.fchunk * (sizeof(double) + sizeof(T));
+  const size_t lds = a.njb ? std::max(tab, jlds_bytes(block)) : tab;
+  const dim3 grid(a.nstep + a.njb);
+  if (ns == 1)
+    hipLaunchKernelGGL(k_sweep_plane_i<T>, grid, dim3(block), lds, st, a);
+  else if (interp == PORTA_INTERP_BEZIER2D)
+    hipLaunchKernelGGL((k_sweep_plane<T, 1>), grid, dim3(block), lds, st, a);
+  else
+    hipLaunchKernelGGL((k_sweep_plane<T, 0>), grid, dim3(block), lds, st, a);
+  return check_launch("sweep_plane");
+}
+
 template <class T>
 int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, int interp,
                const porta_options* o, double* jkq, int accumulate, T* itop, T* ckpt, int C,
-               char* ws, const Layout& L, hipStream_t st) {
+               char* ws, const SweepPlan& P, const Layout& L, hipStream_t st) {
   int rc;
   if ((rc = prepare_tables<T>(ws, L, q, f->w2, st))) return rc;
-  const int nx = g->nx, ny = g->ny, nz = g->nz;
-  const int np = nx * ny;
+  const int nz = g->nz, np = g->nx * g->ny;
   const size_t N = (size_t)np * nz;
   if (jkq && !accumulate)
     if ((rc = fill(jkq, 10 * N, 0.0, st))) return rc;
   const int nh = q->nmu * q->nchi;
-  const int nrb_max = ray_batch(q, o);
   const int ns = nstokes(o);
-  const int block = (o && o->block > 0) ? o->block : 256;
+  const int block = plane_block(g, o);
   if (block % 64 != 0 || block > 256) return fail(PORTA_EINVAL, "block must be 64, 128, 192 or 256");
   const RayConsts* rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
-  const T* phiT = reinterpret_cast<const T*>(ws + L.phiT);
-  const double* wn = reinterpret_cast<const double*>(ws + L.wn);
   T* state[2] = {reinterpret_cast<T*>(ws + L.stateA), reinterpret_cast<T*>(ws + L.stateB)};
   if (faces_of(o))
-    return sweep_faces_impl<T>(g, q, f, o, jkq, itop, ws, L, rays, phiT, wn, state, st);
-  double* jpart[2] = {nullptr, nullptr};
-  if (jkq) {
-    jpart[0] = reinterpret_cast<double*>(ws + L.jpart);
-    jpart[1] = jpart[0] + (size_t)nrb_max * 5 * np;
-  }
-  const dim3 rblk(256), rgrid((np + 255) / 256);
+    return sweep_faces_impl<T>(g, q, f, o, jkq, itop, ws, L, rays,
+                               reinterpret_cast<const T*>(ws + L.phiT),
+                               reinterpret_cast<const double*>(ws + L.wn), state, st);
+  double* jpart[2] = {reinterpret_cast<double*>(ws + L.jpart), nullptr};
+  jpart[1] = jpart[0] + P.jrows * (ns + 1) * np;
 
-  for (int hemi = 0; hemi < 2; ++hemi) {
-    const bool up = (hemi == 0);
-    const int kb = up ? 0 : nz - 1, s = up ? 1 : -1;
-    const T ibound = up ? (T)f->i_bottom : T(0);
-    int lo, hi, up_lo, up_hi;
-    hemi_range(q, o, hemi, lo, hi);
-    hemi_range(q, o, 0, up_lo, up_hi);
-    for (int r0 = lo; r0 < hi; r0 += nrb_max) {
-      const int nrb = std::min(nrb_max, hi - r0);
-      const int ray0 = hemi * nh + r0;
-      const T* prev = nullptr;
-      for (int step = 1; step < nz; ++step) {
-        const int k = kb + s * step;
-        PlaneArgs<T> a;
-        a.kappa = static_cast<const T*>(f->kappa);
-        a.prop = static_cast<const T*>(f->propmat);
-        a.emis = static_cast<const T*>(f->emis);
-        a.rays = rays;
-        a.phi = phiT;
-        a.wn = wn;
-        a.iprev = prev;
-        const bool last = (step == nz - 1);
-        const size_t batch_off = (size_t)r0 * q->nfreq * np * ns;
-        if (last && up && itop)
-          a.inext = itop + batch_off;
-        else if (up && ckpt && is_checkpoint(k, nz, C))   // kept for the adjoint
-          a.inext = ckpt + ((size_t)(k / C - 1) * (up_hi - up_lo) + (r0 - up_lo)) *
+  // batches of both hemispheres: (first ray, rays) within the hemisphere
+  int lo[2], hi[2];
+  for (int m = 0; m < 2; ++m) hemi_range(q, o, m, lo[m], hi[m]);
+  // without J nothing that the call returns depends on the downward rays
+  if (!jkq) hi[1] = lo[1];
+  const int up_lo = lo[0], up_hi = hi[0];
+  const T ibound[2] = {(T)f->i_bottom, T(0)};
+  // one launch per plane step for a batch of upward rays, of downward rays, or of both
+  auto walk = [&](const int r0[2], const int nr[2]) -> int {
+    PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L);
+    a.jkq = jkq;
+    set_chunks(a, launch_chunks(g, q, o, P, nr[0] + nr[1]), nr[0] + nr[1]);
+    // states and partial sums of the downward rays follow those of the upward ones
+    const size_t soff[2] = {0, (size_t)nr[0] * q->nfreq * np * ns};
+    const size_t joff[2] = {0, (size_t)nr[0] * a.nchunk * (ns + 1) * np};
+    const T* prev[2] = {nullptr, nullptr};
+    for (int step = 1; step < nz; ++step) {
+      for (int m = 0; m < 2; ++m) {
+        HemiArgs<T>& h = a.h[m];
+        const int s = m == 0 ? 1 : -1, k = (m == 0 ? 0 : nz - 1) + s * step;
+        const size_t batch_off = (size_t)r0[m] * q->nfreq * np * ns;
+        set_plane(h, g, k, s);
+        h.ray0 = m * nh + r0[m];
+        h.nrb = nr[m];
+        h.ibound = ibound[m];
+        h.iprev = prev[m];
+        if (m == 0 && step == nz - 1 && itop)
+          h.inext = itop + batch_off;
+        else if (m == 0 && ckpt && is_checkpoint(k, nz, C))   // kept for the adjoint
+          h.inext = ckpt + ((size_t)(k / C - 1) * (up_hi - up_lo) + (r0[m] - up_lo)) *
                                q->nfreq * np * 4;
         else
-          a.inext = state[step & 1];
-        // plane k writes partial sums into jpart[step & 1] while the first ray row of
-        // blocks adds those of plane k - s (or the boundary plane) to J
-        a.jpart = jpart[step & 1];
-        a.jkq = jkq;
-        a.jpart_prev = (step == 1) ? nullptr : jpart[(step - 1) & 1];
-        a.prev_off = (size_t)(k - s) * np;
-        a.N = N;
-        a.nx = nx;
-        a.ny = ny;
-        a.np = np;
-        a.nfreq = q->nfreq;
-        a.kO = k;
-        a.kM = k - s;
-        a.kP = last ? -1 : k + s;
-        a.dzM = std::fabs(g->z[k] - g->z[k - s]);
-        a.dzP = last ? 0.0 : std::fabs(g->z[k + s] - g->z[k]);
-        a.inv_dx = nx / g->lx;
-        a.inv_dy = ny / g->ly;
-        a.ray0 = ray0;
-        a.xcd_remap = xcd_chunk(o);
-        a.parabolic = parabolic_of(o);
-        a.ibound = ibound;
-        const size_t lds = (size_t)q->nfreq * (sizeof(double) + sizeof(T));
-        const dim3 grid((np + block - 1) / block, nrb);
-        if (ns == 1)
-          hipLaunchKernelGGL(k_sweep_plane_i<T>, grid, dim3(block), lds, st, a);
-        else if (interp == PORTA_INTERP_BEZIER2D)
-          hipLaunchKernelGGL((k_sweep_plane<T, 1>), grid, dim3(block), lds, st, a);
-        else
-          hipLaunchKernelGGL((k_sweep_plane<T, 0>), grid, dim3(block), lds, st, a);
-        if ((rc = check_launch("sweep_plane"))) return rc;
-        prev = a.inext;
+          h.inext = state[step & 1] + soff[m];
+        // plane k writes partial sums into jpart[step & 1] while the first blocks add
+        // those of plane k - s (or the boundary plane) to J
+        h.jpart = jkq ? jpart[step & 1] + joff[m] : nullptr;
+        h.jpart_prev = (jkq && step > 1) ? jpart[(step - 1) & 1] + joff[m] : nullptr;
+        h.prev_off = (size_t)(k - s) * np;
+        prev[m] = h.inext;
       }
-      if (jkq) {
-        // the last plane of the batch
-        const int klast = kb + s * (nz - 1);
-        hipLaunchKernelGGL(k_jreduce, rgrid, rblk, 0, st, jkq, (const double*)jpart[(nz - 1) & 1],
-                           rays, ray0, nrb, np, N, (size_t)klast * np, 0, 0.0);
-        if ((rc = check_launch("jreduce"))) return rc;
+      a.njb = jkq ? 2 * jblocks(np) : 0;
+      a.jsame = nr[0] > 0 && nr[1] > 0 && a.h[0].kM == a.h[1].kM;
+      int e = launch_plane<T>(a, ns, interp, block, st);
+      if (e) return e;
+    }
+    for (int m = 0; m < 2 && jkq; ++m) {   // the last plane of each hemisphere
+      if (nr[m] == 0) continue;
+      int e = launch_jreduce(jkq, a.h[m].jpart, rays, a.h[m].ray0, nr[m], a.nchunk, ns, np, N,
+                             (size_t)a.h[m].kO * np, 0.0, st);
+      if (e) return e;
+    }
+    return PORTA_OK;
+  };
+  if (P.share) {
+    for (int b = 0;; ++b) {
+      int r0[2], nr[2];
+      for (int m = 0; m < 2; ++m) {
+        r0[m] = std::min(lo[m] + b * P.nrb, hi[m]);
+        nr[m] = std::min(P.nrb, hi[m] - r0[m]);
       }
+      if (nr[0] + nr[1] == 0) return PORTA_OK;
+      if ((rc = walk(r0, nr))) return rc;
     }
   }
+  for (int m = 0; m < 2; ++m)
+    for (int r = lo[m]; r < hi[m]; r += P.nrb) {
+      const int n = std::min(P.nrb, hi[m] - r);
+      const int r0[2] = {m == 0 ? r : 0, m == 0 ? 0 : r}, nr[2] = {m == 0 ? n : 0, m == 0 ? 0 : n};
+      if ((rc = walk(r0, nr))) return rc;
+    }
   return PORTA_OK;
 }
 
@@ -594,44 +734,16 @@ template <class T>
 int forward_plane(const porta_grid* g, const porta_quad* q, const porta_fields* f,
                   const porta_options* o, int interp, char* ws, const Layout& L, int k,
                   const T* prev, T* next, int ray0, int nrb, int block, hipStream_t st) {
-  const int nx = g->nx, ny = g->ny, nz = g->nz, np = nx * ny;
-  PlaneArgs<T> a;
-  a.kappa = static_cast<const T*>(f->kappa);
-  a.prop = static_cast<const T*>(f->propmat);
-  a.emis = static_cast<const T*>(f->emis);
-  a.rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
-  a.phi = reinterpret_cast<const T*>(ws + L.phiT);
-  a.wn = reinterpret_cast<const double*>(ws + L.wn);
-  a.iprev = prev;
-  a.inext = next;
-  a.jpart = nullptr;
-  a.jkq = nullptr;
-  a.jpart_prev = nullptr;
-  a.prev_off = 0;
-  a.N = (size_t)np * nz;
-  a.nx = nx;
-  a.ny = ny;
-  a.np = np;
-  a.nfreq = q->nfreq;
-  a.kO = k;
-  a.kM = k - 1;
-  a.kP = (k == nz - 1) ? -1 : k + 1;
-  a.dzM = std::fabs(g->z[k] - g->z[k - 1]);
-  a.dzP = (k == nz - 1) ? 0.0 : std::fabs(g->z[k + 1] - g->z[k]);
-  a.inv_dx = nx / g->lx;
-  a.inv_dy = ny / g->ly;
-  a.ray0 = ray0;
-  a.xcd_remap = xcd_chunk(o);
-  a.parabolic = parabolic_of(o);
-  a.ibound = (T)f->i_bottom;
-  const size_t lds = (size_t)q->nfreq * (sizeof(double) + sizeof(T));
-  if (interp == PORTA_INTERP_BEZIER2D)
-    hipLaunchKernelGGL((k_sweep_plane<T, 1>), dim3((np + block - 1) / block, nrb), dim3(block),
-                       lds, st, a);
-  else
-    hipLaunchKernelGGL((k_sweep_plane<T, 0>), dim3((np + block - 1) / block, nrb), dim3(block),
-                       lds, st, a);
-  return check_launch("sweep_plane (adjoint recompute)");
+  PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L);
+  set_chunks(a, freq_chunks((int64_t)a.ntile * nrb, q->nfreq), nrb);
+  HemiArgs<T>& h = a.h[0];
+  set_plane(h, g, k, 1);
+  h.iprev = prev;
+  h.inext = next;
+  h.ray0 = ray0;
+  h.nrb = nrb;
+  h.ibound = (T)f->i_bottom;
+  return launch_plane<T>(a, 4, interp, block, st);
 }
 
 template <class T>
@@ -645,7 +757,7 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
   double* grad = reinterpret_cast<double*>(ws + L.grad);
   if ((rc = fill(grad, 13 * N, 0.0, st))) return rc;
   const int nrb_max = ray_batch(q, o);
-  const int block = (o && o->block > 0) ? o->block : 256;
+  const int block = plane_block(g, o);
   if (block % 64 != 0 || block > 256) return fail(PORTA_EINVAL, "block must be 64, 128, 192 or 256");
   const size_t pe = L.plane / sizeof(T);   // elements of one plane state
   T* ck = reinterpret_cast<T*>(ws + L.ck);
@@ -863,8 +975,13 @@ int sweep_entry(const porta_grid* grid, const porta_quad* quad, const porta_fiel
                   ck_bytes, need);
   }
   if (!use_scratch && !workspace) return fail(PORTA_EINVAL, "workspace is NULL");
-  const Layout L = sweep_layout(grid, quad, prec, opts);
+  SweepPlan plan = sweep_plan(grid, quad, opts);
+  Layout L = sweep_layout(grid, quad, prec, opts, plan);
   if (use_scratch) {
+    if (L.total > kScratchBytes) {
+      plan = least_plan(grid, quad, opts);
+      L = sweep_layout(grid, quad, prec, opts, plan);
+    }
     if (L.total > kScratchBytes)
       return fail(PORTA_ENOMEM,
                   "this sweep needs %zu bytes of workspace; the static scratch holds %zu "
@@ -885,10 +1002,10 @@ int sweep_entry(const porta_grid* grid, const porta_quad* quad, const porta_fiel
   if (prec == PORTA_F64)
     return sweep_impl<double>(grid, quad, fields, interp, opts, jkq, accumulate,
                               static_cast<double*>(i_top), static_cast<double*>(checkpoints),
-                              checkpoint_stride, ws, L, st);
+                              checkpoint_stride, ws, plan, L, st);
   return sweep_impl<float>(grid, quad, fields, interp, opts, jkq, accumulate,
                            static_cast<float*>(i_top),
-                           static_cast<float*>(checkpoints), checkpoint_stride, ws, L, st);
+                           static_cast<float*>(checkpoints), checkpoint_stride, ws, plan, L, st);
 }
 
 }  // namespace
@@ -917,7 +1034,7 @@ size_t porta_workspace_size(const porta_grid* grid, const porta_quad* quad, int 
   switch (kind) {
     case PORTA_WS_SWEEP:
       if (validate_grid(grid) || validate_quad(quad)) return 0;
-      return sweep_layout(grid, quad, prec, opts).total;
+      return sweep_layout(grid, quad, prec, opts, sweep_plan(grid, quad, opts)).total;
     case PORTA_WS_ADJOINT:
     case PORTA_WS_ADJOINT_CKPT:
       if (validate_grid(grid) || validate_quad(quad) || checkpoint_stride < 1 ||

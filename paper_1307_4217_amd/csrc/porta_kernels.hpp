@@ -325,56 +325,121 @@ __device__ inline void setup_point(const T* __restrict__ kappa, const T* __restr
 }
 
 // ---------------------------------------------------------------------------
-// Add the frequency-integrated Stokes vectors of a batch of rays on one plane
-// to J^K_Q (Eq. 1) and Lbar, in a fixed ray order (no atomics).  On the
-// boundary plane the Stokes vector is (ibound, 0, 0, 0) at every frequency.
+// One hemisphere's part of a plane step: the plane its rays are solved on, their states,
+// and the previous plane's partial sums of J.
 // ---------------------------------------------------------------------------
-__device__ inline void jreduce_point(double* __restrict__ jkq, const double* __restrict__ jpart,
-                                     const RayConsts* __restrict__ rays, int ray0, int nrb,
-                                     int np, size_t N, size_t plane_off, int p, int boundary,
-                                     double ibound) {
-  double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int rb = 0; rb < nrb; ++rb) {
-    const RayConsts& rc = rays[ray0 + rb];
-    double ib[4], lam;
-    if (boundary) {
-      ib[0] = ibound;
-      ib[1] = ib[2] = ib[3] = 0.0;
-      lam = 0.0;
-    } else {
-      const double* jp = jpart + (size_t)rb * 5 * np + p;
-      ib[0] = jp[0];
-      ib[1] = jp[(size_t)np];
-      ib[2] = jp[2 * (size_t)np];
-      ib[3] = jp[3 * (size_t)np];
-      lam = jp[4 * (size_t)np];
-    }
-    const double w = rc.weight;
+template <class T>
+struct HemiArgs {
+  const T* iprev;    // upwind plane state, or nullptr when the upwind plane is the boundary
+  T* inext;          // state of plane kO
+  double* jpart;     // [ray][chunk][NS + 1][node]: sum_j W_j I_i and sum_j W_j Lambda* over
+                     // the chunk's frequencies, or nullptr
+  const double* jpart_prev;  // partial sums of the previous plane, or nullptr (boundary plane)
+  size_t prev_off;   // offset of the previous plane in jkq
+  int kO, kM, kP;    // plane of O, upwind plane, downwind plane (-1: none)
+  double dzM, dzP;   // |z_kO - z_kM|, |z_kP - z_kO|
+  int ray0, nrb;     // rays [ray0, ray0 + nrb) of the enumeration
+  T ibound;          // Stokes I on the boundary plane of this hemisphere
+};
+
+// ---------------------------------------------------------------------------
+// Add the frequency-integrated Stokes vectors of a batch of rays on one plane to J^K_Q
+// (Eq. 1) and Lbar, in a fixed order (no atomics).  A block takes kJNodes nodes; its
+// threads are (ray group, node), group g summing rays g, g + G, ... over their frequency
+// chunks, and the groups are added in order through LDS.  The loop over rays is a chain
+// of memory latencies: with one thread per node and every ray in turn it took 25 us at
+// 16x16 nodes and 40 rays, 73 us at 128x128 and 80 rays, more than the plane step that
+// had to wait for it.  On the boundary plane the Stokes vector is (ibound, 0, 0, 0) at
+// every frequency.  NS: Stokes parameters in the partial sums (4, or 1: intensity only).
+// ---------------------------------------------------------------------------
+constexpr int kJNodes = 16;   // consecutive nodes of a block: one 128-byte line of doubles
+inline int jblocks(int np) { return (np + kJNodes - 1) / kJNodes; }
+inline size_t jlds_bytes(int block) { return (size_t)block * 10 * sizeof(double); }
+
+// acc += the projections of one ray's integrated Stokes vector.  T^K_Q is zero for
+// Stokes V at K = 0, 2, for I, Q, U at K = 1, and for Q, U at J00 and U at J20.
+template <int NS>
+__device__ inline void jproject(const RayConsts& rc, const double ib[NS], double lam,
+                                double acc[10]) {
+  const double w = rc.weight;
+  acc[0] += w * (rc.proj[0][0] * ib[0]);
+  if constexpr (NS == 4) {
 #pragma unroll
-    for (int c = 0; c < 9; ++c)
-      acc[c] += w * (rc.proj[c][0] * ib[0] + rc.proj[c][1] * ib[1] + rc.proj[c][2] * ib[2] +
-                     rc.proj[c][3] * ib[3]);
-    acc[9] += w * lam;
+    for (int c = 1; c < 4; ++c) acc[c] += w * (rc.proj[c][3] * ib[3]);
+    acc[4] += w * (rc.proj[4][0] * ib[0] + rc.proj[4][1] * ib[1]);
+#pragma unroll
+    for (int c = 5; c < 9; ++c)
+      acc[c] += w * (rc.proj[c][0] * ib[0] + rc.proj[c][1] * ib[1] + rc.proj[c][2] * ib[2]);
+  } else {
+#pragma unroll
+    for (int c = 4; c < 9; ++c) acc[c] += w * (rc.proj[c][0] * ib[0]);
   }
-#pragma unroll
-  for (int c = 0; c < 10; ++c) jkq[c * N + plane_off + p] += acc[c];
+  acc[9] += w * lam;
 }
 
+template <int NS>
+__device__ inline void jsum_rays(const double* __restrict__ jpart,
+                                 const RayConsts* __restrict__ rays, int nrb, int nchunk, int np,
+                                 int p, double ibound, double acc[10]) {
+  const int g = threadIdx.x / kJNodes, G = blockDim.x / kJNodes;
+  for (int rb = g; rb < nrb; rb += G) {
+    double ib[NS], lam = 0.0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) ib[s] = 0.0;
+    if (!jpart) {
+      ib[0] = ibound;
+    } else {
+      const double* jp = jpart + (size_t)rb * nchunk * (NS + 1) * np + p;
+#pragma unroll 4
+      for (int c = 0; c < nchunk; ++c) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) ib[s] += jp[s * (size_t)np];
+        lam += jp[NS * (size_t)np];
+        jp += (NS + 1) * (size_t)np;
+      }
+    }
+    jproject<NS>(rays[rb], ib, lam, acc);
+  }
+}
+
+// lds: jlds_bytes(blockDim.x); every thread of the block calls it.
+__device__ inline void jadd_groups(const double acc[10], double* __restrict__ jkq, size_t N,
+                                   size_t plane_off, int np, int node0, double* lds) {
+  const int n = threadIdx.x % kJNodes, g = threadIdx.x / kJNodes, G = blockDim.x / kJNodes;
+#pragma unroll
+  for (int c = 0; c < 10; ++c) lds[(c * G + g) * kJNodes + n] = acc[c];
+  __syncthreads();
+  for (int e = threadIdx.x; e < 10 * kJNodes; e += blockDim.x) {
+    const int c = e / kJNodes, q = node0 + e % kJNodes;
+    double sum = 0.0;
+    for (int k = 0; k < G; ++k) sum += lds[(c * G + k) * kJNodes + e % kJNodes];
+    if (q < np) jkq[c * N + plane_off + q] += sum;
+  }
+}
+
+template <int NS>
 __global__ void __launch_bounds__(256)
     k_jreduce(double* __restrict__ jkq, const double* __restrict__ jpart,
-              const RayConsts* __restrict__ rays, int ray0, int nrb, int np, size_t N,
-              size_t plane_off, int boundary, double ibound) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= np) return;
-  jreduce_point(jkq, jpart, rays, ray0, nrb, np, N, plane_off, p, boundary, ibound);
+              const RayConsts* __restrict__ rays, int ray0, int nrb, int nchunk, int np, size_t N,
+              size_t plane_off, double ibound) {
+  extern __shared__ double s_tab[];
+  const int node0 = blockIdx.x * kJNodes, p = node0 + threadIdx.x % kJNodes;
+  double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (p < np) jsum_rays<NS>(jpart, rays + ray0, nrb, nchunk, np, p, ibound, acc);
+  jadd_groups(acc, jkq, N, plane_off, np, node0, s_tab);
 }
 
 // ---------------------------------------------------------------------------
-// One plane of the sweep for a batch of rays of one hemisphere and every
-// frequency.  Thread = (node of plane k, ray of the batch); the frequency
-// loop runs inside the thread so that the frequency-independent work
-// (interpolation of the coefficients at M and P, S and K' at M and O, the
-// BESSER control points) is done once per node and ray.
+// One plane step of the sweep for a batch of rays and every frequency: the upward rays
+// (h[0]) on their plane and the downward rays (h[1]) on theirs, which are independent
+// of each other.  Thread = (node, ray, chunk of frequencies); the frequency loop runs
+// inside the thread so that the frequency-independent work (interpolation of the
+// coefficients at M and P, S and K' at M and O, the BESSER control points) is done
+// once per node, ray and chunk.  One chunk holds every frequency unless the launch
+// would leave most of the chip idle (sweep_plan on the host).
+//
+// The last njb blocks add the previous plane's partial sums to J: where the launch takes
+// several rounds of the chip they fill its tail, and otherwise they run beside the others.
 //
 // Plane state layout: [ray in batch][frequency][node][Stokes].
 // ---------------------------------------------------------------------------
@@ -386,43 +451,104 @@ struct PlaneArgs {
   const RayConsts* rays;
   const T* phi;
   const double* wn;
-  const T* iprev;    // upwind plane state, or nullptr when the upwind plane is the boundary
-  T* inext;          // state of plane k
-  double* jpart;     // [ray in batch][5][node]: sum_j W_j I_i and sum_j W_j Lambda*, or nullptr
-  // J of the previous plane (reduced by the blocks of the first ray of the batch)
-  double* jkq;               // [10][N] or nullptr
-  const double* jpart_prev;  // partial sums of the previous plane, or nullptr (boundary plane)
-  size_t prev_off;           // offset of the previous plane in jkq
+  HemiArgs<T> h[2];
+  double* jkq;       // [10][N] or nullptr
   size_t N;
   int nx, ny, np, nfreq;
-  int kO, kM, kP;    // plane of O, upwind plane, downwind plane (-1: none)
-  double dzM, dzP;   // |z_kO - z_kM|, |z_kP - z_kO|
+  int ntile;         // tiles of blockDim.x nodes in a plane
+  int nchunk, fchunk;
+  int nstep;         // blocks of the plane step; the J reduction's follow
+  int njb;           // blocks of the J reduction
+  int jsame;         // both hemispheres' previous plane is the same one: one block adds both
   double inv_dx, inv_dy;
-  int ray0;
   int xcd_remap;     // tiles per XCD per round (0: hardware order), see xcd_tile
   int parabolic;     // control point: 0 BESSER, 1 parabola through M, O, P
-  T ibound;          // Stokes I on the boundary plane of this hemisphere
 };
+
+// The arguments of one hemisphere, field by field: an index into a.h taken at run time
+// would leave the pointers without their address space (flat loads and stores, 2% of
+// the sweep at 256x256x128).
+template <class T>
+__device__ inline HemiArgs<T> hemi_args(const PlaneArgs<T>& a, bool second) {
+  const HemiArgs<T>&u = a.h[0], &d = a.h[1];
+  HemiArgs<T> h;
+  h.iprev = second ? d.iprev : u.iprev;
+  h.inext = second ? d.inext : u.inext;
+  h.jpart = second ? d.jpart : u.jpart;
+  h.jpart_prev = second ? d.jpart_prev : u.jpart_prev;
+  h.prev_off = second ? d.prev_off : u.prev_off;
+  h.kO = second ? d.kO : u.kO;
+  h.kM = second ? d.kM : u.kM;
+  h.kP = second ? d.kP : u.kP;
+  h.dzM = second ? d.dzM : u.dzM;
+  h.dzP = second ? d.dzP : u.dzP;
+  h.ray0 = second ? d.ray0 : u.ray0;
+  h.nrb = second ? d.nrb : u.nrb;
+  h.ibound = second ? d.ibound : u.ibound;
+  return h;
+}
+
+// The J reduction of the previous planes by the last njb blocks of a plane step: half of
+// them for each hemisphere.
+template <int NS, class T>
+__device__ inline void jblock(const PlaneArgs<T>& a, double* lds) {
+  const int b = blockIdx.x - a.nstep, per = a.njb / 2, hemi = b >= per;
+  const int node0 = (b - hemi * per) * kJNodes;
+  const HemiArgs<T> h = hemi_args(a, hemi);
+  if (node0 >= a.np || h.nrb == 0 || (hemi && a.jsame)) return;
+  const int p = node0 + threadIdx.x % kJNodes;
+  double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (p < a.np) {
+    jsum_rays<NS>(h.jpart_prev, a.rays + h.ray0, h.nrb, a.nchunk, a.np, p, (double)h.ibound, acc);
+    if (a.jsame)
+      jsum_rays<NS>(a.h[1].jpart_prev, a.rays + a.h[1].ray0, a.h[1].nrb, a.nchunk, a.np, p,
+                    (double)a.h[1].ibound, acc);
+  }
+  jadd_groups(acc, a.jkq, a.N, h.prev_off, a.np, node0, lds);
+}
 
 // Workgroups are dispatched round-robin over the 8 XCDs of the MI355X, each with
 // its own L2.  With chunk R > 0 the tiles are renumbered so that every XCD takes
 // R consecutive tiles per round (neighbouring rows of one ray then share an L2)
 // while the eight XCDs still advance through the grid together.
+__device__ inline int xcd_order(int chunk, int L, int T) {
+  int Lp = L;
+  if (chunk > 0) {
+    const int round = 8 * chunk;
+    const int Tmain = (T / round) * round;
+    if (L < Tmain) {
+      const int x = L % 8, k = L / 8;
+      Lp = (k / chunk) * round + x * chunk + (k % chunk);
+    }
+  }
+  return Lp;
+}
+
+// The same over a two-dimensional grid of tiles.
 __device__ inline void xcd_tile(int chunk, int& bx, int& by) {
   bx = blockIdx.x;
   by = blockIdx.y;
   if (chunk <= 0) return;
-  const int T = gridDim.x * gridDim.y;
-  const int L = blockIdx.y * gridDim.x + blockIdx.x;
-  const int round = 8 * chunk;
-  const int Tmain = (T / round) * round;
-  int Lp = L;
-  if (L < Tmain) {
-    const int x = L % 8, k = L / 8;
-    Lp = (k / chunk) * round + x * chunk + (k % chunk);
-  }
+  const int Lp = xcd_order(chunk, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   bx = Lp % gridDim.x;
   by = Lp / gridDim.x;
+}
+
+// Tile, ray, frequency chunk and hemisphere of a block of a plane step.
+struct StepBlock {
+  int bx, rb, chunk, hemi;   // rb counts within the hemisphere's rays
+};
+
+template <class T>
+__device__ inline StepBlock step_block(const PlaneArgs<T>& a) {
+  const int L = xcd_order(a.xcd_remap, blockIdx.x, a.nstep);
+  const int row = L / a.ntile, ray = row / a.nchunk;
+  StepBlock b;
+  b.bx = L % a.ntile;
+  b.chunk = row % a.nchunk;
+  b.hemi = ray >= a.h[0].nrb;
+  b.rb = ray - (b.hemi ? a.h[0].nrb : 0);
+  return b;
 }
 
 constexpr int kMaxFreq = 4096;   // frequencies held in LDS by the sweep kernels
@@ -453,37 +579,44 @@ __device__ inline void upwind_bez9(const T* __restrict__ q, const Stencil9& s,
   }
 }
 
+template <class T>
+__device__ inline T bilinear(T w00, T w10, T w01, T w11, T v00, T v10, T v01, T v11) {
+  return fma_t(w11, v11, dot3(w00, v00, w10, v10, w01, v01));
+}
+
 // Occupancy targets: three waves per SIMD for the FP32 bilinear sweep (168 VGPRs,
 // with the next frequency's corners in flight and no spill in the loop; four or five
 // waves were slower), two for the others (the 9-point mode would otherwise drop to
 // one).
 template <class T, int MODE>
 __global__ void __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(MODE == 0 && sizeof(T) == 4 ? 3 : 2)))
+__attribute__((amdgpu_waves_per_eu(MODE == 0 && sizeof(T) == 4 ? 3 : 2,
+                                   MODE == 0 && sizeof(T) == 4 ? 3 : 2)))
 k_sweep_plane(const PlaneArgs<T> a) {
   // per-frequency weights and profile, read from LDS inside the frequency loop so that
   // no vector-memory wait (which on gfx9 also covers earlier stores) sits in the loop
   extern __shared__ double s_tab[];
+  if ((int)blockIdx.x >= a.nstep) {
+    jblock<4>(a, s_tab);
+    return;
+  }
+  const StepBlock sb = step_block(a);
+  const HemiArgs<T> h = hemi_args(a, sb.hemi);
+  const int f0 = sb.chunk * a.fchunk, nf = min(a.fchunk, a.nfreq - f0);
   double* s_wn = s_tab;
-  T* s_phi = reinterpret_cast<T*>(s_tab + a.nfreq);
-  for (int t = threadIdx.x; t < a.nfreq; t += blockDim.x) {
-    s_wn[t] = a.wn[t];
-    s_phi[t] = a.phi[t];
+  T* s_phi = reinterpret_cast<T*>(s_tab + a.fchunk);
+  for (int t = threadIdx.x; t < nf; t += blockDim.x) {
+    s_wn[t] = a.wn[f0 + t];
+    s_phi[t] = a.phi[f0 + t];
   }
   __syncthreads();
-  int bx, rb;
-  xcd_tile(a.xcd_remap, bx, rb);
-  const int p = bx * blockDim.x + threadIdx.x;
-  const bool active = p < a.np;
-  const int pp = active ? p : 0;   // inactive lanes only take part in the barriers
-  if (active && rb == 0 && a.jkq)
-    jreduce_point(a.jkq, a.jpart_prev, a.rays, a.ray0, gridDim.y, a.np, a.N, a.prev_off, p,
-                  a.jpart_prev == nullptr, (double)a.ibound);
-  const RayConsts& rc = a.rays[a.ray0 + rb];
+  const int p = sb.bx * blockDim.x + threadIdx.x;
+  if (p >= a.np) return;   // no barrier follows
+  const RayConsts& rc = a.rays[h.ray0 + sb.rb];
   PointSetup ps;
   Stencil9 sM9;
-  setup_point<MODE>(a.kappa, a.prop, a.emis, a.N, a.nx, a.ny, a.np, a.kO, a.kM, a.kP, a.dzM,
-                    a.dzP, a.inv_dx, a.inv_dy, rc, pp, a.parabolic != 0, ps, sM9);
+  setup_point<MODE>(a.kappa, a.prop, a.emis, a.N, a.nx, a.ny, a.np, h.kO, h.kM, h.kP, h.dzM,
+                    h.dzP, a.inv_dx, a.inv_dy, rc, p, a.parabolic != 0, ps, sM9);
   const BezW<T> bwx = bez_weights(MODE == 1 ? (T)sM9.tx : T(0));
   const BezW<T> bwy = bez_weights(MODE == 1 ? (T)sM9.ty : T(0));
   const Stencil& sM = ps.sM;
@@ -516,13 +649,12 @@ k_sweep_plane(const PlaneArgs<T> a) {
   const T lf = (T)lamfac;
 
   const size_t fstride = (size_t)a.np * 4;
-  const T* ip = a.iprev ? a.iprev + (size_t)rb * a.nfreq * fstride : nullptr;
-  T* op = a.inext + (size_t)rb * a.nfreq * fstride + (size_t)pp * 4;
+  const size_t foff = ((size_t)sb.rb * a.nfreq + f0) * fstride;
+  const T* ip = h.iprev ? h.iprev + foff : nullptr;
+  T* op = h.inext + foff + (size_t)p * 4;
   double jacc0 = 0.0, jacc1 = 0.0, jacc2 = 0.0, jacc3 = 0.0, lacc = 0.0;
 
-  if (!active) return;   // no barrier follows
-
-  // one update (Eq. fsbez solved with Eq. kappa) at frequency f from the upwind
+  // one update (Eq. fsbez solved with Eq. kappa) at frequency f0 + f from the upwind
   // Stokes vector IM
   auto update = [&](int f, T i0, T i1, T i2, T i3) __attribute__((always_inline)) {
     const T IM[4] = {i0, i1, i2, i3};
@@ -533,7 +665,8 @@ k_sweep_plane(const PlaneArgs<T> a) {
     T b[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      b[s] = cf.e * IM[s] - cf.psiM * KI[s] + cf.omM * SMt[s] + cf.omO * SOt[s] + cf.omC * cMt[s];
+      b[s] = fma_t(cf.omC, cMt[s], fma_t(cf.omO, SOt[s], fma_t(cf.omM, SMt[s],
+                   fma_t(cf.e, IM[s], -(cf.psiM * KI[s])))));
     T x[4];
     stokes_solve<1>(KO, stokes_freq(KO, cf.psiO), b, x);
     store4_nt(op + (size_t)f * fstride, x);
@@ -542,46 +675,51 @@ k_sweep_plane(const PlaneArgs<T> a) {
     jacc1 += W * (double)x[1];
     jacc2 += W * (double)x[2];
     jacc3 += W * (double)x[3];
-    lacc += W * (double)(cf.omO + lf * cf.omC);
+    lacc += W * (double)fma_t(lf, cf.omC, cf.omO);
   };
   // bilinear upwind component s from the four corner values
-#define PORTA_BILIN(v, s) (w00 * v[0][s] + w10 * v[1][s] + w01 * v[2][s] + w11 * v[3][s])
+#define PORTA_BILIN(v, s) bilinear(w00, w10, w01, w11, v[0][s], v[1][s], v[2][s], v[3][s])
 
   if (!ip) {
     // the upwind plane is the boundary
-    for (int f = 0; f < a.nfreq; ++f) update(f, a.ibound, T(0), T(0), T(0));
+    for (int f = 0; f < nf; ++f) update(f, h.ibound, T(0), T(0), T(0));
   } else if (MODE == 1) {
-    for (int f = 0; f < a.nfreq; ++f) {
+    for (int f = 0; f < nf; ++f) {
       T IM[4];
       upwind_bez9(ip + (size_t)f * fstride, sM9, bwx, bwy, IM);
       update(f, IM[0], IM[1], IM[2], IM[3]);
     }
   } else {
     if constexpr (sizeof(T) == 4) {
-      // the corners of frequency f + 1 are loaded during the arithmetic of frequency f
-      // (in FP64 the second buffer does not fit without spilling)
+      // The corners of frequency f + 1 are loaded during the arithmetic of frequency f (in
+      // FP64 the second buffer does not fit without spilling).  The loads are never
+      // skipped (past the end the last frequency's are taken again): behind a branch the
+      // wait for the current corners would have to wait for the new ones too.
       T vA[4][4], vB[4][4];
       load_upwind(ip, sM, vA);
-      for (int f = 0; f < a.nfreq; f += 2) {
-        if (f + 1 < a.nfreq) load_upwind(ip + (size_t)(f + 1) * fstride, sM, vB);
+      int f = 0;
+      for (; f + 1 < nf; f += 2) {
+        load_upwind(ip + (size_t)(f + 1) * fstride, sM, vB);
         update(f, PORTA_BILIN(vA, 0), PORTA_BILIN(vA, 1), PORTA_BILIN(vA, 2),
                PORTA_BILIN(vA, 3));
-        if (f + 1 >= a.nfreq) break;
-        if (f + 2 < a.nfreq) load_upwind(ip + (size_t)(f + 2) * fstride, sM, vA);
+        load_upwind(ip + (size_t)min(f + 2, nf - 1) * fstride, sM, vA);
         update(f + 1, PORTA_BILIN(vB, 0), PORTA_BILIN(vB, 1), PORTA_BILIN(vB, 2),
                PORTA_BILIN(vB, 3));
       }
+      if (f < nf)
+        update(f, PORTA_BILIN(vA, 0), PORTA_BILIN(vA, 1), PORTA_BILIN(vA, 2),
+               PORTA_BILIN(vA, 3));
     } else {
       T v[4][4];
-      for (int f = 0; f < a.nfreq; ++f) {
+      for (int f = 0; f < nf; ++f) {
         load_upwind(ip + (size_t)f * fstride, sM, v);
         update(f, PORTA_BILIN(v, 0), PORTA_BILIN(v, 1), PORTA_BILIN(v, 2), PORTA_BILIN(v, 3));
       }
     }
   }
 #undef PORTA_BILIN
-  if (a.jpart) {
-    double* jp = a.jpart + (size_t)rb * 5 * a.np + p;
+  if (h.jpart) {
+    double* jp = h.jpart + ((size_t)sb.rb * a.nchunk + sb.chunk) * 5 * a.np + p;
     jp[0] = jacc0;
     jp[(size_t)a.np] = jacc1;
     jp[2 * (size_t)a.np] = jacc2;

@@ -33,6 +33,17 @@ __host__ __device__ inline float recip(float x) {
 }
 __host__ __device__ inline double recip(double x) { return 1.0 / x; }
 
+// Sums of products in the frequency loops are written as fused multiply-adds, one by one:
+// left to the compiler, the product that is rounded on its own could differ between the
+// copies of a loop body, and a result with the place of its frequency in the loop.
+__host__ __device__ inline float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__host__ __device__ inline double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// a0 b0 + a1 b1 + a2 b2, the first product rounded
+template <class T>
+__host__ __device__ inline T dot3(T a0, T b0, T a1, T b1, T a2, T b2) {
+  return fma_t(a2, b2, fma_t(a1, b1, a0 * b0));
+}
+
 // ---------------------------------------------------------------------------
 // Coefficients of Eq. fsbez (Sect. 3.3):
 //   e = exp(-tau), psi'_M, psi'_O (linear K'I), omega_M, omega_O, omega_C
@@ -79,14 +90,14 @@ __host__ __device__ inline Coefs<float> coefficients(float tau) {
                            -1.0f / 479001600};
     float E3 = kE3[9];
 #pragma unroll
-    for (int n = 8; n >= 0; --n) E3 = E3 * tau + kE3[n];
-    const float E2 = 0.5f - tau * E3;
-    const float E1 = 1.0f - tau * E2;
-    c.e = 1.0f - tau * E1;
+    for (int n = 8; n >= 0; --n) E3 = fma_t(E3, tau, kE3[n]);
+    const float E2 = fma_t(-tau, E3, 0.5f);
+    const float E1 = fma_t(-tau, E2, 1.0f);
+    c.e = fma_t(-tau, E1, 1.0f);
     if constexpr (EM1) c.em1 = tau * E1;
     c.pmt = E1 - E2;
-    c.omt = E1 + 2.0f * (E3 - E2);
-    c.oct = 2.0f * E2 - 4.0f * E3;
+    c.omt = fma_t(2.0f, E3 - E2, E1);
+    c.oct = fma_t(2.0f, E2, -4.0f * E3);
     c.psiO = tau * E2;
     c.psiM = tau * c.pmt;
     c.omO = (2.0f * tau) * E3;
@@ -98,10 +109,10 @@ __host__ __device__ inline Coefs<float> coefficients(float tau) {
     const float it = recip(tau), it2 = it * it;
     const float g = c.e + tau - 1.0f;               // e + tau - 1
     c.psiO = g * it;
-    c.psiM = (1.0f - c.e * (1.0f + tau)) * it;
-    c.omM = (2.0f - c.e * (tau * tau + 2.0f * tau + 2.0f)) * it2;
-    c.omO = 1.0f - 2.0f * g * it2;
-    c.omC = 2.0f * (tau - 2.0f + c.e * (tau + 2.0f)) * it2;
+    c.psiM = fma_t(-c.e, 1.0f + tau, 1.0f) * it;
+    c.omM = fma_t(-c.e, fma_t(tau, tau, 2.0f * tau) + 2.0f, 2.0f) * it2;
+    c.omO = fma_t(-2.0f * g, it2, 1.0f);
+    c.omC = 2.0f * fma_t(c.e, tau + 2.0f, tau - 2.0f) * it2;
     c.pmt = c.psiM * it;
     c.omt = c.omM * it;
     c.oct = c.omC * it;
@@ -244,7 +255,7 @@ __host__ __device__ inline T bez_eval(const BezW<T>& w, T ym, T y0, T yp) {
   const T m = fmin(fmin(fabs(d1), fabs(d2)), T(0.25) * fabs(d1 + d2));
   // a zero difference gives m = 0, so only opposite strict signs need the test
   const T q = ((d1 > T(0)) == (d2 > T(0))) ? copysign(m, d1) : T(0);
-  return w.a * ym + w.b * y0 + w.c * yp + w.e * q;
+  return fma_t(w.e, q, dot3(w.a, ym, w.b, y0, w.c, yp));
 }
 
 // bez_eval with its partial derivatives g = d/d(ym, y0, yp), on the branches the value
@@ -411,8 +422,8 @@ __host__ __device__ inline StokesFreq<T> stokes_freq(const StokesOp<T>& k, T p) 
   StokesFreq<T> F;
   F.p = p;
   F.p2 = p * p;
-  F.inv_den = recip(T(1) + F.p2 * k.rr);
-  F.fden = recip(T(1) - F.p2 * F.inv_den * (k.ee + F.p2 * k.er2));
+  F.inv_den = recip(fma_t(F.p2, k.rr, T(1)));
+  F.fden = recip(fma_t(-(F.p2 * F.inv_den), fma_t(F.p2, k.er2, k.ee), T(1)));
   return F;
 }
 
@@ -422,31 +433,31 @@ __host__ __device__ inline void stokes_solve(const StokesOp<T>& k, const StokesF
                                              const T b[4], T x[4]) {
   const T q = SGN > 0 ? F.p : -F.p;
   const T pb0 = F.p * b[0];
-  const T c[3] = {b[1] - pb0 * k.e[0], b[2] - pb0 * k.e[1], b[3] - pb0 * k.e[2]};
-  const T cx[3] = {c[1] * k.r[2] - c[2] * k.r[1], c[2] * k.r[0] - c[0] * k.r[2],
-                   c[0] * k.r[1] - c[1] * k.r[0]};
-  const T p2cr = F.p2 * (c[0] * k.r[0] + c[1] * k.r[1] + c[2] * k.r[2]);
+  const T c[3] = {fma_t(-pb0, k.e[0], b[1]), fma_t(-pb0, k.e[1], b[2]), fma_t(-pb0, k.e[2], b[3])};
+  const T cx[3] = {fma_t(c[1], k.r[2], -(c[2] * k.r[1])), fma_t(c[2], k.r[0], -(c[0] * k.r[2])),
+                   fma_t(c[0], k.r[1], -(c[1] * k.r[0]))};
+  const T p2cr = F.p2 * dot3(c[1], k.r[1], c[0], k.r[0], c[2], k.r[2]);
   const T s = F.p * F.inv_den;
   T u[3], v[3];
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    u[i] = (c[i] - q * cx[i] + p2cr * k.r[i]) * F.inv_den;
-    v[i] = s * (k.e[i] - q * k.X[i] + F.p2 * k.C[i]);
+    u[i] = fma_t(p2cr, k.r[i], fma_t(-q, cx[i], c[i])) * F.inv_den;
+    v[i] = s * fma_t(F.p2, k.C[i], fma_t(-q, k.X[i], k.e[i]));
   }
-  const T f = F.p * (k.e[0] * u[0] + k.e[1] * u[1] + k.e[2] * u[2]) * F.fden;
-  x[1] = u[0] + f * v[0];
-  x[2] = u[1] + f * v[1];
-  x[3] = u[2] + f * v[2];
-  x[0] = b[0] - F.p * (k.e[0] * x[1] + k.e[1] * x[2] + k.e[2] * x[3]);
+  const T f = F.p * dot3(k.e[1], u[1], k.e[0], u[0], k.e[2], u[2]) * F.fden;
+  x[1] = fma_t(f, v[0], u[0]);
+  x[2] = fma_t(f, v[1], u[1]);
+  x[3] = fma_t(f, v[2], u[2]);
+  x[0] = fma_t(-F.p, dot3(k.e[1], x[2], k.e[0], x[1], k.e[2], x[3]), b[0]);
 }
 
 // K' x for the same layout (eta = e, rho = r).
 template <class T>
 __host__ __device__ inline void kprime_apply(const T e[3], const T r[3], const T x[4], T y[4]) {
-  y[0] = e[0] * x[1] + e[1] * x[2] + e[2] * x[3];
-  y[1] = e[0] * x[0] + r[2] * x[2] - r[1] * x[3];
-  y[2] = e[1] * x[0] - r[2] * x[1] + r[0] * x[3];
-  y[3] = e[2] * x[0] + r[1] * x[1] - r[0] * x[2];
+  y[0] = dot3(e[0], x[1], e[1], x[2], e[2], x[3]);
+  y[1] = dot3(e[0], x[0], r[2], x[2], -r[1], x[3]);
+  y[2] = dot3(-r[2], x[1], e[1], x[0], r[0], x[3]);
+  y[3] = dot3(e[2], x[0], r[1], x[1], -r[0], x[2]);
 }
 
 // ---------------------------------------------------------------------------
