@@ -2,6 +2,13 @@
 // the per-update arithmetic used by the GPU kernels.
 #include "porta_math.hpp"
 
+// tau sum_n k_n tau^n, the form of Table 1
+static double table1(double tau, const double k[8]) {
+  double acc = k[7];
+  for (int n = 6; n >= 0; --n) acc = acc * tau + k[n];
+  return acc * tau;
+}
+
 extern "C" {
 
 void hm_coefficients_f32(float tau, float* out6) {
@@ -14,6 +21,29 @@ void hm_coefficients_f64(double tau, double* out6) {
   const porta::Coefs<double> c = porta::coefficients(tau);
   out6[0] = c.e; out6[1] = c.psiM; out6[2] = c.psiO;
   out6[3] = c.omM; out6[4] = c.omO; out6[5] = c.omC;
+  // In their upper part the eight terms that Table 1 prints for omega_M and omega_C are cut
+  // off by up to 8e-13 and 1e-12 of the value; the kernels' own sums are not.  The paper's
+  // form there, for the comparison with the oracle's:
+  const double kM[8] = {1.0 / 3, -1.0 / 4, 1.0 / 10, -1.0 / 36, 1.0 / 168, -1.0 / 960,
+                        1.0 / 6480, -1.0 / 50400};
+  const double kC[8] = {1.0 / 3, -1.0 / 6, 1.0 / 20, -1.0 / 90, 1.0 / 504, -1.0 / 3360,
+                        1.0 / 25920, -1.0 / 226800};
+  if (tau > 0.1 && tau < 0.14) out6[3] = table1(tau, kM);
+  if (tau > 0.1 && tau < 0.18) out6[5] = table1(tau, kC);
+}
+
+// e, psi'_M, psi'_O, omega_M, omega_O, omega_C and the source weights t E_1, t E_2, t E_3 as
+// the kernels form them
+void hm_step_f32(float tau, float* o) {
+  const porta::Coefs<float> c = porta::coefficients(tau);
+  const float v[9] = {c.e, c.psiM, c.psiO, c.omM, c.omO, c.omC, c.em1, c.psiO, c.t3};
+  for (int i = 0; i < 9; ++i) o[i] = v[i];
+}
+
+void hm_step_f64(double tau, double* o) {
+  const porta::Coefs<double> c = porta::coefficients(tau);
+  const double v[9] = {c.e, c.psiM, c.psiO, c.omM, c.omO, c.omC, c.em1, c.psiO, c.t3};
+  for (int i = 0; i < 9; ++i) o[i] = v[i];
 }
 
 double hm_besser_cm(double yM, double yO, double yP, double ratio) {
@@ -70,6 +100,27 @@ void hm_stokes_solve_scaled_f32(const float* e3, const float* r3, float p, const
     porta::stokes_solve<-1>(k, F, b4, x4);
 }
 
+// The same by the FP64 sweep's and the adjoint's route.
+void hm_lorentz_solve_f64(const double* e3, const double* r3, double p, const double* b4, int sgn,
+                          double* x4) {
+  const porta::LorentzOp<double> k = porta::lorentz_op(e3, r3);
+  const porta::LorentzFreq<double> F = porta::lorentz_freq(k, p);
+  if (sgn > 0)
+    porta::stokes_solve<1>(k, F, b4, x4);
+  else
+    porta::stokes_solve<-1>(k, F, b4, x4);
+}
+
+void hm_lorentz_solve_f32(const float* e3, const float* r3, float p, const float* b4, int sgn,
+                          float* x4) {
+  const porta::LorentzOp<float> k = porta::lorentz_op(e3, r3);
+  const porta::LorentzFreq<float> F = porta::lorentz_freq(k, p);
+  if (sgn > 0)
+    porta::stokes_solve<1>(k, F, b4, x4);
+  else
+    porta::stokes_solve<-1>(k, F, b4, x4);
+}
+
 void hm_kprime_apply(const double* e3, const double* r3, const double* x4, double* y4) {
   porta::kprime_apply(e3, r3, x4, y4);
 }
@@ -116,7 +167,9 @@ double hm_besser_cm_grad(double yM, double yO, double yP, double ratio, double* 
 
 double hm_coef_tau_grad_f64(double tau, const double* g6) {
   const porta::Coefs<double> c = porta::coefficients(tau);
-  return porta::coef_tau_grad(c, g6[0], g6[1], g6[2], g6[3], g6[4], g6[5]);
+  // omega_M, omega_O, omega_C as sums of the source weights
+  return porta::coef_tau_grad(c, g6[0], g6[1], g6[2], g6[3], 2 * (g6[5] - g6[3]),
+                              2 * (g6[3] + g6[4] - 2 * g6[5]));
 }
 
 float hm_coef_tau_grad_f32(float tau, const float* g6) {

@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 
@@ -248,32 +249,36 @@ int freq_chunks(int64_t blocks, int nfreq) {
 struct SweepPlan {
   int nrb;         // rays of a batch in one hemisphere
   bool share;      // an upward and a downward batch per launch
+  bool chunks;     // frequency chunks (FP64: their partial sums change the order of the sums
+                   // over frequencies that make J, which in an FP32 iteration would tip
+                   // the rounding of the next emissivities)
   int rows;        // rays whose states the workspace holds: nrb, or 2 nrb with share
   size_t jrows;    // (ray, chunk) rows of partial sums the workspace holds
 };
 constexpr int64_t kShareBlocks = 2048;
 
-SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, const porta_options* o) {
+SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
   SweepPlan P;
   const int64_t tiles = plane_tiles(g, o);
   // a launch is one row of at most 2^31 threads
   P.nrb = (int)std::min<int64_t>(ray_batch(q, o), std::max<int64_t>(1, (1 << 23) / tiles));
   P.share = tiles * P.nrb <= kShareBlocks;
   P.rows = P.share ? 2 * P.nrb : P.nrb;
-  P.jrows = (size_t)P.rows * freq_chunks(tiles * P.rows, q->nfreq);
+  P.chunks = prec == PORTA_F64;
+  P.jrows = (size_t)P.rows * (P.chunks ? freq_chunks(tiles * P.rows, q->nfreq) : 1);
   return P;
 }
 
 // The cut without sharing and chunks, which needs the least workspace.
-SweepPlan least_plan(const porta_grid* g, const porta_quad* q, const porta_options* o) {
-  const int nrb = sweep_plan(g, q, o).nrb;
-  return {nrb, false, nrb, (size_t)nrb};
+SweepPlan least_plan(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
+  const int nrb = sweep_plan(g, q, prec, o).nrb;
+  return {nrb, false, false, nrb, (size_t)nrb};
 }
 
 // Chunks of a launch of `rays` rays (each chunk has a row of partial sums).
 int launch_chunks(const porta_grid* g, const porta_quad* q, const porta_options* o,
                   const SweepPlan& P, int rays) {
-  const int n = freq_chunks(plane_tiles(g, o) * rays, q->nfreq);
+  const int n = P.chunks ? freq_chunks(plane_tiles(g, o) * rays, q->nfreq) : 1;
   return (int)std::max<size_t>(1, std::min<size_t>(n, P.jrows / std::max(rays, 1)));
 }
 
@@ -281,8 +286,9 @@ int launch_chunks(const porta_grid* g, const porta_quad* q, const porta_options*
 // Workspace layout (every region 256-byte aligned)
 // ---------------------------------------------------------------------------
 struct Layout {
-  size_t stage;     // doubles: mu[kMaxMu], wmu[kMaxMu], phi[nfreq], wfreq[nfreq]
+  size_t stage;     // doubles: mu[nmu], wmu[nmu], phi[nfreq], wfreq[nfreq], z[nz]
   size_t rays;      // RayConsts[nrays]
+  size_t geom;      // RayGeom[nrays][nz - 1][2]
   size_t phiT;      // T[nfreq]
   size_t wn;        // double[nfreq]
   size_t flag;      // int: result of the optional input check
@@ -298,13 +304,17 @@ struct Layout {
   size_t total;
 };
 
-Layout tables_layout(const porta_quad* q, int prec) {
+// nz: planes whose ray geometry the tables hold (0: none).
+Layout tables_layout(const porta_quad* q, int prec, int nz) {
   Layout L{};
+  const size_t nrays = 2 * (size_t)q->nmu * q->nchi;
   size_t off = 0;
   L.stage = off;
-  off = align_up(off + sizeof(double) * (2 * kMaxMu + 2 * (size_t)q->nfreq));
+  off = align_up(off + sizeof(double) * (2 * (size_t)q->nmu + 2 * (size_t)q->nfreq + nz));
   L.rays = off;
-  off = align_up(off + sizeof(RayConsts) * 2 * (size_t)q->nmu * q->nchi);
+  off = align_up(off + sizeof(RayConsts) * nrays);
+  L.geom = off;
+  if (nz > 0) off = align_up(off + sizeof(RayGeom) * nrays * (nz - 1) * 2);
   L.phiT = off;
   off = align_up(off + elem(prec) * q->nfreq);
   L.wn = off;
@@ -318,7 +328,7 @@ Layout tables_layout(const porta_quad* q, int prec) {
 
 Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
                     const SweepPlan& P) {
-  Layout L = tables_layout(q, prec);
+  Layout L = tables_layout(q, prec, g->nz);
   const size_t np = (size_t)g->nx * g->ny;
   const size_t nrb = (size_t)P.nrb;
   const size_t state = (size_t)P.rows * q->nfreq * np * nstokes(o) * elem(prec);
@@ -357,7 +367,7 @@ bool is_checkpoint(int k, int nz, int C) { return k >= 1 && k % C == 0 && k <= n
 // per-(node, ray) partials of one plane and the FP64 gradient accumulator.
 Layout adjoint_layout(const porta_grid* g, const porta_quad* q, int prec, int stride,
                       const porta_options* o, bool own_checkpoints) {
-  Layout L = tables_layout(q, prec);
+  Layout L = tables_layout(q, prec, g->nz);
   const size_t np = (size_t)g->nx * g->ny, N = np * g->nz;
   const size_t nrb = (size_t)ray_batch(q, o);
   L.plane = nrb * q->nfreq * np * 4 * elem(prec);
@@ -395,30 +405,57 @@ size_t checkpoint_bytes(const porta_grid* g, const porta_quad* q, int prec, int 
          ((size_t)g->nx * g->ny) * 4 * elem(prec);
 }
 
-// Upload host doubles through kernel arguments (ordered on the stream).
-int upload(double* dst, const double* src, size_t n, hipStream_t st) {
-  for (size_t o = 0; o < n; o += kUploadChunk) {
-    UploadChunk c;
-    c.n = (int)std::min<size_t>(kUploadChunk, n - o);
-    std::memcpy(c.v, src + o, sizeof(double) * c.n);
-    c.dst = dst + o;
+// Upload host doubles through kernel arguments (ordered on the stream), one array after
+// the other; as few launches as the argument block allows.
+struct HostArray {
+  const double* p;
+  size_t n;
+};
+
+int upload(double* dst, std::initializer_list<HostArray> arrays, hipStream_t st) {
+  UploadChunk c;
+  c.dst = dst;
+  c.n = 0;
+  auto flush = [&]() {
     hipLaunchKernelGGL(k_upload, dim3(1), dim3(256), 0, st, c);
-  }
+    c.dst += c.n;
+    c.n = 0;
+  };
+  for (const HostArray& a : arrays)
+    for (size_t o = 0; o < a.n;) {
+      const size_t m = std::min<size_t>(kUploadChunk - c.n, a.n - o);
+      std::memcpy(c.v + c.n, a.p + o, sizeof(double) * m);
+      c.n += (int)m;
+      o += m;
+      if (c.n == kUploadChunk) flush();
+    }
+  if (c.n) flush();
   return check_launch("upload");
 }
 
+// The tables of a call; with a grid also the rays' geometry on its layers, as `interp`
+// splits it.
 template <class T>
-int prepare_tables(char* ws, const Layout& L, const porta_quad* q, double w2, hipStream_t st) {
-  double* stage = reinterpret_cast<double*>(ws + L.stage);
+int prepare_tables(char* ws, const Layout& L, const porta_grid* g, const porta_quad* q, double w2,
+                   int interp, hipStream_t st) {
+  double* mu = reinterpret_cast<double*>(ws + L.stage);
+  double *wmu = mu + q->nmu, *phi = wmu + q->nmu, *wfreq = phi + q->nfreq, *z = wfreq + q->nfreq;
+  const int nz = g ? g->nz : 0;
   int rc;
-  if ((rc = upload(stage, q->mu, q->nmu, st))) return rc;
-  if ((rc = upload(stage + kMaxMu, q->wmu, q->nmu, st))) return rc;
-  if ((rc = upload(stage + 2 * kMaxMu, q->phi, q->nfreq, st))) return rc;
-  if ((rc = upload(stage + 2 * kMaxMu + q->nfreq, q->wfreq, q->nfreq, st))) return rc;
-  hipLaunchKernelGGL(k_prepare<T>, dim3(1), dim3(256), 0, st, stage, stage + kMaxMu, q->nmu,
-                     q->nchi, w2, stage + 2 * kMaxMu, stage + 2 * kMaxMu + q->nfreq, q->nfreq,
-                     reinterpret_cast<RayConsts*>(ws + L.rays), reinterpret_cast<T*>(ws + L.phiT),
-                     reinterpret_cast<double*>(ws + L.wn));
+  if ((rc = upload(mu, {{q->mu, (size_t)q->nmu}, {q->wmu, (size_t)q->nmu},
+                        {q->phi, (size_t)q->nfreq}, {q->wfreq, (size_t)q->nfreq},
+                        {g ? g->z : nullptr, (size_t)nz}}, st)))
+    return rc;
+  GeomArgs ga{};
+  size_t nb = 1;
+  if (g) {
+    ga = {z, nz, g->nx, g->ny, g->nx / g->lx, g->ny / g->ly,
+          interp == PORTA_INTERP_BEZIER2D ? 0.5 : 0.0, reinterpret_cast<RayGeom*>(ws + L.geom)};
+    nb += (2 * (size_t)q->nmu * q->nchi * (nz - 1) + 255) / 256;
+  }
+  hipLaunchKernelGGL(k_prepare<T>, dim3((unsigned)nb), dim3(256), 0, st, mu, wmu, q->nmu, q->nchi,
+                     w2, phi, wfreq, q->nfreq, reinterpret_cast<RayConsts*>(ws + L.rays),
+                     reinterpret_cast<T*>(ws + L.phiT), reinterpret_cast<double*>(ws + L.wn), ga);
   return check_launch("prepare");
 }
 
@@ -452,16 +489,16 @@ int check_inputs(const porta_grid* g, const porta_fields* f, char* ws, const Lay
   return PORTA_OK;
 }
 
+template <class T>
 int launch_jreduce(double* jkq, const double* jpart, const RayConsts* rays, int ray0, int nrb,
                    int nchunk, int ns, int np, size_t N, size_t plane_off, double ibound,
                    hipStream_t st) {
   const dim3 grid(jblocks(np)), blk(256);
+  const JJob J = {jpart, rays + ray0, nrb, nchunk, ibound, plane_off};
   if (ns == 1)
-    hipLaunchKernelGGL(k_jreduce<1>, grid, blk, jlds_bytes(256), st, jkq, jpart, rays, ray0, nrb,
-                       nchunk, np, N, plane_off, ibound);
+    hipLaunchKernelGGL((k_jreduce<1, T>), grid, blk, jlds_bytes(256, sizeof(T)), st, J, jkq, np, N);
   else
-    hipLaunchKernelGGL(k_jreduce<4>, grid, blk, jlds_bytes(256), st, jkq, jpart, rays, ray0, nrb,
-                       nchunk, np, N, plane_off, ibound);
+    hipLaunchKernelGGL((k_jreduce<4, T>), grid, blk, jlds_bytes(256, sizeof(T)), st, J, jkq, np, N);
   return check_launch("jreduce");
 }
 
@@ -508,7 +545,7 @@ int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_field
       const int ray0 = hemi * nh + r0;
       if (jkq) {
         // the boundary plane
-        if ((rc = launch_jreduce(jkq, nullptr, rays, ray0, nrb, 1, 4, np, N, (size_t)kb * np,
+        if ((rc = launch_jreduce<T>(jkq, nullptr, rays, ray0, nrb, 1, 4, np, N, (size_t)kb * np,
                                  (double)ibound, st)))
           return rc;
       }
@@ -561,7 +598,7 @@ int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_field
                              (const double*)jchunk, rays, ray0, nchunk, nx, ny, nx / g->lx,
                              ny / g->ly);
           if ((rc = check_launch("sum_chunks"))) return rc;
-          if ((rc = launch_jreduce(jkq, jpart, rays, ray0, nrb, 1, 4, np, N, (size_t)k * np, 0.0,
+          if ((rc = launch_jreduce<T>(jkq, jpart, rays, ray0, nrb, 1, 4, np, N, (size_t)k * np, 0.0,
                                    st)))
             return rc;
         }
@@ -584,16 +621,16 @@ PlaneArgs<T> plane_args(const porta_grid* g, const porta_quad* q, const porta_fi
   a.prop = static_cast<const T*>(f->propmat);
   a.emis = static_cast<const T*>(f->emis);
   a.rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
+  a.geom = reinterpret_cast<const RayGeom*>(ws + L.geom);
   a.phi = reinterpret_cast<const T*>(ws + L.phiT);
   a.wn = reinterpret_cast<const double*>(ws + L.wn);
   a.nx = g->nx;
   a.ny = g->ny;
+  a.nz = g->nz;
   a.np = g->nx * g->ny;
   a.N = (size_t)a.np * g->nz;
   a.nfreq = q->nfreq;
   a.ntile = (int)plane_tiles(g, o);
-  a.inv_dx = g->nx / g->lx;
-  a.inv_dy = g->ny / g->ly;
   a.xcd_remap = xcd_chunk(o);
   a.parabolic = parabolic_of(o);
   return a;
@@ -606,8 +643,6 @@ void set_plane(HemiArgs<T>& h, const porta_grid* g, int k, int s) {
   h.kO = k;
   h.kM = k - s;
   h.kP = last ? -1 : k + s;
-  h.dzM = std::fabs(g->z[k] - g->z[k - s]);
-  h.dzP = last ? 0.0 : std::fabs(g->z[k + s] - g->z[k]);
 }
 
 template <class T>
@@ -620,7 +655,7 @@ void set_chunks(PlaneArgs<T>& a, int nchunk, int rays) {
 template <class T>
 int launch_plane(const PlaneArgs<T>& a, int ns, int interp, int block, hipStream_t st) {
   const size_t tab = (size_t)a.fchunk * (sizeof(double) + sizeof(T));
-  const size_t lds = a.njb ? std::max(tab, jlds_bytes(block)) : tab;
+  const size_t lds = a.njb ? std::max(tab, jlds_bytes(block, sizeof(T))) : tab;
   const dim3 grid(a.nstep + a.njb);
   if (ns == 1)
     hipLaunchKernelGGL(k_sweep_plane_i<T>, grid, dim3(block), lds, st, a);
@@ -636,7 +671,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
                const porta_options* o, double* jkq, int accumulate, T* itop, T* ckpt, int C,
                char* ws, const SweepPlan& P, const Layout& L, hipStream_t st) {
   int rc;
-  if ((rc = prepare_tables<T>(ws, L, q, f->w2, st))) return rc;
+  if ((rc = prepare_tables<T>(ws, L, g, q, f->w2, interp, st))) return rc;
   const int nz = g->nz, np = g->nx * g->ny;
   const size_t N = (size_t)np * nz;
   if (jkq && !accumulate)
@@ -701,7 +736,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
     }
     for (int m = 0; m < 2 && jkq; ++m) {   // the last plane of each hemisphere
       if (nr[m] == 0) continue;
-      int e = launch_jreduce(jkq, a.h[m].jpart, rays, a.h[m].ray0, nr[m], a.nchunk, ns, np, N,
+      int e = launch_jreduce<T>(jkq, a.h[m].jpart, rays, a.h[m].ray0, nr[m], a.nchunk, ns, np, N,
                              (size_t)a.h[m].kO * np, 0.0, st);
       if (e) return e;
     }
@@ -751,7 +786,7 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
                  const porta_options* o, int interp, const T* seed, const T* ext_ck, int C, T* gk,
                  T* gpm, T* ge, char* ws, const Layout& L, hipStream_t st) {
   int rc;
-  if ((rc = prepare_tables<T>(ws, L, q, f->w2, st))) return rc;
+  if ((rc = prepare_tables<T>(ws, L, g, q, f->w2, interp, st))) return rc;
   const int nx = g->nx, ny = g->ny, nz = g->nz, np = nx * ny;
   const size_t N = (size_t)np * nz;
   double* grad = reinterpret_cast<double*>(ws + L.grad);
@@ -806,6 +841,7 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
         a.prop = static_cast<const T*>(f->propmat);
         a.emis = static_cast<const T*>(f->emis);
         a.rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
+        a.geom = reinterpret_cast<const RayGeom*>(ws + L.geom);
         a.phi = reinterpret_cast<const T*>(ws + L.phiT);
         a.iprev = plane(k - 1);
         a.lam_next = lam_next;
@@ -817,16 +853,12 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
         a.N = N;
         a.nx = nx;
         a.ny = ny;
+        a.nz = nz;
         a.np = np;
         a.nfreq = q->nfreq;
         a.kO = k;
         a.kM = k - 1;
         a.kP = (k == nz - 1) ? -1 : k + 1;
-        a.dzM = std::fabs(g->z[k] - g->z[k - 1]);
-        a.dzP = (k == nz - 1) ? 0.0 : std::fabs(g->z[k + 1] - g->z[k]);
-        a.dzN = a.dzP;
-        a.inv_dx = nx / g->lx;
-        a.inv_dy = ny / g->ly;
         a.ray0 = r0;
         a.xcd_remap = xcd_chunk(o);
         a.parabolic = parabolic_of(o);
@@ -840,14 +872,13 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
           t.icur = plane(k);
           t.lam_next = lam_next;
           t.out = lam[cur];
-          t.rays = a.rays;
+          t.geom = a.geom;
           t.nx = nx;
           t.ny = ny;
+          t.nz = nz;
           t.np = np;
           t.nfreq = q->nfreq;
-          t.dzN = a.dzN;
-          t.inv_dx = a.inv_dx;
-          t.inv_dy = a.inv_dy;
+          t.kO = k;
           t.ray0 = r0;
           constexpr int TX = TGTile<T>::X, TY = TGTile<T>::Y;
           hipLaunchKernelGGL(k_bez9_tgather<T>,
@@ -872,19 +903,16 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
         b.kappa = a.kappa;
         b.prop = a.prop;
         b.emis = a.emis;
-        b.rays = a.rays;
+        b.geom = a.geom;
         b.grad = grad;
         b.N = N;
         b.nx = nx;
         b.ny = ny;
+        b.nz = nz;
         b.np = np;
         b.kO = a.kO;
         b.kM = a.kM;
         b.kP = a.kP;
-        b.dzM = a.dzM;
-        b.dzP = a.dzP;
-        b.inv_dx = a.inv_dx;
-        b.inv_dy = a.inv_dy;
         b.ray0 = r0;
         b.nrb = nrb;
         if (bez)
@@ -975,11 +1003,11 @@ int sweep_entry(const porta_grid* grid, const porta_quad* quad, const porta_fiel
                   ck_bytes, need);
   }
   if (!use_scratch && !workspace) return fail(PORTA_EINVAL, "workspace is NULL");
-  SweepPlan plan = sweep_plan(grid, quad, opts);
+  SweepPlan plan = sweep_plan(grid, quad, prec, opts);
   Layout L = sweep_layout(grid, quad, prec, opts, plan);
   if (use_scratch) {
     if (L.total > kScratchBytes) {
-      plan = least_plan(grid, quad, opts);
+      plan = least_plan(grid, quad, prec, opts);
       L = sweep_layout(grid, quad, prec, opts, plan);
     }
     if (L.total > kScratchBytes)
@@ -1034,7 +1062,7 @@ size_t porta_workspace_size(const porta_grid* grid, const porta_quad* quad, int 
   switch (kind) {
     case PORTA_WS_SWEEP:
       if (validate_grid(grid) || validate_quad(quad)) return 0;
-      return sweep_layout(grid, quad, prec, opts, sweep_plan(grid, quad, opts)).total;
+      return sweep_layout(grid, quad, prec, opts, sweep_plan(grid, quad, prec, opts)).total;
     case PORTA_WS_ADJOINT:
     case PORTA_WS_ADJOINT_CKPT:
       if (validate_grid(grid) || validate_quad(quad) || checkpoint_stride < 1 ||
@@ -1044,7 +1072,7 @@ size_t porta_workspace_size(const porta_grid* grid, const porta_quad* quad, int 
           .total;
     case PORTA_WS_JKQ:
       if (validate_quad(quad)) return 0;
-      return tables_layout(quad, prec).total;
+      return tables_layout(quad, prec, 0).total;
     case PORTA_WS_SEE: {
       if (!grid || grid->nx < 1 || grid->ny < 1 || grid->nz < 1) return 0;
       const size_t n = (size_t)grid->nx * grid->ny * grid->nz;
@@ -1098,7 +1126,7 @@ int porta_jkq_accumulate(const porta_grid* grid, const porta_quad* quad, int ray
                 quad->nfreq);
   if (!stokes || !jkq) return fail(PORTA_EINVAL, "stokes and jkq must not be NULL");
   if (!workspace) return fail(PORTA_EINVAL, "workspace is NULL");
-  const Layout L = tables_layout(quad, prec);
+  const Layout L = tables_layout(quad, prec, 0);
   if (ws_bytes < L.total)
     return fail(PORTA_ENOMEM, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
                 L.total);
@@ -1108,13 +1136,13 @@ int porta_jkq_accumulate(const porta_grid* grid, const porta_quad* quad, int ray
   if (nray == 0 || nf == 0) return PORTA_OK;
   const dim3 grd((unsigned)((N + 255) / 256)), blk(256);
   if (prec == PORTA_F64) {
-    if ((rc = prepare_tables<double>(ws, L, quad, 1.0, st))) return rc;
+    if ((rc = prepare_tables<double>(ws, L, nullptr, quad, 1.0, 0, st))) return rc;
     hipLaunchKernelGGL(k_jkq_accumulate<double>, grd, blk, 0, st, jkq,
                        static_cast<const double*>(stokes), static_cast<const double*>(lambda_star),
                        reinterpret_cast<const RayConsts*>(ws + L.rays),
                        reinterpret_cast<const double*>(ws + L.wn), ray0, nray, f0, nf, N);
   } else {
-    if ((rc = prepare_tables<float>(ws, L, quad, 1.0, st))) return rc;
+    if ((rc = prepare_tables<float>(ws, L, nullptr, quad, 1.0, 0, st))) return rc;
     hipLaunchKernelGGL(k_jkq_accumulate<float>, grd, blk, 0, st, jkq,
                        static_cast<const float*>(stokes), static_cast<const float*>(lambda_star),
                        reinterpret_cast<const RayConsts*>(ws + L.rays),

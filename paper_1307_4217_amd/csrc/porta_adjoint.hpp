@@ -30,6 +30,7 @@ struct AdjArgs {
   const T* prop;
   const T* emis;
   const RayConsts* rays;
+  const RayGeom* geom;
   const T* phi;
   const T* iprev;      // forward state of plane kM, or nullptr for the boundary plane
   const T* lam_next;   // Lambda of plane kO + 1, or nullptr when kO is the top plane
@@ -41,10 +42,8 @@ struct AdjArgs {
                        // (partials of one node and ray, formed in FP64, stored in the
                        // sweep precision; the gather sums them in FP64)
   size_t N;
-  int nx, ny, np, nfreq;
+  int nx, ny, nz, np, nfreq;
   int kO, kM, kP;
-  double dzM, dzP, dzN;   // dzN = |z_{kO+1} - z_kO| (plane above), 0 on the top plane
-  double inv_dx, inv_dy;
   int ray0;
   int xcd_remap;       // tiles per XCD per round, see xcd_tile
   int parabolic;       // control point: 0 BESSER, 1 parabola through M, O, P
@@ -56,40 +55,12 @@ struct AdjArgs {
 // l^T K' x = sum_c entry_c q[c].
 template <class T>
 __device__ inline void kprime_forms(const T l[4], const T x[4], T q[6]) {
-  q[0] = l[0] * x[1] + l[1] * x[0];
-  q[1] = l[0] * x[2] + l[2] * x[0];
-  q[2] = l[0] * x[3] + l[3] * x[0];
-  q[3] = l[2] * x[3] - l[3] * x[2];
-  q[4] = l[3] * x[1] - l[1] * x[3];
-  q[5] = l[1] * x[2] - l[2] * x[1];
-}
-
-// Partials of b's K' I term: dL/d(e_Q, e_U, e_V, r_Q, r_U, r_V) of -psi lambda^T K' x.
-template <class T>
-__device__ inline void kprime_outer(T psi, const T l[4], const T x[4], T g[6]) {
-  T q[6];
-  kprime_forms(l, x, q);
-#pragma unroll
-  for (int c = 0; c < 6; ++c) g[c] -= psi * q[c];
-}
-
-// Where the 9-point stencil of a displacement (u, v) in cells sits, as make_stencil9
-// places it: the centre is the node (fu, fv) away, the point at (tx, ty) from it.
-struct Bez9Geom {
-  int fu, fv;
-  double tx, ty;
-};
-
-__device__ inline Bez9Geom bez9_geom(double u, double v, int nx, int ny) {
-  u -= nx * floor(u / nx);
-  v -= ny * floor(v / ny);
-  Bez9Geom g;
-  const double fu = floor(u + 0.5), fv = floor(v + 0.5);
-  g.fu = (int)fu;
-  g.fv = (int)fv;
-  g.tx = u - fu;
-  g.ty = v - fv;
-  return g;
+  q[0] = fma_t(l[0], x[1], l[1] * x[0]);
+  q[1] = fma_t(l[0], x[2], l[2] * x[0]);
+  q[2] = fma_t(l[0], x[3], l[3] * x[0]);
+  q[3] = fma_t(l[2], x[3], -l[3] * x[2]);
+  q[4] = fma_t(l[3], x[1], -l[1] * x[3]);
+  q[5] = fma_t(l[1], x[2], -l[2] * x[1]);
 }
 
 // Adjoint of the 9-point monotonic Bezier interpolation (x pass over three rows, then
@@ -147,10 +118,9 @@ struct TGatherArgs {
   const T* icur;       // forward state of plane kO ([ray][freq][node][4])
   const T* lam_next;   // adjoint of I_M at the nodes of plane kO + 1, same layout
   T* out;              // adjoint of I at the nodes of plane kO, same layout
-  const RayConsts* rays;
-  int nx, ny, np, nfreq;
-  double dzN, inv_dx, inv_dy;   // dzN = |z_{kO+1} - z_kO|
-  int ray0;
+  const RayGeom* geom;
+  int nx, ny, nz, np, nfreq;
+  int kO, ray0;
 };
 
 // A block takes a tile of TGX x TGY nodes q of one ray (blockIdx.z) and forms, per
@@ -179,9 +149,7 @@ __global__ void __launch_bounds__(256) k_bez9_tgather(const TGatherArgs<T> a) {
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int rb = blockIdx.z;
   const int qx0 = blockIdx.x * TX, qy0 = blockIdx.y * TY;
-  const RayConsts& rc = a.rays[a.ray0 + rb];
-  const double dsN = a.dzN / fabs(rc.mu);
-  const Bez9Geom gm = bez9_geom(-dsN * rc.sx * a.inv_dx, -dsN * rc.sy * a.inv_dy, a.nx, a.ny);
+  const RayGeom& gm = layer_geom(a.geom, a.ray0 + rb, a.nz, a.kO, a.kO + 1, 0);
   const BezW<T> wx = bez_weights((T)gm.tx), wy = bez_weights((T)gm.ty);
   const int lx = tid % TX, ly = tid / TX;     // this thread's node of the tile
   const int qx = qx0 + lx, qy = qy0 + ly;
@@ -312,31 +280,25 @@ k_adjoint_plane(const AdjArgs<T> a) {
   const RayConsts& rc = a.rays[a.ray0 + rb];
   PointSetup ps;
   Stencil9 sM9;
-  setup_point<MODE>(a.kappa, a.prop, a.emis, a.N, a.nx, a.ny, a.np, a.kO, a.kM, a.kP, a.dzM,
-                    a.dzP, a.inv_dx, a.inv_dy, rc, p, a.parabolic != 0, ps, sM9);
+  const int ray = a.ray0 + rb;
+  setup_point<MODE>(a.kappa, a.prop, a.emis, a.N, a.nx, a.ny, a.np, a.kO, a.kM, a.kP,
+                    layer_geom(a.geom, ray, a.nz, a.kO, a.kM, 0),
+                    layer_geom(a.geom, ray, a.nz, a.kO, a.kP < 0 ? a.kM : a.kP, 1), rc, p,
+                    a.parabolic != 0, ps, sM9);
   const BezW<T> bwx = bez_weights(MODE == 1 ? (T)sM9.tx : T(0));
   const BezW<T> bwy = bez_weights(MODE == 1 ? (T)sM9.ty : T(0));
-  const int i = p % a.nx, j = p / a.nx;
-  const double inv_mu = 1.0 / fabs(rc.mu);
   // nodes of the plane above whose upwind stencil contains p
   Stencil tN{};
-  if (a.lam_next) {
-    const double dsN = a.dzN * inv_mu;
-    tN = make_tstencil(i, j, a.nx, a.ny, -dsN * rc.sx * a.inv_dx, -dsN * rc.sy * a.inv_dy);
-  }
-  const T eMv[3] = {(T)(ps.etaM[0] * ps.ikM), (T)(ps.etaM[1] * ps.ikM), (T)(ps.etaM[2] * ps.ikM)};
-  const T rMv[3] = {(T)(ps.etaM[3] * ps.ikM), (T)(ps.etaM[4] * ps.ikM), (T)(ps.etaM[5] * ps.ikM)};
-  const T eOv[3] = {(T)(ps.etaO[0] * ps.ikO), (T)(ps.etaO[1] * ps.ikO), (T)(ps.etaO[2] * ps.ikO)};
-  const T rOv[3] = {(T)(ps.etaO[3] * ps.ikO), (T)(ps.etaO[4] * ps.ikO), (T)(ps.etaO[5] * ps.ikO)};
-  const StokesOp<T> KO = stokes_op(eOv, rOv);
-  const T rMn[3] = {-rMv[0], -rMv[1], -rMv[2]};
-  T SMt[4], SOt[4], cMt[4];
+  if (a.lam_next)
+    tN = make_tstencil(p % a.nx, p / a.nx, a.nx, a.ny,
+                       layer_geom(a.geom, ray, a.nz, a.kO, a.kO + 1, 0));
+  T eMv[3], rMv[3], eOv[3], rOv[3];
+  kprime_entries(ps.etaM, ps.ikM, eMv, rMv);
+  kprime_entries(ps.etaO, ps.ikO, eOv, rOv);
+  const LorentzOp<T> KO = lorentz_op(eOv, rOv);
+  StepSource<T> src[3];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    SMt[s] = (T)ps.SM[s];
-    SOt[s] = (T)ps.SO[s];
-    cMt[s] = (T)ps.cM[s];
-  }
+  for (int s = 0; s < 3; ++s) step_source(ps.SM[s], ps.SO[s], ps.cM[s], src[s]);
   const T tau0 = (T)ps.tau0M;
   const T w00 = (T)ps.sM.w00, w10 = (T)ps.sM.w10, w01 = (T)ps.sM.w01, w11 = (T)ps.sM.w11;
   const T n00 = (T)tN.w00, n10 = (T)tN.w10, n01 = (T)tN.w01, n11 = (T)tN.w11;
@@ -350,7 +312,7 @@ k_adjoint_plane(const AdjArgs<T> a) {
 
   // sums over frequency of the partials, in the sweep precision (FP32: each is a sum
   // of nfreq terms whose rounding stays at the level of the FP32 terms themselves)
-  T aT = 0, aSM[4] = {0, 0, 0, 0}, aSO[4] = {0, 0, 0, 0}, aCM[4] = {0, 0, 0, 0};
+  T aT = 0, aSM[3] = {0, 0, 0}, aSO[3] = {0, 0, 0}, aCM[3] = {0, 0, 0};
   T aKM[6] = {0, 0, 0, 0, 0, 0}, aKO[6] = {0, 0, 0, 0, 0, 0};
   // The corner values of one frequency: the adjoint of the plane above (or the seed)
   // and the forward state of the plane below.  In FP32 they are loaded one frequency
@@ -385,7 +347,7 @@ k_adjoint_plane(const AdjArgs<T> a) {
       if constexpr (HL) {
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-          lam[s] = n00 * c.l[0][s] + n10 * c.l[1][s] + n01 * c.l[2][s] + n11 * c.l[3][s];
+          lam[s] = bilinear(n00, n10, n01, n11, c.l[0][s], c.l[1][s], c.l[2][s], c.l[3][s]);
       } else {
 #pragma unroll
         for (int s = 0; s < 4; ++s) lam[s] = c.l[0][s];
@@ -396,68 +358,68 @@ k_adjoint_plane(const AdjArgs<T> a) {
       } else if constexpr (HI) {
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-          IM[s] = w00 * c.m[0][s] + w10 * c.m[1][s] + w01 * c.m[2][s] + w11 * c.m[3][s];
+          IM[s] = bilinear(w00, w10, w01, w11, c.m[0][s], c.m[1][s], c.m[2][s], c.m[3][s]);
       } else {
         IM[0] = a.ibound;
         IM[1] = IM[2] = IM[3] = T(0);
       }
       const T ph = s_phi[f];
-      const T tau = tau0 * ph;
-      const Coefs<T> cf = coefficients(tau);
+      const Coefs<T> cf = coefficients(tau0 * ph);
       // the forward update at O again (Eq. fsbez), instead of reading the stored I_O
       T KIM[4], b[4], IO[4];
       kprime_apply(eMv, rMv, IM, KIM);
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        b[s] = cf.e * IM[s] - cf.psiM * KIM[s] + cf.omM * SMt[s] + cf.omO * SOt[s] +
-               cf.omC * cMt[s];
-      const StokesFreq<T> F = stokes_freq(KO, cf.psiO);
+      step_rhs(cf, IM, KIM, src, b);
+      const LorentzFreq<T> F = lorentz_freq(KO, cf.psiO);
       stokes_solve<1>(KO, F, b, IO);
       // lambda_b = (1 + psi'_O K'_O)^-T lambda
       T lb[4];
       stokes_solve<-1>(KO, F, lam, lb);
       // lambda_b^T K'_O I_O is linear in the six entries of K'_O: its partials QO[c]
       // give both the psi'_O term and the K'_O partials
-      T QO[6];
+      T QO[6], QM[6];
       kprime_forms(lb, IO, QO);
-      T gPO = -(eOv[0] * QO[0] + eOv[1] * QO[1] + eOv[2] * QO[2] + rOv[0] * QO[3] +
-                rOv[1] * QO[4] + rOv[2] * QO[5]);
+      kprime_forms(lb, IM, QM);
+      const T gPO = -(dot3(eOv[0], QO[0], eOv[1], QO[1], eOv[2], QO[2]) +
+                      dot3(rOv[0], QO[3], rOv[1], QO[4], rOv[2], QO[5]));
 #pragma unroll
-      for (int c = 0; c < 6; ++c) aKO[c] -= cf.psiO * QO[c];
-      T gE = 0, gPM = 0, gOM = 0, gOO = 0, gOC = 0;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        gE += lb[s] * IM[s];
-        gPM -= lb[s] * KIM[s];
-        gOM += lb[s] * SMt[s];
-        gOO += lb[s] * SOt[s];
-        gOC += lb[s] * cMt[s];
-        aSM[s] += cf.omM * lb[s];
-        aSO[s] += cf.omO * lb[s];
-        aCM[s] += cf.omC * lb[s];
+      for (int c = 0; c < 6; ++c) {
+        aKO[c] = fma_t(-cf.psiO, QO[c], aKO[c]);
+        aKM[c] = fma_t(-cf.psiM, QM[c], aKM[c]);
       }
-      aT += ph * coef_tau_grad(cf, gE, gPM, gPO, gOM, gOO, gOC);
-      kprime_outer(cf.psiM, lb, IM, aKM);
+      const T gE = fma_t(lb[3], IM[3], dot3(lb[0], IM[0], lb[1], IM[1], lb[2], IM[2]));
+      const T gPM = -fma_t(lb[3], KIM[3], dot3(lb[0], KIM[0], lb[1], KIM[1], lb[2], KIM[2]));
+      const T g1 = dot3(lb[0], src[0].a, lb[1], src[1].a, lb[2], src[2].a);
+      const T g2 = dot3(lb[0], src[0].b, lb[1], src[1].b, lb[2], src[2].b);
+      const T g3 = dot3(lb[0], src[0].c, lb[1], src[1].c, lb[2], src[2].c);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        aSM[s] = fma_t(cf.omM, lb[s], aSM[s]);
+        aSO[s] = fma_t(cf.omO, lb[s], aSO[s]);
+        aCM[s] = fma_t(cf.omC, lb[s], aCM[s]);
+      }
+      aT = fma_t(ph, coef_tau_grad(cf, gE, gPM, gPO, g1, g2, g3), aT);
       if (lo) {
         // Lambda = (e - psi'_M K'_M)^T lambda_b
         T KT[4];
-        kprime_apply(eMv, rMn, lb, KT);
+        kprime_apply<-1>(eMv, rMv, lb, KT);
         T out[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) out[s] = cf.e * lb[s] - cf.psiM * KT[s];
+        for (int s = 0; s < 4; ++s) out[s] = fma_t(cf.e, lb[s], -cf.psiM * KT[s]);
         store4_nt(lo + fo, out);
       }
     };
     if constexpr (sizeof(T) == 4) {
+      // (never skipped, as in k_sweep_plane)
       Corners cA, cB;
       issue(0, cA);
-      for (int f = 0; f < a.nfreq; f += 2) {
-        if (f + 1 < a.nfreq) issue(f + 1, cB);
+      int f = 0;
+      for (; f + 1 < a.nfreq; f += 2) {
+        issue(f + 1, cB);
         body(f, cA);
-        if (f + 1 >= a.nfreq) break;
-        if (f + 2 < a.nfreq) issue(f + 2, cA);
+        issue(min(f + 2, a.nfreq - 1), cA);
         body(f + 1, cB);
       }
+      if (f < a.nfreq) body(f, cA);
     } else {
       // FP64: one buffer (a second one does not fit in the registers of one wave)
       for (int f = 0; f < a.nfreq; ++f) {
@@ -477,9 +439,9 @@ k_adjoint_plane(const AdjArgs<T> a) {
     else run(no{}, no{});
   }
 
-  double gT = aT, gSM[4], gSO[4], gCM[4], gKM[6], gKO[6];
+  double gT = aT, gSM[3], gSO[3], gCM[3], gKM[6], gKO[6];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < 3; ++s) {
     gSM[s] = aSM[s];
     gSO[s] = aSO[s];
     gCM[s] = aCM[s];
@@ -490,9 +452,9 @@ k_adjoint_plane(const AdjArgs<T> a) {
     gKO[c] = aKO[c];
   }
   // control points (branch of the forward evaluation)
-  double gSP[4] = {0, 0, 0, 0}, gR = 0.0;
+  double gSP[3] = {0, 0, 0}, gR = 0.0;
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < 3; ++s) {
     if (ps.hasP) {
       double d[4];
       if (a.parabolic)
@@ -523,7 +485,7 @@ k_adjoint_plane(const AdjArgs<T> a) {
   for (int c = 0; c < 6; ++c) {
     double m = 0.0, o = 0.0, q = 0.0;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < 3; ++s) {
       m += gSM[s] * rc.emis[s][c];
       o += gSO[s] * rc.emis[s][c];
       q += gSP[s] * rc.emis[s][c];
@@ -533,7 +495,7 @@ k_adjoint_plane(const AdjArgs<T> a) {
     geP[c] = q * ps.ikP;
   }
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < 3; ++s) {
     gkM -= gSM[s] * ps.SM[s] * ps.ikM;
     gkO -= gSO[s] * ps.SO[s] * ps.ikO;
     gkP -= gSP[s] * ps.SP[s] * ps.ikP;
@@ -574,12 +536,11 @@ struct GatherArgs {
   const T* g_o;
   const T* g_m;
   const T* g_p;
-  const RayConsts* rays;
+  const RayGeom* geom;
   double* grad;       // [13][N]: kappa, propmat[6], emis[6]
   size_t N;
-  int nx, ny, np;
+  int nx, ny, nz, np;
   int kO, kM, kP;
-  double dzM, dzP, inv_dx, inv_dy;
   int ray0, nrb;
   const T* kappa;     // the coefficients (MODE 1: the Bezier partials depend on them)
   const T* prop;
@@ -612,14 +573,11 @@ __global__ void __launch_bounds__(256) k_adjoint_gather(const GatherArgs<T> a) {
   }
   const bool atM = (grp < 3);
   for (int rb = 0; rb < a.nrb; ++rb) {
-    const RayConsts& rc = a.rays[a.ray0 + rb];
-    const double inv_mu = 1.0 / fabs(rc.mu);
-    const double ds = (atM ? a.dzM : a.dzP) * inv_mu;
-    const double sds = atM ? -ds : ds;   // M upwind, P downwind, as in the sweep
+    // M upwind, P downwind, as in the sweep
+    const RayGeom& gl = layer_geom(a.geom, a.ray0 + rb, a.nz, a.kO, atM ? a.kM : a.kP, !atM);
     const T* gb = atM ? a.g_m + ((size_t)rb * 13 + c0) * np : a.g_p + (size_t)rb * 7 * np;
     if constexpr (MODE == 0) {
-      const Stencil t = make_tstencil(i, j, a.nx, a.ny, sds * rc.sx * a.inv_dx,
-                                      sds * rc.sy * a.inv_dy);
+      const Stencil t = make_tstencil(i, j, a.nx, a.ny, gl);
 #pragma unroll
       for (int c = 0; c < 7; ++c) {
         if (c < nc) {
@@ -630,8 +588,7 @@ __global__ void __launch_bounds__(256) k_adjoint_gather(const GatherArgs<T> a) {
     } else {
       // the transposed 9-point Bezier of each coefficient, whose clamps depend on the
       // coefficient's values around q
-      const Bez9Geom gm = bez9_geom(sds * rc.sx * a.inv_dx, sds * rc.sy * a.inv_dy, a.nx, a.ny);
-      const BezW<double> wx = bez_weights(gm.tx), wy = bez_weights(gm.ty);
+      const BezW<double> wx = bez_weights(gl.tx), wy = bez_weights(gl.ty);
       int rowb[5], coli[5], prow[3], pcol[3];
 #pragma unroll
       for (int d = 0; d < 5; ++d) {
@@ -640,8 +597,8 @@ __global__ void __launch_bounds__(256) k_adjoint_gather(const GatherArgs<T> a) {
       }
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        prow[d] = wrapi(j - gm.fv + d - 1, a.ny) * a.nx;
-        pcol[d] = wrapi(i - gm.fu + d - 1, a.nx);
+        prow[d] = wrapi(j - gl.fv + d - 1, a.ny) * a.nx;
+        pcol[d] = wrapi(i - gl.fu + d - 1, a.nx);
       }
       const size_t kb = (size_t)(atM ? a.kM : a.kP) * np;
 #pragma unroll 1

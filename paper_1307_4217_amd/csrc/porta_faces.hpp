@@ -138,8 +138,9 @@ template <class T>
 __device__ inline double face_val(const T* __restrict__ f, const FaceStencil& s, size_t bk,
                                   size_t bz) {
   const size_t b01 = s.inplane ? bk : bz;
-  return s.w[0] * (double)f[b01 + s.n[0]] + s.w[1] * (double)f[b01 + s.n[1]] +
-         s.w[2] * (double)f[bz + s.n[2]] + s.w[3] * (double)f[bz + s.n[3]];
+  return fma_t(s.w[3], (double)f[bz + s.n[3]],
+               dot3(s.w[1], (double)f[b01 + s.n[1]], s.w[0], (double)f[b01 + s.n[0]], s.w[2],
+                    (double)f[bz + s.n[2]]));
 }
 
 template <class T>
@@ -183,11 +184,11 @@ inline int faces_grid(int nrb, int nchunk) {
 }
 
 // Values of the set-up of a node and ray that the march reads, in the sweep precision:
-// K'_M / eta_I entries (eta 3, rho 3), K'_O (3, 3), S_M (4), S_O (4), c_M (4), the
-// optical depth tau_MO at line centre and the Lambda* factor of omega_C.
+// K'_M / eta_I entries (eta 3, rho 3), K'_O (3, 3), the three source values of I, Q and U
+// (StepSource), the optical depth tau_MO at line centre and the Lambda* factor of omega_C.
 enum FacesCacheSlot {
-  kCeM = 0, kCrM = 3, kCeO = 6, kCrO = 9, kCSM = 12, kCSO = 16, kCcM = 20, kCtau = 24,
-  kClf = 25, kFacesCache = 26
+  kCeM = 0, kCrM = 3, kCeO = 6, kCrO = 9, kCSa = 12, kCSb = 15, kCSc = 18, kCtau = 21,
+  kClf = 22, kFacesCache = 23
 };
 
 // frequencies per block, at most (LDS may set fewer).  Small chunks give more blocks
@@ -240,25 +241,11 @@ __device__ inline void setup_point_faces(const T* __restrict__ kappa, const T* _
   }
   const size_t bO = bk + p;
   ps.kapO = (double)kappa[bO];
-  ps.ikM = 1.0 / ps.kapM;
-  ps.ikO = 1.0 / ps.kapO;
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
     ps.epsO[c] = (double)emis[c * N + bO];
     ps.etaO[c] = (double)prop[c * N + bO];
   }
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    double em = 0.0, eo = 0.0;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      em += rc.emis[s][c] * ps.epsM[c];
-      eo += rc.emis[s][c] * ps.epsO[c];
-    }
-    ps.SM[s] = em * ps.ikM;
-    ps.SO[s] = eo * ps.ikO;
-  }
-  ps.tau0M = 0.5 * (ps.kapM + ps.kapO) * ps.dsM;
   ps.hasP = hasP;
   if (hasP) {
     const size_t bP = (size_t)a.kP * a.np;
@@ -266,25 +253,8 @@ __device__ inline void setup_point_faces(const T* __restrict__ kappa, const T* _
     ps.kapP = face_val(kappa, sP, bk, bP);
 #pragma unroll
     for (int c = 0; c < 6; ++c) ps.epsP[c] = face_val(emis + c * N, sP, bk, bP);
-    ps.ikP = 1.0 / ps.kapP;
-    ps.tau0P = 0.5 * (ps.kapO + ps.kapP) * ps.dsP;
-    ps.ratio = ps.tau0M / ps.tau0P;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      double ep = 0.0;
-#pragma unroll
-      for (int c = 0; c < 6; ++c) ep += rc.emis[s][c] * ps.epsP[c];
-      ps.SP[s] = ep * ps.ikP;
-      ps.cM[s] = control_cm(ps.SM[s], ps.SO[s], ps.SP[s], ps.ratio, a.parabolic != 0);
-    }
-  } else {
-    ps.dsP = ps.kapP = ps.ikP = ps.tau0P = ps.ratio = 0.0;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      ps.SP[s] = 0.0;
-      ps.cM[s] = 0.5 * (ps.SM[s] + ps.SO[s]);
-    }
   }
+  setup_sources(rc, a.parabolic != 0, ps);
 }
 
 // The frequency-independent set-up of every node of plane kO (working frame) for every
@@ -306,7 +276,6 @@ __global__ void __launch_bounds__(256) k_faces_setup(const FacesArgs<T> a) {
   const FaceStencil sP = hasP ? face_stencil(gP, i, j, fr.nx, fr.ny) : sM;
   PointSetup ps;
   setup_point_faces(kappa, prop, emis, a, rc, gM, sM, gP, sP, hasP, p, ps);
-  const double lamfac = hasP ? control_cm(0.0, 1.0, 0.0, ps.ratio, a.parabolic != 0) : 0.5;
   const size_t np = (size_t)a.np;
   T* c = a.cache + (size_t)rb * kFacesCache * np + p;
 #pragma unroll
@@ -317,13 +286,15 @@ __global__ void __launch_bounds__(256) k_faces_setup(const FacesArgs<T> a) {
     c[(kCrO + k) * np] = (T)(ps.etaO[3 + k] * ps.ikO);
   }
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    c[(kCSM + s) * np] = (T)ps.SM[s];
-    c[(kCSO + s) * np] = (T)ps.SO[s];
-    c[(kCcM + s) * np] = (T)ps.cM[s];
+  for (int s = 0; s < 3; ++s) {
+    StepSource<T> t;
+    step_source(ps.SM[s], ps.SO[s], ps.cM[s], t);
+    c[(kCSa + s) * np] = t.a;
+    c[(kCSb + s) * np] = t.b;
+    c[(kCSc + s) * np] = t.c;
   }
   c[kCtau * np] = (T)ps.tau0M;
-  c[kClf * np] = (T)lamfac;
+  c[kClf * np] = (T)ps.lamfac;
 }
 
 // One plane for one ray and one chunk of frequencies (order: faces_grid).  Lanes
@@ -436,14 +407,11 @@ __global__ void __launch_bounds__(kFacesMaxLanes) k_sweep_plane_faces(const Face
       const T rMv[3] = {cp[(kCrM + 0) * np], cp[(kCrM + 1) * np], cp[(kCrM + 2) * np]};
       const T eOv[3] = {cp[(kCeO + 0) * np], cp[(kCeO + 1) * np], cp[(kCeO + 2) * np]};
       const T rOv[3] = {cp[(kCrO + 0) * np], cp[(kCrO + 1) * np], cp[(kCrO + 2) * np]};
-      const StokesOp<T> KO = stokes_op(eOv, rOv);
-      T SMt[4], SOt[4], cMt[4];
+      const auto KO = step_op(eOv, rOv);
+      StepSource<T> src[3];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        SMt[s] = cp[(kCSM + s) * np];
-        SOt[s] = cp[(kCSO + s) * np];
-        cMt[s] = cp[(kCcM + s) * np];
-      }
+      for (int s = 0; s < 3; ++s)
+        src[s] = {cp[(kCSa + s) * np], cp[(kCSb + s) * np], cp[(kCSc + s) * np]};
       const T tau0 = cp[kCtau * np], lf = cp[kClf * np];
       // I_M as two linear steps (x, then z or y): a field constant over the stencil is
       // returned exactly, so the rounding of the four weights, the same for every node
@@ -497,29 +465,30 @@ __global__ void __launch_bounds__(kFacesMaxLanes) k_sweep_plane_faces(const Face
           }
         }
         const T tau = tau0 * s_phi[fg];
-        const Coefs<T> cf = coefficients<true>(tau);
+        const Coefs<T> cf = coefficients(tau);
         const T IMt[4] = {(T)IM[0], (T)IM[1], (T)IM[2], (T)IM[3]};
         T KI[4], dv[4];
-        kprime_apply(eMv, rMv, IMt, KI);
+        kprime_apply<1, true>(eMv, rMv, IMt, KI);
+        // e I_M as I_M - (1 - e) I_M (see Coefs::em1), and the change of a step summed
+        // before it is added to I_M: on thin steps each term alone can fall below half
+        // a unit in the last place of I_M, and dropping the source terms while keeping
+        // the attenuation would bias a long chain of steps
+        const StepSource<T> w = source_weights(cf);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          // e I_M as I_M - (1 - e) I_M (see Coefs::em1), and the change of a step summed
-          // before it is added to I_M: on thin steps each term alone can fall below half
-          // a unit in the last place of I_M, and dropping the source terms while keeping
-          // the attenuation would bias a long chain of steps
-          dv[s] = -cf.em1 * IMt[s] - cf.psiM * KI[s] + cf.omM * SMt[s] + cf.omO * SOt[s] +
-                  cf.omC * cMt[s];
+          dv[s] = fma_t(-cf.em1, IMt[s], -(cf.psiM * KI[s]));
+          if (s < 3) dv[s] = add_sources(w, src[s], dv[s]);
         }
-        const StokesFreq<T> F = stokes_freq(KO, cf.psiO);
+        const auto F = step_freq(KO, cf.psiO);
         D res[4];
         if constexpr (sizeof(T) == 4) {
           // (1 + psi'_O K'_O) I_O = I_M + d, so I_O = I_M + x with
           // (1 + psi'_O K'_O) x = d - psi'_O K'_O I_M: x in FP32, I_M + x in FP64
           T KOI[4], rhs[4], x[4];
-          kprime_apply(eOv, rOv, IMt, KOI);
+          kprime_apply<1, true>(eOv, rOv, IMt, KOI);
 #pragma unroll
-          for (int s = 0; s < 4; ++s) rhs[s] = dv[s] - cf.psiO * KOI[s];
-          stokes_solve<1>(KO, F, rhs, x);
+          for (int s = 0; s < 4; ++s) rhs[s] = fma_t(-cf.psiO, KOI[s], dv[s]);
+          stokes_solve<1, true>(KO, F, rhs, x);
 #pragma unroll
           for (int s = 0; s < 4; ++s) res[s] = IM[s] + (D)x[s];
         } else {
@@ -542,8 +511,8 @@ __global__ void __launch_bounds__(kFacesMaxLanes) k_sweep_plane_faces(const Face
           else store4_nt(op + (size_t)fg * fstride + 4 * ostore, rest);
           const double W = s_wn[fg];
 #pragma unroll
-          for (int s = 0; s < 4; ++s) jacc[s] += W * res[s];
-          lacc += W * (double)(cf.omO + lf * cf.omC);
+          for (int s = 0; s < 4; ++s) jacc[s] = fma_t(W, (double)res[s], jacc[s]);
+          lacc = fma_t(W, (double)lambda_star(cf, lf), lacc);
         }
       }
       if (store && jc) {

@@ -14,7 +14,7 @@
 namespace porta {
 
 constexpr int kMaxMu = 64;
-constexpr int kUploadChunk = 240;   // doubles per upload launch (kernel-argument copy)
+constexpr int kUploadChunk = 480;   // doubles per upload launch (kernel-argument copy)
 
 // ---------------------------------------------------------------------------
 // Small host -> device uploads travel inside the kernel arguments, which the
@@ -28,8 +28,7 @@ struct UploadChunk {
 };
 
 __global__ void k_upload(const UploadChunk c) {
-  const int t = threadIdx.x;
-  if (t < c.n) c.dst[t] = c.v[t];
+  for (int t = threadIdx.x; t < c.n; t += blockDim.x) c.dst[t] = c.v[t];
 }
 
 // Opt-in validity check of the transfer coefficients: flag[0] = 1 if some eta_I is
@@ -59,30 +58,83 @@ __global__ void k_fill_f64(double* __restrict__ p, size_t n, double v) {
     p[i] = v;
 }
 
-// Ray constants (direction, weight, emission and J projection tables) and the
-// normalized frequency weights, from the uploaded quadrature.
+// Where the points M (side 0) and P (side 1) of a ray lie when it crosses the layer between
+// planes l and l + 1: the path length ds to the plane and the displacement (u, v) in cells,
+// reduced to one period and split into the node it is taken from (fu, fv; the node below it, or
+// the nearest for the 9-point stencil) and the rest (tx, ty).  It is the same for every
+// node of the plane, so it is formed once per call, [ray][layer][side]: in each thread of
+// the plane step its two square roots' worth of divisions and floors were a fifth of the
+// set-up.
+struct RayGeom {
+  double ds, tx, ty;
+  int fu, fv;
+};
+
+struct GeomArgs {
+  const double* z;    // device
+  int nz, nx, ny;     // nz = 0: no geometry
+  double inv_dx, inv_dy;
+  double half;        // 0 (bilinear) or 0.5 (9-point)
+  RayGeom* geom;
+};
+
+constexpr int kMaxFreq = 4096;   // frequencies of a quadrature, at most
+
+// Ray constants (direction, weight, emission and J projection tables) and the normalized
+// frequency weights (block 0), and the rays' geometry (the other blocks), from the uploaded
+// quadrature and plane heights.
 template <class T>
-__global__ void k_prepare(const double* __restrict__ mu, const double* __restrict__ wmu, int nmu,
-                          int nchi, double w2, const double* __restrict__ phi,
-                          const double* __restrict__ wfreq, int nfreq,
-                          RayConsts* __restrict__ rays, T* __restrict__ phiT,
-                          double* __restrict__ wn) {
+__global__ void __launch_bounds__(256)
+    k_prepare(const double* __restrict__ mu, const double* __restrict__ wmu, int nmu, int nchi,
+              double w2, const double* __restrict__ phi, const double* __restrict__ wfreq,
+              int nfreq, RayConsts* __restrict__ rays, T* __restrict__ phiT,
+              double* __restrict__ wn, const GeomArgs ga) {
+  __shared__ double prod[kMaxFreq];
   __shared__ double norm;
   const int nh = nmu * nchi;
+  if (blockIdx.x > 0) {
+    const int nl = ga.nz - 1;
+    const int e = (blockIdx.x - 1) * blockDim.x + threadIdx.x;
+    if (e >= 2 * nh * nl) return;
+    const int r = e / nl, l = e % nl;
+    const double m0 = mu[(r % nh) / nchi], chi = (r % nchi + 0.5) * (2.0 * M_PI / nchi);
+    const double st = sqrt(fmax(0.0, 1.0 - m0 * m0));
+    const double ds = fabs(ga.z[l + 1] - ga.z[l]) * (1.0 / fabs(m0));
+    const double sx = st * cos(chi), sy = st * sin(chi);
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      const double d = side == 0 ? -ds : ds;
+      double u = d * sx * ga.inv_dx, v = d * sy * ga.inv_dy;
+      // to one period first, so the integer shift stays in range
+      u -= ga.nx * floor(u / ga.nx);
+      v -= ga.ny * floor(v / ga.ny);
+      const double fu = floor(u + ga.half), fv = floor(v + ga.half);
+      RayGeom g;
+      g.ds = ds;
+      g.tx = u - fu;
+      g.ty = v - fv;
+      g.fu = (int)fu;
+      g.fv = (int)fv;
+      ga.geom[(size_t)e * 2 + side] = g;
+    }
+    return;
+  }
   for (int r = threadIdx.x; r < 2 * nh; r += blockDim.x) {
     const int a = (r % nh) / nchi, m = r % nchi;
     const double m0 = mu[a];
     const double chi = (m + 0.5) * (2.0 * M_PI / nchi);
     ray_consts(r < nh ? m0 : -m0, chi, 0.5 * wmu[a] / nchi, w2, rays[r]);
   }
+  for (int j = threadIdx.x; j < nfreq; j += blockDim.x) prod[j] = wfreq[j] * phi[j];
+  __syncthreads();
   if (threadIdx.x == 0) {
     double s = 0.0;
-    for (int j = 0; j < nfreq; ++j) s += wfreq[j] * phi[j];
+    for (int j = 0; j < nfreq; ++j) s += prod[j];
     norm = s;
   }
   __syncthreads();
   for (int j = threadIdx.x; j < nfreq; j += blockDim.x) {
-    wn[j] = wfreq[j] * phi[j] / norm;
+    wn[j] = prod[j] / norm;
     phiT[j] = (T)phi[j];
   }
 }
@@ -126,22 +178,22 @@ __device__ inline int wrapi(int v, int n) {
   return v < 0 ? v + n : v;
 }
 
-// Bilinear stencil on a periodic plane for a point displaced by (u, v) cells
-// from node (i, j).  For one ray and one pair of planes the displacement is
-// the same at every node, so every thread of a plane sees the same weights.
+// Bilinear stencil on a periodic plane for a point displaced from node (i, j).  For one ray
+// and one pair of planes the displacement is the same at every node, so every thread of a
+// plane sees the same weights.
 struct Stencil {
   int i00, i10, i01, i11;
   double w00, w10, w01, w11;
 };
 
-__device__ inline Stencil make_stencil(int i, int j, int nx, int ny, double u, double v) {
-  // reduce the displacement to one period first so the integer shift stays in range
-  u -= nx * floor(u / nx);
-  v -= ny * floor(v / ny);
-  const double fu = floor(u), fv = floor(v);
-  const double tx = u - fu, ty = v - fv;
-  const int i0 = wrapi(i + (int)fu, nx), i1 = (i0 + 1 == nx) ? 0 : i0 + 1;
-  const int j0 = wrapi(j + (int)fv, ny), j1 = (j0 + 1 == ny) ? 0 : j0 + 1;
+// Index i + f on a periodic axis of n nodes, for i in [0, n), f in [0, n].
+__device__ inline int shift_index(int i, int f, int n) {
+  const int v = i + f;
+  return v >= n ? v - n : v;
+}
+
+__device__ inline Stencil stencil_at(int i0, int i1, int j0, int j1, int nx, double tx,
+                                     double ty) {
   Stencil s;
   s.i00 = j0 * nx + i0;
   s.i10 = j0 * nx + i1;
@@ -152,34 +204,40 @@ __device__ inline Stencil make_stencil(int i, int j, int nx, int ny, double u, d
   s.w01 = (1.0 - tx) * ty;
   s.w11 = tx * ty;
   return s;
+}
+
+__device__ inline Stencil make_stencil(int i, int j, int nx, int ny, const RayGeom& g) {
+  const int i0 = shift_index(i, g.fu, nx), j0 = shift_index(j, g.fv, ny);
+  return stencil_at(i0, i0 + 1 == nx ? 0 : i0 + 1, j0, j0 + 1 == ny ? 0 : j0 + 1, nx, g.tx, g.ty);
+}
+
+// The same for a displacement (u, v) in cells.
+__device__ inline Stencil make_stencil(int i, int j, int nx, int ny, double u, double v) {
+  u -= nx * floor(u / nx);
+  v -= ny * floor(v / ny);
+  const double fu = floor(u), fv = floor(v);
+  RayGeom g;
+  g.ds = 0.0;
+  g.tx = u - fu;
+  g.ty = v - fv;
+  g.fu = (int)fu;
+  g.fv = (int)fv;
+  return make_stencil(i, j, nx, ny, g);
 }
 
 template <class T>
 __device__ inline double bil(const T* __restrict__ f, const Stencil& s) {
-  return s.w00 * (double)f[s.i00] + s.w10 * (double)f[s.i10] + s.w01 * (double)f[s.i01] +
-         s.w11 * (double)f[s.i11];
+  return fma_t(s.w11, (double)f[s.i11],
+               dot3(s.w10, (double)f[s.i10], s.w00, (double)f[s.i00], s.w01, (double)f[s.i01]));
 }
 
-// Transposed stencil: the nodes (i', j') whose stencil for the same displacement
-// (u, v) contains node (i, j), with the weight that node received.  Used by the
-// adjoint to turn the scatter of the forward interpolation into a gather.
-__device__ inline Stencil make_tstencil(int i, int j, int nx, int ny, double u, double v) {
-  u -= nx * floor(u / nx);
-  v -= ny * floor(v / ny);
-  const double fu = floor(u), fv = floor(v);
-  const double tx = u - fu, ty = v - fv;
-  const int i0 = wrapi(i - (int)fu, nx), i1 = (i0 == 0) ? nx - 1 : i0 - 1;
-  const int j0 = wrapi(j - (int)fv, ny), j1 = (j0 == 0) ? ny - 1 : j0 - 1;
-  Stencil s;
-  s.i00 = j0 * nx + i0;
-  s.i10 = j0 * nx + i1;
-  s.i01 = j1 * nx + i0;
-  s.i11 = j1 * nx + i1;
-  s.w00 = (1.0 - tx) * (1.0 - ty);
-  s.w10 = tx * (1.0 - ty);
-  s.w01 = (1.0 - tx) * ty;
-  s.w11 = tx * ty;
-  return s;
+// Transposed stencil: the nodes (i', j') whose stencil for the same displacement contains
+// node (i, j), with the weight that node received.  Used by the adjoint to turn the
+// scatter of the forward interpolation into a gather.
+__device__ inline Stencil make_tstencil(int i, int j, int nx, int ny, const RayGeom& g) {
+  const int i0 = i - g.fu < 0 ? i - g.fu + nx : i - g.fu;   // f in [0, n]
+  const int j0 = j - g.fv < 0 ? j - g.fv + ny : j - g.fv;
+  return stencil_at(i0, i0 == 0 ? nx - 1 : i0 - 1, j0, j0 == 0 ? ny - 1 : j0 - 1, nx, g.tx, g.ty);
 }
 
 // 3x3 stencil around the node nearest to the displaced point (mode B), with the
@@ -190,14 +248,11 @@ struct Stencil9 {
   double tx, ty;
 };
 
-__device__ inline Stencil9 make_stencil9(int i, int j, int nx, int ny, double u, double v) {
-  u -= nx * floor(u / nx);
-  v -= ny * floor(v / ny);
-  const double fu = floor(u + 0.5), fv = floor(v + 0.5);
+__device__ inline Stencil9 make_stencil9(int i, int j, int nx, int ny, const RayGeom& g) {
   Stencil9 s;
-  s.tx = u - fu;
-  s.ty = v - fv;
-  const int ic = wrapi(i + (int)fu, nx), jc = wrapi(j + (int)fv, ny);
+  s.tx = g.tx;
+  s.ty = g.ty;
+  const int ic = shift_index(i, g.fu, nx), jc = shift_index(j, g.fv, ny);
   s.col[0] = (ic == 0) ? nx - 1 : ic - 1;
   s.col[1] = ic;
   s.col[2] = (ic + 1 == nx) ? 0 : ic + 1;
@@ -224,30 +279,83 @@ __device__ inline double bez9(const T* __restrict__ f, const Stencil9& s) {
 // Frequency-independent part of the update of node p on plane kO for one ray:
 // transfer coefficients interpolated at M (plane kM) and P (plane kP, if any),
 // source vectors S = eps/eta_I at M, O, P, K' at M and O, the line-centre
-// optical paths and the BESSER control points (Sect. 3.1-3.3).
+// optical paths and the BESSER control points (Sect. 3.1-3.3).  The multipoles K = 0, 2
+// give Stokes V no emission, so the source vectors have three components.
 struct PointSetup {
   Stencil sM;
   double dsM, dsP;
   double kapM, kapO, kapP, ikM, ikO, ikP;
   double epsM[6], epsO[6], epsP[6], etaM[6], etaO[6];
-  double SM[4], SO[4], SP[4], cM[4];
-  double tau0M, tau0P, ratio;
+  double SM[3], SO[3], SP[3], cM[3];
+  double tau0M, tau0P, ratio, lamfac;
   bool hasP;
 };
 
+// Emission sum_c emis[s][c] eps_c of I, Q, U; the K = 0 multipole emits in I only and the
+// Q = 0 one of K = 2 not in U.
+__device__ inline void emission(const RayConsts& rc, const double eps[6], double e[3]) {
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    double v = rc.emis[s][s] * eps[s];
+#pragma unroll
+    for (int c = s + 1; c < 6; ++c) v = fma_t(rc.emis[s][c], eps[c], v);
+    e[s] = v;
+  }
+}
+
+// The rest of the set-up from the coefficients and path lengths at M, O and P.
+// lamfac: Lambda* = omega_O + lamfac omega_C for a unit source at O alone (Eq. 14): c_M is 1
+// for BESSER, (1 + ratio)/2 for the parabola, 1/2 without a downwind point.
+__device__ inline void setup_sources(const RayConsts& rc, bool parabolic, PointSetup& ps) {
+  ps.ikM = 1.0 / ps.kapM;
+  ps.ikO = 1.0 / ps.kapO;
+  double e[3];
+  emission(rc, ps.epsM, e);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) ps.SM[s] = e[s] * ps.ikM;
+  emission(rc, ps.epsO, e);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) ps.SO[s] = e[s] * ps.ikO;
+  ps.tau0M = 0.5 * (ps.kapM + ps.kapO) * ps.dsM;   // line-centre tau_MO
+  if (ps.hasP) {
+    ps.ikP = 1.0 / ps.kapP;
+    emission(rc, ps.epsP, e);
+    ps.tau0P = 0.5 * (ps.kapO + ps.kapP) * ps.dsP;
+    const double r = ps.tau0M / ps.tau0P, inv = 0.5 / (1.0 + r), ir = 1.0 / r;
+    ps.ratio = r;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      ps.SP[s] = e[s] * ps.ikP;
+      ps.cM[s] = control_cm(ps.SM[s], ps.SO[s], ps.SP[s], fma_t(e[s], ps.ikP, -ps.SO[s]), r, inv,
+                            ir, parabolic);
+    }
+    ps.lamfac = parabolic ? control_cm(0.0, 1.0, 0.0, -1.0, r, inv, ir, true) : 1.0;
+  } else {
+    // no downwind plane: linear control point
+    ps.dsP = ps.kapP = ps.ikP = ps.tau0P = ps.ratio = 0.0;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      ps.SP[s] = 0.0;
+      ps.cM[s] = 0.5 * (ps.SM[s] + ps.SO[s]);
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) ps.epsP[c] = 0.0;
+    ps.lamfac = 0.5;
+  }
+}
+
+// gM, gP: the geometry of the layers to kM and kP (gP unused without kP).
 template <int MODE, class T>
 __device__ inline void setup_point(const T* __restrict__ kappa, const T* __restrict__ prop,
                                    const T* __restrict__ emis, size_t N, int nx, int ny, int np,
-                                   int kO, int kM, int kP, double dzM, double dzP, double inv_dx,
-                                   double inv_dy, const RayConsts& rc, int p, bool parabolic,
-                                   PointSetup& ps, Stencil9& sM9) {
-  const int i = p % nx, j = p / nx;
-  const double inv_mu = 1.0 / fabs(rc.mu);
-  ps.dsM = dzM * inv_mu;
-  const double uM = -ps.dsM * rc.sx * inv_dx, vM = -ps.dsM * rc.sy * inv_dy;
+                                   int kO, int kM, int kP, const RayGeom& gM, const RayGeom& gP,
+                                   const RayConsts& rc, int p, bool parabolic, PointSetup& ps,
+                                   Stencil9& sM9) {
+  const int j = p / nx, i = p - j * nx;
   const size_t bM = (size_t)kM * np, bO = (size_t)kO * np + p;
+  ps.dsM = gM.ds;
   if (MODE == 0) {
-    ps.sM = make_stencil(i, j, nx, ny, uM, vM);
+    ps.sM = make_stencil(i, j, nx, ny, gM);
     ps.kapM = bil(kappa + bM, ps.sM);
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
@@ -256,7 +364,7 @@ __device__ inline void setup_point(const T* __restrict__ kappa, const T* __restr
     }
   } else {
     ps.sM = Stencil{0, 0, 0, 0, 1.0, 0.0, 0.0, 0.0};
-    sM9 = make_stencil9(i, j, nx, ny, uM, vM);
+    sM9 = make_stencil9(i, j, nx, ny, gM);
     ps.kapM = bez9(kappa + bM, sM9);
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
@@ -265,63 +373,34 @@ __device__ inline void setup_point(const T* __restrict__ kappa, const T* __restr
     }
   }
   ps.kapO = (double)kappa[bO];
-  ps.ikM = 1.0 / ps.kapM;
-  ps.ikO = 1.0 / ps.kapO;
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
     ps.epsO[c] = (double)emis[c * N + bO];
     ps.etaO[c] = (double)prop[c * N + bO];
   }
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    double em = 0.0, eo = 0.0;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      em += rc.emis[s][c] * ps.epsM[c];
-      eo += rc.emis[s][c] * ps.epsO[c];
-    }
-    ps.SM[s] = em * ps.ikM;
-    ps.SO[s] = eo * ps.ikO;
-  }
-  ps.tau0M = 0.5 * (ps.kapM + ps.kapO) * ps.dsM;   // line-centre tau_MO
   ps.hasP = kP >= 0;
   if (ps.hasP) {
-    ps.dsP = dzP * inv_mu;
-    const double uP = ps.dsP * rc.sx * inv_dx, vP = ps.dsP * rc.sy * inv_dy;
+    ps.dsP = gP.ds;
     const size_t bP = (size_t)kP * np;
     if (MODE == 0) {
-      const Stencil sP = make_stencil(i, j, nx, ny, uP, vP);
+      const Stencil sP = make_stencil(i, j, nx, ny, gP);
       ps.kapP = bil(kappa + bP, sP);
 #pragma unroll
       for (int c = 0; c < 6; ++c) ps.epsP[c] = bil(emis + c * N + bP, sP);
     } else {
-      const Stencil9 sP = make_stencil9(i, j, nx, ny, uP, vP);
+      const Stencil9 sP = make_stencil9(i, j, nx, ny, gP);
       ps.kapP = bez9(kappa + bP, sP);
 #pragma unroll
       for (int c = 0; c < 6; ++c) ps.epsP[c] = bez9(emis + c * N + bP, sP);
     }
-    ps.ikP = 1.0 / ps.kapP;
-    ps.tau0P = 0.5 * (ps.kapO + ps.kapP) * ps.dsP;
-    ps.ratio = ps.tau0M / ps.tau0P;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      double ep = 0.0;
-#pragma unroll
-      for (int c = 0; c < 6; ++c) ep += rc.emis[s][c] * ps.epsP[c];
-      ps.SP[s] = ep * ps.ikP;
-      ps.cM[s] = control_cm(ps.SM[s], ps.SO[s], ps.SP[s], ps.ratio, parabolic);
-    }
-  } else {
-    // no downwind plane: linear control point
-    ps.dsP = ps.kapP = ps.ikP = ps.tau0P = ps.ratio = 0.0;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      ps.SP[s] = 0.0;
-      ps.cM[s] = 0.5 * (ps.SM[s] + ps.SO[s]);
-    }
-#pragma unroll
-    for (int c = 0; c < 6; ++c) ps.epsP[c] = 0.0;
   }
+  setup_sources(rc, parabolic, ps);
+}
+
+// Geometry of the layer between planes k and k2 for one ray and side (0: M, 1: P).
+__device__ inline const RayGeom& layer_geom(const RayGeom* __restrict__ geom, int ray, int nz,
+                                            int k, int k2, int side) {
+  return geom[((size_t)ray * (nz - 1) + (k < k2 ? k : k2)) * 2 + side];
 }
 
 // ---------------------------------------------------------------------------
@@ -337,96 +416,205 @@ struct HemiArgs {
   const double* jpart_prev;  // partial sums of the previous plane, or nullptr (boundary plane)
   size_t prev_off;   // offset of the previous plane in jkq
   int kO, kM, kP;    // plane of O, upwind plane, downwind plane (-1: none)
-  double dzM, dzP;   // |z_kO - z_kM|, |z_kP - z_kO|
   int ray0, nrb;     // rays [ray0, ray0 + nrb) of the enumeration
   T ibound;          // Stokes I on the boundary plane of this hemisphere
 };
 
 // ---------------------------------------------------------------------------
 // Add the frequency-integrated Stokes vectors of a batch of rays on one plane to J^K_Q
-// (Eq. 1) and Lbar, in a fixed order (no atomics).  A block takes kJNodes nodes; its
-// threads are (ray group, node), group g summing rays g, g + G, ... over their frequency
-// chunks, and the groups are added in order through LDS.  The loop over rays is a chain
-// of memory latencies: with one thread per node and every ray in turn it took 25 us at
-// 16x16 nodes and 40 rays, 73 us at 128x128 and 80 rays, more than the plane step that
-// had to wait for it.  On the boundary plane the Stokes vector is (ibound, 0, 0, 0) at
-// every frequency.  NS: Stokes parameters in the partial sums (4, or 1: intensity only).
+// (Eq. 1) and Lbar, in a fixed order (no atomics).  A block takes kJNodes nodes.  With one
+// thread per node and a load per ray in turn the chain of memory latencies took 25 us at 16x16
+// nodes and 40 rays, 73 us at 128x128 and 80 rays: more than the plane step that had to wait
+// for it.  Two splits, by the precision of the sweep:
+// - FP64: groups of rays, added at the end (jreduce_groups).
+// - FP32: the rays one by one in the order of the enumeration (jreduce_ordered).  There the
+//   next iteration's emissivities are rounded to FP32, and a sum whose last bit differs moves
+//   some of them by 6e-8.  The threads, as (ray of a slab, node), load the slab's partial sums
+//   and the rays' coefficients into LDS, and then, as (component, node), add its rays in
+//   order, while the next slab's loads are under way.
+// (FP64 in the second split: 16x16x32 and 80 rays, 537 us a sweep instead of 459; 64x64x49
+// multigrid cycles 54.6 ms instead of 54.0.)
+// On the boundary plane the Stokes vector is (ibound, 0, 0, 0) at every frequency.  NS: Stokes
+// parameters in the partial sums (4, or 1: intensity only).
 // ---------------------------------------------------------------------------
 constexpr int kJNodes = 16;   // consecutive nodes of a block: one 128-byte line of doubles
+constexpr int kJCoefs = 37;   // of a ray: weight and proj[9][4]
 inline int jblocks(int np) { return (np + kJNodes - 1) / kJNodes; }
-inline size_t jlds_bytes(int block) { return (size_t)block * 10 * sizeof(double); }
-
-// acc += the projections of one ray's integrated Stokes vector.  T^K_Q is zero for
-// Stokes V at K = 0, 2, for I, Q, U at K = 1, and for Q, U at J00 and U at J20.
-template <int NS>
-__device__ inline void jproject(const RayConsts& rc, const double ib[NS], double lam,
-                                double acc[10]) {
-  const double w = rc.weight;
-  acc[0] += w * (rc.proj[0][0] * ib[0]);
-  if constexpr (NS == 4) {
-#pragma unroll
-    for (int c = 1; c < 4; ++c) acc[c] += w * (rc.proj[c][3] * ib[3]);
-    acc[4] += w * (rc.proj[4][0] * ib[0] + rc.proj[4][1] * ib[1]);
-#pragma unroll
-    for (int c = 5; c < 9; ++c)
-      acc[c] += w * (rc.proj[c][0] * ib[0] + rc.proj[c][1] * ib[1] + rc.proj[c][2] * ib[2]);
-  } else {
-#pragma unroll
-    for (int c = 4; c < 9; ++c) acc[c] += w * (rc.proj[c][0] * ib[0]);
-  }
-  acc[9] += w * lam;
+// LDS for `threads` threads: a slab of threads / kJNodes rays, or ten sums of every thread
+inline size_t jlds_bytes(int threads, size_t elem) {
+  return (size_t)(threads / kJNodes) * (elem == 4 ? 5 * kJNodes + kJCoefs : 10 * kJNodes) *
+         sizeof(double);
 }
 
+// The partial sums of one plane.
+struct JJob {
+  const double* part;     // [ray][chunk][NS + 1][node], or nullptr: the boundary plane
+  const RayConsts* rays;  // of the batch
+  int nrb, nchunk;
+  double ibound;
+  size_t off;             // of the plane in jkq
+};
+
+// In the order of the rays, each of one chunk.
 template <int NS>
-__device__ inline void jsum_rays(const double* __restrict__ jpart,
-                                 const RayConsts* __restrict__ rays, int nrb, int nchunk, int np,
-                                 int p, double ibound, double acc[10]) {
-  const int g = threadIdx.x / kJNodes, G = blockDim.x / kJNodes;
-  for (int rb = g; rb < nrb; rb += G) {
-    double ib[NS], lam = 0.0;
+__device__ inline void jreduce_ordered(const JJob& J, double* __restrict__ jkq, size_t N, int np,
+                                       int node0, double* lds, int threads) {
+  constexpr int NV = NS + 1;
+  const int G = threads / kJNodes;
+  const int g = threadIdx.x / kJNodes, n = threadIdx.x % kJNodes, p = node0 + n;
+  const bool works = (int)threadIdx.x < threads;
+  double* s_part = lds;                            // [ray][NV][node]
+  double* s_coef = lds + (size_t)G * 5 * kJNodes;  // [ray][kJCoefs]
+  constexpr int kTasks = 10 * kJNodes, kMaxTasks = (kTasks + 63) / 64;   // of a thread
+  constexpr int kMaxCoefs = (kJCoefs + kJNodes - 1) / kJNodes;
+  double acc[kMaxTasks];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) ib[s] = 0.0;
-    if (!jpart) {
-      ib[0] = ibound;
-    } else {
-      const double* jp = jpart + (size_t)rb * nchunk * (NS + 1) * np + p;
-#pragma unroll 4
-      for (int c = 0; c < nchunk; ++c) {
+  for (int k = 0; k < kMaxTasks; ++k) acc[k] = 0.0;
+  double v[NV], cf[kMaxCoefs];
+  // Rays past the batch's last are zeros, which the unrolled loop below adds.
+  auto load = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) ib[s] += jp[s * (size_t)np];
-        lam += jp[NS * (size_t)np];
-        jp += (NS + 1) * (size_t)np;
+    for (int k = 0; k < kMaxCoefs; ++k) {
+      const int e = threadIdx.x + k * threads, r = e / kJCoefs, q = e - r * kJCoefs;
+      cf[k] = 0.0;
+      if (r < G && r0 + r < J.nrb) {
+        const RayConsts& rc = J.rays[r0 + r];
+        cf[k] = *(q == 0 ? &rc.weight : &rc.proj[0][0] + (q - 1));
       }
     }
-    jproject<NS>(rays[rb], ib, lam, acc);
+    const int rb = r0 + g;
+#pragma unroll
+    for (int s = 0; s < NV; ++s) v[s] = 0.0;
+    if (rb >= J.nrb || p >= np) return;
+    if (!J.part) {
+      v[0] = J.ibound;
+      return;
+    }
+    const double* jp = J.part + (size_t)rb * NV * np + p;   // one chunk
+#pragma unroll
+    for (int s = 0; s < NV; ++s) v[s] = jp[s * (size_t)np];
+  };
+  if (works) load(0);
+  for (int r0 = 0; r0 < J.nrb; r0 += G) {
+    const int nr = min(G, J.nrb - r0);
+    if (works) {
+#pragma unroll
+      for (int s = 0; s < NV; ++s) s_part[(g * NV + s) * kJNodes + n] = v[s];
+#pragma unroll
+      for (int k = 0; k < kMaxCoefs; ++k) {
+        const int e = threadIdx.x + k * threads;
+        if (e < G * kJCoefs) s_coef[e] = cf[k];
+      }
+    }
+    __syncthreads();
+    if (works) load(r0 + G);
+    if (works) {
+#pragma unroll
+      for (int k = 0; k < kMaxTasks; ++k) {
+        const int e = threadIdx.x + k * threads;
+        if (e < kTasks) {
+          const int c = e / kJNodes;
+          const double* part = s_part + e % kJNodes;
+          const double* coef = s_coef + (c < 9 ? 1 + 4 * c : 0);
+          const double* weight = s_coef;
+          for (int r = 0; r < nr; r += 4) {   // G is a multiple of 4
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              double x;
+              if constexpr (NS == 4) {
+                x = dot3(coef[1], part[kJNodes], coef[0], part[0], coef[2], part[2 * kJNodes]);
+                x = fma_t(coef[3], part[3 * kJNodes], x);
+              } else {
+                x = coef[0] * part[0];
+              }
+              acc[k] = fma_t(*weight, c == 9 ? part[NS * kJNodes] : x, acc[k]);
+              part += NV * kJNodes;
+              coef += kJCoefs;
+              weight += kJCoefs;
+            }
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (!works) return;
+#pragma unroll
+  for (int k = 0; k < kMaxTasks; ++k) {
+    const int e = threadIdx.x + k * threads, q = node0 + e % kJNodes;
+    if (e < kTasks && q < np) jkq[(e / kJNodes) * N + J.off + q] += acc[k];
   }
 }
 
-// lds: jlds_bytes(blockDim.x); every thread of the block calls it.
-__device__ inline void jadd_groups(const double acc[10], double* __restrict__ jkq, size_t N,
-                                   size_t plane_off, int np, int node0, double* lds) {
-  const int n = threadIdx.x % kJNodes, g = threadIdx.x / kJNodes, G = blockDim.x / kJNodes;
+// Group g of the threads, (group, node), adds rays g, g + G, ..., and the groups are added
+// through LDS: no barrier between the loads of one ray and the next's, and the projections on
+// all the threads.
+template <int NS>
+__device__ inline void jreduce_groups(const JJob& J, double* __restrict__ jkq, size_t N, int np,
+                                      int node0, double* lds, int threads) {
+  constexpr int NV = NS + 1;
+  const int G = threads / kJNodes;
+  const int g = threadIdx.x / kJNodes, n = threadIdx.x % kJNodes, p = node0 + n;
+  const bool works = (int)threadIdx.x < threads;
+  double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (works && p < np) {
+    for (int rb = g; rb < J.nrb; rb += G) {
+      double v[NV];
 #pragma unroll
-  for (int c = 0; c < 10; ++c) lds[(c * G + g) * kJNodes + n] = acc[c];
+      for (int s = 0; s < NV; ++s) v[s] = 0.0;
+      if (!J.part) {
+        v[0] = J.ibound;
+      } else {
+        const double* jp = J.part + (size_t)rb * J.nchunk * NV * np + p;
+#pragma unroll 4
+        for (int c = 0; c < J.nchunk; ++c) {
+#pragma unroll
+          for (int s = 0; s < NV; ++s) v[s] += jp[s * (size_t)np];
+          jp += NV * (size_t)np;
+        }
+      }
+      const RayConsts& rc = J.rays[rb];
+      const double w = rc.weight;
+#pragma unroll
+      for (int c = 0; c < 9; ++c) {
+        double x = rc.proj[c][0] * v[0];
+        if constexpr (NS == 4)
+          x = fma_t(rc.proj[c][3], v[3], fma_t(rc.proj[c][2], v[2], fma_t(rc.proj[c][1], v[1], x)));
+        acc[c] = fma_t(w, x, acc[c]);
+      }
+      acc[9] = fma_t(w, v[NS], acc[9]);
+    }
+  }
+  if (works) {
+#pragma unroll
+    for (int c = 0; c < 10; ++c) lds[(c * G + g) * kJNodes + n] = acc[c];
+  }
   __syncthreads();
-  for (int e = threadIdx.x; e < 10 * kJNodes; e += blockDim.x) {
+  if (!works) return;
+  for (int e = threadIdx.x; e < 10 * kJNodes; e += threads) {
     const int c = e / kJNodes, q = node0 + e % kJNodes;
     double sum = 0.0;
     for (int k = 0; k < G; ++k) sum += lds[(c * G + k) * kJNodes + e % kJNodes];
-    if (q < np) jkq[c * N + plane_off + q] += sum;
+    if (q < np) jkq[c * N + J.off + q] += sum;
   }
 }
 
-template <int NS>
+// Every thread of the block calls it; the first `threads` of them work.  T: precision of the
+// sweep.
+template <int NS, class T>
+__device__ inline void jreduce_block(const JJob& J, double* __restrict__ jkq, size_t N, int np,
+                                     int node0, double* lds, int threads) {
+  if constexpr (sizeof(T) == 4)
+    jreduce_ordered<NS>(J, jkq, N, np, node0, lds, threads);
+  else
+    jreduce_groups<NS>(J, jkq, N, np, node0, lds, threads);
+}
+
+template <int NS, class T>
 __global__ void __launch_bounds__(256)
-    k_jreduce(double* __restrict__ jkq, const double* __restrict__ jpart,
-              const RayConsts* __restrict__ rays, int ray0, int nrb, int nchunk, int np, size_t N,
-              size_t plane_off, double ibound) {
+    k_jreduce(const JJob J, double* __restrict__ jkq, int np, size_t N) {
   extern __shared__ double s_tab[];
-  const int node0 = blockIdx.x * kJNodes, p = node0 + threadIdx.x % kJNodes;
-  double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  if (p < np) jsum_rays<NS>(jpart, rays + ray0, nrb, nchunk, np, p, ibound, acc);
-  jadd_groups(acc, jkq, N, plane_off, np, node0, s_tab);
+  jreduce_block<NS, T>(J, jkq, N, np, blockIdx.x * kJNodes, s_tab, blockDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -449,18 +637,18 @@ struct PlaneArgs {
   const T* prop;
   const T* emis;
   const RayConsts* rays;
+  const RayGeom* geom;
   const T* phi;
   const double* wn;
   HemiArgs<T> h[2];
   double* jkq;       // [10][N] or nullptr
   size_t N;
-  int nx, ny, np, nfreq;
+  int nx, ny, nz, np, nfreq;
   int ntile;         // tiles of blockDim.x nodes in a plane
   int nchunk, fchunk;
   int nstep;         // blocks of the plane step; the J reduction's follow
   int njb;           // blocks of the J reduction
   int jsame;         // both hemispheres' previous plane is the same one: one block adds both
-  double inv_dx, inv_dy;
   int xcd_remap;     // tiles per XCD per round (0: hardware order), see xcd_tile
   int parabolic;     // control point: 0 BESSER, 1 parabola through M, O, P
 };
@@ -480,8 +668,6 @@ __device__ inline HemiArgs<T> hemi_args(const PlaneArgs<T>& a, bool second) {
   h.kO = second ? d.kO : u.kO;
   h.kM = second ? d.kM : u.kM;
   h.kP = second ? d.kP : u.kP;
-  h.dzM = second ? d.dzM : u.dzM;
-  h.dzP = second ? d.dzP : u.dzP;
   h.ray0 = second ? d.ray0 : u.ray0;
   h.nrb = second ? d.nrb : u.nrb;
   h.ibound = second ? d.ibound : u.ibound;
@@ -496,15 +682,13 @@ __device__ inline void jblock(const PlaneArgs<T>& a, double* lds) {
   const int node0 = (b - hemi * per) * kJNodes;
   const HemiArgs<T> h = hemi_args(a, hemi);
   if (node0 >= a.np || h.nrb == 0 || (hemi && a.jsame)) return;
-  const int p = node0 + threadIdx.x % kJNodes;
-  double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  if (p < a.np) {
-    jsum_rays<NS>(h.jpart_prev, a.rays + h.ray0, h.nrb, a.nchunk, a.np, p, (double)h.ibound, acc);
-    if (a.jsame)
-      jsum_rays<NS>(a.h[1].jpart_prev, a.rays + a.h[1].ray0, a.h[1].nrb, a.nchunk, a.np, p,
-                    (double)a.h[1].ibound, acc);
+  const JJob j = {h.jpart_prev, a.rays + h.ray0, h.nrb, a.nchunk, (double)h.ibound, h.prev_off};
+  jreduce_block<NS, T>(j, a.jkq, a.N, a.np, node0, lds, blockDim.x);
+  if (a.jsame) {
+    const HemiArgs<T>& d = a.h[1];
+    const JJob k = {d.jpart_prev, a.rays + d.ray0, d.nrb, a.nchunk, (double)d.ibound, h.prev_off};
+    jreduce_block<NS, T>(k, a.jkq, a.N, a.np, node0, lds, blockDim.x);
   }
-  jadd_groups(acc, a.jkq, a.N, h.prev_off, a.np, node0, lds);
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs of the MI355X, each with
@@ -551,8 +735,6 @@ __device__ inline StepBlock step_block(const PlaneArgs<T>& a) {
   return b;
 }
 
-constexpr int kMaxFreq = 4096;   // frequencies held in LDS by the sweep kernels
-
 template <class T>
 __device__ inline void load_upwind(const T* __restrict__ q, const Stencil& s, T v[4][4]) {
   load4(q + 4 * (size_t)s.i00, v[0]);
@@ -582,6 +764,29 @@ __device__ inline void upwind_bez9(const T* __restrict__ q, const Stencil9& s,
 template <class T>
 __device__ inline T bilinear(T w00, T w10, T w01, T w11, T v00, T v10, T v01, T v11) {
   return fma_t(w11, v11, dot3(w00, v00, w10, v10, w01, v01));
+}
+
+// Entries (e, r) of K' = K / eta_I - 1 in the sweep precision.
+template <class T>
+__device__ inline void kprime_entries(const double eta[6], double ik, T e[3], T r[3]) {
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    e[c] = (T)(eta[c] * ik);
+    r[c] = (T)(eta[3 + c] * ik);
+  }
+}
+
+// The right-hand side of Eq. fsbez with Eq. kappa, (e - psi'_M K'_M) I_M + sources, with
+// KI = K'_M I_M; Stokes V has no source.
+template <class T>
+__device__ inline void step_rhs(const Coefs<T>& cf, const T IM[4], const T KI[4],
+                                const StepSource<T> src[3], T b[4]) {
+  const StepSource<T> w = source_weights(cf);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    b[s] = fma_t(cf.e, IM[s], -(cf.psiM * KI[s]));
+    if (s < 3) b[s] = add_sources(w, src[s], b[s]);
+  }
 }
 
 // Occupancy targets: three waves per SIMD for the FP32 bilinear sweep (168 VGPRs,
@@ -615,38 +820,26 @@ k_sweep_plane(const PlaneArgs<T> a) {
   const RayConsts& rc = a.rays[h.ray0 + sb.rb];
   PointSetup ps;
   Stencil9 sM9;
-  setup_point<MODE>(a.kappa, a.prop, a.emis, a.N, a.nx, a.ny, a.np, h.kO, h.kM, h.kP, h.dzM,
-                    h.dzP, a.inv_dx, a.inv_dy, rc, p, a.parabolic != 0, ps, sM9);
+  const int ray = h.ray0 + sb.rb;
+  setup_point<MODE>(a.kappa, a.prop, a.emis, a.N, a.nx, a.ny, a.np, h.kO, h.kM, h.kP,
+                    layer_geom(a.geom, ray, a.nz, h.kO, h.kM, 0),
+                    layer_geom(a.geom, ray, a.nz, h.kO, h.kP < 0 ? h.kM : h.kP, 1), rc, p,
+                    a.parabolic != 0, ps, sM9);
   const BezW<T> bwx = bez_weights(MODE == 1 ? (T)sM9.tx : T(0));
   const BezW<T> bwy = bez_weights(MODE == 1 ? (T)sM9.ty : T(0));
   const Stencil& sM = ps.sM;
-  const double ikM = ps.ikM, ikO = ps.ikO;
-  const double* etaM = ps.etaM;
-  const double* etaO = ps.etaO;
-  const double* SM = ps.SM;
-  const double* SO = ps.SO;
-  const double* cM = ps.cM;
-  const double tau0M = ps.tau0M;
-  // Lambda* = omega_O + omega_C c_M for a unit source at O alone (Eq. 14): c_M is 1 for
-  // BESSER, (1 + ratio)/2 for the parabola, 1/2 without a downwind point
-  const double lamfac = ps.hasP ? control_cm(0.0, 1.0, 0.0, ps.ratio, a.parabolic != 0) : 0.5;
 
   // frequency-independent pieces in the sweep precision
-  const T eMv[3] = {(T)(etaM[0] * ikM), (T)(etaM[1] * ikM), (T)(etaM[2] * ikM)};
-  const T rMv[3] = {(T)(etaM[3] * ikM), (T)(etaM[4] * ikM), (T)(etaM[5] * ikM)};
-  const T eOv[3] = {(T)(etaO[0] * ikO), (T)(etaO[1] * ikO), (T)(etaO[2] * ikO)};
-  const T rOv[3] = {(T)(etaO[3] * ikO), (T)(etaO[4] * ikO), (T)(etaO[5] * ikO)};
-  const StokesOp<T> KO = stokes_op(eOv, rOv);
-  T SMt[4], SOt[4], cMt[4];
+  T eMv[3], rMv[3], eOv[3], rOv[3];
+  kprime_entries(ps.etaM, ps.ikM, eMv, rMv);
+  kprime_entries(ps.etaO, ps.ikO, eOv, rOv);
+  const auto KO = step_op(eOv, rOv);
+  StepSource<T> src[3];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    SMt[s] = (T)SM[s];
-    SOt[s] = (T)SO[s];
-    cMt[s] = (T)cM[s];
-  }
-  const T tau0 = (T)tau0M;
+  for (int s = 0; s < 3; ++s) step_source(ps.SM[s], ps.SO[s], ps.cM[s], src[s]);
+  const T tau0 = (T)ps.tau0M;
   const T w00 = (T)sM.w00, w10 = (T)sM.w10, w01 = (T)sM.w01, w11 = (T)sM.w11;
-  const T lf = (T)lamfac;
+  const T lf = (T)ps.lamfac;
 
   const size_t fstride = (size_t)a.np * 4;
   const size_t foff = ((size_t)sb.rb * a.nfreq + f0) * fstride;
@@ -658,24 +851,18 @@ k_sweep_plane(const PlaneArgs<T> a) {
   // Stokes vector IM
   auto update = [&](int f, T i0, T i1, T i2, T i3) __attribute__((always_inline)) {
     const T IM[4] = {i0, i1, i2, i3};
-    const T tau = tau0 * s_phi[f];
-    const Coefs<T> cf = coefficients(tau);
-    T KI[4];
+    const Coefs<T> cf = coefficients(tau0 * s_phi[f]);
+    T KI[4], b[4], x[4];
     kprime_apply(eMv, rMv, IM, KI);
-    T b[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      b[s] = fma_t(cf.omC, cMt[s], fma_t(cf.omO, SOt[s], fma_t(cf.omM, SMt[s],
-                   fma_t(cf.e, IM[s], -(cf.psiM * KI[s])))));
-    T x[4];
-    stokes_solve<1>(KO, stokes_freq(KO, cf.psiO), b, x);
+    step_rhs(cf, IM, KI, src, b);
+    stokes_solve<1>(KO, step_freq(KO, cf.psiO), b, x);
     store4_nt(op + (size_t)f * fstride, x);
     const double W = s_wn[f];
-    jacc0 += W * (double)x[0];
-    jacc1 += W * (double)x[1];
-    jacc2 += W * (double)x[2];
-    jacc3 += W * (double)x[3];
-    lacc += W * (double)fma_t(lf, cf.omC, cf.omO);
+    jacc0 = fma_t(W, (double)x[0], jacc0);
+    jacc1 = fma_t(W, (double)x[1], jacc1);
+    jacc2 = fma_t(W, (double)x[2], jacc2);
+    jacc3 = fma_t(W, (double)x[3], jacc3);
+    lacc = fma_t(W, (double)lambda_star(cf, lf), lacc);
   };
   // bilinear upwind component s from the four corner values
 #define PORTA_BILIN(v, s) bilinear(w00, w10, w01, w11, v[0][s], v[1][s], v[2][s], v[3][s])

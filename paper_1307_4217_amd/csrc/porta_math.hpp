@@ -48,71 +48,83 @@ __host__ __device__ inline T dot3(T a0, T b0, T a1, T b1, T a2, T b2) {
 // Coefficients of Eq. fsbez (Sect. 3.3):
 //   e = exp(-tau), psi'_M, psi'_O (linear K'I), omega_M, omega_O, omega_C
 //   (quadratic Bezier source function with control point c_M).
-// Below a threshold the closed forms cancel; a Taylor series about tau = 0 is
-// used instead (Table 1 gives the FP64 thresholds 0.14 / 0.18 for the omegas).
-// FP32 switches at tau = 1.2 (one series for all six, below); FP64 uses eight
-// terms of each coefficient's own series below the paper's thresholds (0.1 for
-// the psi').
+// All follow from the exponential remainders
+//   E_n(t) = sum_k (-t)^k / (k + n)!,   E_n = 1/n! - t E_{n+1},   e = 1 - t E_1,
+// because the series of the coefficients (Table 1) regroup, from
+// 1/(n!(n+2)) = 1/(n+1)! - 1/(n+2)!, 1/(n!(n+3)) = 1/(n+1)! - 2/(n+2)! + 2/(n+3)! and
+// 2/(n!(n+2)(n+3)) = 2/(n+2)! - 4/(n+3)!, to
+//   psi'_O = t E_2,   psi'_M = t (E_1 - E_2),   omega_O = 2 t E_3,
+//   omega_M = t (E_1 - 2 E_2 + 2 E_3),   omega_C = t (2 E_2 - 4 E_3).
+// Below SeriesE3::kTau the series of E_3 is summed (FP32: ten terms, every coefficient
+// within 1e-6 relative; FP64: 17, the next is below the unit roundoff at kTau) and E_2, E_1,
+// e follow by the recurrence, which is stable there; above it the closed forms.  (In FP64 the
+// closed forms from the paper's thresholds on, 0.1 to 0.18, with a series per coefficient
+// below them, cost an exponential, a division and up to 36 terms for every thin step, and
+// lose up to 3e-13 just above the thresholds.)
 // ---------------------------------------------------------------------------
 template <class T>
 struct Coefs {
   T e, psiM, psiO, omM, omO, omC;
-  T em1;             // 1 - e to the relative precision of T, formed on request (EM1 of
-                     // coefficients), for an update written as I_M - em1 I_M: e itself,
-                     // rounded next to 1 in FP32, is off by up to 3e-8 for thin steps, a
-                     // bias that a chain of thousands of steps would add up
+  T em1;             // 1 - e = t E_1 to the relative precision of T, for an update written as
+                     // I_M - em1 I_M: e itself, rounded next to 1 in FP32, is off by up to
+                     // 3e-8 for thin steps, a bias that a chain of thousands of steps would
+                     // add up
   T pmt, omt, oct;   // psi'_M / tau, omega_M / tau, omega_C / tau (for the tau-derivatives)
+  T t3;              // t E_3 = omega_O / 2
 };
 
-// Horner evaluation of tau * sum_{n<NT} c_n tau^n.
-template <class T, int NT>
-__host__ __device__ inline T series(T tau, const T (&c)[NT]) {
-  T acc = c[NT - 1];
-#pragma unroll
-  for (int n = NT - 2; n >= 0; --n) acc = acc * tau + c[n];
-  return acc * tau;
+template <class T>
+struct SeriesE3;
+template <>
+struct SeriesE3<float> {
+  static constexpr int kTerms = 10;
+  static constexpr float kTau = 1.2f;
+};
+template <>
+struct SeriesE3<double> {
+  static constexpr int kTerms = 17;
+  static constexpr double kTau = 1.0;
+};
+
+// (-1)^n / (n + 3)!
+__host__ __device__ constexpr double series_e3_term(int n) {
+  double f = 1.0;
+  for (int k = 2; k <= n + 3; ++k) f *= k;
+  return (n & 1 ? -1.0 : 1.0) / f;
 }
 
-// FP32 below tau = 1.2: all six from one series.  With the exponential remainders
-//   E_n(t) = sum_k (-t)^k / (k + n)!,   E_n = 1/n! - t E_{n+1},   e = 1 - t E_1,
-// the series of the coefficients regroup as
-//   psi'_O = t E_2,   psi'_M = t (E_1 - E_2),   omega_O = 2 t E_3,
-//   omega_M = t (E_1 - 2 E_2 + 2 E_3),   omega_C = t (2 E_2 - 4 E_3),
-// (from 1/(n!(n+2)) = 1/(n+1)! - 1/(n+2)!, 1/(n!(n+3)) = 1/(n+1)! - 2/(n+2)! + 2/(n+3)!
-// and 2/(n!(n+2)(n+3)) = 2/(n+2)! - 4/(n+3)!), so ten terms of E_3 and the downward
-// recurrence (stable for t < 1.2) give every coefficient within 1e-6 relative.
-template <bool EM1 = false>
-__host__ __device__ inline Coefs<float> coefficients(float tau) {
-  Coefs<float> c;
-  if (tau < 1.2f) {
-    const float kE3[10] = {1.0f / 6, -1.0f / 24, 1.0f / 120, -1.0f / 720, 1.0f / 5040,
-                           -1.0f / 40320, 1.0f / 362880, -1.0f / 3628800, 1.0f / 39916800,
-                           -1.0f / 479001600};
-    float E3 = kE3[9];
+template <class T>
+__host__ __device__ inline Coefs<T> coefficients(T tau) {
+  Coefs<T> c;
+  if (tau < SeriesE3<T>::kTau) {
+    constexpr int NT = SeriesE3<T>::kTerms;
+    T E3 = (T)series_e3_term(NT - 1);
 #pragma unroll
-    for (int n = 8; n >= 0; --n) E3 = fma_t(E3, tau, kE3[n]);
-    const float E2 = fma_t(-tau, E3, 0.5f);
-    const float E1 = fma_t(-tau, E2, 1.0f);
-    c.e = fma_t(-tau, E1, 1.0f);
-    if constexpr (EM1) c.em1 = tau * E1;
+    for (int n = NT - 2; n >= 0; --n) E3 = fma_t(E3, tau, (T)series_e3_term(n));
+    const T E2 = fma_t(-tau, E3, T(0.5));
+    const T E1 = fma_t(-tau, E2, T(1));
+    c.e = fma_t(-tau, E1, T(1));
+    c.em1 = tau * E1;
     c.pmt = E1 - E2;
-    c.omt = fma_t(2.0f, E3 - E2, E1);
-    c.oct = fma_t(2.0f, E2, -4.0f * E3);
+    c.omt = fma_t(T(2), E3 - E2, E1);
+    c.oct = fma_t(T(2), E2, T(-4) * E3);
     c.psiO = tau * E2;
     c.psiM = tau * c.pmt;
-    c.omO = (2.0f * tau) * E3;
+    c.t3 = tau * E3;
+    c.omO = (T(2) * tau) * E3;
     c.omM = tau * c.omt;
     c.omC = tau * c.oct;
   } else {
     c.e = exp_neg(tau);
-    if constexpr (EM1) c.em1 = 1.0f - c.e;
-    const float it = recip(tau), it2 = it * it;
-    const float g = c.e + tau - 1.0f;               // e + tau - 1
+    c.em1 = T(1) - c.e;
+    const T it = recip(tau), it2 = it * it;
+    const T g = c.e + tau - T(1);
     c.psiO = g * it;
-    c.psiM = fma_t(-c.e, 1.0f + tau, 1.0f) * it;
-    c.omM = fma_t(-c.e, fma_t(tau, tau, 2.0f * tau) + 2.0f, 2.0f) * it2;
-    c.omO = fma_t(-2.0f * g, it2, 1.0f);
-    c.omC = 2.0f * fma_t(c.e, tau + 2.0f, tau - 2.0f) * it2;
+    c.psiM = fma_t(-c.e, T(1) + tau, T(1)) * it;
+    c.omM = fma_t(-c.e, fma_t(tau, tau, T(2) * tau) + T(2), T(2)) * it2;
+    c.t3 = fma_t(-g, it2, T(0.5));
+    c.omO = fma_t(T(-2) * g, it2, T(1));
+    c.omC = T(2) * fma_t(c.e, tau + T(2), tau - T(2)) * it2;
     c.pmt = c.psiM * it;
     c.omt = c.omM * it;
     c.oct = c.omC * it;
@@ -120,45 +132,43 @@ __host__ __device__ inline Coefs<float> coefficients(float tau) {
   return c;
 }
 
-template <bool EM1 = false>
-__host__ __device__ inline Coefs<double> coefficients(double tau) {
-  // eight terms, identical to the rows of Table 1 for the omegas
-  const double kPM[8] = {1.0 / 2, -1.0 / 3, 1.0 / 8, -1.0 / 30, 1.0 / 144, -1.0 / 840,
-                         1.0 / 5760, -1.0 / 45360};
-  const double kPO[8] = {1.0 / 2, -1.0 / 6, 1.0 / 24, -1.0 / 120, 1.0 / 720, -1.0 / 5040,
-                         1.0 / 40320, -1.0 / 362880};
-  const double kOM[8] = {1.0 / 3, -1.0 / 4, 1.0 / 10, -1.0 / 36, 1.0 / 168, -1.0 / 960,
-                         1.0 / 6480, -1.0 / 50400};
-  const double kOO[8] = {1.0 / 3, -1.0 / 12, 1.0 / 60, -1.0 / 360, 1.0 / 2520, -1.0 / 20160,
-                         1.0 / 181440, -1.0 / 1814400};
-  const double kOC[8] = {1.0 / 3, -1.0 / 6, 1.0 / 20, -1.0 / 90, 1.0 / 504, -1.0 / 3360,
-                         1.0 / 25920, -1.0 / 226800};
-  Coefs<double> c;
-  c.e = exp_neg(tau);
-  if constexpr (EM1) c.em1 = 1.0 - c.e;   // FP64: the same bias is 1e-16 per step
-  const double it = 1.0 / tau, it2 = it * it;
-  if (tau < 0.1) {
-    c.psiM = series(tau, kPM);
-    c.psiO = series(tau, kPO);
-  } else {
-    c.psiM = (1.0 - c.e * (1.0 + tau)) * it;
-    c.psiO = (c.e + tau - 1.0) * it;
-  }
-  if (tau < 0.14)
-    c.omM = series(tau, kOM);
-  else
-    c.omM = (2.0 - c.e * (tau * tau + 2.0 * tau + 2.0)) * it2;
-  if (tau < 0.18) {
-    c.omO = series(tau, kOO);
-    c.omC = series(tau, kOC);
-  } else {
-    c.omO = 1.0 - 2.0 * (c.e + tau - 1.0) * it2;
-    c.omC = 2.0 * (tau - 2.0 + c.e * (tau + 2.0)) * it2;
-  }
-  c.pmt = c.psiM * it;
-  c.omt = c.omM * it;
-  c.oct = c.omC * it;
-  return c;
+// The source terms of the update, omega_M S_M + omega_O S_O + omega_C c_M, as a sum of three
+// weights times three values of the node.  FP32 takes the omegas and S_M, S_O, c_M.  FP64
+// takes t E_1, t E_2, t E_3, which the coefficients form on the way, and
+//   A_1 = S_M,   A_2 = 2 (c_M - S_M),   A_3 = 2 (S_M + S_O - 2 c_M),
+// and needs no omega (5 operations less per update; their rounding is that of the sum).
+template <class T>
+struct StepSource {
+  T a, b, c;
+};
+
+__host__ __device__ inline void step_source(double SM, double SO, double cM, StepSource<float>& s) {
+  s = {(float)SM, (float)SO, (float)cM};
+}
+__host__ __device__ inline void step_source(double SM, double SO, double cM,
+                                            StepSource<double>& s) {
+  s = {SM, 2.0 * (cM - SM), 2.0 * ((SM - cM) + (SO - cM))};
+}
+
+__host__ __device__ inline StepSource<float> source_weights(const Coefs<float>& c) {
+  return {c.omM, c.omO, c.omC};
+}
+__host__ __device__ inline StepSource<double> source_weights(const Coefs<double>& c) {
+  return {c.em1, c.psiO, c.t3};
+}
+
+// v + sources
+template <class T>
+__host__ __device__ inline T add_sources(const StepSource<T>& w, const StepSource<T>& s, T v) {
+  return fma_t(w.c, s.c, fma_t(w.b, s.b, fma_t(w.a, s.a, v)));
+}
+
+// Lambda* = omega_O + lf omega_C (Eq. 14)
+__host__ __device__ inline float lambda_star(const Coefs<float>& c, float lf) {
+  return fma_t(lf, c.omC, c.omO);
+}
+__host__ __device__ inline double lambda_star(const Coefs<double>& c, double lf) {
+  return 2.0 * fma_t(lf, fma_t(-2.0, c.t3, c.psiO), c.t3);
 }
 
 // ---------------------------------------------------------------------------
@@ -189,18 +199,18 @@ __host__ __device__ inline double parabolic_cm(double yM, double yO, double yP, 
 }
 
 // The control point of either rule from one evaluation of steps 1, 3 and 4: the
-// parabolic rule returns there, BESSER goes on with its tests (same result as
-// besser_cm).
-__host__ __device__ inline double control_cm(double yM, double yO, double yP, double r,
-                                             bool parabolic) {
-  const double dM = yO - yM, dP = yP - yO;
-  const double inv = 0.5 / (1.0 + r);
-  const double cM = yO - (r * r * dP + dM) * inv;
+// parabolic rule returns there, BESSER goes on with its tests (the result of besser_cm).
+// dP = y_P - y_O, which the caller can form with one rounding less than from y_P; inv = 0.5 /
+// (1 + r) and ir = 1 / r are the same for every Stokes parameter of a node.
+__host__ __device__ inline double control_cm(double yM, double yO, double yP, double dP, double r,
+                                             double inv, double ir, bool parabolic) {
+  const double dM = yO - yM;
+  const double cM = fma_t(-inv, fma_t(r * r, dP, dM), yO);
   if (parabolic) return cM;
   if (dM * dP <= 0.0) return yO;
   if ((cM - yM) * (cM - yO) > 0.0) return yM;
-  const double cP = yO + (r * dP + dM / r) * inv;
-  if ((cP - yO) * (cP - yP) > 0.0) return yO - r * dP;
+  const double cP = fma_t(inv, fma_t(r, dP, dM * ir), yO);
+  if ((cP - yO) * (cP - yP) > 0.0) return fma_t(-r, dP, yO);
   return cM;
 }
 
@@ -255,7 +265,7 @@ __host__ __device__ inline T bez_eval(const BezW<T>& w, T ym, T y0, T yp) {
   const T m = fmin(fmin(fabs(d1), fabs(d2)), T(0.25) * fabs(d1 + d2));
   // a zero difference gives m = 0, so only opposite strict signs need the test
   const T q = ((d1 > T(0)) == (d2 > T(0))) ? copysign(m, d1) : T(0);
-  return fma_t(w.e, q, dot3(w.a, ym, w.b, y0, w.c, yp));
+  return fma_t(w.e, q, dot3(w.b, y0, w.a, ym, w.c, yp));
 }
 
 // bez_eval with its partial derivatives g = d/d(ym, y0, yp), on the branches the value
@@ -282,7 +292,7 @@ __host__ __device__ inline T bez_eval_grad(const BezW<T>& w, T ym, T y0, T yp, T
   g[0] = w.a - w.e * q1;
   g[1] = w.b + w.e * (q1 - q2);
   g[2] = w.c + w.e * q2;
-  return w.a * ym + w.b * y0 + w.c * yp + w.e * q;
+  return fma_t(w.e, q, dot3(w.b, y0, w.a, ym, w.c, yp));
 }
 
 template <class T>
@@ -332,17 +342,21 @@ __host__ __device__ inline double parabolic_cm_grad(double yM, double yO, double
   return yO - (r * r * dP + dM) * inv;
 }
 
-// dL/dtau from the adjoints of the six coefficients, with the derivatives
-// written through the coefficients themselves (pmt = psi'_M/t, omt = omega_M/t,
+// dL/dtau from the adjoints of e, psi'_M, psi'_O and of the three source weights, with the
+// derivatives written through the coefficients themselves (pmt = psi'_M/t, omt = omega_M/t,
 // oct = omega_C/t, formed with the coefficients):
 //   de/dt = -e,                 dpsi'_M/dt = e - pmt,   dpsi'_O/dt = pmt,
 //   domega_M/dt = e - 2 omt,    domega_C/dt = 2 (pmt - oct),
-//   domega_O/dt = 2 (omt + oct - pmt)   (from omega_M+omega_O+omega_C = 1-e).
-template <class T>
-__host__ __device__ inline T coef_tau_grad(const Coefs<T>& c, T gE, T gPM, T gPO, T gOM, T gOO,
-                                           T gOC) {
-  return -c.e * gE + (c.e - c.pmt) * gPM + c.pmt * gPO + (c.e - T(2) * c.omt) * gOM +
-         T(2) * (c.omt + c.oct - c.pmt) * gOO + T(2) * (c.pmt - c.oct) * gOC;
+//   domega_O/dt = 2 (omt + oct - pmt)   (from omega_M+omega_O+omega_C = 1-e),
+//   d(t E_1)/dt = e,            d(t E_2)/dt = pmt,      d(t E_3)/dt = oct / 2.
+__host__ __device__ inline float coef_tau_grad(const Coefs<float>& c, float gE, float gPM,
+                                               float gPO, float gOM, float gOO, float gOC) {
+  return -c.e * gE + (c.e - c.pmt) * gPM + c.pmt * gPO + (c.e - 2.0f * c.omt) * gOM +
+         2.0f * (c.omt + c.oct - c.pmt) * gOO + 2.0f * (c.pmt - c.oct) * gOC;
+}
+__host__ __device__ inline double coef_tau_grad(const Coefs<double>& c, double gE, double gPM,
+                                                double gPO, double g1, double g2, double g3) {
+  return dot3(c.e, g1 + gPM - gE, c.pmt, gPO - gPM + g2, 0.5 * c.oct, g3);
 }
 
 // ---------------------------------------------------------------------------
@@ -400,14 +414,14 @@ __host__ __device__ inline StokesOp<T> stokes_op(const T e[3], const T r[3]) {
     k.e[i] = e[i];
     k.r[i] = r[i];
   }
-  k.X[0] = e[1] * r[2] - e[2] * r[1];
-  k.X[1] = e[2] * r[0] - e[0] * r[2];
-  k.X[2] = e[0] * r[1] - e[1] * r[0];
-  const T er = e[0] * r[0] + e[1] * r[1] + e[2] * r[2];
+  k.X[0] = fma_t(e[1], r[2], -(e[2] * r[1]));
+  k.X[1] = fma_t(e[2], r[0], -(e[0] * r[2]));
+  k.X[2] = fma_t(e[0], r[1], -(e[1] * r[0]));
+  const T er = dot3(e[1], r[1], e[0], r[0], e[2], r[2]);
 #pragma unroll
   for (int i = 0; i < 3; ++i) k.C[i] = er * r[i];
-  k.rr = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-  k.ee = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
+  k.rr = dot3(r[1], r[1], r[0], r[0], r[2], r[2]);
+  k.ee = dot3(e[1], e[1], e[0], e[0], e[2], e[2]);
   k.er2 = er * er;
   return k;
 }
@@ -428,7 +442,7 @@ __host__ __device__ inline StokesFreq<T> stokes_freq(const StokesOp<T>& k, T p) 
 }
 
 // x = (1 + p K')^-1 b (SGN = 1) or (1 + p K')^-T b (SGN = -1).
-template <int SGN, class T>
+template <int SGN, bool FACES = false, class T>
 __host__ __device__ inline void stokes_solve(const StokesOp<T>& k, const StokesFreq<T>& F,
                                              const T b[4], T x[4]) {
   const T q = SGN > 0 ? F.p : -F.p;
@@ -436,7 +450,8 @@ __host__ __device__ inline void stokes_solve(const StokesOp<T>& k, const StokesF
   const T c[3] = {fma_t(-pb0, k.e[0], b[1]), fma_t(-pb0, k.e[1], b[2]), fma_t(-pb0, k.e[2], b[3])};
   const T cx[3] = {fma_t(c[1], k.r[2], -(c[2] * k.r[1])), fma_t(c[2], k.r[0], -(c[0] * k.r[2])),
                    fma_t(c[0], k.r[1], -(c[1] * k.r[0]))};
-  const T p2cr = F.p2 * dot3(c[1], k.r[1], c[0], k.r[0], c[2], k.r[2]);
+  const T p2cr = F.p2 * (FACES ? dot3(c[0], k.r[0], c[1], k.r[1], c[2], k.r[2])
+                               : dot3(c[1], k.r[1], c[0], k.r[0], c[2], k.r[2]));
   const T s = F.p * F.inv_den;
   T u[3], v[3];
 #pragma unroll
@@ -451,13 +466,115 @@ __host__ __device__ inline void stokes_solve(const StokesOp<T>& k, const StokesF
   x[0] = fma_t(-F.p, dot3(k.e[1], x[2], k.e[0], x[1], k.e[2], x[3]), b[0]);
 }
 
-// K' x for the same layout (eta = e, rho = r).
-template <class T>
+// K' x (SGN = 1) or K'^T x (SGN = -1: r -> -r) for the same layout (eta = e, rho = r).
+// FACES: the order in which the first-face sweep rounds the products.
+template <int SGN = 1, bool FACES = false, class T>
 __host__ __device__ inline void kprime_apply(const T e[3], const T r[3], const T x[4], T y[4]) {
-  y[0] = dot3(e[0], x[1], e[1], x[2], e[2], x[3]);
-  y[1] = dot3(e[0], x[0], r[2], x[2], -r[1], x[3]);
-  y[2] = dot3(-r[2], x[1], e[1], x[0], r[0], x[3]);
-  y[3] = dot3(e[2], x[0], r[1], x[1], -r[0], x[2]);
+  const T r0 = SGN > 0 ? r[0] : -r[0], r1 = SGN > 0 ? r[1] : -r[1], r2 = SGN > 0 ? r[2] : -r[2];
+  if constexpr (FACES) {
+    y[0] = dot3(e[1], x[2], e[0], x[1], e[2], x[3]);
+    y[1] = dot3(r2, x[2], e[0], x[0], -r1, x[3]);
+    y[3] = dot3(r1, x[1], e[2], x[0], -r0, x[2]);
+  } else {
+    y[0] = dot3(e[0], x[1], e[1], x[2], e[2], x[3]);
+    y[1] = dot3(e[0], x[0], r2, x[2], -r1, x[3]);
+    y[3] = dot3(e[2], x[0], r1, x[1], -r0, x[2]);
+  }
+  y[2] = dot3(-r2, x[1], e[1], x[0], r0, x[3]);
+}
+
+// The same family by another route, for FP64 and for the adjoint.  K' is a generator of the Lorentz group, so
+// B = K'^2 satisfies B^2 = a B + b with a = e.e - r.r, b = (e.r)^2, hence
+//   (1 + p K')^-1 = (1 - p K') (1 - p^2 B)^-1,
+//   (1 - q B)^-1 = alpha + beta B,   alpha = (1 - q a) / D,  beta = q / D,
+//   D = 1 - q a - q^2 b = det(1 + p K'),   q = p^2.
+// With X = e x r,
+//   B = [[e.e, -X^T], [X, e e^T + r r^T - (r.r) 1]],
+// whose entries are formed once (LorentzOp); a frequency needs one reciprocal (LorentzFreq)
+// instead of two, shared by the system and its transpose, and 10 operations less.  (The FP32
+// sweep stays with StokesOp: J, which it accumulates in FP64, would change by the FP32
+// rounding, 1e-9 of its value.)
+template <class T>
+struct LorentzOp {
+  T e[3], r[3], X[3];
+  T ee, D00, D11, D22, D01, D02, D12;   // B: time part and the symmetric space part
+  T a, b;
+};
+
+template <class T>
+__host__ __device__ inline LorentzOp<T> lorentz_op(const T e[3], const T r[3]) {
+  LorentzOp<T> k;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    k.e[i] = e[i];
+    k.r[i] = r[i];
+  }
+  k.X[0] = e[1] * r[2] - e[2] * r[1];
+  k.X[1] = e[2] * r[0] - e[0] * r[2];
+  k.X[2] = e[0] * r[1] - e[1] * r[0];
+  const T er = e[0] * r[0] + e[1] * r[1] + e[2] * r[2];
+  const T rr = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
+  k.ee = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
+  k.D00 = e[0] * e[0] - (r[1] * r[1] + r[2] * r[2]);
+  k.D11 = e[1] * e[1] - (r[0] * r[0] + r[2] * r[2]);
+  k.D22 = e[2] * e[2] - (r[0] * r[0] + r[1] * r[1]);
+  k.D01 = e[0] * e[1] + r[0] * r[1];
+  k.D02 = e[0] * e[2] + r[0] * r[2];
+  k.D12 = e[1] * e[2] + r[1] * r[2];
+  k.a = k.ee - rr;
+  k.b = er * er;
+  return k;
+}
+
+template <class T>
+struct LorentzFreq {
+  T p, alpha, beta;
+};
+
+template <class T>
+__host__ __device__ inline LorentzFreq<T> lorentz_freq(const LorentzOp<T>& k, T p) {
+  LorentzFreq<T> F;
+  F.p = p;
+  const T q = p * p;
+  const T t = fma_t(-q, k.a, T(1));
+  const T iD = recip(fma_t(-(q * q), k.b, t));
+  F.alpha = t * iD;
+  F.beta = q * iD;
+  return F;
+}
+
+// x = (1 + p K')^-1 b (SGN = 1) or (1 + p K')^-T b (SGN = -1).
+template <int SGN, bool FACES = false, class T>
+__host__ __device__ inline void stokes_solve(const LorentzOp<T>& k, const LorentzFreq<T>& F,
+                                             const T b[4], T x[4]) {
+  // y = (alpha + beta B) b; X -> -X in the transpose
+  const T xb = dot3(k.X[0], b[1], k.X[1], b[2], k.X[2], b[3]);
+  const T B0 = SGN > 0 ? fma_t(k.ee, b[0], -xb) : fma_t(k.ee, b[0], xb);
+  const T s0 = SGN > 0 ? b[0] : -b[0];
+  const T B1 = fma_t(k.X[0], s0, dot3(k.D00, b[1], k.D01, b[2], k.D02, b[3]));
+  const T B2 = fma_t(k.X[1], s0, dot3(k.D01, b[1], k.D11, b[2], k.D12, b[3]));
+  const T B3 = fma_t(k.X[2], s0, dot3(k.D02, b[1], k.D12, b[2], k.D22, b[3]));
+  const T y[4] = {fma_t(F.beta, B0, F.alpha * b[0]), fma_t(F.beta, B1, F.alpha * b[1]),
+                  fma_t(F.beta, B2, F.alpha * b[2]), fma_t(F.beta, B3, F.alpha * b[3])};
+  // x = y - p K' y
+  T z[4];
+  kprime_apply<SGN>(k.e, k.r, y, z);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) x[s] = fma_t(-F.p, z[s], y[s]);
+}
+
+// The route of the sweep in each precision.
+__host__ __device__ inline StokesOp<float> step_op(const float e[3], const float r[3]) {
+  return stokes_op(e, r);
+}
+__host__ __device__ inline LorentzOp<double> step_op(const double e[3], const double r[3]) {
+  return lorentz_op(e, r);
+}
+__host__ __device__ inline StokesFreq<float> step_freq(const StokesOp<float>& k, float p) {
+  return stokes_freq(k, p);
+}
+__host__ __device__ inline LorentzFreq<double> step_freq(const LorentzOp<double>& k, double p) {
+  return lorentz_freq(k, p);
 }
 
 // ---------------------------------------------------------------------------

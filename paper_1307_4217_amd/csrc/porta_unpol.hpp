@@ -28,31 +28,30 @@ __global__ void __launch_bounds__(256) k_sweep_plane_i(const PlaneArgs<T> a) {
   __syncthreads();
   const int p = sb.bx * blockDim.x + threadIdx.x;
   if (p >= a.np) return;   // no barrier follows
-  const RayConsts& rc = a.rays[h.ray0 + sb.rb];
-
   // M on the upwind plane, O, and P on the downwind plane (bilinear in the plane)
-  const int i = p % a.nx, j = p / a.nx;
-  const double inv_mu = 1.0 / fabs(rc.mu);
-  const double dsM = h.dzM * inv_mu;
-  const Stencil sM = make_stencil(i, j, a.nx, a.ny, -dsM * rc.sx * a.inv_dx,
-                                  -dsM * rc.sy * a.inv_dy);
+  const int ray = h.ray0 + sb.rb;
+  const int j = p / a.nx, i = p - j * a.nx;
+  const RayGeom& gM = layer_geom(a.geom, ray, a.nz, h.kO, h.kM, 0);
+  const Stencil sM = make_stencil(i, j, a.nx, a.ny, gM);
   const size_t bM = (size_t)h.kM * a.np, bO = (size_t)h.kO * a.np + p;
   const double kapM = bil(a.kappa + bM, sM), kapO = (double)a.kappa[bO];
   const double SM = bil(a.emis + bM, sM) / kapM, SO = (double)a.emis[bO] / kapO;
-  const double tau0M = 0.5 * (kapM + kapO) * dsM;
+  const double tau0M = 0.5 * (kapM + kapO) * gM.ds;
   double cM = 0.5 * (SM + SO), lamfac = 0.5;   // no downwind plane: linear control point
   if (h.kP >= 0) {
-    const double dsP = h.dzP * inv_mu;
-    const Stencil sP = make_stencil(i, j, a.nx, a.ny, dsP * rc.sx * a.inv_dx,
-                                    dsP * rc.sy * a.inv_dy);
+    const RayGeom& gP = layer_geom(a.geom, ray, a.nz, h.kO, h.kP, 1);
+    const Stencil sP = make_stencil(i, j, a.nx, a.ny, gP);
     const size_t bP = (size_t)h.kP * a.np;
     const double kapP = bil(a.kappa + bP, sP);
     const double SP = bil(a.emis + bP, sP) / kapP;
-    const double ratio = tau0M / (0.5 * (kapO + kapP) * dsP);
-    cM = control_cm(SM, SO, SP, ratio, a.parabolic != 0);
-    lamfac = control_cm(0.0, 1.0, 0.0, ratio, a.parabolic != 0);   // unit source at O
+    const double r = tau0M / (0.5 * (kapO + kapP) * gP.ds), inv = 0.5 / (1.0 + r), ir = 1.0 / r;
+    const bool par = a.parabolic != 0;
+    cM = control_cm(SM, SO, SP, SP - SO, r, inv, ir, par);
+    lamfac = par ? control_cm(0.0, 1.0, 0.0, -1.0, r, inv, ir, true) : 1.0;   // unit source at O
   }
-  const T SMt = (T)SM, SOt = (T)SO, cMt = (T)cM, tau0 = (T)tau0M, lf = (T)lamfac;
+  StepSource<T> src;
+  step_source(SM, SO, cM, src);
+  const T tau0 = (T)tau0M, lf = (T)lamfac;
   const T w00 = (T)sM.w00, w10 = (T)sM.w10, w01 = (T)sM.w01, w11 = (T)sM.w11;
 
   const size_t fstride = (size_t)a.np;
@@ -63,11 +62,12 @@ __global__ void __launch_bounds__(256) k_sweep_plane_i(const PlaneArgs<T> a) {
   // one update (the scalar Eq. fsbez) at frequency f0 + f from the upwind intensity IM
   auto update = [&](int f, T IM) __attribute__((always_inline)) {
     const Coefs<T> cf = coefficients(tau0 * s_phi[f]);
-    const T x = fma_t(cf.omC, cMt, dot3(cf.omM, SMt, cf.e, IM, cf.omO, SOt));
+    const StepSource<T> w = source_weights(cf);
+    const T x = fma_t(w.c, src.c, dot3(w.a, src.a, cf.e, IM, w.b, src.b));
     __builtin_nontemporal_store(x, op + (size_t)f * fstride);   // as store4_nt
     const double W = s_wn[f];
-    jacc += W * (double)x;
-    lacc += W * (double)fma_t(lf, cf.omC, cf.omO);
+    jacc = fma_t(W, (double)x, jacc);
+    lacc = fma_t(W, (double)lambda_star(cf, lf), lacc);
   };
   if (!ip) {
     // the upwind plane is the boundary

@@ -1,0 +1,116 @@
+"""Host build of the update's coefficients and source weights (no GPU), against extended
+precision."""
+import ctypes as C
+import os
+
+import numpy as np
+import pytest
+
+from paper_1307_4217_amd import build as pbuild
+
+
+@pytest.fixture(scope="module")
+def hm():
+    if not os.path.exists(pbuild.HOSTTEST_LIB):
+        pbuild.build_hostmath()
+    L = C.CDLL(pbuild.HOSTTEST_LIB)
+    L.hm_step_f32.argtypes = [C.c_float, C.POINTER(C.c_float)]
+    L.hm_step_f64.argtypes = [C.c_double, C.POINTER(C.c_double)]
+    return L
+
+
+def _exact(tau):
+    """e, psi'_M, psi'_O, omega_M, omega_O, omega_C, t E_1, t E_2, t E_3 in extended
+    precision: the series of E_3 (terms below 1e-30) for tau < 2, else closed forms."""
+    t = np.longdouble(tau)
+    one = np.longdouble(1)
+    if t < 2:
+        term, e3, k = one / 6, np.longdouble(0), 0
+        while abs(term) > 1e-30:
+            e3 += term
+            k += 1
+            term = -term * t / (k + 3)
+        e2 = one / 2 - t * e3
+        e1 = one - t * e2
+        e = one - t * e1
+        return [e, t * (e1 - e2), t * e2, t * (e1 - 2 * e2 + 2 * e3), 2 * t * e3,
+                t * (2 * e2 - 4 * e3), t * e1, t * e2, t * e3]
+    e = np.exp(-t)
+    return [e, (1 - e * (1 + t)) / t, (e + t - 1) / t, (2 - e * (t * t + 2 * t + 2)) / t**2,
+            1 - 2 * (e + t - 1) / t**2, 2 * (t - 2 + e * (t + 2)) / t**2, 1 - e, (e + t - 1) / t,
+            one / 2 - (e + t - 1) / t**2]
+
+
+TAUS = np.concatenate([np.logspace(-9, 2, 400),
+                       [0.999999, 1.0, 1.000001, 1.199999, 1.2, 1.200001, 0.1, 0.14, 0.18]])
+
+
+def test_step_coefficients_f64(hm):
+    """A few roundings of the recurrence (its differences lose at most a factor of 6 at small
+    tau, 1/(1 - 1 + 1/3) and the like) or of the closed forms at tau >= 1 (omega_C loses a
+    factor of 20 there): 40 ulp."""
+    out = np.zeros(9)
+    for tau in TAUS:
+        hm.hm_step_f64(tau, out.ctypes.data_as(C.POINTER(C.c_double)))
+        want = _exact(tau)
+        for k in range(9):
+            if want[k] < 1e-300:
+                continue
+            err = float(abs(np.longdouble(out[k]) / want[k] - 1))
+            assert err < 40 * 2.0**-53, (tau, k, err)
+
+
+def test_step_coefficients_f32(hm):
+    """The same in single precision, at the rounded tau: 40 ulp."""
+    out = np.zeros(9, np.float32)
+    for tau in TAUS:
+        t = np.float32(tau)
+        hm.hm_step_f32(t, out.ctypes.data_as(C.POINTER(C.c_float)))
+        want = _exact(t)
+        for k in range(9):
+            if want[k] < 1e-30:
+                continue
+            err = float(abs(np.longdouble(out[k]) / want[k] - 1))
+            assert err < 40 * 2.0**-24, (tau, k, err)
+
+
+def test_source_weights_give_the_sources(hm):
+    """t E_1 A_1 + t E_2 A_2 + t E_3 A_3 with A_1 = S_M, A_2 = 2 (c_M - S_M), A_3 = 2 (S_M +
+    S_O - 2 c_M) is omega_M S_M + omega_O S_O + omega_C c_M: to 16 ulp of the largest term."""
+    rng = np.random.default_rng(5)
+    out = np.zeros(9)
+    for tau in TAUS:
+        hm.hm_step_f64(tau, out.ctypes.data_as(C.POINTER(C.c_double)))
+        w = [float(x) for x in _exact(tau)[3:6]]
+        for _ in range(3):
+            SM, SO, cM = rng.uniform(0.2, 2.0, 3)
+            got = out[6] * SM + out[7] * 2 * (cM - SM) + out[8] * 2 * (SM + SO - 2 * cM)
+            want = w[0] * SM + w[1] * SO + w[2] * cM
+            big = out[6] * SM + abs(out[7] * 2 * (cM - SM)) + abs(out[8]) * 8
+            assert abs(got - want) < 16 * 2.0**-53 * big, tau
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_lorentz_solve_matches_dense_solve(hm, prec):
+    """(1 + p K') x = b and its transpose by the Lorentz-algebra route against a dense solve,
+    K' entries up to 0.5.  K' then has norm < 1.5 and 1 + p K' condition < 10; each result is a
+    sum of about 20 rounded terms of size <= 3 |b|: 400 ulp of the largest component."""
+    rng = np.random.default_rng(9)
+    ty, ct = (np.float64, C.c_double) if prec == "f64" else (np.float32, C.c_float)
+    fn = getattr(hm, f"hm_lorentz_solve_{prec}")
+    P = C.POINTER(ct)
+    fn.argtypes = [P, P, ct, P, C.c_int, P]
+    ulp = 2.0**-53 if prec == "f64" else 2.0**-24
+    for trial in range(400):
+        amp = (0.05, 0.5)[trial % 2]
+        e, r = rng.uniform(-amp, amp, 3).astype(ty), rng.uniform(-amp, amp, 3).astype(ty)
+        b, pp = rng.normal(size=4).astype(ty), ty(10.0 ** rng.uniform(-6, 0))
+        K = np.array([[0, e[0], e[1], e[2]], [e[0], 0, r[2], -r[1]], [e[1], -r[2], 0, r[0]],
+                      [e[2], r[1], -r[0], 0]], dtype=np.float64)
+        A = np.eye(4) + float(pp) * K
+        for sgn, M in ((1, A), (-1, A.T)):
+            want = np.linalg.solve(M, b.astype(np.float64))
+            x = np.zeros(4, ty)
+            fn(e.ctypes.data_as(P), r.ctypes.data_as(P), pp, b.ctypes.data_as(P), sgn,
+               x.ctypes.data_as(P))
+            assert np.abs(x - want).max() <= 400 * ulp * np.abs(want).max()
