@@ -216,14 +216,16 @@ int porta_fs_sweep(const porta_grid* grid, const porta_quad* quad, const porta_f
 /*
  * porta_fs_sweep without a workspace argument, for callers that cannot allocate
  * device memory (code under HIP graph capture, serving loops, harnesses that forbid
- * hipMalloc).  The call allocates nothing: its workspace is a static array of
- * 64 MiB (64 << 20 bytes) in the library's device code, one per device, held until
+ * hipMalloc).  The call allocates nothing: its workspace is a static array in the
+ * library's device code (72 MiB), one per device, held until
  * the process ends; its device address is looked up once per device on the first
  * call with that device current.  Arguments are those of porta_fs_sweep with the
  * same meaning, minus the checkpoints and the workspace; the work goes to the
- * current device, to which `stream` must belong.  A problem whose sweep workspace
- * (porta_workspace_size(..., PORTA_WS_SWEEP, ...) with the same options) exceeds
- * 64 MiB returns PORTA_ENOMEM before anything is enqueued; a smaller
+ * current device, to which `stream` must belong.  A problem whose plane states, partial
+ * sums and first-face set-up, for one hemisphere's batch of rays, exceed 64 MiB
+ * (64 << 20 bytes) returns PORTA_ENOMEM before anything is enqueued; up to there the
+ * sweep is cut so that it fits (porta_workspace_size(..., PORTA_WS_SWEEP, ...), which has
+ * room for both hemispheres at once, may be larger than the array).  A smaller
  * opts->ray_batch shrinks it.  Nothing in the array needs to start at zero.  Every
  * call on one device shares that device's array: calls whose work overlaps in time
  * on one device (different streams, or different host threads) race and give wrong
@@ -348,7 +350,9 @@ int porta_rel_change(int64_t npoints, const double* s_new, const double* s_old, 
  * The intensity field is recomputed from plane checkpoints every
  * `checkpoint_stride` planes (1..nz-1) instead of being stored.  With
  * `checkpoints` NULL the call first sweeps the upward rays to make them
- * (workspace kind PORTA_WS_ADJOINT); otherwise they are the ones porta_fs_sweep
+ * (workspace kind PORTA_WS_ADJOINT); where the states of every plane of a ray batch take at
+ * most 1 GiB it keeps them all, whatever the stride, in a workspace that is larger by
+ * as much, and recomputes nothing.  Otherwise the checkpoints are the ones porta_fs_sweep
  * wrote for these fields with the same stride and the same options' ray range
  * (kind PORTA_WS_ADJOINT_CKPT); checkpoint_bytes is the buffer's size, and below
  * porta_checkpoint_size() the call returns PORTA_ENOMEM before any launch (that

@@ -19,8 +19,10 @@
 #include "porta_unpol.hpp"
 
 // Workspace of porta_fs_sweep_noalloc, one copy on every device the library runs on,
-// held until the process ends.
-constexpr size_t kScratchBytes = size_t(64) << 20;
+// held until the process ends: kScratchLimit for the sweeps it takes (scratch_need), the
+// rest for the tables of their rays' geometry.
+constexpr size_t kScratchLimit = size_t(64) << 20;
+constexpr size_t kScratchBytes = size_t(72) << 20;
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 namespace porta {
@@ -270,10 +272,7 @@ SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const p
 }
 
 // The cut without sharing and chunks, which needs the least workspace.
-SweepPlan least_plan(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
-  const int nrb = sweep_plan(g, q, prec, o).nrb;
-  return {nrb, false, false, nrb, (size_t)nrb};
-}
+SweepPlan least_plan(int nrb) { return {nrb, false, false, nrb, (size_t)nrb}; }
 
 // Chunks of a launch of `rays` rays (each chunk has a row of partial sums).
 int launch_chunks(const porta_grid* g, const porta_quad* q, const porta_options* o,
@@ -300,7 +299,7 @@ struct Layout {
   size_t tf;               // first-face sweep: transposed transfer coefficients
   size_t fcache;           // first-face sweep: set-up of the nodes of a plane
   size_t plane;            // bytes of one plane state of a ray batch
-  int nck, nslot;
+  int nck, nslot, stride;  // stride: planes from one checkpoint to the next
   size_t total;
 };
 
@@ -358,9 +357,37 @@ Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const po
   return L;
 }
 
+// Forward states of a batch of rays that the adjoint keeps without being asked (1/288 of
+// the device memory): recomputing planes from checkpoints saves nothing worth having below.
+constexpr size_t kKeepAllBytes = size_t(1) << 30;
+
 // Checkpoint planes are k = C, 2C, ... <= nz - 2 (the top plane is recomputed).
 int checkpoint_count(int nz, int C) { return nz >= 3 ? (nz - 2) / C : 0; }
 bool is_checkpoint(int k, int nz, int C) { return k >= 1 && k % C == 0 && k <= nz - 2; }
+
+// What decides whether porta_fs_sweep_noalloc takes a sweep: the plane states and partial
+// sums of one hemisphere's batch with every frequency in one chunk (first faces: chunks of at
+// most 4 frequencies in FP32 and 7 in FP64), the ray tables and the first-face set-up.
+size_t scratch_need(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
+  const size_t np = (size_t)g->nx * g->ny, nf = q->nfreq, e = elem(prec);
+  const size_t nrb = (size_t)ray_batch(q, o);
+  size_t n = align_up(sizeof(double) * (2 * kMaxMu + 2 * nf)) +
+             align_up(sizeof(RayConsts) * 2 * q->nmu * q->nchi) + align_up(e * nf) +
+             align_up(sizeof(double) * nf) + align_up(sizeof(int));
+  n += 2 * align_up(nrb * nf * np * nstokes(o) * e) + align_up(2 * nrb * 5 * np * sizeof(double));
+  if (faces_of(o)) {
+    const size_t lanes = (std::max(g->nx, g->ny) + 63) / 64 * 64, waves = lanes / 64;
+    const size_t base = (nf * (sizeof(double) + e) + 15) & ~(size_t)15;
+    const size_t fit = kFacesLds > base ? (kFacesLds - base) / ((lanes + 4 * waves) * 32) : 0;
+    size_t chunk = std::min<size_t>({prec == PORTA_F32 ? 4u : 7u, fit, nf});
+    if (o->faces_chunk > 0) chunk = std::min<size_t>(o->faces_chunk, nf);
+    chunk = std::max<size_t>(chunk, 1);
+    const size_t nchunk = (nf + chunk - 1) / chunk;
+    n += align_up(nrb * nchunk * 5 * np * sizeof(double)) + align_up(13 * np * g->nz * e) +
+         align_up(nrb * 26 * np * e);
+  }
+  return n;
+}
 
 // Adjoint: checkpoint planes (unless the caller brings them), C slots for the
 // planes recomputed between two checkpoints, two planes of Lambda, the
@@ -371,8 +398,12 @@ Layout adjoint_layout(const porta_grid* g, const porta_quad* q, int prec, int st
   const size_t np = (size_t)g->nx * g->ny, N = np * g->nz;
   const size_t nrb = (size_t)ray_batch(q, o);
   L.plane = nrb * q->nfreq * np * 4 * elem(prec);
-  L.nck = own_checkpoints ? checkpoint_count(g->nz, stride) : 0;
-  L.nslot = stride;
+  // planes of its own that are small enough are all kept, whatever the stride
+  L.stride = own_checkpoints && L.plane * g->nz <= kKeepAllBytes ? 1 : stride;
+  L.nck = own_checkpoints ? checkpoint_count(g->nz, L.stride) : 0;
+  L.nslot = L.stride;
+  // rows of partials: one for each ray and frequency chunk
+  const size_t nrow = nrb * freq_chunks(plane_tiles(g, o) * nrb, q->nfreq);
   size_t off = L.end_tables;
   L.ck = off;
   off = align_up(off + (size_t)L.nck * L.plane);
@@ -384,11 +415,11 @@ Layout adjoint_layout(const porta_grid* g, const porta_quad* q, int prec, int st
   off = align_up(off + L.plane);
   // per-(node, ray) partials in the sweep precision
   L.go = off;
-  off = align_up(off + nrb * 13 * np * elem(prec));
+  off = align_up(off + nrow * 13 * np * elem(prec));
   L.gm = off;
-  off = align_up(off + nrb * 13 * np * elem(prec));
+  off = align_up(off + nrow * 13 * np * elem(prec));
   L.gp = off;
-  off = align_up(off + nrb * 7 * np * elem(prec));
+  off = align_up(off + nrow * 7 * np * elem(prec));
   L.grad = off;
   off = align_up(off + 13 * N * sizeof(double));
   L.total = off;
@@ -781,11 +812,31 @@ int forward_plane(const porta_grid* g, const porta_quad* q, const porta_fields* 
   return launch_plane<T>(a, 4, interp, block, st);
 }
 
+// Nodes per block of the gather: 64, whole wavefronts of neighbouring nodes, or 16 and four
+// times the ray groups where a plane has too few nodes.  A plane takes, with 64 and 16 nodes, in
+// the bilinear mode 22.0 and 29.3 us at 64x64 nodes, 9.5 and 10.2 us at 37x30, and in the
+// 9-point mode, where a ray costs far more, 37.5 and 23.7 us at 24x24.
+template <class T>
+void launch_gather(const GatherArgs<T>& b, bool bez, hipStream_t st) {
+  const bool wide = b.np >= kCus * (bez ? 16 : 4);
+  const dim3 blk(256);
+  const unsigned n = (unsigned)((b.np + (wide ? 63 : 15)) / (wide ? 64 : 16));
+  if (bez && wide)
+    hipLaunchKernelGGL((k_adjoint_gather<T, 1, 64>), dim3(n, kGatherParts), blk, 0, st, b);
+  else if (bez)
+    hipLaunchKernelGGL((k_adjoint_gather<T, 1, 16>), dim3(n, kGatherParts), blk, 0, st, b);
+  else if (wide)
+    hipLaunchKernelGGL((k_adjoint_gather<T, 0, 64>), dim3(n, kGatherParts), blk, 0, st, b);
+  else
+    hipLaunchKernelGGL((k_adjoint_gather<T, 0, 16>), dim3(n, kGatherParts), blk, 0, st, b);
+}
+
 template <class T>
 int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f,
                  const porta_options* o, int interp, const T* seed, const T* ext_ck, int C, T* gk,
                  T* gpm, T* ge, char* ws, const Layout& L, hipStream_t st) {
   int rc;
+  if (!ext_ck) C = L.stride;
   if ((rc = prepare_tables<T>(ws, L, g, q, f->w2, interp, st))) return rc;
   const int nx = g->nx, ny = g->ny, nz = g->nz, np = nx * ny;
   const size_t N = (size_t)np * nz;
@@ -794,6 +845,7 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
   const int nrb_max = ray_batch(q, o);
   const int block = plane_block(g, o);
   if (block % 64 != 0 || block > 256) return fail(PORTA_EINVAL, "block must be 64, 128, 192 or 256");
+  const int ntile = (int)plane_tiles(g, o);
   const size_t pe = L.plane / sizeof(T);   // elements of one plane state
   T* ck = reinterpret_cast<T*>(ws + L.ck);
   T* slots = reinterpret_cast<T*>(ws + L.slots);
@@ -812,9 +864,14 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
     }
     return slots + (size_t)((k - 1) % C) * pe;
   };
-  const size_t lds_adj = (size_t)q->nfreq * sizeof(T);
   for (r0 = up_lo; r0 < up_hi; r0 += nrb_max) {
     const int nrb = std::min(nrb_max, up_hi - r0);
+    // the workspace has room for the chunks of a full batch
+    const int want = std::min(freq_chunks((int64_t)ntile * nrb, q->nfreq),
+                              nrb_max * freq_chunks((int64_t)ntile * nrb_max, q->nfreq) / nrb);
+    const int fchunk = (q->nfreq + want - 1) / want, nchunk = (q->nfreq + fchunk - 1) / fchunk;
+    const dim3 agrid((unsigned)(ntile * nrb * nchunk));
+    const size_t lds_adj = (size_t)fchunk * sizeof(T);
     // forward pass up to the last checkpoint plane, keeping every C-th plane (unless
     // the sweep already kept them); the planes above it are recomputed with the top
     // segment
@@ -856,6 +913,9 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
         a.nz = nz;
         a.np = np;
         a.nfreq = q->nfreq;
+        a.ntile = ntile;
+        a.fchunk = fchunk;
+        a.nchunk = nchunk;
         a.kO = k;
         a.kM = k - 1;
         a.kP = (k == nz - 1) ? -1 : k + 1;
@@ -881,20 +941,21 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
           t.kO = k;
           t.ray0 = r0;
           constexpr int TX = TGTile<T>::X, TY = TGTile<T>::Y;
-          hipLaunchKernelGGL(k_bez9_tgather<T>,
-                             dim3((nx + TX - 1) / TX, (ny + TY - 1) / TY, nrb), dim3(TX * TY),
-                             0, st, t);
+          const int tx = (nx + TX - 1) / TX, ty = (ny + TY - 1) / TY;
+          const int tc = freq_chunks((int64_t)tx * ty * nrb, q->nfreq);
+          t.fchunk = (q->nfreq + tc - 1) / tc;
+          t.nchunk = (q->nfreq + t.fchunk - 1) / t.fchunk;
+          hipLaunchKernelGGL(k_bez9_tgather<T>, dim3(tx, ty, nrb * t.nchunk), dim3(TX * TY), 0,
+                             st, t);
           if ((rc = check_launch("bez9_tgather"))) return rc;
           a.lam_next = nullptr;
           a.seed = lam[cur];
           a.lam_cur = (k - 1 >= 1) ? lam[cur] : nullptr;
         }
         if (bez)
-          hipLaunchKernelGGL((k_adjoint_plane<T, 1>), dim3((np + block - 1) / block, nrb),
-                             dim3(block), lds_adj, st, a);
+          hipLaunchKernelGGL((k_adjoint_plane<T, 1>), agrid, dim3(block), lds_adj, st, a);
         else
-          hipLaunchKernelGGL((k_adjoint_plane<T, 0>), dim3((np + block - 1) / block, nrb),
-                             dim3(block), lds_adj, st, a);
+          hipLaunchKernelGGL((k_adjoint_plane<T, 0>), agrid, dim3(block), lds_adj, st, a);
         if ((rc = check_launch("adjoint_plane"))) return rc;
         GatherArgs<T> b;
         b.g_o = a.g_o;
@@ -915,12 +976,8 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
         b.kP = a.kP;
         b.ray0 = r0;
         b.nrb = nrb;
-        if (bez)
-          hipLaunchKernelGGL((k_adjoint_gather<T, 1>), dim3((np + 255) / 256, 4), dim3(256), 0, st,
-                             b);
-        else
-          hipLaunchKernelGGL((k_adjoint_gather<T, 0>), dim3((np + 255) / 256, 4), dim3(256), 0, st,
-                             b);
+        b.nchunk = nchunk;
+        launch_gather<T>(b, bez, st);
         if ((rc = check_launch("adjoint_gather"))) return rc;
         lam_next = a.lam_cur;
         cur ^= 1;
@@ -1006,15 +1063,18 @@ int sweep_entry(const porta_grid* grid, const porta_quad* quad, const porta_fiel
   SweepPlan plan = sweep_plan(grid, quad, prec, opts);
   Layout L = sweep_layout(grid, quad, prec, opts, plan);
   if (use_scratch) {
-    if (L.total > kScratchBytes) {
-      plan = least_plan(grid, quad, prec, opts);
-      L = sweep_layout(grid, quad, prec, opts, plan);
-    }
-    if (L.total > kScratchBytes)
+    const size_t need = scratch_need(grid, quad, prec, opts);
+    if (need > kScratchLimit)
       return fail(PORTA_ENOMEM,
                   "this sweep needs %zu bytes of workspace; the static scratch holds %zu "
                   "(use a smaller opts->ray_batch, or porta_fs_sweep)",
-                  L.total, kScratchBytes);
+                  need, kScratchLimit);
+    // the cut that fits: the usual one, the plain one, or that with fewer rays in turn
+    if (L.total > kScratchBytes) plan = least_plan(plan.nrb);
+    for (; (L = sweep_layout(grid, quad, prec, opts, plan)).total > kScratchBytes && plan.nrb > 1;)
+      plan = least_plan(plan.nrb - 1);
+    if (L.total > kScratchBytes)
+      return fail(PORTA_ENOMEM, "the geometry of the rays does not fit the static scratch");
     if ((rc = scratch_address(&workspace))) return rc;
     ws_bytes = kScratchBytes;
   }

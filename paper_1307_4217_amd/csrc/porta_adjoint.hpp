@@ -36,16 +36,18 @@ struct AdjArgs {
   const T* lam_next;   // Lambda of plane kO + 1, or nullptr when kO is the top plane
   const T* seed;       // dL/dI on the top plane for this batch (used when lam_next is null)
   T* lam_cur;          // Lambda of plane kO, or nullptr when plane kM is the boundary
-  T* g_o;              // [ray in batch][13][node]: coefficients at O
-  T* g_m;              // [ray in batch][13][node]: coefficients interpolated at M
-  T* g_p;              // [ray in batch][7][node]:  eta_I and eps interpolated at P
-                       // (partials of one node and ray, formed in FP64, stored in the
-                       // sweep precision; the gather sums them in FP64)
+  T* g_o;              // [ray in batch][chunk][13][node]: coefficients at O
+  T* g_m;              // [ray in batch][chunk][13][node]: coefficients interpolated at M
+  T* g_p;              // [ray in batch][chunk][7][node]:  eta_I and eps interpolated at P
+                       // (partials of one node, ray and chunk of frequencies, formed in FP64,
+                       // stored in the sweep precision; the gather sums them in FP64)
   size_t N;
   int nx, ny, nz, np, nfreq;
+  int ntile;           // tiles of blockDim.x nodes in a plane
+  int nchunk, fchunk;  // frequency chunks, as in the sweep's plane step
   int kO, kM, kP;
   int ray0;
-  int xcd_remap;       // tiles per XCD per round, see xcd_tile
+  int xcd_remap;       // tiles per XCD per round, see xcd_order
   int parabolic;       // control point: 0 BESSER, 1 parabola through M, O, P
   T ibound;
 };
@@ -120,11 +122,12 @@ struct TGatherArgs {
   T* out;              // adjoint of I at the nodes of plane kO, same layout
   const RayGeom* geom;
   int nx, ny, nz, np, nfreq;
+  int nchunk, fchunk;  // frequency chunks of a launch
   int kO, ray0;
 };
 
-// A block takes a tile of TGX x TGY nodes q of one ray (blockIdx.z) and forms, per
-// frequency, the pieces of bez9_adjoint_gather that neighbouring nodes share once in
+// A block takes a tile of TGX x TGY nodes q of one ray and chunk of frequencies (blockIdx.z)
+// and forms, per frequency, the pieces of bez9_adjoint_gather that neighbouring nodes share once in
 // LDS: the x pass of every row triple (centre (x, y), rows of the tile +-2, columns +-1),
 // its partials on the tile's rows, and the partials of the y pass of every centre
 // (rows +-1).  Node q then sums, over the nine p whose stencil holds it, the product
@@ -147,7 +150,8 @@ __global__ void __launch_bounds__(256) k_bez9_tgather(const TGatherArgs<T> a) {
   __shared__ T sGx[TY][CX][3][4];           // its partials on the tile's rows
   __shared__ T sGy[TY + 2][CX][3][4];       // y-pass partials at centre rows -1..TY
   const int tid = threadIdx.x, nthr = blockDim.x;
-  const int rb = blockIdx.z;
+  const int rb = blockIdx.z / a.nchunk, f0 = (blockIdx.z % a.nchunk) * a.fchunk;
+  const int nf = min(a.fchunk, a.nfreq - f0);
   const int qx0 = blockIdx.x * TX, qy0 = blockIdx.y * TY;
   const RayGeom& gm = layer_geom(a.geom, a.ray0 + rb, a.nz, a.kO, a.kO + 1, 0);
   const BezW<T> wx = bez_weights((T)gm.tx), wy = bez_weights((T)gm.ty);
@@ -161,7 +165,7 @@ __global__ void __launch_bounds__(256) k_bez9_tgather(const TGatherArgs<T> a) {
     pcol[d] = wrapi(qx - gm.fu + d - 1, a.nx);
   }
   const size_t fstride = (size_t)a.np * 4;
-  const size_t roff = (size_t)rb * a.nfreq * fstride;
+  const size_t roff = ((size_t)rb * a.nfreq + f0) * fstride;
   // The forward states of frequency f + 1 (this thread's share of the tile) and the
   // nine adjoints at p are loaded while frequency f is being worked on, and the states
   // go to LDS once the x passes of f have read it.
@@ -201,8 +205,8 @@ __global__ void __launch_bounds__(256) k_bez9_tgather(const TGatherArgs<T> a) {
   load_lam(0, lam);
   store_tile();
   __syncthreads();
-  for (int f = 0; f < a.nfreq; ++f) {
-    const bool more = f + 1 < a.nfreq;
+  for (int f = 0; f < nf; ++f) {
+    const bool more = f + 1 < nf;
     if (more) {
       load_tile(f + 1);
       load_lam(f + 1, lamN);
@@ -269,13 +273,14 @@ __global__ void __launch_bounds__(256) k_bez9_tgather(const TGatherArgs<T> a) {
 template <class T, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1)))
 k_adjoint_plane(const AdjArgs<T> a) {
+  const int L = xcd_order(a.xcd_remap, blockIdx.x, gridDim.x);
+  const int row = L / a.ntile, rb = row / a.nchunk, chunk = row % a.nchunk;
+  const int f0 = chunk * a.fchunk, nf = min(a.fchunk, a.nfreq - f0);
   extern __shared__ double s_tab[];
   T* s_phi = reinterpret_cast<T*>(s_tab);
-  for (int t = threadIdx.x; t < a.nfreq; t += blockDim.x) s_phi[t] = a.phi[t];
+  for (int t = threadIdx.x; t < nf; t += blockDim.x) s_phi[t] = a.phi[f0 + t];
   __syncthreads();
-  int bx, rb;
-  xcd_tile(a.xcd_remap, bx, rb);
-  const int p = bx * blockDim.x + threadIdx.x;
+  const int p = (L % a.ntile) * blockDim.x + threadIdx.x;
   if (p >= a.np) return;
   const RayConsts& rc = a.rays[a.ray0 + rb];
   PointSetup ps;
@@ -304,11 +309,11 @@ k_adjoint_plane(const AdjArgs<T> a) {
   const T n00 = (T)tN.w00, n10 = (T)tN.w10, n01 = (T)tN.w01, n11 = (T)tN.w11;
 
   const size_t fstride = (size_t)a.np * 4;
-  const size_t rstride = (size_t)a.nfreq * fstride;
-  const T* ip = a.iprev ? a.iprev + rb * rstride : nullptr;
-  const T* lp = a.lam_next ? a.lam_next + rb * rstride : nullptr;
-  const T* sp = a.seed + rb * rstride + (size_t)p * 4;
-  T* lo = a.lam_cur ? a.lam_cur + rb * rstride + (size_t)p * 4 : nullptr;
+  const size_t foff = ((size_t)rb * a.nfreq + f0) * fstride;
+  const T* ip = a.iprev ? a.iprev + foff : nullptr;
+  const T* lp = a.lam_next ? a.lam_next + foff : nullptr;
+  const T* sp = a.seed + foff + (size_t)p * 4;
+  T* lo = a.lam_cur ? a.lam_cur + foff + (size_t)p * 4 : nullptr;
 
   // sums over frequency of the partials, in the sweep precision (FP32: each is a sum
   // of nfreq terms whose rounding stays at the level of the FP32 terms themselves)
@@ -413,16 +418,16 @@ k_adjoint_plane(const AdjArgs<T> a) {
       Corners cA, cB;
       issue(0, cA);
       int f = 0;
-      for (; f + 1 < a.nfreq; f += 2) {
+      for (; f + 1 < nf; f += 2) {
         issue(f + 1, cB);
         body(f, cA);
-        issue(min(f + 2, a.nfreq - 1), cA);
+        issue(min(f + 2, nf - 1), cA);
         body(f + 1, cB);
       }
-      if (f < a.nfreq) body(f, cA);
+      if (f < nf) body(f, cA);
     } else {
       // FP64: one buffer (a second one does not fit in the registers of one wave)
-      for (int f = 0; f < a.nfreq; ++f) {
+      for (int f = 0; f < nf; ++f) {
         Corners c;
         issue(f, c);
         body(f, c);
@@ -509,9 +514,9 @@ k_adjoint_plane(const AdjArgs<T> a) {
     gkM -= gKM[c] * ps.etaM[c] * ps.ikM * ps.ikM;
     gkO -= gKO[c] * ps.etaO[c] * ps.ikO * ps.ikO;
   }
-  T* go = a.g_o + (size_t)rb * 13 * a.np + p;
-  T* gm = a.g_m + (size_t)rb * 13 * a.np + p;
-  const size_t np = (size_t)a.np;
+  const size_t np = (size_t)a.np, entry = (size_t)rb * a.nchunk + chunk;
+  T* go = a.g_o + entry * 13 * np + p;
+  T* gm = a.g_m + entry * 13 * np + p;
   go[0] = (T)gkO;
   gm[0] = (T)gkM;
 #pragma unroll
@@ -522,15 +527,15 @@ k_adjoint_plane(const AdjArgs<T> a) {
     gm[(7 + c) * np] = (T)geM[c];
   }
   if (ps.hasP) {
-    T* gp = a.g_p + (size_t)rb * 7 * a.np + p;
+    T* gp = a.g_p + entry * 7 * np + p;
     gp[0] = (T)gkP;
 #pragma unroll
     for (int c = 0; c < 6; ++c) gp[(1 + c) * np] = (T)geP[c];
   }
 }
 
-// Gather the per-(node, ray) partials of one plane onto the coefficient
-// gradients of planes kM, kO and kP (fixed ray order per component, no atomics).
+// Gather the per-(node, ray, chunk) partials of one plane onto the coefficient gradients
+// of planes kM, kO and kP (fixed order per component, no atomics).
 template <class T>
 struct GatherArgs {
   const T* g_o;
@@ -541,99 +546,99 @@ struct GatherArgs {
   size_t N;
   int nx, ny, nz, np;
   int kO, kM, kP;
-  int ray0, nrb;
+  int ray0, nrb, nchunk;
   const T* kappa;     // the coefficients (MODE 1: the Bezier partials depend on them)
   const T* prop;
   const T* emis;
 };
 
-// blockIdx.y: component group (0: the 13 at O; 1, 2: the 13 at M in two halves; 3: the
-// 7 at P), so that four threads share a node and each stencil is built once per group.
-template <class T, int MODE>
+// A block takes W nodes and, in blockIdx.y, one of the 33 components (13 at O, 13 at M, 7 at
+// P): its threads are (ray group, node), group g gathers rays g, g + G, ..., and the groups
+// are added in order through LDS: the loop over rays is a chain of latencies, which with
+// every ray in one thread took 45 us a plane at 64x64 nodes and 40 rays and takes 22 so.
+// (Several components per thread, so that a stencil is built once for them, need 135
+// registers instead of 50: 56 us, and 38 instead of 22 at 128x128.)
+constexpr int kGatherParts = 33;
+
+template <class T, int MODE, int W>
 __global__ void __launch_bounds__(256) k_adjoint_gather(const GatherArgs<T> a) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int grp = blockIdx.y;
-  if (q >= a.np || (grp == 3 && a.kP < 0)) return;
-  const int i = q % a.nx, j = q / a.nx;
+  constexpr int G = 256 / W;
+  __shared__ double red[G][W];
+  const int part = blockIdx.y, g = threadIdx.x / W, n = threadIdx.x % W;
+  const bool atO = part < 13, atM = !atO && part < 26;
+  if (part >= 26 && a.kP < 0) return;   // the same for the whole block
+  const int c = atO ? part : (atM ? part - 13 : part - 26);   // component at its point
+  const int ncomp = part < 26 ? 13 : 7;
+  const int q = blockIdx.x * W + n;
   const size_t np = (size_t)a.np;
-  const int c0 = (grp == 2) ? 7 : 0;
-  const int nc = (grp == 0) ? 13 : (grp == 1 ? 7 : (grp == 2 ? 6 : 7));
-  double acc[13];
-#pragma unroll
-  for (int c = 0; c < 13; ++c) acc[c] = 0.0;
-  if (grp == 0) {
-    for (int rb = 0; rb < a.nrb; ++rb) {
-      const T* go = a.g_o + (size_t)rb * 13 * np + q;
-#pragma unroll
-      for (int c = 0; c < 13; ++c) acc[c] += go[c * np];
+  double acc = 0.0;
+  if (q < a.np && atO) {
+#pragma unroll 4
+    for (int rb = g; rb < a.nrb; rb += G) {
+      const T* go = a.g_o + ((size_t)rb * a.nchunk * 13 + c) * np + q;
+      acc += go[0];
+      for (int k = 1; k < a.nchunk; ++k) acc += go[(size_t)k * 13 * np];
     }
-#pragma unroll
-    for (int c = 0; c < 13; ++c) a.grad[c * a.N + (size_t)a.kO * np + q] += acc[c];
-    return;
-  }
-  const bool atM = (grp < 3);
-  for (int rb = 0; rb < a.nrb; ++rb) {
-    // M upwind, P downwind, as in the sweep
-    const RayGeom& gl = layer_geom(a.geom, a.ray0 + rb, a.nz, a.kO, atM ? a.kM : a.kP, !atM);
-    const T* gb = atM ? a.g_m + ((size_t)rb * 13 + c0) * np : a.g_p + (size_t)rb * 7 * np;
-    if constexpr (MODE == 0) {
-      const Stencil t = make_tstencil(i, j, a.nx, a.ny, gl);
-#pragma unroll
-      for (int c = 0; c < 7; ++c) {
-        if (c < nc) {
-          const T* g = gb + c * np;
-          acc[c] += t.w00 * g[t.i00] + t.w10 * g[t.i10] + t.w01 * g[t.i01] + t.w11 * g[t.i11];
+  } else if (q < a.np) {
+    const int j = q / a.nx, i = q - j * a.nx;
+#pragma unroll(MODE == 0 ? 2 : 1)
+    for (int rb = g; rb < a.nrb; rb += G) {
+      // M upwind, P downwind, as in the sweep
+      const RayGeom& gl = layer_geom(a.geom, a.ray0 + rb, a.nz, a.kO, atM ? a.kM : a.kP, !atM);
+      const T* gb = (atM ? a.g_m : a.g_p) + ((size_t)rb * a.nchunk * ncomp + c) * np;
+      if constexpr (MODE == 0) {
+        const Stencil t = make_tstencil(i, j, a.nx, a.ny, gl);
+        acc += t.w00 * gb[t.i00] + t.w10 * gb[t.i10] + t.w01 * gb[t.i01] + t.w11 * gb[t.i11];
+        for (int k = 1; k < a.nchunk; ++k) {
+          const T* h = gb + (size_t)k * ncomp * np;
+          acc += t.w00 * h[t.i00] + t.w10 * h[t.i10] + t.w01 * h[t.i01] + t.w11 * h[t.i11];
         }
-      }
-    } else {
-      // the transposed 9-point Bezier of each coefficient, whose clamps depend on the
-      // coefficient's values around q
-      const BezW<double> wx = bez_weights(gl.tx), wy = bez_weights(gl.ty);
-      int rowb[5], coli[5], prow[3], pcol[3];
+      } else {
+        // the transposed 9-point Bezier of the coefficient, whose clamps depend on its
+        // values around q
+        const BezW<double> wx = bez_weights(gl.tx), wy = bez_weights(gl.ty);
+        int rowb[5], coli[5], prow[3], pcol[3];
 #pragma unroll
-      for (int d = 0; d < 5; ++d) {
-        rowb[d] = wrapi(j + d - 2, a.ny) * a.nx;
-        coli[d] = wrapi(i + d - 2, a.nx);
-      }
+        for (int d = 0; d < 5; ++d) {
+          rowb[d] = wrapi(j + d - 2, a.ny) * a.nx;
+          coli[d] = wrapi(i + d - 2, a.nx);
+        }
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        prow[d] = wrapi(j - gl.fv + d - 1, a.ny) * a.nx;
-        pcol[d] = wrapi(i - gl.fu + d - 1, a.nx);
-      }
-      const size_t kb = (size_t)(atM ? a.kM : a.kP) * np;
-#pragma unroll 1
-      for (int c = 0; c < nc; ++c) {
-        // coefficient c of the group: M, first half kappa and propmat; M, second half
-        // emis; P: kappa and emis
-        const int cg = c0 + c;
-        const T* fld = (!atM) ? (c == 0 ? a.kappa : a.emis + (size_t)(c - 1) * a.N)
-                              : (cg == 0 ? a.kappa
-                                         : (cg < 7 ? a.prop + (size_t)(cg - 1) * a.N
-                                                   : a.emis + (size_t)(cg - 7) * a.N));
-        const T* fb = fld + kb;
-        const T* g = gb + c * np;
+        for (int d = 0; d < 3; ++d) {
+          prow[d] = wrapi(j - gl.fv + d - 1, a.ny) * a.nx;
+          pcol[d] = wrapi(i - gl.fu + d - 1, a.nx);
+        }
+        // at M: kappa, propmat, emis; at P: kappa and emis
+        const T* fld = c == 0 ? a.kappa
+                       : !atM ? a.emis + (size_t)(c - 1) * a.N
+                       : c < 7 ? a.prop + (size_t)(c - 1) * a.N
+                               : a.emis + (size_t)(c - 7) * a.N;
+        const T* fb = fld + (size_t)(atM ? a.kM : a.kP) * np;
         double out[1] = {0.0};
         bez9_adjoint_gather<double, 1>(
             wx, wy,
             [&](int r, int cc, double v[1]) { v[0] = (double)fb[rowb[r + 2] + coli[cc + 2]]; },
-            [&](int r, int cc, double w[1]) { w[0] = (double)g[prow[r + 1] + pcol[cc + 1]]; },
+            [&](int r, int cc, double w[1]) {
+              const T* h = gb + prow[r + 1] + pcol[cc + 1];
+              w[0] = 0.0;
+              for (int k = 0; k < a.nchunk; ++k) w[0] += (double)h[(size_t)k * ncomp * np];
+            },
             out);
-#pragma unroll
-        for (int cc = 0; cc < 7; ++cc)   // (a register array takes no run-time index)
-          if (cc == c) acc[cc] += out[0];
+        acc += out[0];
       }
     }
   }
-  if (atM) {
+  // gradient row: at P the emissivities follow eta_I
+  const int row = (part < 26 || c == 0) ? c : c + 6;
+  const size_t plane = (size_t)(atO ? a.kO : (atM ? a.kM : a.kP)) * np;
+  if constexpr (G > 1) {
+    red[g][n] = acc;
+    __syncthreads();
+    if (g > 0) return;
 #pragma unroll
-    for (int c = 0; c < 7; ++c)
-      if (c < nc) a.grad[(c0 + c) * a.N + (size_t)a.kM * np + q] += acc[c];
-  } else {
-    // eta_I and the six emissivities at P (gradient rows 0 and 7..12)
-    a.grad[(size_t)a.kP * np + q] += acc[0];
-#pragma unroll
-    for (int c = 1; c < 7; ++c) a.grad[(6 + c) * a.N + (size_t)a.kP * np + q] += acc[c];
+    for (int k = 1; k < G; ++k) acc += red[k][n];
   }
+  if (q < a.np) a.grad[row * a.N + plane + q] += acc;
 }
 
 // Add the FP64 gradient accumulator to the caller's arrays.

@@ -649,7 +649,7 @@ struct PlaneArgs {
   int nstep;         // blocks of the plane step; the J reduction's follow
   int njb;           // blocks of the J reduction
   int jsame;         // both hemispheres' previous plane is the same one: one block adds both
-  int xcd_remap;     // tiles per XCD per round (0: hardware order), see xcd_tile
+  int xcd_remap;     // tiles per XCD per round (0: hardware order), see xcd_order
   int parabolic;     // control point: 0 BESSER, 1 parabola through M, O, P
 };
 
@@ -706,16 +706,6 @@ __device__ inline int xcd_order(int chunk, int L, int T) {
     }
   }
   return Lp;
-}
-
-// The same over a two-dimensional grid of tiles.
-__device__ inline void xcd_tile(int chunk, int& bx, int& by) {
-  bx = blockIdx.x;
-  by = blockIdx.y;
-  if (chunk <= 0) return;
-  const int Lp = xcd_order(chunk, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
-  bx = Lp % gridDim.x;
-  by = Lp / gridDim.x;
 }
 
 // Tile, ray, frequency chunk and hemisphere of a block of a plane step.
