@@ -165,10 +165,9 @@ typedef struct {
                                checkpoints, nx and ny <= 512; porta_fs_adjoint returns
                                PORTA_EUNSUPPORTED */
   int32_t faces_chunk;      /* with faces = 1: frequencies one block of the first-face
-                               kernel carries through a plane (0: 4 in FP32, 7 in FP64,
-                               fewer where 64 KiB of LDS holds fewer rows of that width,
-                               evened out over the chunks); PORTA_EUNSUPPORTED if more
-                               than fit */
+                               kernel carries through a plane (0: chosen by the number of
+                               rays, frequencies and columns, and so that the rows fit
+                               64 KiB of LDS); PORTA_EUNSUPPORTED if more than fit */
 } porta_options;
 
 typedef enum { PORTA_CONTROL_BESSER = 0, PORTA_CONTROL_PARABOLIC = 1 } porta_control;

@@ -145,33 +145,6 @@ int validate_options(const porta_options* o) {
 
 bool faces_of(const porta_options* o) { return o && o->faces == 1; }
 
-// Lanes of a block of the first-face kernel (the columns of a plane in either frame)
-// and the frequencies it holds: the options' faces_chunk if it fits, else as many as
-// its LDS (kFacesLds) has room for, at most faces_chunk<T>(), spread evenly over the
-// chunks; 0 if they do not fit.
-void faces_shape(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
-                 int& lanes, int& fchunk) {
-  const int n = std::max(g->nx, g->ny);
-  lanes = (n + 63) / 64 * 64;
-  const bool f32 = prec == PORTA_F32;
-  const size_t base = f32 ? faces_lds_bytes<float>(q->nfreq, 0, lanes)
-                          : faces_lds_bytes<double>(q->nfreq, 0, lanes);
-  const size_t per = (f32 ? faces_lds_bytes<float>(q->nfreq, 1, lanes)
-                          : faces_lds_bytes<double>(q->nfreq, 1, lanes)) - base;
-  const size_t cap = f32 ? faces_chunk<float>() : faces_chunk<double>();
-  const size_t fit = kFacesLds > base ? (kFacesLds - base) / per : 0;
-  if (o && o->faces_chunk > 0) {
-    const int want = std::min(o->faces_chunk, q->nfreq);
-    fchunk = (size_t)want <= fit ? want : 0;
-    return;
-  }
-  fchunk = (int)std::min<size_t>({cap, fit, (size_t)q->nfreq});
-  if (fchunk > 0) {
-    const int nchunk = (q->nfreq + fchunk - 1) / fchunk;
-    fchunk = (q->nfreq + nchunk - 1) / nchunk;
-  }
-}
-
 int validate_rays(const porta_quad* q, const porta_options* o) {
   if (o && o->ray_count > 0 && (int64_t)o->ray_first + o->ray_count > 2LL * q->nmu * q->nchi)
     return fail(PORTA_EINVAL, "ray range %d + %d beyond the %d rays", o->ray_first, o->ray_count,
@@ -264,11 +237,61 @@ SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const p
   const int64_t tiles = plane_tiles(g, o);
   // a launch is one row of at most 2^31 threads
   P.nrb = (int)std::min<int64_t>(ray_batch(q, o), std::max<int64_t>(1, (1 << 23) / tiles));
+  if (faces_of(o)) P.nrb = std::min(P.nrb, 6553);   // 5 blocks per ray in a grid's z of 65535
   P.share = tiles * P.nrb <= kShareBlocks;
   P.rows = P.share ? 2 * P.nrb : P.nrb;
   P.chunks = prec == PORTA_F64;
   P.jrows = (size_t)P.rows * (P.chunks ? freq_chunks(tiles * P.rows, q->nfreq) : 1);
   return P;
+}
+
+// The cut of the first-face march for a launch of `rays` rays (porta_faces.hpp): columns,
+// ways and frequencies of a block.  The options' faces_chunk, if given, is the chunk of one
+// way.  fchunk is 0 if it does not fit the LDS.
+struct FacesShape {
+  int lanes, ways, fchunk, nchunk;
+};
+
+template <class T>
+FacesShape faces_shape_t(const porta_grid* g, const porta_quad* q, const porta_options* o,
+                         int rays) {
+  FacesShape S;
+  const int nf = q->nfreq;
+  S.lanes = (std::max(g->nx, g->ny) + 63) / 64 * 64;
+  auto fit = [&](int ways, int want) {   // the chunk that fits, `ways` sets of at most want/ways
+    while (want > 0 && faces_lds_bytes<T>(want, S.lanes, ways) > kFacesLds) want -= ways;
+    return std::max(want, 0);
+  };
+  S.ways = 1;
+  if (o && o->faces_chunk > 0) {
+    const int want = std::min(o->faces_chunk, nf);
+    S.fchunk = faces_lds_bytes<T>(want, S.lanes, 1) <= kFacesLds ? want : 0;
+  } else {
+    // frequencies in turn in one thread: one while their wavefronts fit on the chip
+    const int64_t waves = (int64_t)rays * nf * (S.lanes / 64);
+    const int serial = (int)std::min<int64_t>(faces_serial<T>(),
+                                              (waves + faces_waves<T>() - 1) / faces_waves<T>());
+    const int ways = std::min({kFacesMaxWays, kFacesThreads / S.lanes, nf});
+    if (serial == 1 && ways > 1) {
+      S.fchunk = fit(1, ways);   // one frequency per way: as many ways as fit
+      while (S.fchunk > 1 && faces_lds_bytes<T>(S.fchunk, S.lanes, S.fchunk) > kFacesLds) --S.fchunk;
+    } else {
+      S.fchunk = fit(1, std::min(serial, nf));
+    }
+    if (S.fchunk > 0) {   // even chunks
+      const int n = (nf + S.fchunk - 1) / S.fchunk;
+      S.fchunk = (nf + n - 1) / n;
+      if (serial == 1 && ways > 1) S.ways = S.fchunk;
+    }
+  }
+  S.nchunk = S.fchunk > 0 ? (nf + S.fchunk - 1) / S.fchunk : 1;
+  return S;
+}
+
+FacesShape faces_shape(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
+                       int rays) {
+  return prec == PORTA_F32 ? faces_shape_t<float>(g, q, o, rays)
+                           : faces_shape_t<double>(g, q, o, rays);
 }
 
 // The cut without sharing and chunks, which needs the least workspace.
@@ -298,6 +321,7 @@ struct Layout {
   size_t ck, slots, lamA, lamB, go, gm, gp, grad;
   size_t tf;               // first-face sweep: transposed transfer coefficients
   size_t fcache;           // first-face sweep: set-up of the nodes of a plane
+  FacesShape fshape;       // first-face sweep: the cut of its march
   size_t plane;            // bytes of one plane state of a ray batch
   int nck, nslot, stride;  // stride: planes from one checkpoint to the next
   size_t total;
@@ -329,7 +353,6 @@ Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const po
                     const SweepPlan& P) {
   Layout L = tables_layout(q, prec, g->nz);
   const size_t np = (size_t)g->nx * g->ny;
-  const size_t nrb = (size_t)P.nrb;
   const size_t state = (size_t)P.rows * q->nfreq * np * nstokes(o) * elem(prec);
   size_t off = L.end_tables;
   L.stateA = off;
@@ -340,18 +363,17 @@ Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const po
   // double-buffered partial sums
   off = align_up(off + 2 * P.jrows * (nstokes(o) + 1) * np * sizeof(double));
   if (faces_of(o)) {
-    // per-chunk partial sums of the first-face kernel
-    int lanes, fchunk;
-    faces_shape(g, q, prec, o, lanes, fchunk);
-    const size_t nchunk = fchunk > 0 ? (q->nfreq + fchunk - 1) / fchunk : 1;
+    // per-chunk partial sums of the first-face kernel; a call's smaller launches may be cut
+    // finer, into at most one chunk per row of these
+    L.fshape = faces_shape(g, q, prec, o, P.rows);
     L.ck = off;
-    off = align_up(off + nrb * nchunk * 5 * np * sizeof(double));
+    off = align_up(off + (size_t)P.rows * L.fshape.nchunk * 5 * np * sizeof(double));
     // the transfer coefficients with x and y exchanged in every plane
     L.tf = off;
     off = align_up(off + 13 * np * g->nz * elem(prec));
     // the set-up of every node and ray of one plane
     L.fcache = off;
-    off = align_up(off + nrb * kFacesCache * np * elem(prec));
+    off = align_up(off + (size_t)P.rows * kFacesCache * np * elem(prec));
   }
   L.total = off;
   return L;
@@ -533,25 +555,51 @@ int launch_jreduce(double* jkq, const double* jpart, const RayConsts* rays, int 
   return check_launch("jreduce");
 }
 
+// The batches of a sweep in turn: walk(r0, nr) with the first ray and the number of rays of
+// either hemisphere, together where the plan shares launches.  up_only: nothing that the
+// call returns depends on the downward rays (no J).
+template <class Walk>
+int walk_batches(const porta_quad* q, const porta_options* o, const SweepPlan& P, bool up_only,
+                 Walk walk) {
+  int rc, lo[2], hi[2];
+  for (int m = 0; m < 2; ++m) hemi_range(q, o, m, lo[m], hi[m]);
+  if (up_only) hi[1] = lo[1];
+  if (P.share) {
+    for (int b = 0;; ++b) {
+      int r0[2], nr[2];
+      for (int m = 0; m < 2; ++m) {
+        r0[m] = std::min(lo[m] + b * P.nrb, hi[m]);
+        nr[m] = std::min(P.nrb, hi[m] - r0[m]);
+      }
+      if (nr[0] + nr[1] == 0) return PORTA_OK;
+      if ((rc = walk(r0, nr))) return rc;
+    }
+  }
+  for (int m = 0; m < 2; ++m)
+    for (int r = lo[m]; r < hi[m]; r += P.nrb) {
+      const int n = std::min(P.nrb, hi[m] - r);
+      const int r0[2] = {m == 0 ? r : 0, m == 0 ? 0 : r}, nr[2] = {m == 0 ? n : 0, m == 0 ? 0 : n};
+      if ((rc = walk(r0, nr))) return rc;
+    }
+  return PORTA_OK;
+}
+
 // ---------------------------------------------------------------------------
 // Forward sweep with M and P on the first face crossed (options.faces = 1)
 // ---------------------------------------------------------------------------
 template <class T>
 int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f,
-                     const porta_options* o, double* jkq, T* itop, char* ws, const Layout& L,
-                     const RayConsts* rays, const T* phiT, const double* wn, T* state[2],
-                     hipStream_t st) {
+                     const porta_options* o, double* jkq, T* itop, char* ws, const SweepPlan& P,
+                     const Layout& L, hipStream_t st) {
   int rc;
   const int nx = g->nx, ny = g->ny, nz = g->nz, np = nx * ny;
   const size_t N = (size_t)np * nz;
   const int nh = q->nmu * q->nchi;
-  const int nrb_max = ray_batch(q, o);
-  int lanes, fchunk;
-  faces_shape(g, q, sizeof(T) == 4 ? PORTA_F32 : PORTA_F64, o, lanes, fchunk);
-  const int nchunk = (q->nfreq + fchunk - 1) / fchunk;
+  const FacesShape& S = L.fshape;
+  const RayConsts* rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
+  T* state[2] = {reinterpret_cast<T*>(ws + L.stateA), reinterpret_cast<T*>(ws + L.stateB)};
   double* jpart = reinterpret_cast<double*>(ws + L.jpart);
   double* jchunk = reinterpret_cast<double*>(ws + L.ck);
-  const size_t lds = faces_lds_bytes<T>(q->nfreq, fchunk, lanes);
   // rays that meet an x face first read the fields with x and y exchanged
   T* tf = reinterpret_cast<T*>(ws + L.tf);
   {
@@ -565,79 +613,86 @@ int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_field
       if ((rc = check_launch("transpose_planes"))) return rc;
     }
   }
-  for (int hemi = 0; hemi < 2; ++hemi) {
-    const bool up = (hemi == 0);
-    const int kb = up ? 0 : nz - 1, s = up ? 1 : -1;
-    const T ibound = up ? (T)f->i_bottom : T(0);
-    int lo, hi;
-    hemi_range(q, o, hemi, lo, hi);
-    for (int r0 = lo; r0 < hi; r0 += nrb_max) {
-      const int nrb = std::min(nrb_max, hi - r0);
-      const int ray0 = hemi * nh + r0;
-      if (jkq) {
-        // the boundary plane
-        if ((rc = launch_jreduce<T>(jkq, nullptr, rays, ray0, nrb, 1, 4, np, N, (size_t)kb * np,
-                                 (double)ibound, st)))
-          return rc;
+  FacesArgs<T> a{};
+  a.kappa = static_cast<const T*>(f->kappa);
+  a.prop = static_cast<const T*>(f->propmat);
+  a.emis = static_cast<const T*>(f->emis);
+  a.kappa_t = tf;
+  a.prop_t = tf + N;
+  a.emis_t = tf + 7 * N;
+  a.rays = rays;
+  a.phi = reinterpret_cast<const T*>(ws + L.phiT);
+  a.wn = reinterpret_cast<const double*>(ws + L.wn);
+  a.jchunk = jkq ? jchunk : nullptr;
+  a.cache = reinterpret_cast<T*>(ws + L.fcache);
+  a.N = N;
+  a.nx = nx;
+  a.ny = ny;
+  a.np = np;
+  a.nfreq = q->nfreq;
+  a.fchunk = S.fchunk;
+  a.nchunk = S.nchunk;
+  a.lanes = S.lanes;
+  a.inv_dx = nx / g->lx;
+  a.inv_dy = ny / g->ly;
+  a.parabolic = parabolic_of(o);
+  a.tol = sizeof(T) == 4 ? 0x1p-24 : 0x1p-53;   // the unit roundoff of the sweep precision
+  const size_t lds = faces_lds_bytes<T>(S.fchunk, S.lanes, S.ways);
+  const bool one = S.ways == S.fchunk;
+  const T ibound[2] = {(T)f->i_bottom, T(0)};
+  auto walk = [&](const int r0[2], const int nr[2]) -> int {
+    const int rows = nr[0] + nr[1];
+    const T* prev[2] = {nullptr, nullptr};
+    const size_t soff[2] = {0, (size_t)nr[0] * q->nfreq * np * 4};
+    const size_t joff[2] = {0, (size_t)nr[0] * 5 * np};
+    int e;
+    for (int m = 0; m < 2 && jkq; ++m)   // the boundary planes
+      if (nr[m] > 0 && (e = launch_jreduce<T>(jkq, nullptr, rays, m * nh + r0[m], nr[m], 1, 4, np, N,
+                                           (size_t)(m == 0 ? 0 : nz - 1) * np, (double)ibound[m],
+                                           st)))
+        return e;
+    for (int step = 1; step < nz; ++step) {
+      const bool last = (step == nz - 1);
+      for (int m = 0; m < 2; ++m) {
+        FacesHemi<T>& h = a.h[m];
+        const int s = m == 0 ? 1 : -1, k = (m == 0 ? 0 : nz - 1) + s * step;
+        h.iprev = prev[m];
+        h.top = m == 0 && last && itop;
+        h.inext = h.top ? itop + (size_t)r0[m] * q->nfreq * np * 4 : state[step & 1] + soff[m];
+        h.kO = k;
+        h.kM = k - s;
+        h.kP = last ? -1 : k + s;
+        h.dzM = std::fabs(g->z[k] - g->z[k - s]);
+        h.dzP = last ? 0.0 : std::fabs(g->z[k + s] - g->z[k]);
+        h.ray0 = m * nh + r0[m];
+        h.nrb = nr[m];
+        h.ibound = ibound[m];
+        prev[m] = h.inext;
       }
-      const T* prev = nullptr;
-      for (int step = 1; step < nz; ++step) {
-        const int k = kb + s * step;
-        const bool last = (step == nz - 1);
-        FacesArgs<T> a;
-        a.kappa = static_cast<const T*>(f->kappa);
-        a.prop = static_cast<const T*>(f->propmat);
-        a.emis = static_cast<const T*>(f->emis);
-        a.kappa_t = tf;
-        a.prop_t = tf + N;
-        a.emis_t = tf + 7 * N;
-        a.rays = rays;
-        a.phi = phiT;
-        a.wn = wn;
-        a.iprev = prev;
-        a.top = last && up && itop;
-        a.inext = a.top ? itop + (size_t)r0 * q->nfreq * np * 4 : state[step & 1];
-        a.jchunk = jkq ? jchunk : nullptr;
-        a.N = N;
-        a.nx = nx;
-        a.ny = ny;
-        a.np = np;
-        a.nfreq = q->nfreq;
-        a.fchunk = fchunk;
-        a.nchunk = nchunk;
-        a.kO = k;
-        a.kM = k - s;
-        a.kP = last ? -1 : k + s;
-        a.dzM = std::fabs(g->z[k] - g->z[k - s]);
-        a.dzP = last ? 0.0 : std::fabs(g->z[k + s] - g->z[k]);
-        a.inv_dx = nx / g->lx;
-        a.inv_dy = ny / g->ly;
-        a.ray0 = ray0;
-        a.parabolic = parabolic_of(o);
-        a.tol = sizeof(T) == 4 ? 0x1p-24 : 0x1p-53;   // the unit roundoff of the sweep precision
-        a.ibound = ibound;
-        a.cache = reinterpret_cast<T*>(ws + L.fcache);
-        a.nrb = nrb;
-        hipLaunchKernelGGL(k_faces_setup<T>, dim3((np + 255) / 256, nrb), dim3(256), 0, st, a);
-        if ((rc = check_launch("faces_setup"))) return rc;
-        hipLaunchKernelGGL(k_sweep_plane_faces<T>, dim3(faces_grid(nrb, nchunk)), dim3(lanes),
-                           lds, st, a);
-        if ((rc = check_launch("sweep_plane_faces"))) return rc;
-        if (jkq) {
-          const unsigned tiles = (unsigned)((std::max(nx, ny) + kSumTile - 1) / kSumTile);
-          hipLaunchKernelGGL(k_sum_chunks, dim3(tiles, tiles, nrb), dim3(256), 0, st, jpart,
-                             (const double*)jchunk, rays, ray0, nchunk, nx, ny, nx / g->lx,
-                             ny / g->ly);
-          if ((rc = check_launch("sum_chunks"))) return rc;
-          if ((rc = launch_jreduce<T>(jkq, jpart, rays, ray0, nrb, 1, 4, np, N, (size_t)k * np, 0.0,
-                                   st)))
-            return rc;
-        }
-        prev = a.inext;
+      a.nrb = rows;
+      hipLaunchKernelGGL(k_faces_setup<T>, dim3((np + 255) / 256, rows), dim3(256), 0, st, a);
+      if ((e = check_launch("faces_setup"))) return e;
+      const dim3 grid(faces_grid(rows, S.nchunk)), blk(S.lanes * S.ways);
+      if (one)
+        hipLaunchKernelGGL((k_sweep_plane_faces<T, true>), grid, blk, lds, st, a);
+      else
+        hipLaunchKernelGGL((k_sweep_plane_faces<T, false>), grid, blk, lds, st, a);
+      if ((e = check_launch("sweep_plane_faces"))) return e;
+      if (jkq) {
+        const unsigned tiles = (unsigned)((std::max(nx, ny) + kSumTile - 1) / kSumTile);
+        hipLaunchKernelGGL(k_sum_chunks, dim3(tiles, tiles, rows * 5), dim3(256), 0, st, jpart,
+                           (const double*)jchunk, rays, a.h[0].ray0, nr[0], a.h[1].ray0, S.nchunk,
+                           nx, ny, a.inv_dx, a.inv_dy);
+        if ((e = check_launch("sum_chunks"))) return e;
+        for (int m = 0; m < 2; ++m)
+          if (nr[m] > 0 && (e = launch_jreduce<T>(jkq, jpart + joff[m], rays, a.h[m].ray0, nr[m], 1, 4,
+                                               np, N, (size_t)a.h[m].kO * np, 0.0, st)))
+            return e;
       }
     }
-  }
-  return PORTA_OK;
+    return PORTA_OK;
+  };
+  return walk_batches(q, o, P, jkq == nullptr, walk);
 }
 
 // ---------------------------------------------------------------------------
@@ -714,18 +769,12 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
   const RayConsts* rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
   T* state[2] = {reinterpret_cast<T*>(ws + L.stateA), reinterpret_cast<T*>(ws + L.stateB)};
   if (faces_of(o))
-    return sweep_faces_impl<T>(g, q, f, o, jkq, itop, ws, L, rays,
-                               reinterpret_cast<const T*>(ws + L.phiT),
-                               reinterpret_cast<const double*>(ws + L.wn), state, st);
+    return sweep_faces_impl<T>(g, q, f, o, jkq, itop, ws, P, L, st);
   double* jpart[2] = {reinterpret_cast<double*>(ws + L.jpart), nullptr};
   jpart[1] = jpart[0] + P.jrows * (ns + 1) * np;
 
-  // batches of both hemispheres: (first ray, rays) within the hemisphere
-  int lo[2], hi[2];
-  for (int m = 0; m < 2; ++m) hemi_range(q, o, m, lo[m], hi[m]);
-  // without J nothing that the call returns depends on the downward rays
-  if (!jkq) hi[1] = lo[1];
-  const int up_lo = lo[0], up_hi = hi[0];
+  int up_lo, up_hi;
+  hemi_range(q, o, 0, up_lo, up_hi);
   const T ibound[2] = {(T)f->i_bottom, T(0)};
   // one launch per plane step for a batch of upward rays, of downward rays, or of both
   auto walk = [&](const int r0[2], const int nr[2]) -> int {
@@ -773,24 +822,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
     }
     return PORTA_OK;
   };
-  if (P.share) {
-    for (int b = 0;; ++b) {
-      int r0[2], nr[2];
-      for (int m = 0; m < 2; ++m) {
-        r0[m] = std::min(lo[m] + b * P.nrb, hi[m]);
-        nr[m] = std::min(P.nrb, hi[m] - r0[m]);
-      }
-      if (nr[0] + nr[1] == 0) return PORTA_OK;
-      if ((rc = walk(r0, nr))) return rc;
-    }
-  }
-  for (int m = 0; m < 2; ++m)
-    for (int r = lo[m]; r < hi[m]; r += P.nrb) {
-      const int n = std::min(P.nrb, hi[m] - r);
-      const int r0[2] = {m == 0 ? r : 0, m == 0 ? 0 : r}, nr[2] = {m == 0 ? n : 0, m == 0 ? 0 : n};
-      if ((rc = walk(r0, nr))) return rc;
-    }
-  return PORTA_OK;
+  return walk_batches(q, o, P, jkq == nullptr, walk);
 }
 
 // ---------------------------------------------------------------------------
@@ -1045,9 +1077,7 @@ int sweep_entry(const porta_grid* grid, const porta_quad* quad, const porta_fiel
                   "faces = 1 is for the bilinear Stokes-vector sweep without checkpoints");
     if (std::max(grid->nx, grid->ny) > kFacesMaxLanes)
       return fail(PORTA_EUNSUPPORTED, "faces = 1 needs nx, ny <= %d", kFacesMaxLanes);
-    int lanes, fchunk;
-    faces_shape(grid, quad, prec, opts, lanes, fchunk);
-    if (fchunk < 1)
+    if (faces_shape(grid, quad, prec, opts, 1).fchunk < 1)
       return fail(PORTA_EUNSUPPORTED, "faces = 1: the LDS of a block has no room for %s",
                   opts->faces_chunk > 0 ? "faces_chunk frequencies" : "one frequency");
   }
