@@ -16,6 +16,7 @@
 #include "porta_faces.hpp"
 #include "porta_host.hpp"
 #include "porta_kernels.hpp"
+#include "porta_pair.hpp"
 #include "porta_unpol.hpp"
 
 // Workspace of porta_fs_sweep_noalloc, one copy on every device the library runs on,
@@ -224,6 +225,7 @@ int freq_chunks(int64_t blocks, int nfreq) {
 struct SweepPlan {
   int nrb;         // rays of a batch in one hemisphere
   bool share;      // an upward and a downward batch per launch
+  bool pair;       // two planes per launch (porta_pair.hpp)
   bool chunks;     // frequency chunks (FP64: their partial sums change the order of the sums
                    // over frequencies that make J, which in an FP32 iteration would tip
                    // the rounding of the next emissivities)
@@ -232,6 +234,16 @@ struct SweepPlan {
 };
 constexpr int64_t kShareBlocks = 2048;
 
+// Sweeps whose planes can go in pairs: bilinear Stokes-vector plane hops at the default block
+// size (the 9-point mode, known only at the call, goes plane by plane).  They do where the
+// hemispheres do not share launches: a sweep of 128x128x96, 80 rays, FP64 (2560 blocks a
+// hemisphere) takes 131.7 ms by pairs and 162.3 plane by plane, FP64 multigrid cycles on
+// 64x64x49 (640 blocks) 54.9 ms by pairs and 54.0 shared, and on smaller planes sharing and
+// frequency chunks are what fills the chip.
+bool pair_of(const porta_options* o) {
+  return nstokes(o) == 4 && !faces_of(o) && !(o && o->block > 0);
+}
+
 SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
   SweepPlan P;
   const int64_t tiles = plane_tiles(g, o);
@@ -239,6 +251,7 @@ SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const p
   P.nrb = (int)std::min<int64_t>(ray_batch(q, o), std::max<int64_t>(1, (1 << 23) / tiles));
   if (faces_of(o)) P.nrb = std::min(P.nrb, 6553);   // 5 blocks per ray in a grid's z of 65535
   P.share = tiles * P.nrb <= kShareBlocks;
+  P.pair = !P.share && pair_of(o);
   P.rows = P.share ? 2 * P.nrb : P.nrb;
   P.chunks = prec == PORTA_F64;
   P.jrows = (size_t)P.rows * (P.chunks ? freq_chunks(tiles * P.rows, q->nfreq) : 1);
@@ -295,7 +308,7 @@ FacesShape faces_shape(const porta_grid* g, const porta_quad* q, int prec, const
 }
 
 // The cut without sharing and chunks, which needs the least workspace.
-SweepPlan least_plan(int nrb) { return {nrb, false, false, nrb, (size_t)nrb}; }
+SweepPlan least_plan(int nrb) { return {nrb, false, false, false, nrb, (size_t)nrb}; }
 
 // Chunks of a launch of `rays` rays (each chunk has a row of partial sums).
 int launch_chunks(const porta_grid* g, const porta_quad* q, const porta_options* o,
@@ -360,8 +373,8 @@ Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const po
   L.stateB = off;
   off = align_up(off + state);
   L.jpart = off;
-  // double-buffered partial sums
-  off = align_up(off + 2 * P.jrows * (nstokes(o) + 1) * np * sizeof(double));
+  // double-buffered partial sums, of one plane or two
+  off = align_up(off + (P.pair ? 4 : 2) * P.jrows * (nstokes(o) + 1) * np * sizeof(double));
   if (faces_of(o)) {
     // per-chunk partial sums of the first-face kernel; a call's smaller launches may be cut
     // finer, into at most one chunk per row of these
@@ -770,12 +783,19 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
   T* state[2] = {reinterpret_cast<T*>(ws + L.stateA), reinterpret_cast<T*>(ws + L.stateB)};
   if (faces_of(o))
     return sweep_faces_impl<T>(g, q, f, o, jkq, itop, ws, P, L, st);
-  double* jpart[2] = {reinterpret_cast<double*>(ws + L.jpart), nullptr};
-  jpart[1] = jpart[0] + P.jrows * (ns + 1) * np;
-
+  double* const jbase = reinterpret_cast<double*>(ws + L.jpart);
+  const size_t jslot = P.jrows * (ns + 1) * np;   // partial sums of one plane
   int up_lo, up_hi;
   hemi_range(q, o, 0, up_lo, up_hi);
   const T ibound[2] = {(T)f->i_bottom, T(0)};
+  // where the state of plane k of a batch goes if it is to be kept: I_top, a checkpoint for
+  // the adjoint, or nowhere
+  auto kept = [&](int m, int k, int r0) -> T* {
+    if (m != 0) return nullptr;
+    if (k == nz - 1) return itop ? itop + (size_t)r0 * q->nfreq * np * ns : nullptr;
+    if (!ckpt || !is_checkpoint(k, nz, C)) return nullptr;
+    return ckpt + ((size_t)(k / C - 1) * (up_hi - up_lo) + (r0 - up_lo)) * q->nfreq * np * 4;
+  };
   // one launch per plane step for a batch of upward rays, of downward rays, or of both
   auto walk = [&](const int r0[2], const int nr[2]) -> int {
     PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L);
@@ -789,23 +809,17 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
       for (int m = 0; m < 2; ++m) {
         HemiArgs<T>& h = a.h[m];
         const int s = m == 0 ? 1 : -1, k = (m == 0 ? 0 : nz - 1) + s * step;
-        const size_t batch_off = (size_t)r0[m] * q->nfreq * np * ns;
         set_plane(h, g, k, s);
         h.ray0 = m * nh + r0[m];
         h.nrb = nr[m];
         h.ibound = ibound[m];
         h.iprev = prev[m];
-        if (m == 0 && step == nz - 1 && itop)
-          h.inext = itop + batch_off;
-        else if (m == 0 && ckpt && is_checkpoint(k, nz, C))   // kept for the adjoint
-          h.inext = ckpt + ((size_t)(k / C - 1) * (up_hi - up_lo) + (r0[m] - up_lo)) *
-                               q->nfreq * np * 4;
-        else
-          h.inext = state[step & 1] + soff[m];
-        // plane k writes partial sums into jpart[step & 1] while the first blocks add
+        h.inext = kept(m, k, r0[m]);
+        if (!h.inext) h.inext = state[step & 1] + soff[m];
+        // plane k writes partial sums into slot step & 1 while the first blocks add
         // those of plane k - s (or the boundary plane) to J
-        h.jpart = jkq ? jpart[step & 1] + joff[m] : nullptr;
-        h.jpart_prev = (jkq && step > 1) ? jpart[(step - 1) & 1] + joff[m] : nullptr;
+        h.jpart = jkq ? jbase + (step & 1) * jslot + joff[m] : nullptr;
+        h.jpart_prev = (jkq && step > 1) ? jbase + ((step - 1) & 1) * jslot + joff[m] : nullptr;
         h.prev_off = (size_t)(k - s) * np;
         prev[m] = h.inext;
       }
@@ -822,6 +836,71 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
     }
     return PORTA_OK;
   };
+  // two planes per launch, for a batch of one hemisphere; of an even number of planes the first
+  // one goes alone
+  auto walk_pairs = [&](const int r0s[2], const int nr[2]) -> int {
+    const int m = nr[0] > 0 ? 0 : 1, r0 = r0s[m], s = m == 0 ? 1 : -1, kb = m == 0 ? 0 : nz - 1;
+    PairArgs<T> A{};
+    PlaneArgs<T>& a = A.a;
+    a = plane_args<T>(g, q, f, o, ws, L);
+    a.jkq = jkq;
+    auto set = [&](HemiArgs<T>& h, int k, const T* prev, T* next, int slot) {
+      set_plane(h, g, k, s);
+      h.ray0 = m * nh + r0;
+      h.nrb = nr[m];
+      h.ibound = ibound[m];
+      h.iprev = prev;
+      h.inext = next;
+      h.jpart = jkq ? jbase + slot * jslot : nullptr;
+    };
+    // planes whose partial sums are still to be added to J
+    A.jp[0] = {nullptr, (size_t)kb * np};
+    A.njprev = 1;
+    const T* prev = nullptr;
+    int step = 1, launch = 0, e;
+    if (nz % 2 == 0) {
+      const int k = kb + s;
+      T* next = kept(m, k, r0);
+      if (!next) next = state[0];
+      set(a.h[0], k, nullptr, next, 0);
+      a.h[0].prev_off = (size_t)kb * np;
+      set_chunks(a, 1, nr[m]);
+      a.njb = jkq ? 2 * jblocks(np) : 0;
+      if ((e = launch_plane<T>(a, ns, interp, block, st))) return e;
+      A.jp[0] = {a.h[0].jpart, (size_t)k * np};
+      prev = next;
+      step = 2;
+      launch = 1;
+    }
+    A.ntx = (g->nx + kPairX - 1) / kPairX;
+    a.ntile = pair_tiles(g->nx, g->ny);
+    a.nstep = a.ntile * nr[m];
+    a.njb = jkq ? 2 * jblocks(np) : 0;
+    a.fchunk = a.nfreq;
+    a.nchunk = 1;
+    const size_t lds = std::max((size_t)a.nfreq * (sizeof(double) + sizeof(T)),
+                                jkq ? jlds_bytes(kPairGroup, sizeof(T)) : 0);
+    for (; step < nz; step += 2, ++launch) {
+      const int k = kb + s * step, slot = (launch & 1) * 2;
+      T* next = kept(m, k + s, r0);
+      if (!next) next = state[launch & 1];
+      set(a.h[0], k, prev, kept(m, k, r0), slot);
+      set(A.n, k + s, nullptr, next, slot + 1);
+      hipLaunchKernelGGL(k_sweep_pair<T>, dim3(a.nstep + a.njb), dim3(kPairThreads), lds, st, A);
+      if ((e = check_launch("sweep_pair"))) return e;
+      A.jp[0] = {a.h[0].jpart, (size_t)k * np};
+      A.jp[1] = {A.n.jpart, (size_t)(k + s) * np};
+      A.njprev = 2;
+      prev = next;
+    }
+    for (int c = 0; c < A.njprev && jkq; ++c)
+      if ((e = launch_jreduce<T>(jkq, A.jp[c].part, rays, m * nh + r0, nr[m], 1, ns, np, N,
+                              A.jp[c].off, (double)ibound[m], st)))
+        return e;
+    return PORTA_OK;
+  };
+  if (P.pair && interp == PORTA_INTERP_BILINEAR)
+    return walk_batches(q, o, P, jkq == nullptr, walk_pairs);
   return walk_batches(q, o, P, jkq == nullptr, walk);
 }
 
