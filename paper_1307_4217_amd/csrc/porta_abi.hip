@@ -235,13 +235,34 @@ struct SweepPlan {
 constexpr int64_t kShareBlocks = 2048;
 
 // Sweeps whose planes can go in pairs: bilinear Stokes-vector plane hops at the default block
-// size (the 9-point mode, known only at the call, goes plane by plane).  They do where the
-// hemispheres do not share launches: a sweep of 128x128x96, 80 rays, FP64 (2560 blocks a
-// hemisphere) takes 131.7 ms by pairs and 162.3 plane by plane, FP64 multigrid cycles on
-// 64x64x49 (640 blocks) 54.9 ms by pairs and 54.0 shared, and on smaller planes sharing and
-// frequency chunks are what fills the chip.
+// size (the 9-point mode, known only at the call, goes plane by plane).
 bool pair_of(const porta_options* o) {
   return nstokes(o) == 4 && !faces_of(o) && !(o && o->block > 0);
+}
+
+// Whether two planes take less time by a launch of both (pairs of `rows` rays) than by two of
+// one (rows in n frequency chunks): a pair reads and writes half the states, but its set-up
+// is not spread over as many wavefronts, its tiles have a rim, and its blocks are twice as
+// large.  Times in us: rounds of the chip, times the frequencies and a set-up in units of them,
+// times the time of one.  Measured (rows of both hemispheres where they share launches), pairs
+// and planes, a sweep: FP64 128x128x33, 40 rays, 2, 7, 12 frequencies 6.2 and 4.4, 8.5 and
+// 7.6, 10.5 and 10.4 ms; 256x256x17, 41 frequencies 43.1 and 53.9; shared, 64x64x49, 5, 31, 101
+// frequencies 2.8 and 2.6, 7.0 and 8.1, 18.8 and 24.2; 37x30x45, 80 rays, 31 frequencies
+// (9 tiles for 1110 nodes) 5.4 and 5.0.  FP32 256x256, 40 rays, 9 and 41 frequencies, 33 and 17
+// planes 19.5 and 16.2, 21.6 and 22.5; 256x256x128, 101 frequencies 724 and 845.
+bool pair_faster(const porta_grid* g, int prec, int64_t tiles, int64_t rows, int nfreq, int n) {
+  const bool f64 = prec == PORTA_F64;
+  // the tables of the frequencies and the tiles within 64 KiB of LDS
+  if (nfreq * (f64 ? 16 : 12) + (f64 ? sizeof(PairLds<double>) : sizeof(PairLds<float>)) > 65536)
+    return false;
+  const int64_t pairs = pair_tiles(g->nx, g->ny) * rows, slots = f64 ? kCus : 2 * kCus;
+  // (below a wavefront per SIMD an update takes about half as long as with two)
+  const double rounds = std::max(0.5, double(tiles * rows * n) / (f64 ? 2 * kCus : 3 * kCus));
+  const int per = (nfreq + n - 1) / n;
+  const double pair = double((pairs + slots - 1) / slots) *
+                      (f64 ? 1.02 * (12.5 + nfreq) : 0.96 * (17.0 + nfreq));
+  const double plane = 2.0 * rounds * (f64 ? 1.91 * (5.1 + per) : 1.07 * (9.5 + per));
+  return pair < plane;
 }
 
 SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
@@ -251,10 +272,13 @@ SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const p
   P.nrb = (int)std::min<int64_t>(ray_batch(q, o), std::max<int64_t>(1, (1 << 23) / tiles));
   if (faces_of(o)) P.nrb = std::min(P.nrb, 6553);   // 5 blocks per ray in a grid's z of 65535
   P.share = tiles * P.nrb <= kShareBlocks;
-  P.pair = !P.share && pair_of(o);
   P.rows = P.share ? 2 * P.nrb : P.nrb;
   P.chunks = prec == PORTA_F64;
-  P.jrows = (size_t)P.rows * (P.chunks ? freq_chunks(tiles * P.rows, q->nfreq) : 1);
+  const int n = P.chunks ? freq_chunks(tiles * P.rows, q->nfreq) : 1;
+  P.jrows = (size_t)P.rows * n;
+  // (a pair of launches of both hemispheres: kPairBoth)
+  P.pair = pair_of(o) && (!P.share || prec == PORTA_F64) &&
+           pair_faster(g, prec, tiles, P.rows, q->nfreq, n);
   return P;
 }
 
@@ -836,67 +860,85 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
     }
     return PORTA_OK;
   };
-  // two planes per launch, for a batch of one hemisphere; of an even number of planes the first
-  // one goes alone
-  auto walk_pairs = [&](const int r0s[2], const int nr[2]) -> int {
-    const int m = nr[0] > 0 ? 0 : 1, r0 = r0s[m], s = m == 0 ? 1 : -1, kb = m == 0 ? 0 : nz - 1;
+  // two planes per launch; of an even number of planes the first one goes alone
+  auto walk_pairs = [&](const int r0[2], const int nr[2]) -> int {
     PairArgs<T> A{};
     PlaneArgs<T>& a = A.a;
     a = plane_args<T>(g, q, f, o, ws, L);
     a.jkq = jkq;
-    auto set = [&](HemiArgs<T>& h, int k, const T* prev, T* next, int slot) {
-      set_plane(h, g, k, s);
-      h.ray0 = m * nh + r0;
+    const size_t soff[2] = {0, (size_t)nr[0] * q->nfreq * np * ns};
+    const size_t joff[2] = {0, (size_t)nr[0] * (ns + 1) * np};
+    const int kb[2] = {0, nz - 1}, up[2] = {1, -1};   // boundary planes, directions
+    // where the launch's arguments of a hemisphere are; the hemispheres that it has
+    const int at[2] = {0, kPairBoth<T> ? 1 : 0}, m0 = nr[0] > 0 ? 0 : 1, m1 = nr[1] > 0 ? 2 : 1;
+    auto set = [&](HemiArgs<T>& h, int m, int k, const T* prev, T* next, int slot) {
+      set_plane(h, g, k, up[m]);
+      h.ray0 = m * nh + r0[m];
       h.nrb = nr[m];
       h.ibound = ibound[m];
       h.iprev = prev;
       h.inext = next;
-      h.jpart = jkq ? jbase + slot * jslot : nullptr;
+      h.jpart = jkq ? jbase + slot * jslot + joff[m] : nullptr;
     };
     // planes whose partial sums are still to be added to J
-    A.jp[0] = {nullptr, (size_t)kb * np};
-    A.njprev = 1;
-    const T* prev = nullptr;
+    for (int m = m0; m < m1; ++m) {
+      A.jp[at[m]][0] = {nullptr, (size_t)kb[m] * np};
+      A.njprev[at[m]] = 1;
+    }
+    const T* prev[2] = {nullptr, nullptr};
     int step = 1, launch = 0, e;
     if (nz % 2 == 0) {
-      const int k = kb + s;
-      T* next = kept(m, k, r0);
-      if (!next) next = state[0];
-      set(a.h[0], k, nullptr, next, 0);
-      a.h[0].prev_off = (size_t)kb * np;
-      set_chunks(a, 1, nr[m]);
+      for (int m = m0; m < m1; ++m) {
+        const int k = kb[m] + up[m];
+        T* next = kept(m, k, r0[m]);
+        if (!next) next = state[0] + soff[m];
+        set(a.h[at[m]], m, k, nullptr, next, 0);
+        a.h[at[m]].prev_off = (size_t)kb[m] * np;
+        A.jp[at[m]][0] = {a.h[at[m]].jpart, (size_t)k * np};
+        prev[m] = next;
+      }
+      set_chunks(a, 1, nr[0] + nr[1]);
       a.njb = jkq ? 2 * jblocks(np) : 0;
       if ((e = launch_plane<T>(a, ns, interp, block, st))) return e;
-      A.jp[0] = {a.h[0].jpart, (size_t)k * np};
-      prev = next;
       step = 2;
       launch = 1;
     }
     A.ntx = (g->nx + kPairX - 1) / kPairX;
     a.ntile = pair_tiles(g->nx, g->ny);
-    a.nstep = a.ntile * nr[m];
-    a.njb = jkq ? 2 * jblocks(np) : 0;
+    a.nstep = a.ntile * (nr[0] + nr[1]);
+    a.njb = jkq ? (kPairBoth<T> ? 4 : 2) * jblocks(np) : 0;
     a.fchunk = a.nfreq;
     a.nchunk = 1;
     const size_t lds = std::max((size_t)a.nfreq * (sizeof(double) + sizeof(T)),
                                 jkq ? jlds_bytes(kPairGroup, sizeof(T)) : 0);
     for (; step < nz; step += 2, ++launch) {
-      const int k = kb + s * step, slot = (launch & 1) * 2;
-      T* next = kept(m, k + s, r0);
-      if (!next) next = state[launch & 1];
-      set(a.h[0], k, prev, kept(m, k, r0), slot);
-      set(A.n, k + s, nullptr, next, slot + 1);
+      const int slot = (launch & 1) * 2;
+      a.jsame = 0;
+      for (int i = 0; i < A.njprev[0] && nr[0] > 0 && nr[1] > 0; ++i)
+        for (int j = 0; j < A.njprev[1]; ++j) a.jsame |= A.jp[0][i].off == A.jp[1][j].off;
+      T* next[2];
+      for (int m = m0; m < m1; ++m) {
+        const int k = kb[m] + up[m] * step, s = up[m];
+        next[m] = kept(m, k + s, r0[m]);
+        if (!next[m]) next[m] = state[launch & 1] + soff[m];
+        set(a.h[at[m]], m, k, prev[m], kept(m, k, r0[m]), slot);
+        set(A.n[at[m]], m, k + s, nullptr, next[m], slot + 1);
+      }
       hipLaunchKernelGGL(k_sweep_pair<T>, dim3(a.nstep + a.njb), dim3(kPairThreads), lds, st, A);
       if ((e = check_launch("sweep_pair"))) return e;
-      A.jp[0] = {a.h[0].jpart, (size_t)k * np};
-      A.jp[1] = {A.n.jpart, (size_t)(k + s) * np};
-      A.njprev = 2;
-      prev = next;
+      for (int m = m0; m < m1; ++m) {
+        const int k = kb[m] + up[m] * step;
+        A.jp[at[m]][0] = {a.h[at[m]].jpart, (size_t)k * np};
+        A.jp[at[m]][1] = {A.n[at[m]].jpart, (size_t)(k + up[m]) * np};
+        A.njprev[at[m]] = 2;
+        prev[m] = next[m];
+      }
     }
-    for (int c = 0; c < A.njprev && jkq; ++c)
-      if ((e = launch_jreduce<T>(jkq, A.jp[c].part, rays, m * nh + r0, nr[m], 1, ns, np, N,
-                              A.jp[c].off, (double)ibound[m], st)))
-        return e;
+    for (int m = m0; m < m1 && jkq; ++m)
+      for (int c = 0; c < A.njprev[at[m]]; ++c)
+        if ((e = launch_jreduce<T>(jkq, A.jp[at[m]][c].part, rays, m * nh + r0[m], nr[m], 1, ns, np, N,
+                                   A.jp[at[m]][c].off, (double)ibound[m], st)))
+          return e;
     return PORTA_OK;
   };
   if (P.pair && interp == PORTA_INTERP_BILINEAR)

@@ -653,12 +653,11 @@ struct PlaneArgs {
   int parabolic;     // control point: 0 BESSER, 1 parabola through M, O, P
 };
 
-// The arguments of one hemisphere, field by field: an index into a.h taken at run time
-// would leave the pointers without their address space (flat loads and stores, 2% of
+// The arguments of one hemisphere, field by field: an index into an array of them taken at run
+// time would leave the pointers without their address space (flat loads and stores, 2% of
 // the sweep at 256x256x128).
 template <class T>
-__device__ inline HemiArgs<T> hemi_args(const PlaneArgs<T>& a, bool second) {
-  const HemiArgs<T>&u = a.h[0], &d = a.h[1];
+__device__ inline HemiArgs<T> hemi_pick(const HemiArgs<T>& u, const HemiArgs<T>& d, bool second) {
   HemiArgs<T> h;
   h.iprev = second ? d.iprev : u.iprev;
   h.inext = second ? d.inext : u.inext;
@@ -673,6 +672,10 @@ __device__ inline HemiArgs<T> hemi_args(const PlaneArgs<T>& a, bool second) {
   h.ibound = second ? d.ibound : u.ibound;
   return h;
 }
+template <class T>
+__device__ inline HemiArgs<T> hemi_args(const PlaneArgs<T>& a, bool second) {
+  return hemi_pick(a.h[0], a.h[1], second);
+}
 
 // The J reduction of the previous planes by the last njb blocks of a plane step: half of
 // them for each hemisphere.
@@ -685,6 +688,7 @@ __device__ inline void jblock(const PlaneArgs<T>& a, double* lds) {
   const JJob j = {h.jpart_prev, a.rays + h.ray0, h.nrb, a.nchunk, (double)h.ibound, h.prev_off};
   jreduce_block<NS, T>(j, a.jkq, a.N, a.np, node0, lds, blockDim.x);
   if (a.jsame) {
+    __syncthreads();   // the first one's LDS has been read
     const HemiArgs<T>& d = a.h[1];
     const JJob k = {d.jpart_prev, a.rays + d.ray0, d.nrb, a.nchunk, (double)d.ibound, h.prev_off};
     jreduce_block<NS, T>(k, a.jkq, a.N, a.np, node0, lds, blockDim.x);

@@ -40,12 +40,20 @@ struct JPrev {
   size_t off;           // of the plane in jkq
 };
 
+// Whether a launch can hold both hemispheres, for sweeps whose one does not fill the chip: in
+// FP64.  In FP32 the choice costs scalar registers and gains nothing over a plane of both per
+// launch (64x64x49, 40 rays each, 31 frequencies: 3.8 ms either way).
+template <class T>
+constexpr bool kPairBoth = sizeof(T) == 8;
+
 template <class T>
 struct PairArgs {
-  PlaneArgs<T> a;      // h[0]: the first plane (inext: nullptr unless its state is kept)
-  HemiArgs<T> n;       // the second plane (iprev unused)
-  JPrev jp[2];
-  int njprev;          // planes of the previous launch whose partial sums this one adds to J
+  PlaneArgs<T> a;      // h[m]: the first plane of a hemisphere (inext: nullptr unless kept; not
+                       // kPairBoth: h[0] is the launch's only one); jsame: both hemispheres add
+                       // partial sums to the same plane of J
+  HemiArgs<T> n[2];    // the second planes (iprev unused)
+  JPrev jp[2][2];      // planes of the previous launch whose partial sums this one adds to J
+  int njprev[2];       // how many of each hemisphere
   int ntx;             // tiles in a row of tiles
 };
 
@@ -91,13 +99,32 @@ k_sweep_pair(const PairArgs<T> A) {
   const PlaneArgs<T>& a = A.a;
   extern __shared__ double s_tab[];
   if ((int)blockIdx.x >= a.nstep) {
-    const int b = blockIdx.x - a.nstep, per = a.njb / 2, second = b >= per;
-    if (second && A.njprev < 2) return;
-    const int node0 = (b - second * per) * kJNodes;
-    // the second half of the threads only synchronises
-    const JJob j = {second ? A.jp[1].part : A.jp[0].part, a.rays + a.h[0].ray0, a.h[0].nrb, 1,
-                    (double)a.h[0].ibound, second ? A.jp[1].off : A.jp[0].off};
-    jreduce_block<4, T>(j, a.jkq, a.N, a.np, node0, s_tab, kPairGroup);
+    // jblocks of them for each hemisphere and plane; where both hemispheres add to a plane, the
+    // first jblocks do everything in turn.  The second half of the threads only synchronises.
+    if constexpr (!kPairBoth<T>) {
+      const int b = blockIdx.x - a.nstep, per = a.njb / 2, second = b >= per;
+      if (second && A.njprev[0] < 2) return;
+      const JJob j = {second ? A.jp[0][1].part : A.jp[0][0].part, a.rays + a.h[0].ray0, a.h[0].nrb,
+                      1, (double)a.h[0].ibound, second ? A.jp[0][1].off : A.jp[0][0].off};
+      jreduce_block<4, T>(j, a.jkq, a.N, a.np, (b - second * per) * kJNodes, s_tab, kPairGroup);
+      return;
+    }
+    const int b = blockIdx.x - a.nstep, per = a.njb / 4, first = b / per;
+    const int node0 = (b - first * per) * kJNodes;
+    if (a.jsame && first > 0) return;
+    for (int e = first; e < (a.jsame ? 4 : first + 1); ++e) {
+      const bool down = e >= 2, second = e & 1;
+      const HemiArgs<T> h = hemi_args(a, down);
+      if (h.nrb == 0 || second >= (down ? A.njprev[1] : A.njprev[0])) continue;
+      const double* up_part = second ? A.jp[0][1].part : A.jp[0][0].part;
+      const double* down_part = second ? A.jp[1][1].part : A.jp[1][0].part;
+      const size_t up_off = second ? A.jp[0][1].off : A.jp[0][0].off;
+      const size_t down_off = second ? A.jp[1][1].off : A.jp[1][0].off;
+      const JJob j = {down ? down_part : up_part, a.rays + h.ray0, h.nrb, 1, (double)h.ibound,
+                      down ? down_off : up_off};
+      __syncthreads();   // the last one's LDS has been read
+      jreduce_block<4, T>(j, a.jkq, a.N, a.np, node0, s_tab, kPairGroup);
+    }
     return;
   }
   __shared__ PairLds<T> lds;
@@ -108,19 +135,22 @@ k_sweep_pair(const PairArgs<T> A) {
     s_phi[t] = a.phi[t];
   }
   const int L = xcd_order(a.xcd_remap, blockIdx.x, a.nstep);
-  const int tile = L % a.ntile, rb = L / a.ntile;
+  const int tile = L % a.ntile, r = L / a.ntile;
+  const bool down = kPairBoth<T> && r >= a.h[0].nrb;
+  const int rb = down ? r - a.h[0].nrb : r;
+  const HemiArgs<T> h = kPairBoth<T> ? hemi_args(a, down) : a.h[0];
+  const HemiArgs<T> hn = kPairBoth<T> ? hemi_pick(A.n[0], A.n[1], down) : A.n[0];
   const int ox = (tile % A.ntx) * kPairX, oy = (tile / A.ntx) * kPairY;
   const int nx = a.nx, ny = a.ny;
   const int ex = min(kPairX, nx - ox), ey = min(kPairY, ny - oy);   // nodes of this tile
   // which group: the same for every lane of a wavefront
   const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / kPairGroup);
   const int t = threadIdx.x % kPairGroup;
-  const int ray = a.h[0].ray0 + rb;
+  const int ray = h.ray0 + rb;
   const RayConsts& rc = a.rays[ray];
-  const int kO = grp ? A.n.kO : a.h[0].kO, kM = grp ? A.n.kM : a.h[0].kM,
-            kP = grp ? A.n.kP : a.h[0].kP;
-  const RayGeom& g1 = layer_geom(a.geom, ray, a.nz, a.h[0].kO, a.h[0].kM, 0);   // first plane's M
-  const RayGeom& g2 = layer_geom(a.geom, ray, a.nz, A.n.kO, A.n.kM, 0);         // second plane's M
+  const int kO = grp ? hn.kO : h.kO, kM = grp ? hn.kM : h.kM, kP = grp ? hn.kP : h.kP;
+  const RayGeom& g1 = layer_geom(a.geom, ray, a.nz, h.kO, h.kM, 0);     // first plane's M
+  const RayGeom& g2 = layer_geom(a.geom, ray, a.nz, hn.kO, hn.kM, 0);   // second plane's M
   // the node of this thread: (cx, cy) of its plane's tile
   const int w = grp ? kPairX : kMidX;
   const int cy = t / w, cx = t - cy * w;
@@ -148,14 +178,14 @@ k_sweep_pair(const PairArgs<T> A) {
   const size_t fstride = (size_t)a.np * 4;
   const size_t roff = (size_t)rb * a.nfreq * fstride;
   // the upwind node that this thread brings: entry threadIdx.x of the upwind tile
-  const T* ip = a.h[0].iprev;
+  const T* ip = h.iprev;
   const bool brings = ip && threadIdx.x < kUpX * kUpY;
   if (brings) {
     const int uy = threadIdx.x / kUpX, ux = threadIdx.x - uy * kUpX;
     const int ui = wrapi(ox + ux + fu2 + g1.fu, nx), uj = wrapi(oy + uy + fv2 + g1.fv, ny);
     ip += roff + 4 * ((size_t)uj * nx + ui);
   }
-  T* out = grp ? A.n.inext : a.h[0].inext;
+  T* out = grp ? hn.inext : h.inext;
   const bool stores = out && active && (grp || owner);
   if (stores) out += roff + 4 * (size_t)p;
   double jacc0 = 0.0, jacc1 = 0.0, jacc2 = 0.0, jacc3 = 0.0, lacc = 0.0;
@@ -192,7 +222,7 @@ k_sweep_pair(const PairArgs<T> A) {
       for (int q = 0; q < 4; ++q)
         IM[q] = bilinear(w00, w10, w01, w11, v[0][q], v[1][q], v[2][q], v[3][q]);
       if (!grp && !ip) {   // the upwind plane is the boundary
-        IM[0] = a.h[0].ibound;
+        IM[0] = h.ibound;
         IM[1] = IM[2] = IM[3] = T(0);
       }
       const Coefs<T> cf = coefficients(tau0 * s_phi[f]);
@@ -211,7 +241,7 @@ k_sweep_pair(const PairArgs<T> A) {
     }
     __syncthreads();
   }
-  double* jp = grp ? A.n.jpart : a.h[0].jpart;
+  double* jp = grp ? hn.jpart : h.jpart;
   if (jp && active && (grp || owner)) {
     jp += (size_t)rb * 5 * a.np + p;
     jp[0] = jacc0;
