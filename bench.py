@@ -101,14 +101,16 @@ def parse():
     return args
 
 
-def sweep_launch_bytes(cfg, nrb, elem, nst=4):
-    """Algorithmic HBM bytes of one plane launch of the sweep kernel: the upwind
+def sweep_launch_bytes(cfg, nrb, elem, nst=4, pair=False, kept=False):
+    """Algorithmic HBM bytes of one plane of the sweep for a batch of rays: the upwind
     Stokes vector (nst components) read and the new one written per update, three
     planes of the 13 transfer coefficients, and the FP64 read-modify-write of the 10 J
-    values of the previous plane."""
+    values of the previous plane.  pair: by launches of two planes, where the state between
+    them is neither read nor, unless every plane is kept, written."""
     np_ = cfg.nx * cfg.ny
     updates = nrb * cfg.nfreq * np_
-    return updates * 2 * nst * elem + 3 * np_ * 13 * elem + np_ * 10 * 8 * 2, updates
+    states = (1.5 if kept else 1.0) if pair else 2.0
+    return updates * states * nst * elem + 3 * np_ * 13 * elem + np_ * 10 * 8 * 2, updates
 
 
 def adjoint_launch_bytes(cfg, nrb, elem):
@@ -124,14 +126,16 @@ def adjoint_launch_bytes(cfg, nrb, elem):
 KERNEL_SYMBOLS = {
     "k_sweep_plane<float, 0>": "_ZN5porta13k_sweep_planeIfLi0EEEvNS_9PlaneArgsIT_EE",
     "k_sweep_plane<double, 0>": "_ZN5porta13k_sweep_planeIdLi0EEEvNS_9PlaneArgsIT_EE",
+    "k_sweep_pair<float>": "_ZN5porta12k_sweep_pairIfEEvNS_8PairArgsIT_EE",
+    "k_sweep_pair<double>": "_ZN5porta12k_sweep_pairIdEEvNS_8PairArgsIT_EE",
     "k_adjoint_plane<float, 0>": "_ZN5porta15k_adjoint_planeIfLi0EEEvNS_7AdjArgsIT_EE",
-    "k_adjoint_gather<float, 0>": "_ZN5porta16k_adjoint_gatherIfLi0EEEvNS_10GatherArgsIT_EE",
+    "k_adjoint_gather<float, 0>": "_ZN5porta16k_adjoint_gatherIfLi0ELi64EEEvNS_10GatherArgsIT_EE",
     "k_sweep_plane<float, 1>": "_ZN5porta13k_sweep_planeIfLi1EEEvNS_9PlaneArgsIT_EE",
     "k_sweep_plane_i<float>": "_ZN5porta15k_sweep_plane_iIfEEvNS_9PlaneArgsIT_EE",
-    "k_sweep_plane_faces<float>": "_ZN5porta19k_sweep_plane_facesIfEEvNS_9FacesArgsIT_EE",
+    "k_sweep_plane_faces<float>": "_ZN5porta19k_sweep_plane_facesIfLb0EEEvNS_9FacesArgsIT_EE",
     "k_faces_setup<float>": "_ZN5porta13k_faces_setupIfEEvNS_9FacesArgsIT_EE",
     "k_adjoint_plane<float, 1>": "_ZN5porta15k_adjoint_planeIfLi1EEEvNS_7AdjArgsIT_EE",
-    "k_adjoint_gather<float, 1>": "_ZN5porta16k_adjoint_gatherIfLi1EEEvNS_10GatherArgsIT_EE",
+    "k_adjoint_gather<float, 1>": "_ZN5porta16k_adjoint_gatherIfLi1ELi64EEEvNS_10GatherArgsIT_EE",
     "k_bez9_tgather<float>": "_ZN5porta14k_bez9_tgatherIfEEvNS_11TGatherArgsIT_EE",
 }
 
@@ -499,20 +503,25 @@ def main():
     adj_updates = per_ray_freq * (cfg.nrays // 2) * cfg.nfreq if adj else 0
     value = (fwd_updates + adj_updates) * args.steps / wall
 
-    # every plane launch of the sweep kernel in one step: its rays and algorithmic bytes
+    # every plane of the sweep in one step, by batch: its rays and algorithmic bytes.  At the
+    # default block size the bilinear Stokes sweep takes two planes in a launch; the figures
+    # are per plane.
     if inter:
         shapes = inter.launch_ray_counts()
     else:
         shapes = [min(nrb, nh - r) for r in range(0, nh, nrb)] * 2
+    pair = nst == 4 and not args.faces and interp == porta.BILINEAR and args.block == 0
     launches = (cfg.nz - 1) * len(shapes)
-    lbytes = (cfg.nz - 1) * sum(sweep_launch_bytes(cfg, n, elem, nst)[0]
-                                for n in shapes) / launches
+    kept = len(inter.ranges) if inter else 0   # batches of which every plane is kept
+    lbytes = (cfg.nz - 1) * sum(sweep_launch_bytes(cfg, n, elem, nst, pair, i < kept)[0]
+                                for i, n in enumerate(shapes)) / launches
     lupd = fwd_updates / launches
     launch_ms = sweep_ms / launches
     achieved = lbytes / (launch_ms * 1e-3) / 1e9
     tname = "float" if elem == 4 else "double"
     kname = (f"k_sweep_plane_i<{tname}>" if nst == 1 else
              f"k_sweep_plane_faces<{tname}>" if args.faces else
+             f"k_sweep_pair<{tname}>" if pair else
              f"k_sweep_plane<{tname}, {1 if interp == porta.BEZIER2D else 0}>")
     workload = counter_workload(cfg, args.prec, schedule, nrb,
                                 inter.range_rays if inter else 0)
@@ -623,10 +632,12 @@ def main():
         # algorithmic bytes and, where committed, its counters
         shapes64 = [min(nrb, nh - r) for r in range(0, nh, nrb)] * 2
         n64 = (cfg.nz - 1) * len(shapes64)
-        b64 = (cfg.nz - 1) * sum(sweep_launch_bytes(cfg, n, 8, nst)[0] for n in shapes64) / n64
+        b64 = (cfg.nz - 1) * sum(sweep_launch_bytes(cfg, n, 8, nst, pair)[0]
+                                 for n in shapes64) / n64
         a64 = b64 / (ms64 / n64 * 1e-3) / 1e9
         k64name = ("k_sweep_plane_i<double>" if nst == 1 else
                    "k_sweep_plane_faces<double>" if args.faces else
+                   "k_sweep_pair<double>" if pair else
                    f"k_sweep_plane<double, {1 if interp == porta.BEZIER2D else 0}>")
         c64 = (measured_counters(k64name, counter_workload(cfg, "f64", "shared", nrb, 0))
                if args.block in (0, 256) and args.xcd_remap == -1 and args.faces_chunk == 0
