@@ -968,11 +968,17 @@ int forward_plane(const porta_grid* g, const porta_quad* q, const porta_fields* 
 // Nodes per block of the gather: 64, whole wavefronts of neighbouring nodes, or 16 and four
 // times the ray groups where a plane has too few nodes.  A plane takes, with 64 and 16 nodes, in
 // the bilinear mode 22.0 and 29.3 us at 64x64 nodes, 9.5 and 10.2 us at 37x30, and in the
-// 9-point mode, where a ray costs far more, 37.5 and 23.7 us at 24x24.
+// 9-point mode, where a ray costs far more, 37.5 and 23.7 us at 24x24.  Bilinear planes of
+// one node per thread from 24576 nodes: 16 rays in FP32 take 24 and 39 us at 192x176 with and
+// without, 21 and 20 at 128x128.
 template <class T>
 void launch_gather(const GatherArgs<T>& b, bool bez, hipStream_t st) {
-  const bool wide = b.np >= kCus * (bez ? 16 : 4);
   const dim3 blk(256);
+  if (!bez && b.nchunk == 1 && b.np >= kCus * 96) {
+    hipLaunchKernelGGL(k_adjoint_gather_wide<T>, dim3((b.np + 255) / 256, 4), blk, 0, st, b);
+    return;
+  }
+  const bool wide = b.np >= kCus * (bez ? 16 : 4);
   const unsigned n = (unsigned)((b.np + (wide ? 63 : 15)) / (wide ? 64 : 16));
   if (bez && wide)
     hipLaunchKernelGGL((k_adjoint_gather<T, 1, 64>), dim3(n, kGatherParts), blk, 0, st, b);

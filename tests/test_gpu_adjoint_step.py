@@ -1,8 +1,8 @@
 """Adjoint launches of small planes, cut into frequency chunks, and their gather with rays
 split into groups: the gradient against the oracle's reverse mode, every component, at the
 edges of the cut (one frequency; a chunk count that does not divide the frequencies; planes of
-less than a wavefront, of ragged blocks, and large enough for the gather's wide blocks; ray
-batches whose last is smaller).  Bars as for the whole adjoint (test_gpu_adjoint_oracle)."""
+less than a wavefront, of ragged blocks, and large enough for the gather's wide blocks and for
+one thread per node; ray batches whose last is smaller).  Bars as for the whole adjoint (test_gpu_adjoint_oracle)."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ from test_gpu_adjoint_oracle import _compare, _gpu_grad, _oracle_grad, _problem
 pytestmark = pytest.mark.gpu
 
 SIZES = [(5, 3, 7, 2, 4, 1), (13, 5, 2, 1, 4, 22), (16, 16, 6, 3, 8, 23), (33, 20, 5, 2, 3, 5),
-         (96, 86, 3, 1, 4, 2)]
+         (96, 86, 3, 1, 4, 2), (181, 140, 3, 1, 4, 2)]
 MODES = [(porta.F64, porta.BILINEAR), (porta.F32, porta.BILINEAR), (porta.F64, porta.BEZIER2D)]
 
 
