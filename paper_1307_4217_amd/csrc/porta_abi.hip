@@ -840,7 +840,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
         h.iprev = prev[m];
         h.inext = kept(m, k, r0[m]);
         if (!h.inext) h.inext = state[step & 1] + soff[m];
-        // plane k writes partial sums into slot step & 1 while the first blocks add
+        // plane k writes partial sums into slot step & 1 while the last blocks add
         // those of plane k - s (or the boundary plane) to J
         h.jpart = jkq ? jbase + (step & 1) * jslot + joff[m] : nullptr;
         h.jpart_prev = (jkq && step > 1) ? jbase + ((step - 1) & 1) * jslot + joff[m] : nullptr;
