@@ -579,7 +579,7 @@ k_sweep_plane_faces(const FacesArgs<T> a) {
           kprime_apply<1, true>(node.eO, node.rO, IMt, KOI);
 #pragma unroll
           for (int s = 0; s < 4; ++s) rhs[s] = fma_t(-cf.psiO, KOI[s], dv[s]);
-          stokes_solve<1, true>(KO, F, rhs, x);
+          stokes_solve<1>(KO, F, rhs, x, true);
 #pragma unroll
           for (int s = 0; s < 4; ++s) res[s] = IM[s] + (D)x[s];
         } else {

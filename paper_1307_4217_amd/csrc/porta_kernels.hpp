@@ -842,14 +842,14 @@ k_sweep_plane(const PlaneArgs<T> a) {
   double jacc0 = 0.0, jacc1 = 0.0, jacc2 = 0.0, jacc3 = 0.0, lacc = 0.0;
 
   // one update (Eq. fsbez solved with Eq. kappa) at frequency f0 + f from the upwind
-  // Stokes vector IM
-  auto update = [&](int f, T i0, T i1, T i2, T i3) __attribute__((always_inline)) {
+  // Stokes vector IM; odd: of an interior plane's bilinear loop, f is (stokes_solve)
+  auto update = [&](int f, T i0, T i1, T i2, T i3, bool odd) __attribute__((always_inline)) {
     const T IM[4] = {i0, i1, i2, i3};
     const Coefs<T> cf = coefficients(tau0 * s_phi[f]);
     T KI[4], b[4], x[4];
     kprime_apply(eMv, rMv, IM, KI);
     step_rhs(cf, IM, KI, src, b);
-    stokes_solve<1>(KO, step_freq(KO, cf.psiO), b, x);
+    stokes_solve<1>(KO, step_freq(KO, cf.psiO), b, x, odd);
     store4_nt(op + (size_t)f * fstride, x);
     const double W = s_wn[f];
     jacc0 = fma_t(W, (double)x[0], jacc0);
@@ -863,12 +863,12 @@ k_sweep_plane(const PlaneArgs<T> a) {
 
   if (!ip) {
     // the upwind plane is the boundary
-    for (int f = 0; f < nf; ++f) update(f, h.ibound, T(0), T(0), T(0));
+    for (int f = 0; f < nf; ++f) update(f, h.ibound, T(0), T(0), T(0), false);
   } else if (MODE == 1) {
     for (int f = 0; f < nf; ++f) {
       T IM[4];
       upwind_bez9(ip + (size_t)f * fstride, sM9, bwx, bwy, IM);
-      update(f, IM[0], IM[1], IM[2], IM[3]);
+      update(f, IM[0], IM[1], IM[2], IM[3], false);
     }
   } else {
     if constexpr (sizeof(T) == 4) {
@@ -882,19 +882,19 @@ k_sweep_plane(const PlaneArgs<T> a) {
       for (; f + 1 < nf; f += 2) {
         load_upwind(ip + (size_t)(f + 1) * fstride, sM, vB);
         update(f, PORTA_BILIN(vA, 0), PORTA_BILIN(vA, 1), PORTA_BILIN(vA, 2),
-               PORTA_BILIN(vA, 3));
+               PORTA_BILIN(vA, 3), false);
         load_upwind(ip + (size_t)min(f + 2, nf - 1) * fstride, sM, vA);
         update(f + 1, PORTA_BILIN(vB, 0), PORTA_BILIN(vB, 1), PORTA_BILIN(vB, 2),
-               PORTA_BILIN(vB, 3));
+               PORTA_BILIN(vB, 3), true);
       }
       if (f < nf)
         update(f, PORTA_BILIN(vA, 0), PORTA_BILIN(vA, 1), PORTA_BILIN(vA, 2),
-               PORTA_BILIN(vA, 3));
+               PORTA_BILIN(vA, 3), false);
     } else {
       T v[4][4];
       for (int f = 0; f < nf; ++f) {
         load_upwind(ip + (size_t)f * fstride, sM, v);
-        update(f, PORTA_BILIN(v, 0), PORTA_BILIN(v, 1), PORTA_BILIN(v, 2), PORTA_BILIN(v, 3));
+        update(f, PORTA_BILIN(v, 0), PORTA_BILIN(v, 1), PORTA_BILIN(v, 2), PORTA_BILIN(v, 3), false);
       }
     }
   }

@@ -441,17 +441,23 @@ __host__ __device__ inline StokesFreq<T> stokes_freq(const StokesOp<T>& k, T p) 
   return F;
 }
 
-// x = (1 + p K')^-1 b (SGN = 1) or (1 + p K')^-T b (SGN = -1).
-template <int SGN, bool FACES = false, class T>
+// x = (1 + p K')^-1 b (SGN = 1) or (1 + p K')^-T b (SGN = -1).  r0_first: the order in which
+// c.r is rounded.  It moves few results by their last bit, and is kept frequency by frequency as
+// it has been, for iterations that round their emissivities to FP32.
+template <int SGN, class T>
 __host__ __device__ inline void stokes_solve(const StokesOp<T>& k, const StokesFreq<T>& F,
-                                             const T b[4], T x[4]) {
+                                             const T b[4], T x[4], bool r0_first = false) {
   const T q = SGN > 0 ? F.p : -F.p;
   const T pb0 = F.p * b[0];
   const T c[3] = {fma_t(-pb0, k.e[0], b[1]), fma_t(-pb0, k.e[1], b[2]), fma_t(-pb0, k.e[2], b[3])};
   const T cx[3] = {fma_t(c[1], k.r[2], -(c[2] * k.r[1])), fma_t(c[2], k.r[0], -(c[0] * k.r[2])),
                    fma_t(c[0], k.r[1], -(c[1] * k.r[0]))};
-  const T p2cr = F.p2 * (FACES ? dot3(c[0], k.r[0], c[1], k.r[1], c[2], k.r[2])
-                               : dot3(c[1], k.r[1], c[0], k.r[0], c[2], k.r[2]));
+  T cr;
+  if (r0_first)
+    cr = dot3(c[0], k.r[0], c[1], k.r[1], c[2], k.r[2]);
+  else
+    cr = dot3(c[1], k.r[1], c[0], k.r[0], c[2], k.r[2]);
+  const T p2cr = F.p2 * cr;
   const T s = F.p * F.inv_den;
   T u[3], v[3];
 #pragma unroll
@@ -544,9 +550,9 @@ __host__ __device__ inline LorentzFreq<T> lorentz_freq(const LorentzOp<T>& k, T 
 }
 
 // x = (1 + p K')^-1 b (SGN = 1) or (1 + p K')^-T b (SGN = -1).
-template <int SGN, bool FACES = false, class T>
+template <int SGN, class T>
 __host__ __device__ inline void stokes_solve(const LorentzOp<T>& k, const LorentzFreq<T>& F,
-                                             const T b[4], T x[4]) {
+                                             const T b[4], T x[4], bool = false) {
   // y = (alpha + beta B) b; X -> -X in the transpose
   const T xb = dot3(k.X[0], b[1], k.X[1], b[2], k.X[2], b[3]);
   const T B0 = SGN > 0 ? fma_t(k.ee, b[0], -xb) : fma_t(k.ee, b[0], xb);

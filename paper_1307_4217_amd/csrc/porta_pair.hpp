@@ -229,7 +229,7 @@ k_sweep_pair(const PairArgs<T> A) {
       T KI[4], b[4], x[4];
       kprime_apply(eMv, rMv, IM, KI);
       step_rhs(cf, IM, KI, src, b);
-      stokes_solve<1>(KO, step_freq(KO, cf.psiO), b, x);
+      stokes_solve<1>(KO, step_freq(KO, cf.psiO), b, x, (f & 1) && (grp || h.iprev));
       if (!grp) lds.mid[f & 1].put(cy * kMidX + cx, x);
       if (stores) store4_nt(out + (size_t)f * fstride, x);
       const double W = s_wn[f];
