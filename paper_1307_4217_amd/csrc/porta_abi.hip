@@ -249,7 +249,7 @@ bool pair_of(const porta_options* o) {
 // 7.6, 10.5 and 10.4 ms; 256x256x17, 41 frequencies 43.1 and 53.9; shared, 64x64x49, 5, 31, 101
 // frequencies 2.8 and 2.6, 7.0 and 8.1, 18.8 and 24.2; 37x30x45, 80 rays, 31 frequencies
 // (9 tiles for 1110 nodes) 5.4 and 5.0.  FP32 256x256, 40 rays, 9 and 41 frequencies, 33 and 17
-// planes 19.5 and 16.2, 21.6 and 22.5; 256x256x128, 101 frequencies 724 and 845.
+// planes 19.5 and 16.2, 21.6 and 22.5; 256x256x128, 101 frequencies 738 and 845.
 bool pair_faster(const porta_grid* g, int prec, int64_t tiles, int64_t rows, int nfreq, int n) {
   const bool f64 = prec == PORTA_F64;
   // the tables of the frequencies and the tiles within 64 KiB of LDS
