@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 VALU_PEAK_TLANE = 256 * 4 * 16 * 2.4e9 / 1e12   # unpacked FP32 VALU, lane instructions/s
 # kernels whose rocprofv3 VALU-busy figure shows them bound by the vector ALU rather than
-# by HBM (the 9-point Bezier sweep, 78% busy at 3.2 TB/s; two planes per launch, 83% busy
+# by HBM (the 9-point Bezier sweep, 78% busy at 3.2 TB/s; two planes per launch, 85% busy
 # at 4.0 TB/s, counted per plane); the others are reported against HBM
 ALU_BOUND_KERNELS = ("k_sweep_plane<float, 1>", "k_sweep_pair<float>")
 PROFILES = os.path.join(ROOT, "profiles")
