@@ -100,7 +100,7 @@ void hm_stokes_solve_scaled_f32(const float* e3, const float* r3, float p, const
     porta::stokes_solve<-1>(k, F, b4, x4);
 }
 
-// The same by the FP64 sweep's and the adjoint's route.
+// The same by the route of FP64.
 void hm_lorentz_solve_f64(const double* e3, const double* r3, double p, const double* b4, int sgn,
                           double* x4) {
   const porta::LorentzOp<double> k = porta::lorentz_op(e3, r3);

@@ -300,7 +300,7 @@ k_adjoint_plane(const AdjArgs<T> a) {
   T eMv[3], rMv[3], eOv[3], rOv[3];
   kprime_entries(ps.etaM, ps.ikM, eMv, rMv);
   kprime_entries(ps.etaO, ps.ikO, eOv, rOv);
-  const LorentzOp<T> KO = lorentz_op(eOv, rOv);
+  const auto KO = step_op(eOv, rOv);
   StepSource<T> src[3];
 #pragma unroll
   for (int s = 0; s < 3; ++s) step_source(ps.SM[s], ps.SO[s], ps.cM[s], src[s]);
@@ -374,7 +374,7 @@ k_adjoint_plane(const AdjArgs<T> a) {
       T KIM[4], b[4], IO[4];
       kprime_apply(eMv, rMv, IM, KIM);
       step_rhs(cf, IM, KIM, src, b);
-      const LorentzFreq<T> F = lorentz_freq(KO, cf.psiO);
+      const auto F = step_freq(KO, cf.psiO);
       stokes_solve<1>(KO, F, b, IO);
       // lambda_b = (1 + psi'_O K'_O)^-T lambda
       T lb[4];

@@ -489,22 +489,28 @@ __host__ __device__ inline void kprime_apply(const T e[3], const T r[3], const T
   y[2] = dot3(-r2, x[1], e[1], x[0], r0, x[3]);
 }
 
-// The same family by another route, for FP64 and for the adjoint.  K' is a generator of the Lorentz group, so
-// B = K'^2 satisfies B^2 = a B + b with a = e.e - r.r, b = (e.r)^2, hence
-//   (1 + p K')^-1 = (1 - p K') (1 - p^2 B)^-1,
-//   (1 - q B)^-1 = alpha + beta B,   alpha = (1 - q a) / D,  beta = q / D,
-//   D = 1 - q a - q^2 b = det(1 + p K'),   q = p^2.
-// With X = e x r,
-//   B = [[e.e, -X^T], [X, e e^T + r r^T - (r.r) 1]],
-// whose entries are formed once (LorentzOp); a frequency needs one reciprocal (LorentzFreq)
-// instead of two, shared by the system and its transpose, and 10 operations less.  (The FP32
-// sweep stays with StokesOp: J, which it accumulates in FP64, would change by the FP32
-// rounding, 1e-9 of its value.)
+// The same family by another route, for FP64.  K' is a generator of the Lorentz group, so
+// B = K'^2 satisfies B^2 = a B + b with a = e.e - r.r, b = (e.r)^2, hence with q = p^2 and
+// D = 1 - q a - q^2 b = det(1 + p K')
+//   (1 + p K')^-1 = (1 - p K') (1 - q B)^-1 = (1 - p K') (1 - q a + q B) / D.
+// B and B K' are written out, with X = e x r and, from K'(e, r)^3 = a K'(e, r) + (e.r) K'(r, -e),
+// R = r - q (e.r) e:
+//   D x_0 = (1 + q r.r) b_0 - q X.b_v - p (e.b_v + q (e.r) (r.b_v))
+//   D x_v = (1 - q e.e) b_v + e (q e.b_v - p b_0) + r (q r.b_v - p q (e.r) b_0) + q b_0 X
+//           - p b_v x R.
+// Every term keeps its size relative to D however large the dispersion r is: 1 + q r.r and
+// 1 - q e.e come from the products and not from 1 - q a + q B, whose parts of size q r.r cancel
+// in the components perpendicular to r.  (Formed so, and with K' applied to its result, a
+// solve was off by 82 ulp of |x| on average at r = 100 and 770 at r = 1000; this form by 1.1,
+// StokesOp by 0.8, at any r.)  A frequency needs one reciprocal (LorentzFreq) instead of two,
+// shared by the system and its transpose: a Jacobi step on 128x128x96, 80 rays, 41 frequencies
+// takes 134.3 ms with it and 139.0 with StokesOp.  (FP32 stays with StokesOp in the sweep,
+// whose J, accumulated in FP64, would change by the FP32 rounding, 1e-9 of its value, and in
+// the adjoint, which forms the state of the sweep again and takes the same time either way.)
 template <class T>
 struct LorentzOp {
   T e[3], r[3], X[3];
-  T ee, D00, D11, D22, D01, D02, D12;   // B: time part and the symmetric space part
-  T a, b;
+  T ee, rr, er;
 };
 
 template <class T>
@@ -515,58 +521,56 @@ __host__ __device__ inline LorentzOp<T> lorentz_op(const T e[3], const T r[3]) {
     k.e[i] = e[i];
     k.r[i] = r[i];
   }
-  k.X[0] = e[1] * r[2] - e[2] * r[1];
-  k.X[1] = e[2] * r[0] - e[0] * r[2];
-  k.X[2] = e[0] * r[1] - e[1] * r[0];
-  const T er = e[0] * r[0] + e[1] * r[1] + e[2] * r[2];
-  const T rr = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-  k.ee = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
-  k.D00 = e[0] * e[0] - (r[1] * r[1] + r[2] * r[2]);
-  k.D11 = e[1] * e[1] - (r[0] * r[0] + r[2] * r[2]);
-  k.D22 = e[2] * e[2] - (r[0] * r[0] + r[1] * r[1]);
-  k.D01 = e[0] * e[1] + r[0] * r[1];
-  k.D02 = e[0] * e[2] + r[0] * r[2];
-  k.D12 = e[1] * e[2] + r[1] * r[2];
-  k.a = k.ee - rr;
-  k.b = er * er;
+  k.X[0] = fma_t(e[1], r[2], -(e[2] * r[1]));
+  k.X[1] = fma_t(e[2], r[0], -(e[0] * r[2]));
+  k.X[2] = fma_t(e[0], r[1], -(e[1] * r[0]));
+  k.er = dot3(e[0], r[0], e[1], r[1], e[2], r[2]);
+  k.rr = dot3(r[0], r[0], r[1], r[1], r[2], r[2]);
+  k.ee = dot3(e[0], e[0], e[1], e[1], e[2], e[2]);
   return k;
 }
 
+// The factors of a frequency, each divided by D: 1 + q r.r, 1 - q e.e, q, p, p q (e.r), p R.
 template <class T>
 struct LorentzFreq {
-  T p, alpha, beta;
+  T g0, gv, q, p, pqer, R[3];
 };
 
 template <class T>
 __host__ __device__ inline LorentzFreq<T> lorentz_freq(const LorentzOp<T>& k, T p) {
   LorentzFreq<T> F;
-  F.p = p;
-  const T q = p * p;
-  const T t = fma_t(-q, k.a, T(1));
-  const T iD = recip(fma_t(-(q * q), k.b, t));
-  F.alpha = t * iD;
-  F.beta = q * iD;
+  const T q = p * p, qer = q * k.er;
+  const T g0 = fma_t(q, k.rr, T(1));
+  const T iD = recip(fma_t(-qer, qer, fma_t(-q, k.ee, g0)));
+  F.g0 = g0 * iD;
+  F.gv = fma_t(-q, k.ee, T(1)) * iD;
+  F.q = q * iD;
+  F.p = p * iD;
+  F.pqer = F.p * qer;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) F.R[i] = fma_t(F.p, k.r[i], -(F.pqer * k.e[i]));
   return F;
 }
 
-// x = (1 + p K')^-1 b (SGN = 1) or (1 + p K')^-T b (SGN = -1).
+// x = (1 + p K')^-1 b (SGN = 1) or (1 + p K')^-T b (SGN = -1: r -> -r, which turns the signs of
+// X, R and e.r).
 template <int SGN, class T>
 __host__ __device__ inline void stokes_solve(const LorentzOp<T>& k, const LorentzFreq<T>& F,
                                              const T b[4], T x[4], bool = false) {
-  // y = (alpha + beta B) b; X -> -X in the transpose
-  const T xb = dot3(k.X[0], b[1], k.X[1], b[2], k.X[2], b[3]);
-  const T B0 = SGN > 0 ? fma_t(k.ee, b[0], -xb) : fma_t(k.ee, b[0], xb);
-  const T s0 = SGN > 0 ? b[0] : -b[0];
-  const T B1 = fma_t(k.X[0], s0, dot3(k.D00, b[1], k.D01, b[2], k.D02, b[3]));
-  const T B2 = fma_t(k.X[1], s0, dot3(k.D01, b[1], k.D11, b[2], k.D12, b[3]));
-  const T B3 = fma_t(k.X[2], s0, dot3(k.D02, b[1], k.D12, b[2], k.D22, b[3]));
-  const T y[4] = {fma_t(F.beta, B0, F.alpha * b[0]), fma_t(F.beta, B1, F.alpha * b[1]),
-                  fma_t(F.beta, B2, F.alpha * b[2]), fma_t(F.beta, B3, F.alpha * b[3])};
-  // x = y - p K' y
-  T z[4];
-  kprime_apply<SGN>(k.e, k.r, y, z);
+  const T eb = dot3(k.e[0], b[1], k.e[1], b[2], k.e[2], b[3]);
+  const T rb = dot3(k.r[0], b[1], k.r[1], b[2], k.r[2], b[3]);
+  const T Xb = dot3(k.X[0], b[1], k.X[1], b[2], k.X[2], b[3]);
+  const T qs = SGN > 0 ? F.q : -F.q, qb0 = qs * b[0];
+  const T ae = fma_t(F.q, eb, -(F.p * b[0])), ar = fma_t(F.q, rb, -(F.pqer * b[0]));
+  x[0] = fma_t(F.g0, b[0], -fma_t(qs, Xb, fma_t(F.p, eb, F.pqer * rb)));
+  const T R0 = SGN > 0 ? F.R[0] : -F.R[0], R1 = SGN > 0 ? F.R[1] : -F.R[1],
+          R2 = SGN > 0 ? F.R[2] : -F.R[2];
+  const T c[3] = {fma_t(b[3], R1, -(b[2] * R2)), fma_t(b[1], R2, -(b[3] * R0)),
+                  fma_t(b[2], R0, -(b[1] * R1))};   // - b_v x R
 #pragma unroll
-  for (int s = 0; s < 4; ++s) x[s] = fma_t(-F.p, z[s], y[s]);
+  for (int i = 0; i < 3; ++i)
+    x[1 + i] = fma_t(F.gv, b[1 + i],
+                     fma_t(k.e[i], ae, fma_t(k.r[i], ar, fma_t(k.X[i], qb0, c[i]))));
 }
 
 // The route of the sweep in each precision.

@@ -114,3 +114,48 @@ def test_lorentz_solve_matches_dense_solve(hm, prec):
             fn(e.ctypes.data_as(P), r.ctypes.data_as(P), pp, b.ctypes.data_as(P), sgn,
                x.ctypes.data_as(P))
             assert np.abs(x - want).max() <= 400 * ulp * np.abs(want).max()
+
+
+def _solve_longdouble(M, b):
+    """Gaussian elimination with row pivoting in extended precision."""
+    A = np.concatenate([M, b[:, None]], axis=1).astype(np.longdouble)
+    n = len(b)
+    for c in range(n):
+        k = c + int(np.argmax(np.abs(A[c:, c])))
+        A[[c, k]] = A[[k, c]]
+        for r in range(c + 1, n):
+            A[r] -= A[c] * (A[r, c] / A[c, c])
+    x = np.zeros(n, np.longdouble)
+    for r in range(n - 1, -1, -1):
+        x[r] = (A[r, n] - A[r, r + 1:n] @ x[r + 1:]) / A[r, r]
+    return x
+
+
+@pytest.mark.parametrize("disp", [0.5, 3.0, 10.0, 30.0, 100.0, 1000.0])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_lorentz_solve_under_strong_dispersion(hm, prec, disp):
+    """The same solve where the dispersion exceeds the absorption by up to 1000, with dichroism
+    up to 0.3.  No part of the solution exceeds about |b| there (the inverse damps what is
+    perpendicular to the dispersion), and each is a sum of at most 20 terms of that size with
+    some ten roundings each, so the error stays below 100 ulp of |b| at any dispersion; a form
+    that takes 1 + p^2 r.r apart again loses p^2 r.r ulp."""
+    rng = np.random.default_rng(17)
+    ty, ct = (np.float64, C.c_double) if prec == "f64" else (np.float32, C.c_float)
+    fn = getattr(hm, f"hm_lorentz_solve_{prec}")
+    P = C.POINTER(ct)
+    fn.argtypes = [P, P, ct, P, C.c_int, P]
+    ulp = 2.0**-53 if prec == "f64" else 2.0**-24
+    for trial in range(300):
+        e, r = rng.uniform(-0.3, 0.3, 3).astype(ty), rng.normal(size=3)
+        r = (disp * r / np.linalg.norm(r)).astype(ty)
+        b, pp = rng.normal(size=4).astype(ty), ty((0.9, 0.5, 0.1)[trial % 3])
+        eL, rL = e.astype(np.longdouble), r.astype(np.longdouble)
+        K = np.array([[0, eL[0], eL[1], eL[2]], [eL[0], 0, rL[2], -rL[1]],
+                      [eL[1], -rL[2], 0, rL[0]], [eL[2], rL[1], -rL[0], 0]], dtype=np.longdouble)
+        A = np.eye(4, dtype=np.longdouble) + np.longdouble(pp) * K
+        for sgn, M in ((1, A), (-1, A.T)):
+            want = _solve_longdouble(M, b.astype(np.longdouble))
+            x = np.zeros(4, ty)
+            fn(e.ctypes.data_as(P), r.ctypes.data_as(P), pp, b.ctypes.data_as(P), sgn,
+               x.ctypes.data_as(P))
+            assert np.abs(x - want).max() <= 100 * ulp * np.abs(b).max(), (disp, trial, sgn)
