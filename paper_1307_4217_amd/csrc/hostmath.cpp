@@ -32,18 +32,31 @@ void hm_coefficients_f64(double tau, double* out6) {
   if (tau > 0.1 && tau < 0.18) out6[5] = table1(tau, kC);
 }
 
-// e, psi'_M, psi'_O, omega_M, omega_O, omega_C and the source weights t E_1, t E_2, t E_3 as
-// the kernels form them
+// e, psi'_M, psi'_O, omega_M, omega_O, omega_C and t E_1, t E_2, t E_3 as the kernels
+// form them
 void hm_step_f32(float tau, float* o) {
   const porta::Coefs<float> c = porta::coefficients(tau);
-  const float v[9] = {c.e, c.psiM, c.psiO, c.omM, c.omO, c.omC, c.em1, c.psiO, c.t3};
+  const float v[9] = {c.e, c.psiM, c.psiO, c.omM, c.omO, c.omC, c.em1, c.psiO, c.omO / 2};
   for (int i = 0; i < 9; ++i) o[i] = v[i];
 }
 
 void hm_step_f64(double tau, double* o) {
   const porta::Coefs<double> c = porta::coefficients(tau);
-  const double v[9] = {c.e, c.psiM, c.psiO, c.omM, c.omO, c.omC, c.em1, c.psiO, c.t3};
+  const double v[9] = {c.e, c.psiM, c.psiO, c.omM, c.omO, c.omC, c.em1, c.psiO, c.omO / 2};
   for (int i = 0; i < 9; ++i) o[i] = v[i];
+}
+
+// The source terms of an update of optical depth tau.
+double hm_sources_f64(double tau, double SM, double SO, double cM) {
+  porta::StepSource<double> s;
+  porta::step_source(SM, SO, cM, s);
+  return porta::add_sources(porta::source_weights(porta::coefficients(tau)), s, 0.0);
+}
+
+float hm_sources_f32(float tau, float SM, float SO, float cM) {
+  porta::StepSource<float> s;
+  porta::step_source(SM, SO, cM, s);
+  return porta::add_sources(porta::source_weights(porta::coefficients(tau)), s, 0.0f);
 }
 
 double hm_besser_cm(double yM, double yO, double yP, double ratio) {
@@ -167,9 +180,9 @@ double hm_besser_cm_grad(double yM, double yO, double yP, double ratio, double* 
 
 double hm_coef_tau_grad_f64(double tau, const double* g6) {
   const porta::Coefs<double> c = porta::coefficients(tau);
-  // omega_M, omega_O, omega_C as sums of the source weights
-  return porta::coef_tau_grad(c, g6[0], g6[1], g6[2], g6[3], 2 * (g6[5] - g6[3]),
-                              2 * (g6[3] + g6[4] - 2 * g6[5]));
+  // adjoints of the omegas as those of the source weights
+  return porta::coef_tau_grad(c, g6[0], g6[1], g6[2], g6[4], 2 * (g6[5] - g6[4]),
+                              g6[3] + g6[4] - 2 * g6[5]);
 }
 
 float hm_coef_tau_grad_f32(float tau, const float* g6) {

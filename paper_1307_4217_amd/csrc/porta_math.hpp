@@ -70,7 +70,6 @@ struct Coefs {
                      // 3e-8 for thin steps, a bias that a chain of thousands of steps would
                      // add up
   T pmt, omt, oct;   // psi'_M / tau, omega_M / tau, omega_C / tau (for the tau-derivatives)
-  T t3;              // t E_3 = omega_O / 2
 };
 
 template <class T>
@@ -110,7 +109,6 @@ __host__ __device__ inline Coefs<T> coefficients(T tau) {
     c.oct = fma_t(T(2), E2, T(-4) * E3);
     c.psiO = tau * E2;
     c.psiM = tau * c.pmt;
-    c.t3 = tau * E3;
     c.omO = (T(2) * tau) * E3;
     c.omM = tau * c.omt;
     c.omC = tau * c.oct;
@@ -121,8 +119,10 @@ __host__ __device__ inline Coefs<T> coefficients(T tau) {
     const T g = c.e + tau - T(1);
     c.psiO = g * it;
     c.psiM = fma_t(-c.e, T(1) + tau, T(1)) * it;
-    c.omM = fma_t(-c.e, fma_t(tau, tau, T(2) * tau) + T(2), T(2)) * it2;
-    c.t3 = fma_t(-g, it2, T(0.5));
+    if constexpr (sizeof(T) == 8)
+      c.omM = fma_t(T(2) * it, c.psiM, -c.e);   // loses less, and costs less
+    else
+      c.omM = fma_t(-c.e, fma_t(tau, tau, T(2) * tau) + T(2), T(2)) * it2;
     c.omO = fma_t(T(-2) * g, it2, T(1));
     c.omC = T(2) * fma_t(c.e, tau + T(2), tau - T(2)) * it2;
     c.pmt = c.psiM * it;
@@ -134,9 +134,14 @@ __host__ __device__ inline Coefs<T> coefficients(T tau) {
 
 // The source terms of the update, omega_M S_M + omega_O S_O + omega_C c_M, as a sum of three
 // weights times three values of the node.  FP32 takes the omegas and S_M, S_O, c_M.  FP64
-// takes t E_1, t E_2, t E_3, which the coefficients form on the way, and
-//   A_1 = S_M,   A_2 = 2 (c_M - S_M),   A_3 = 2 (S_M + S_O - 2 c_M),
-// and needs no omega (5 operations less per update; their rounding is that of the sum).
+// takes 1 - e, psi'_M and omega_M, the moments of the source along the ray, and the source as
+// a polynomial in the distance from O,
+//   A_1 = S_O,   A_2 = 2 (c_M - S_O),   A_3 = S_M - 2 c_M + S_O,
+// and needs no omega_O and omega_C.  Each weight decays with the thickness as the omega of the
+// value that it brings in, so that the parts of a value add up to at most 7 times its share,
+// in thin steps, and to its share in thick ones.  (About M, with t E_1, t E_2 and t E_3, the
+// parts of S_M cancel in thick steps, off by 2e-10 where S_M is 10^6 S_O; the omegas themselves
+// cost 8% of a Jacobi step on 128x128x96, 145.2 ms against 135.1.)
 template <class T>
 struct StepSource {
   T a, b, c;
@@ -147,14 +152,14 @@ __host__ __device__ inline void step_source(double SM, double SO, double cM, Ste
 }
 __host__ __device__ inline void step_source(double SM, double SO, double cM,
                                             StepSource<double>& s) {
-  s = {SM, 2.0 * (cM - SM), 2.0 * ((SM - cM) + (SO - cM))};
+  s = {SO, 2.0 * (cM - SO), (SM - cM) + (SO - cM)};
 }
 
 __host__ __device__ inline StepSource<float> source_weights(const Coefs<float>& c) {
   return {c.omM, c.omO, c.omC};
 }
 __host__ __device__ inline StepSource<double> source_weights(const Coefs<double>& c) {
-  return {c.em1, c.psiO, c.t3};
+  return {c.em1, c.psiM, c.omM};
 }
 
 // v + sources
@@ -168,7 +173,7 @@ __host__ __device__ inline float lambda_star(const Coefs<float>& c, float lf) {
   return fma_t(lf, c.omC, c.omO);
 }
 __host__ __device__ inline double lambda_star(const Coefs<double>& c, double lf) {
-  return 2.0 * fma_t(lf, fma_t(-2.0, c.t3, c.psiO), c.t3);
+  return fma_t(2.0 * (lf - 1.0), c.psiM - c.omM, c.em1 - c.omM);
 }
 
 // ---------------------------------------------------------------------------
@@ -347,8 +352,7 @@ __host__ __device__ inline double parabolic_cm_grad(double yM, double yO, double
 // oct = omega_C/t, formed with the coefficients):
 //   de/dt = -e,                 dpsi'_M/dt = e - pmt,   dpsi'_O/dt = pmt,
 //   domega_M/dt = e - 2 omt,    domega_C/dt = 2 (pmt - oct),
-//   domega_O/dt = 2 (omt + oct - pmt)   (from omega_M+omega_O+omega_C = 1-e),
-//   d(t E_1)/dt = e,            d(t E_2)/dt = pmt,      d(t E_3)/dt = oct / 2.
+//   domega_O/dt = 2 (omt + oct - pmt)   (from omega_M+omega_O+omega_C = 1-e).
 __host__ __device__ inline float coef_tau_grad(const Coefs<float>& c, float gE, float gPM,
                                                float gPO, float gOM, float gOO, float gOC) {
   return -c.e * gE + (c.e - c.pmt) * gPM + c.pmt * gPO + (c.e - 2.0f * c.omt) * gOM +
@@ -356,7 +360,7 @@ __host__ __device__ inline float coef_tau_grad(const Coefs<float>& c, float gE, 
 }
 __host__ __device__ inline double coef_tau_grad(const Coefs<double>& c, double gE, double gPM,
                                                 double gPO, double g1, double g2, double g3) {
-  return dot3(c.e, g1 + gPM - gE, c.pmt, gPO - gPM + g2, 0.5 * c.oct, g3);
+  return fma_t(c.e - 2.0 * c.omt, g3, dot3(c.e, g1 - gE, c.e - c.pmt, gPM + g2, c.pmt, gPO));
 }
 
 // ---------------------------------------------------------------------------
@@ -504,7 +508,7 @@ __host__ __device__ inline void kprime_apply(const T e[3], const T r[3], const T
 // solve was off by 82 ulp of |x| on average at r = 100 and 770 at r = 1000; this form by 1.1,
 // StokesOp by 0.8, at any r.)  A frequency needs one reciprocal (LorentzFreq) instead of two,
 // shared by the system and its transpose: a Jacobi step on 128x128x96, 80 rays, 41 frequencies
-// takes 134.3 ms with it and 139.0 with StokesOp.  (FP32 stays with StokesOp in the sweep,
+// takes 4.7 ms less with it than with StokesOp (134.3 and 139.0).  (FP32 stays with StokesOp in the sweep,
 // whose J, accumulated in FP64, would change by the FP32 rounding, 1e-9 of its value, and in
 // the adjoint, which forms the state of the sweep again and takes the same time either way.)
 template <class T>

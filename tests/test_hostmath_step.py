@@ -159,3 +159,22 @@ def test_lorentz_solve_under_strong_dispersion(hm, prec, disp):
             fn(e.ctypes.data_as(P), r.ctypes.data_as(P), pp, b.ctypes.data_as(P), sgn,
                x.ctypes.data_as(P))
             assert np.abs(x - want).max() <= 100 * ulp * np.abs(b).max(), (disp, trial, sgn)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_sources_of_steep_and_thick_steps(hm, prec):
+    """omega_M S_M + omega_O S_O + omega_C c_M as the kernels form it, where S_M and S_O differ
+    by up to 10^8 and the step is up to 10^6 thick: three positive terms, each of a coefficient
+    within 40 ulp and one more rounding, added with two: 44 ulp of their sum."""
+    fn = getattr(hm, f"hm_sources_{prec}")
+    ty, ct = (np.float64, C.c_double) if prec == "f64" else (np.float32, C.c_float)
+    fn.argtypes, fn.restype = [ct] * 4, ct
+    ulp = 2.0**-53 if prec == "f64" else 2.0**-24
+    for tau in np.concatenate([TAUS[TAUS > 1e-6], [1e3, 1e4, 1e5, 1e6]]).astype(ty):
+        w = _exact(tau)[3:6]
+        for steep in (1.0, 1e2, 1e4, 1e6, 1e8):
+            for SM, SO in ((steep, 0.7), (0.7, steep)):
+                for part in (0.0, 0.3, 1.0):   # the control point between the two
+                    S = np.array([SM, SO, SM + part * (SO - SM)]).astype(ty)
+                    want = sum(c * np.longdouble(v) for c, v in zip(w, S))
+                    assert abs(np.longdouble(fn(tau, *S)) - want) <= 44 * ulp * want, (tau, S)
