@@ -768,9 +768,13 @@ void set_plane(HemiArgs<T>& h, const porta_grid* g, int k, int s) {
   h.kP = last ? -1 : k + s;
 }
 
+// In FP32 chunks of an even number of frequencies: there the solve rounds c.r by the parity of
+// a frequency's place in its chunk (stokes_solve), which is then that of the frequency, and
+// the planes that the adjoint sweeps again are those of the sweep bit for bit.
 template <class T>
 void set_chunks(PlaneArgs<T>& a, int nchunk, int rays) {
   a.fchunk = (a.nfreq + nchunk - 1) / nchunk;
+  if (sizeof(T) == 4 && nchunk > 1) a.fchunk += a.fchunk & 1;
   a.nchunk = (a.nfreq + a.fchunk - 1) / a.fchunk;
   a.nstep = a.ntile * rays * a.nchunk;
 }

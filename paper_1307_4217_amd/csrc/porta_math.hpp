@@ -35,7 +35,8 @@ __host__ __device__ inline double recip(double x) { return 1.0 / x; }
 
 // Sums of products in the frequency loops are written as fused multiply-adds, one by one:
 // left to the compiler, the product that is rounded on its own could differ between the
-// copies of a loop body, and a result with the place of its frequency in the loop.
+// copies of a loop body, and a result with the place of its frequency in the loop.  (Where it
+// does depend on the frequency's parity, r0_first of stokes_solve, that is written out.)
 __host__ __device__ inline float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __host__ __device__ inline double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 // a0 b0 + a1 b1 + a2 b2, the first product rounded
@@ -446,8 +447,9 @@ __host__ __device__ inline StokesFreq<T> stokes_freq(const StokesOp<T>& k, T p) 
 }
 
 // x = (1 + p K')^-1 b (SGN = 1) or (1 + p K')^-T b (SGN = -1).  r0_first: the order in which
-// c.r is rounded.  It moves few results by their last bit, and is kept frequency by frequency as
-// it has been, for iterations that round their emissivities to FP32.
+// c.r is rounded, which moves few results by their last bit.  The bilinear FP32 sweep takes it
+// at odd frequencies, but not next to the boundary plane, whatever kernel and cut a plane falls
+// to, so that iterations that round their emissivities to FP32 go on as they have.
 template <int SGN, class T>
 __host__ __device__ inline void stokes_solve(const StokesOp<T>& k, const StokesFreq<T>& F,
                                              const T b[4], T x[4], bool r0_first = false) {
