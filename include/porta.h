@@ -59,7 +59,7 @@ typedef enum {
   PORTA_OK = 0,
   PORTA_EINVAL = -1,       /* invalid argument (shape, pointer, range) */
   PORTA_EUNSUPPORTED = -2, /* valid but not implemented combination */
-  PORTA_ENOMEM = -3,       /* workspace smaller than porta_workspace_size() */
+  PORTA_ENOMEM = -3,       /* workspace too small: porta_workspace_size() bytes are enough */
   PORTA_EDEVICE = -4,      /* a HIP call failed */
   PORTA_ENONFINITE = -5    /* opts->check_inputs: a transfer coefficient is not finite,
                               or eta_I <= 0 somewhere */
@@ -172,8 +172,9 @@ typedef struct {
 
 typedef enum { PORTA_CONTROL_BESSER = 0, PORTA_CONTROL_PARABOLIC = 1 } porta_control;
 
-/* Bytes of device workspace needed by one call of the given kind (0 on invalid
- * arguments).  `prec` selects the sweep precision; `checkpoint_stride` is
+/* Bytes of device workspace that serve one call of the given kind (0 on invalid
+ * arguments), and every call that differs from it in having fewer rays: a part of the ray range,
+ * a smaller ray_batch.  `prec` selects the sweep precision; `checkpoint_stride` is
  * used by the two adjoint kinds only. */
 size_t porta_workspace_size(const porta_grid* grid, const porta_quad* quad, int prec,
                             int kind, int checkpoint_stride, const porta_options* opts);

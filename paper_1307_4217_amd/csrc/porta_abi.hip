@@ -164,16 +164,17 @@ void hemi_range(const porta_quad* q, const porta_options* o, int hemi, int& lo, 
   if (hi < lo) hi = lo;
 }
 
+int hemi_count(const porta_quad* q, const porta_options* o, int hemi) {
+  int lo, hi;
+  hemi_range(q, o, hemi, lo, hi);
+  return hi - lo;
+}
+
 // Rays swept together: the options' batch, at most the call's rays in one hemisphere.
 int ray_batch(const porta_quad* q, const porta_options* o) {
   const int nh = q->nmu * q->nchi;
-  int rb = (o && o->ray_batch > 0) ? o->ray_batch : nh, cap = 1;
-  for (int hemi = 0; hemi < 2; ++hemi) {
-    int lo, hi;
-    hemi_range(q, o, hemi, lo, hi);
-    cap = std::max(cap, hi - lo);
-  }
-  return std::min(rb, cap);
+  const int rb = (o && o->ray_batch > 0) ? o->ray_batch : nh;
+  return std::min(rb, std::max({1, hemi_count(q, o, 0), hemi_count(q, o, 1)}));
 }
 
 // ---------------------------------------------------------------------------
@@ -207,6 +208,8 @@ int freq_chunks(int64_t blocks, int nfreq) {
   int best = 1;
   int64_t cost = 0;
   for (int n = 1; n <= std::min<int64_t>(nfreq, kMaxChunks); ++n) {
+    // no n from here on costs less than its share of the chip, without the rounding up
+    if (n > 1 && (kSetup * n + nfreq) * blocks >= cost * kCus) break;
     const int64_t per = (nfreq + n - 1) / n;
     if (n > 1 && per == (nfreq + n - 2) / (n - 1)) continue;   // no shorter chunk than n - 1
     const int64_t c = (kSetup + per) * ((blocks * n + kCus - 1) / kCus);
@@ -221,7 +224,8 @@ int freq_chunks(int64_t blocks, int nfreq) {
 // The cut of a sweep: whether the two hemispheres' batches share launches, and the
 // frequency chunks.  Sharing halves the number of dependent launches and fills each of
 // them; it takes the plane states of both batches, so it is for launches that leave
-// room on the chip (at most kShareBlocks blocks, about 8 per CU, from one hemisphere).
+// room on the chip (at most kShareBlocks blocks, about 8 per CU, from one hemisphere) and whose
+// states do not fill the memory (kShareBytes, 1/36 of it, for both).
 struct SweepPlan {
   int nrb;         // rays of a batch in one hemisphere
   bool share;      // an upward and a downward batch per launch
@@ -229,10 +233,11 @@ struct SweepPlan {
   bool chunks;     // frequency chunks (FP64: their partial sums change the order of the sums
                    // over frequencies that make J, which in an FP32 iteration would tip
                    // the rounding of the next emissivities)
-  int rows;        // rays whose states the workspace holds: nrb, or 2 nrb with share
+  int rows;        // rays whose states the workspace holds: nrb, or those of both batches
   size_t jrows;    // (ray, chunk) rows of partial sums the workspace holds
 };
 constexpr int64_t kShareBlocks = 2048;
+constexpr size_t kShareBytes = size_t(8) << 30;
 
 // Sweeps whose planes can go in pairs: bilinear Stokes-vector plane hops at the default block
 // size (the 9-point mode, known only at the call, goes plane by plane).
@@ -265,21 +270,41 @@ bool pair_faster(const porta_grid* g, int prec, int64_t tiles, int64_t rows, int
   return pair < plane;
 }
 
-SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
+// Rays of a batch in one hemisphere.
+int sweep_batch(const porta_grid* g, const porta_quad* q, const porta_options* o) {
+  // a launch is one row of at most 2^31 threads
+  const int64_t most = std::max<int64_t>(1, (1 << 23) / plane_tiles(g, o));
+  const int nrb = (int)std::min<int64_t>(ray_batch(q, o), most);
+  return faces_of(o) ? std::min(nrb, 6553) : nrb;   // 5 blocks per ray in a grid's z of 65535
+}
+
+// The largest batch whose launches both hemispheres share.
+int share_batch(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
+  const size_t state = (size_t)g->nx * g->ny * q->nfreq * nstokes(o) * elem(prec);
+  return (int)std::min<size_t>(kShareBlocks / plane_tiles(g, o), kShareBytes / (4 * state));
+}
+
+// The cut for launches of `rows` rays, `nrb` of them in a hemisphere.
+SweepPlan plan_rows(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
+                    int nrb, int rows) {
   SweepPlan P;
   const int64_t tiles = plane_tiles(g, o);
-  // a launch is one row of at most 2^31 threads
-  P.nrb = (int)std::min<int64_t>(ray_batch(q, o), std::max<int64_t>(1, (1 << 23) / tiles));
-  if (faces_of(o)) P.nrb = std::min(P.nrb, 6553);   // 5 blocks per ray in a grid's z of 65535
-  P.share = tiles * P.nrb <= kShareBlocks;
-  P.rows = P.share ? 2 * P.nrb : P.nrb;
+  P.nrb = nrb;
+  P.share = rows > nrb;
+  P.rows = rows;
   P.chunks = prec == PORTA_F64;
-  const int n = P.chunks ? freq_chunks(tiles * P.rows, q->nfreq) : 1;
-  P.jrows = (size_t)P.rows * n;
+  const int n = P.chunks ? freq_chunks(tiles * rows, q->nfreq) : 1;
+  P.jrows = (size_t)rows * n;
   // (a pair of launches of both hemispheres: kPairBoth)
-  P.pair = pair_of(o) && (!P.share || prec == PORTA_F64) &&
-           pair_faster(g, prec, tiles, P.rows, q->nfreq, n);
+  P.pair = pair_of(o) && (prec == PORTA_F64 || tiles * nrb > kShareBlocks) &&
+           pair_faster(g, prec, tiles, rows, q->nfreq, n);
   return P;
+}
+
+SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
+  const int nrb = sweep_batch(g, q, o), up = hemi_count(q, o, 0), down = hemi_count(q, o, 1);
+  const bool share = nrb <= share_batch(g, q, prec, o) && up > 0 && down > 0;
+  return plan_rows(g, q, prec, o, nrb, share ? std::min(nrb, up) + std::min(nrb, down) : nrb);
 }
 
 // The cut of the first-face march for a launch of `rays` rays (porta_faces.hpp): columns,
@@ -400,8 +425,7 @@ Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const po
   // double-buffered partial sums, of one plane or two
   off = align_up(off + (P.pair ? 4 : 2) * P.jrows * (nstokes(o) + 1) * np * sizeof(double));
   if (faces_of(o)) {
-    // per-chunk partial sums of the first-face kernel; a call's smaller launches may be cut
-    // finer, into at most one chunk per row of these
+    // per-chunk partial sums of the first-face kernel
     L.fshape = faces_shape(g, q, prec, o, P.rows);
     L.ck = off;
     off = align_up(off + (size_t)P.rows * L.fshape.nchunk * 5 * np * sizeof(double));
@@ -414,6 +438,18 @@ Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const po
   }
   L.total = off;
   return L;
+}
+
+// Bytes that serve a sweep with these options and any of fewer rays, a part of the range or a
+// smaller batch: those may be cut otherwise (both hemispheres in a launch, more chunks, two
+// planes) and take more than a larger one.
+size_t sweep_bytes(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
+  const int nrb = sweep_batch(g, q, o);
+  const int rows = std::max(nrb, 2 * std::min(nrb, share_batch(g, q, prec, o)));
+  size_t n = 0;
+  for (int r = 1; r <= rows; ++r)
+    n = std::max(n, sweep_layout(g, q, prec, o, plan_rows(g, q, prec, o, std::min(r, nrb), r)).total);
+  return n;
 }
 
 // Forward states of a batch of rays that the adjoint keeps without being asked (1/288 of
@@ -452,10 +488,9 @@ size_t scratch_need(const porta_grid* g, const porta_quad* q, int prec, const po
 // planes recomputed between two checkpoints, two planes of Lambda, the
 // per-(node, ray) partials of one plane and the FP64 gradient accumulator.
 Layout adjoint_layout(const porta_grid* g, const porta_quad* q, int prec, int stride,
-                      const porta_options* o, bool own_checkpoints) {
+                      const porta_options* o, bool own_checkpoints, size_t nrb) {
   Layout L = tables_layout(q, prec, g->nz);
   const size_t np = (size_t)g->nx * g->ny, N = np * g->nz;
-  const size_t nrb = (size_t)ray_batch(q, o);
   L.plane = nrb * q->nfreq * np * 4 * elem(prec);
   // planes of its own that are small enough are all kept, whatever the stride
   L.stride = own_checkpoints && L.plane * g->nz <= kKeepAllBytes ? 1 : stride;
@@ -483,6 +518,16 @@ Layout adjoint_layout(const porta_grid* g, const porta_quad* q, int prec, int st
   off = align_up(off + 13 * N * sizeof(double));
   L.total = off;
   return L;
+}
+
+// Bytes that serve an adjoint with these options and any of fewer rays: a smaller batch may keep
+// every plane or be cut into more chunks.
+size_t adjoint_bytes(const porta_grid* g, const porta_quad* q, int prec, int stride,
+                     const porta_options* o, bool own_checkpoints) {
+  size_t n = 0;
+  for (int r = ray_batch(q, o); r >= 1; --r)
+    n = std::max(n, adjoint_layout(g, q, prec, stride, o, own_checkpoints, r).total);
+  return n;
 }
 
 // Checkpoints hold the upward rays of the call's ray range:
@@ -1283,14 +1328,13 @@ size_t porta_workspace_size(const porta_grid* grid, const porta_quad* quad, int 
   switch (kind) {
     case PORTA_WS_SWEEP:
       if (validate_grid(grid) || validate_quad(quad)) return 0;
-      return sweep_layout(grid, quad, prec, opts, sweep_plan(grid, quad, prec, opts)).total;
+      return sweep_bytes(grid, quad, prec, opts);
     case PORTA_WS_ADJOINT:
     case PORTA_WS_ADJOINT_CKPT:
       if (validate_grid(grid) || validate_quad(quad) || checkpoint_stride < 1 ||
           checkpoint_stride > grid->nz - 1)
         return 0;
-      return adjoint_layout(grid, quad, prec, checkpoint_stride, opts, kind == PORTA_WS_ADJOINT)
-          .total;
+      return adjoint_bytes(grid, quad, prec, checkpoint_stride, opts, kind == PORTA_WS_ADJOINT);
     case PORTA_WS_JKQ:
       if (validate_quad(quad)) return 0;
       return tables_layout(quad, prec, 0).total;
@@ -1399,7 +1443,8 @@ int porta_fs_adjoint(const porta_grid* grid, const porta_quad* quad, const porta
                   ck_bytes, need);
   }
   if (!workspace) return fail(PORTA_EINVAL, "workspace is NULL");
-  const Layout L = adjoint_layout(grid, quad, prec, checkpoint_stride, opts, !checkpoints);
+  const Layout L = adjoint_layout(grid, quad, prec, checkpoint_stride, opts, !checkpoints,
+                                  (size_t)ray_batch(quad, opts));
   if (ws_bytes < L.total)
     return fail(PORTA_ENOMEM, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
                 L.total);

@@ -1,0 +1,78 @@
+"""Workspaces: a buffer of porta_workspace_size() bytes serves the call that it was asked for and
+every call with fewer rays, a part of the ray range or a smaller batch.  CPU only: sizes, and
+calls that end at the workspace check or, past it, for want of a device."""
+import ctypes as C
+import random
+
+import numpy as np
+import pytest
+
+from paper_1307_4217_amd import inputs, porta, schedule
+
+
+def _grid(nx, ny, nz, nmu, nchi, nfreq):
+    cfg = inputs.Config("ws", nx, ny, nz, nmu, nchi, nfreq, True)
+    q = inputs.make_quadrature(cfg)
+    return porta.HostGrid(nx, ny, nz, 2000.0, 2000.0, np.linspace(0.0, 2000.0, nz), q.mu, q.wmu,
+                          q.nchi, q.phi, q.wfreq)
+
+
+# the last one: the range of 24 rays shares launches, which that of 28 does not
+SIZES = [(37, 177, 82, 1, 8, 4), (16, 16, 32, 5, 8, 21), (64, 64, 49, 5, 8, 31),
+         (200, 3, 2, 3, 7, 1), (150, 130, 64, 5, 16, 101)]
+
+
+@pytest.mark.parametrize("kind", [porta.WS_SWEEP, porta.WS_ADJOINT, porta.WS_ADJOINT_CKPT])
+@pytest.mark.parametrize("prec", [porta.F64, porta.F32])
+@pytest.mark.parametrize("dims", SIZES)
+def test_fewer_rays_need_no_more(dims, prec, kind):
+    hg = _grid(*dims)
+    nh = hg.nray_up
+    rng = random.Random(str(dims))
+    stride = min(5, hg.nz - 1)
+
+    def size(**kw):
+        return porta.workspace_size(hg, prec, kind, stride, porta.options(**kw))
+
+    more = [{}] + ([{"stokes": 1}, {"faces": 1}, {"faces": 1, "faces_chunk": 1}]
+                   if kind == porta.WS_SWEEP else [])
+    for m in more:
+        last = 0
+        for n in range(1, nh + 1):   # batches
+            now = size(ray_batch=n, **m)
+            assert now >= last, (dims, m, n)
+            last = now
+        assert size(**m) == last
+        for _ in range(60):   # ranges of a range
+            a = rng.randrange(2 * nh)
+            b = rng.randrange(a, 2 * nh)
+            c = rng.randrange(a, b + 1)
+            d = rng.randrange(c, b + 1)
+            rb = rng.choice([0, rng.randint(1, nh)])
+            whole = size(ray_first=a, ray_count=b + 1 - a, ray_batch=rb, **m)
+            part = size(ray_first=c, ray_count=d + 1 - c, ray_batch=rb, **m)
+            assert part <= whole, (dims, m, (a, b), (c, d), rb)
+
+
+@pytest.mark.parametrize("dims,range_rays,ray_batch,prec", [
+    ((150, 130, 64, 5, 16, 101), 28, 40, porta.F32),
+    ((150, 130, 64, 5, 16, 101), 28, 40, porta.F64),
+    ((37, 177, 82, 1, 8, 4), 3, 4, porta.F32)])
+def test_interleaved_workspace_serves_every_range(dims, range_rays, ray_batch, prec):
+    hg = _grid(*dims)
+    s = schedule.InterleavedSweep(hg, prec, range_rays, ray_batch=ray_batch, device="meta")
+    for o in s.range_opts + [s.down_opts]:
+        assert porta.workspace_size(hg, prec, porta.WS_SWEEP, 1, o) <= s.workspace.numel()
+    for o in s.range_opts:
+        assert (porta.workspace_size(hg, prec, porta.WS_ADJOINT_CKPT, 1, o)
+                <= s.workspace.numel())
+
+
+def test_sharing_is_bounded():
+    """The states of both hemispheres at once, where they share launches: at most 8 GiB more than
+    those of a batch."""
+    hg = _grid(256, 256, 3, 1, 8, 4000)
+    state = 2 * 4000 * 65536 * 32
+    for n in (1, 2, 3, 8):
+        full = porta.workspace_size(hg, porta.F64, porta.WS_SWEEP, opts=porta.options(ray_batch=n))
+        assert full <= n * state + (9 << 30), n
