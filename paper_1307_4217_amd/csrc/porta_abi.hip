@@ -182,6 +182,9 @@ int ray_batch(const porta_quad* q, const porta_options* o) {
 // ---------------------------------------------------------------------------
 constexpr int kCus = 256;
 
+// A launch has fewer than 2^32 threads in each dimension.
+bool fits_launch(int64_t blocks, int threads) { return blocks <= 0xffffffffLL / threads; }
+
 // Nodes per block of the plane kernels: the options' choice, else 256, fewer on planes
 // that fit in fewer wavefronts.
 int plane_block(const porta_grid* g, const porta_options* o) {
@@ -296,7 +299,9 @@ SweepPlan plan_rows(const porta_grid* g, const porta_quad* q, int prec, const po
   const int n = P.chunks ? freq_chunks(tiles * rows, q->nfreq) : 1;
   P.jrows = (size_t)rows * n;
   // (a pair of launches of both hemispheres: kPairBoth)
+  const int64_t jb = (int64_t)jblocks(g->nx * g->ny) * (prec == PORTA_F64 ? 4 : 2);
   P.pair = pair_of(o) && (prec == PORTA_F64 || tiles * nrb > kShareBlocks) &&
+           fits_launch((int64_t)pair_tiles(g->nx, g->ny) * rows + jb, kPairThreads) &&
            pair_faster(g, prec, tiles, rows, q->nfreq, n);
   return P;
 }
@@ -628,12 +633,17 @@ template <class T>
 int launch_jreduce(double* jkq, const double* jpart, const RayConsts* rays, int ray0, int nrb,
                    int nchunk, int ns, int np, size_t N, size_t plane_off, double ibound,
                    hipStream_t st) {
-  const dim3 grid(jblocks(np)), blk(256);
   const JJob J = {jpart, rays + ray0, nrb, nchunk, ibound, plane_off};
-  if (ns == 1)
-    hipLaunchKernelGGL((k_jreduce<1, T>), grid, blk, jlds_bytes(256, sizeof(T)), st, J, jkq, np, N);
-  else
-    hipLaunchKernelGGL((k_jreduce<4, T>), grid, blk, jlds_bytes(256, sizeof(T)), st, J, jkq, np, N);
+  const dim3 blk(256);
+  const size_t lds = jlds_bytes(256, sizeof(T));
+  constexpr int most = int(0xffffffffLL / 256);   // fits_launch
+  for (int first = 0, all = jblocks(np); first < all; first += most) {
+    const dim3 grid(std::min(all - first, most));
+    if (ns == 1)
+      hipLaunchKernelGGL((k_jreduce<1, T>), grid, blk, lds, st, J, jkq, np, N, first);
+    else
+      hipLaunchKernelGGL((k_jreduce<4, T>), grid, blk, lds, st, J, jkq, np, N, first);
+  }
   return check_launch("jreduce");
 }
 
@@ -877,6 +887,18 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
     // states and partial sums of the downward rays follow those of the upward ones
     const size_t soff[2] = {0, (size_t)nr[0] * q->nfreq * np * ns};
     const size_t joff[2] = {0, (size_t)nr[0] * a.nchunk * (ns + 1) * np};
+    // the reduction of J rides on the plane steps (planes of 2^27 nodes: launches of its own,
+    // too many threads for one)
+    const bool fused = jkq && fits_launch((int64_t)a.nstep + 2 * jblocks(np), block);
+    a.njb = fused ? 2 * jblocks(np) : 0;
+    auto reduce = [&](int m, const double* part, int k) -> int {
+      if (nr[m] == 0) return PORTA_OK;
+      return launch_jreduce<T>(jkq, part, rays, m * nh + r0[m], nr[m], a.nchunk, ns, np, N,
+                               (size_t)k * np, (double)ibound[m], st);
+    };
+    int e;
+    for (int m = 0; m < 2 && jkq && !fused; ++m)
+      if ((e = reduce(m, nullptr, m == 0 ? 0 : nz - 1))) return e;
     const T* prev[2] = {nullptr, nullptr};
     for (int step = 1; step < nz; ++step) {
       for (int m = 0; m < 2; ++m) {
@@ -896,16 +918,11 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
         h.prev_off = (size_t)(k - s) * np;
         prev[m] = h.inext;
       }
-      a.njb = jkq ? 2 * jblocks(np) : 0;
       a.jsame = nr[0] > 0 && nr[1] > 0 && a.h[0].kM == a.h[1].kM;
-      int e = launch_plane<T>(a, ns, interp, block, st);
-      if (e) return e;
-    }
-    for (int m = 0; m < 2 && jkq; ++m) {   // the last plane of each hemisphere
-      if (nr[m] == 0) continue;
-      int e = launch_jreduce<T>(jkq, a.h[m].jpart, rays, a.h[m].ray0, nr[m], a.nchunk, ns, np, N,
-                             (size_t)a.h[m].kO * np, 0.0, st);
-      if (e) return e;
+      if ((e = launch_plane<T>(a, ns, interp, block, st))) return e;
+      for (int m = 0; m < 2 && jkq; ++m)   // fused: the last plane of each hemisphere
+        if (!fused || step == nz - 1)
+          if ((e = reduce(m, a.h[m].jpart, a.h[m].kO))) return e;
     }
     return PORTA_OK;
   };
@@ -1150,7 +1167,9 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
           t.ray0 = r0;
           constexpr int TX = TGTile<T>::X, TY = TGTile<T>::Y;
           const int tx = (nx + TX - 1) / TX, ty = (ny + TY - 1) / TY;
-          const int tc = freq_chunks((int64_t)tx * ty * nrb, q->nfreq);
+          // (at most 65535 in a grid's z)
+          const int tc = std::min(freq_chunks((int64_t)tx * ty * nrb, q->nfreq),
+                                  std::max(1, 65535 / nrb));
           t.fchunk = (q->nfreq + tc - 1) / tc;
           t.nchunk = (q->nfreq + t.fchunk - 1) / t.fchunk;
           hipLaunchKernelGGL(k_bez9_tgather<T>, dim3(tx, ty, nrb * t.nchunk), dim3(TX * TY), 0,

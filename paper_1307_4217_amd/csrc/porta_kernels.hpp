@@ -439,7 +439,7 @@ struct HemiArgs {
 // ---------------------------------------------------------------------------
 constexpr int kJNodes = 16;   // consecutive nodes of a block: one 128-byte line of doubles
 constexpr int kJCoefs = 37;   // of a ray: weight and proj[9][4]
-inline int jblocks(int np) { return (np + kJNodes - 1) / kJNodes; }
+inline int jblocks(int np) { return (np - 1) / kJNodes + 1; }
 // LDS for `threads` threads: a slab of threads / kJNodes rays, or ten sums of every thread
 inline size_t jlds_bytes(int threads, size_t elem) {
   return (size_t)(threads / kJNodes) * (elem == 4 ? 5 * kJNodes + kJCoefs : 10 * kJNodes) *
@@ -610,11 +610,12 @@ __device__ inline void jreduce_block(const JJob& J, double* __restrict__ jkq, si
     jreduce_groups<NS>(J, jkq, N, np, node0, lds, threads);
 }
 
+// first: the first block's place among the plane's jblocks.
 template <int NS, class T>
 __global__ void __launch_bounds__(256)
-    k_jreduce(const JJob J, double* __restrict__ jkq, int np, size_t N) {
+    k_jreduce(const JJob J, double* __restrict__ jkq, int np, size_t N, int first) {
   extern __shared__ double s_tab[];
-  jreduce_block<NS, T>(J, jkq, N, np, blockIdx.x * kJNodes, s_tab, blockDim.x);
+  jreduce_block<NS, T>(J, jkq, N, np, (first + (int)blockIdx.x) * kJNodes, s_tab, blockDim.x);
 }
 
 // ---------------------------------------------------------------------------

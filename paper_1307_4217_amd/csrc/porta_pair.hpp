@@ -31,7 +31,7 @@ constexpr int kUpX = kPairX + 2, kUpY = kPairY + 2;     // upwind plane
 static_assert(kMidX * kMidY <= kPairGroup && kUpX * kUpY <= kPairThreads, "tiles fit the groups");
 
 inline int pair_tiles(int nx, int ny) {
-  return ((nx + kPairX - 1) / kPairX) * ((ny + kPairY - 1) / kPairY);
+  return ((nx - 1) / kPairX + 1) * ((ny - 1) / kPairY + 1);
 }
 
 // Partial sums of J of one earlier plane.
