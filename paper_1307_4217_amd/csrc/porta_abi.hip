@@ -238,6 +238,7 @@ struct SweepPlan {
                    // the rounding of the next emissivities)
   int rows;        // rays whose states the workspace holds: nrb, or those of both batches
   size_t jrows;    // (ray, chunk) rows of partial sums the workspace holds
+  int window;      // layers of the rays' geometry that the workspace holds (0: all, of all rays)
 };
 constexpr int64_t kShareBlocks = 2048;
 constexpr size_t kShareBytes = size_t(8) << 30;
@@ -273,6 +274,18 @@ bool pair_faster(const porta_grid* g, int prec, int64_t tiles, int64_t rows, int
   return pair < plane;
 }
 
+// The geometry of every ray on every layer takes 64 bytes each; from kGeomBytes on (160 rays on
+// 26 thousand layers, 8192 on 512) a call holds that of one batch on a window of layers, which it
+// makes anew as the march moves on.  A window serves one hemisphere, plane by plane.
+constexpr size_t kGeomBytes = size_t(256) << 20;
+constexpr size_t kGeomEntry = 2 * sizeof(RayGeom);
+
+int geom_window(const porta_grid* g, const porta_quad* q, size_t rays) {
+  if (2 * (size_t)q->nmu * q->nchi * (g->nz - 1) * kGeomEntry <= kGeomBytes) return 0;
+  const size_t n = std::max<size_t>(2, kGeomBytes / (rays * kGeomEntry));
+  return (int)std::min<size_t>(n, g->nz - 1);
+}
+
 // Rays of a batch in one hemisphere.
 int sweep_batch(const porta_grid* g, const porta_quad* q, const porta_options* o) {
   // a launch is one row of at most 2^31 threads
@@ -284,6 +297,7 @@ int sweep_batch(const porta_grid* g, const porta_quad* q, const porta_options* o
 // The largest batch whose launches both hemispheres share.
 int share_batch(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o) {
   const size_t state = (size_t)g->nx * g->ny * q->nfreq * nstokes(o) * elem(prec);
+  if (!faces_of(o) && geom_window(g, q, 1)) return 0;
   return (int)std::min<size_t>(kShareBlocks / plane_tiles(g, o), kShareBytes / (4 * state));
 }
 
@@ -298,9 +312,10 @@ SweepPlan plan_rows(const porta_grid* g, const porta_quad* q, int prec, const po
   P.chunks = prec == PORTA_F64;
   const int n = P.chunks ? freq_chunks(tiles * rows, q->nfreq) : 1;
   P.jrows = (size_t)rows * n;
+  P.window = faces_of(o) ? 0 : geom_window(g, q, nrb);
   // (a pair of launches of both hemispheres: kPairBoth)
   const int64_t jb = (int64_t)jblocks(g->nx * g->ny) * (prec == PORTA_F64 ? 4 : 2);
-  P.pair = pair_of(o) && (prec == PORTA_F64 || tiles * nrb > kShareBlocks) &&
+  P.pair = pair_of(o) && P.window == 0 && (prec == PORTA_F64 || tiles * nrb > kShareBlocks) &&
            fits_launch((int64_t)pair_tiles(g->nx, g->ny) * rows + jb, kPairThreads) &&
            pair_faster(g, prec, tiles, rows, q->nfreq, n);
   return P;
@@ -362,7 +377,9 @@ FacesShape faces_shape(const porta_grid* g, const porta_quad* q, int prec, const
 }
 
 // The cut without sharing and chunks, which needs the least workspace.
-SweepPlan least_plan(int nrb) { return {nrb, false, false, false, nrb, (size_t)nrb}; }
+SweepPlan least_plan(const porta_grid* g, int nrb) {
+  return {nrb, false, false, false, nrb, (size_t)nrb, std::min(2, g->nz - 1)};
+}
 
 // Chunks of a launch of `rays` rays (each chunk has a row of partial sums).
 int launch_chunks(const porta_grid* g, const porta_quad* q, const porta_options* o,
@@ -377,7 +394,8 @@ int launch_chunks(const porta_grid* g, const porta_quad* q, const porta_options*
 struct Layout {
   size_t stage;     // doubles: mu[nmu], wmu[nmu], phi[nfreq], wfreq[nfreq], z[nz]
   size_t rays;      // RayConsts[nrays]
-  size_t geom;      // RayGeom[nrays][nz - 1][2]
+  size_t geom;      // RayGeom[nrays][nz - 1][2], or of a batch and a window of layers
+  int window;       // layers of that window, 0: all
   size_t phiT;      // T[nfreq]
   size_t wn;        // double[nfreq]
   size_t flag;      // int: result of the optional input check
@@ -394,17 +412,20 @@ struct Layout {
   size_t total;
 };
 
-// nz: planes whose ray geometry the tables hold (0: none).
-Layout tables_layout(const porta_quad* q, int prec, int nz) {
+// nz: planes whose ray geometry the tables hold (0: none); window: layers of it at a time, for
+// `batch` rays (0: all of both).
+Layout tables_layout(const porta_quad* q, int prec, int nz, int window = 0, int batch = 0) {
   Layout L{};
   const size_t nrays = 2 * (size_t)q->nmu * q->nchi;
+  const size_t planes = window > 0 ? window + 1 : nz;
   size_t off = 0;
   L.stage = off;
-  off = align_up(off + sizeof(double) * (2 * (size_t)q->nmu + 2 * (size_t)q->nfreq + nz));
+  off = align_up(off + sizeof(double) * (2 * (size_t)q->nmu + 2 * (size_t)q->nfreq + planes));
   L.rays = off;
   off = align_up(off + sizeof(RayConsts) * nrays);
   L.geom = off;
-  if (nz > 0) off = align_up(off + sizeof(RayGeom) * nrays * (nz - 1) * 2);
+  L.window = window;
+  if (planes > 0) off = align_up(off + kGeomEntry * (window > 0 ? batch : nrays) * (planes - 1));
   L.phiT = off;
   off = align_up(off + elem(prec) * q->nfreq);
   L.wn = off;
@@ -418,7 +439,9 @@ Layout tables_layout(const porta_quad* q, int prec, int nz) {
 
 Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
                     const SweepPlan& P) {
-  Layout L = tables_layout(q, prec, g->nz);
+  // (the first-face kernels form their own geometry)
+  Layout L = faces_of(o) ? tables_layout(q, prec, 0)
+                         : tables_layout(q, prec, g->nz, P.window, P.nrb);
   const size_t np = (size_t)g->nx * g->ny;
   const size_t state = (size_t)P.rows * q->nfreq * np * nstokes(o) * elem(prec);
   size_t off = L.end_tables;
@@ -494,7 +517,7 @@ size_t scratch_need(const porta_grid* g, const porta_quad* q, int prec, const po
 // per-(node, ray) partials of one plane and the FP64 gradient accumulator.
 Layout adjoint_layout(const porta_grid* g, const porta_quad* q, int prec, int stride,
                       const porta_options* o, bool own_checkpoints, size_t nrb) {
-  Layout L = tables_layout(q, prec, g->nz);
+  Layout L = tables_layout(q, prec, g->nz, geom_window(g, q, nrb), (int)nrb);
   const size_t np = (size_t)g->nx * g->ny, N = np * g->nz;
   L.plane = nrb * q->nfreq * np * 4 * elem(prec);
   // planes of its own that are small enough are all kept, whatever the stride
@@ -573,14 +596,50 @@ int upload(double* dst, std::initializer_list<HostArray> arrays, hipStream_t st)
   return check_launch("upload");
 }
 
+// The geometry of the rays: the table of a call (k_prepare), or a window of it.
+struct Geometry {
+  const porta_grid* g;
+  const porta_quad* q;
+  GeomArgs a;
+  const double* mu;   // device
+  int window;         // layers, 0: the table holds everything
+  int l0;             // first layer of the window
+
+  // The layers next to plane k for these rays, before a launch that solves it (dir: the way the
+  // planes go).  Makes a window that starts, or for dir < 0 ends, with them unless they are there.
+  int need(int ray0, int nray, int k, int dir, hipStream_t st) {
+    const int lo = std::max(k - 1, 0), hi = std::min(k + 1, g->nz - 1);
+    if (window == 0 || (ray0 == a.ray0 && nray == a.nray && lo >= l0 && hi <= l0 + a.nl))
+      return PORTA_OK;
+    l0 = dir > 0 ? lo : std::max(0, hi - window);
+    a.nl = std::min(window, g->nz - 1 - l0);
+    a.ray0 = ray0;
+    a.nray = nray;
+    const int rc = upload(const_cast<double*>(a.z), {{g->z + l0, (size_t)a.nl + 1}}, st);
+    if (rc) return rc;
+    const size_t nb = ((size_t)nray * a.nl + 255) / 256;
+    hipLaunchKernelGGL(k_geom, dim3((unsigned)nb), dim3(256), 0, st, a, mu, q->nmu * q->nchi,
+                       q->nchi);
+    return check_launch("geom");
+  }
+
+  // Where layer_geom finds them.
+  template <class Args>
+  void set(Args& args) const {
+    const ptrdiff_t skip = window ? (ptrdiff_t)a.ray0 * window + l0 : 0;
+    args.geom = a.geom - 2 * skip;
+    args.nz = a.stride + 1;
+  }
+};
+
 // The tables of a call; with a grid also the rays' geometry on its layers, as `interp`
-// splits it.
+// splits it, into `geo`.
 template <class T>
 int prepare_tables(char* ws, const Layout& L, const porta_grid* g, const porta_quad* q, double w2,
-                   int interp, hipStream_t st) {
+                   int interp, Geometry* geo, hipStream_t st) {
   double* mu = reinterpret_cast<double*>(ws + L.stage);
   double *wmu = mu + q->nmu, *phi = wmu + q->nmu, *wfreq = phi + q->nfreq, *z = wfreq + q->nfreq;
-  const int nz = g ? g->nz : 0;
+  const int nz = geo && L.window == 0 ? g->nz : 0;   // planes whose layers k_prepare takes
   int rc;
   if ((rc = upload(mu, {{q->mu, (size_t)q->nmu}, {q->wmu, (size_t)q->nmu},
                         {q->phi, (size_t)q->nfreq}, {q->wfreq, (size_t)q->nfreq},
@@ -588,10 +647,13 @@ int prepare_tables(char* ws, const Layout& L, const porta_grid* g, const porta_q
     return rc;
   GeomArgs ga{};
   size_t nb = 1;
-  if (g) {
-    ga = {z, nz, g->nx, g->ny, g->nx / g->lx, g->ny / g->ly,
-          interp == PORTA_INTERP_BEZIER2D ? 0.5 : 0.0, reinterpret_cast<RayGeom*>(ws + L.geom)};
-    nb += (2 * (size_t)q->nmu * q->nchi * (nz - 1) + 255) / 256;
+  if (geo) {
+    const int nrays = 2 * q->nmu * q->nchi;
+    ga = {z, 0, nz ? nrays : 0, nz ? nz - 1 : 0, nz ? nz - 1 : L.window, g->nx, g->ny,
+          g->nx / g->lx, g->ny / g->ly, interp == PORTA_INTERP_BEZIER2D ? 0.5 : 0.0,
+          reinterpret_cast<RayGeom*>(ws + L.geom)};
+    nb += ((size_t)ga.nray * ga.nl + 255) / 256;
+    *geo = {g, q, ga, mu, L.window, 0};
   }
   hipLaunchKernelGGL(k_prepare<T>, dim3((unsigned)nb), dim3(256), 0, st, mu, wmu, q->nmu, q->nchi,
                      w2, phi, wfreq, q->nfreq, reinterpret_cast<RayConsts*>(ws + L.rays),
@@ -793,18 +855,17 @@ int sweep_faces_impl(const porta_grid* g, const porta_quad* q, const porta_field
 // The parts of a plane step's arguments that do not change from plane to plane.
 template <class T>
 PlaneArgs<T> plane_args(const porta_grid* g, const porta_quad* q, const porta_fields* f,
-                        const porta_options* o, char* ws, const Layout& L) {
+                        const porta_options* o, char* ws, const Layout& L, const Geometry& geo) {
   PlaneArgs<T> a{};
   a.kappa = static_cast<const T*>(f->kappa);
   a.prop = static_cast<const T*>(f->propmat);
   a.emis = static_cast<const T*>(f->emis);
   a.rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
-  a.geom = reinterpret_cast<const RayGeom*>(ws + L.geom);
+  geo.set(a);
   a.phi = reinterpret_cast<const T*>(ws + L.phiT);
   a.wn = reinterpret_cast<const double*>(ws + L.wn);
   a.nx = g->nx;
   a.ny = g->ny;
-  a.nz = g->nz;
   a.np = g->nx * g->ny;
   a.N = (size_t)a.np * g->nz;
   a.nfreq = q->nfreq;
@@ -853,7 +914,9 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
                const porta_options* o, double* jkq, int accumulate, T* itop, T* ckpt, int C,
                char* ws, const SweepPlan& P, const Layout& L, hipStream_t st) {
   int rc;
-  if ((rc = prepare_tables<T>(ws, L, g, q, f->w2, interp, st))) return rc;
+  Geometry geo;
+  if ((rc = prepare_tables<T>(ws, L, g, q, f->w2, interp, faces_of(o) ? nullptr : &geo, st)))
+    return rc;
   const int nz = g->nz, np = g->nx * g->ny;
   const size_t N = (size_t)np * nz;
   if (jkq && !accumulate)
@@ -881,7 +944,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
   };
   // one launch per plane step for a batch of upward rays, of downward rays, or of both
   auto walk = [&](const int r0[2], const int nr[2]) -> int {
-    PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L);
+    PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L, geo);
     a.jkq = jkq;
     set_chunks(a, launch_chunks(g, q, o, P, nr[0] + nr[1]), nr[0] + nr[1]);
     // states and partial sums of the downward rays follow those of the upward ones
@@ -917,7 +980,9 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
         h.jpart_prev = (jkq && step > 1) ? jbase + ((step - 1) & 1) * jslot + joff[m] : nullptr;
         h.prev_off = (size_t)(k - s) * np;
         prev[m] = h.inext;
+        if (nr[m] > 0 && (e = geo.need(h.ray0, nr[m], k, s, st))) return e;
       }
+      geo.set(a);
       a.jsame = nr[0] > 0 && nr[1] > 0 && a.h[0].kM == a.h[1].kM;
       if ((e = launch_plane<T>(a, ns, interp, block, st))) return e;
       for (int m = 0; m < 2 && jkq; ++m)   // fused: the last plane of each hemisphere
@@ -930,7 +995,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
   auto walk_pairs = [&](const int r0[2], const int nr[2]) -> int {
     PairArgs<T> A{};
     PlaneArgs<T>& a = A.a;
-    a = plane_args<T>(g, q, f, o, ws, L);
+    a = plane_args<T>(g, q, f, o, ws, L, geo);
     a.jkq = jkq;
     const size_t soff[2] = {0, (size_t)nr[0] * q->nfreq * np * ns};
     const size_t joff[2] = {0, (size_t)nr[0] * (ns + 1) * np};
@@ -1017,9 +1082,11 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
 // ---------------------------------------------------------------------------
 template <class T>
 int forward_plane(const porta_grid* g, const porta_quad* q, const porta_fields* f,
-                  const porta_options* o, int interp, char* ws, const Layout& L, int k,
+                  const porta_options* o, int interp, char* ws, const Layout& L, Geometry& geo, int k,
                   const T* prev, T* next, int ray0, int nrb, int block, hipStream_t st) {
-  PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L);
+  const int rc = geo.need(ray0, nrb, k, 1, st);
+  if (rc) return rc;
+  PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L, geo);
   set_chunks(a, freq_chunks((int64_t)a.ntile * nrb, q->nfreq), nrb);
   HemiArgs<T>& h = a.h[0];
   set_plane(h, g, k, 1);
@@ -1062,7 +1129,8 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
                  T* gpm, T* ge, char* ws, const Layout& L, hipStream_t st) {
   int rc;
   if (!ext_ck) C = L.stride;
-  if ((rc = prepare_tables<T>(ws, L, g, q, f->w2, interp, st))) return rc;
+  Geometry geo;
+  if ((rc = prepare_tables<T>(ws, L, g, q, f->w2, interp, &geo, st))) return rc;
   const int nx = g->nx, ny = g->ny, nz = g->nz, np = nx * ny;
   const size_t N = (size_t)np * nz;
   double* grad = reinterpret_cast<double*>(ws + L.grad);
@@ -1102,7 +1170,7 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
     // segment
     if (!ext_ck)
       for (int k = 1; k <= C * checkpoint_count(nz, C); ++k)
-        if ((rc = forward_plane<T>(g, q, f, o, interp, ws, L, k, plane(k - 1), plane(k), r0,
+        if ((rc = forward_plane<T>(g, q, f, o, interp, ws, L, geo, k, plane(k - 1), plane(k), r0,
                                    nrb, block, st)))
           return rc;
     // reverse pass, one segment between checkpoints at a time
@@ -1114,16 +1182,17 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
       // plane of a segment needs no state
       for (int k = s0 + 1; k < khi; ++k)
         if (!is_checkpoint(k, nz, C))
-          if ((rc = forward_plane<T>(g, q, f, o, interp, ws, L, k, plane(k - 1), plane(k), r0,
+          if ((rc = forward_plane<T>(g, q, f, o, interp, ws, L, geo, k, plane(k - 1), plane(k), r0,
                                      nrb, block, st)))
             return rc;
       for (int k = khi; k > s0; --k) {
+        if ((rc = geo.need(r0, nrb, k, -1, st))) return rc;
         AdjArgs<T> a;
         a.kappa = static_cast<const T*>(f->kappa);
         a.prop = static_cast<const T*>(f->propmat);
         a.emis = static_cast<const T*>(f->emis);
         a.rays = reinterpret_cast<const RayConsts*>(ws + L.rays);
-        a.geom = reinterpret_cast<const RayGeom*>(ws + L.geom);
+        geo.set(a);
         a.phi = reinterpret_cast<const T*>(ws + L.phiT);
         a.iprev = plane(k - 1);
         a.lam_next = lam_next;
@@ -1135,7 +1204,6 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
         a.N = N;
         a.nx = nx;
         a.ny = ny;
-        a.nz = nz;
         a.np = np;
         a.nfreq = q->nfreq;
         a.ntile = ntile;
@@ -1160,7 +1228,7 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
           t.geom = a.geom;
           t.nx = nx;
           t.ny = ny;
-          t.nz = nz;
+          t.nz = a.nz;
           t.np = np;
           t.nfreq = q->nfreq;
           t.kO = k;
@@ -1196,7 +1264,7 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
         b.N = N;
         b.nx = nx;
         b.ny = ny;
-        b.nz = nz;
+        b.nz = a.nz;
         b.np = np;
         b.kO = a.kO;
         b.kM = a.kM;
@@ -1294,12 +1362,21 @@ int sweep_entry(const porta_grid* grid, const porta_quad* quad, const porta_fiel
                   "this sweep needs %zu bytes of workspace; the static scratch holds %zu "
                   "(use a smaller opts->ray_batch, or porta_fs_sweep)",
                   need, kScratchLimit);
-    // the cut that fits: the usual one, the plain one, or that with fewer rays in turn
-    if (L.total > kScratchBytes) plan = least_plan(plan.nrb);
-    for (; (L = sweep_layout(grid, quad, prec, opts, plan)).total > kScratchBytes && plan.nrb > 1;)
-      plan = least_plan(plan.nrb - 1);
-    if (L.total > kScratchBytes)
-      return fail(PORTA_ENOMEM, "the geometry of the rays does not fit the static scratch");
+    // the cut that fits: the usual one, the plain one, or that with fewer rays in turn, whose
+    // window of the rays' geometry takes what is left
+    if (L.total > kScratchBytes) {
+      plan = least_plan(grid, plan.nrb);
+      for (; (L = sweep_layout(grid, quad, prec, opts, plan)).total > kScratchBytes && plan.nrb > 1;)
+        plan = least_plan(grid, plan.nrb - 1);
+      if (L.total > kScratchBytes)
+        return fail(PORTA_ENOMEM, "this sweep does not fit the static scratch of %zu bytes",
+                    kScratchBytes);
+      const size_t layer = plan.nrb * kGeomEntry + sizeof(double), align = 2 * kAlign;
+      if (L.window > 0 && kScratchBytes - L.total > align)
+        plan.window = (int)std::min<size_t>(
+            grid->nz - 1, L.window + (kScratchBytes - L.total - align) / layer);
+      L = sweep_layout(grid, quad, prec, opts, plan);
+    }
     if ((rc = scratch_address(&workspace))) return rc;
     ws_bytes = kScratchBytes;
   }
@@ -1420,13 +1497,13 @@ int porta_jkq_accumulate(const porta_grid* grid, const porta_quad* quad, int ray
   if (nray == 0 || nf == 0) return PORTA_OK;
   const dim3 grd((unsigned)((N + 255) / 256)), blk(256);
   if (prec == PORTA_F64) {
-    if ((rc = prepare_tables<double>(ws, L, nullptr, quad, 1.0, 0, st))) return rc;
+    if ((rc = prepare_tables<double>(ws, L, nullptr, quad, 1.0, 0, nullptr, st))) return rc;
     hipLaunchKernelGGL(k_jkq_accumulate<double>, grd, blk, 0, st, jkq,
                        static_cast<const double*>(stokes), static_cast<const double*>(lambda_star),
                        reinterpret_cast<const RayConsts*>(ws + L.rays),
                        reinterpret_cast<const double*>(ws + L.wn), ray0, nray, f0, nf, N);
   } else {
-    if ((rc = prepare_tables<float>(ws, L, nullptr, quad, 1.0, 0, st))) return rc;
+    if ((rc = prepare_tables<float>(ws, L, nullptr, quad, 1.0, 0, nullptr, st))) return rc;
     hipLaunchKernelGGL(k_jkq_accumulate<float>, grd, blk, 0, st, jkq,
                        static_cast<const float*>(stokes), static_cast<const float*>(lambda_star),
                        reinterpret_cast<const RayConsts*>(ws + L.rays),

@@ -42,7 +42,8 @@ struct AdjArgs {
                        // (partials of one node, ray and chunk of frequencies, formed in FP64,
                        // stored in the sweep precision; the gather sums them in FP64)
   size_t N;
-  int nx, ny, nz, np, nfreq;
+  int nx, ny, np, nfreq;
+  int nz;              // of the geometry table (layer_geom)
   int ntile;           // tiles of blockDim.x nodes in a plane
   int nchunk, fchunk;  // frequency chunks, as in the sweep's plane step
   int kO, kM, kP;
@@ -121,7 +122,8 @@ struct TGatherArgs {
   const T* lam_next;   // adjoint of I_M at the nodes of plane kO + 1, same layout
   T* out;              // adjoint of I at the nodes of plane kO, same layout
   const RayGeom* geom;
-  int nx, ny, nz, np, nfreq;
+  int nx, ny, np, nfreq;
+  int nz;              // of the geometry table (layer_geom)
   int nchunk, fchunk;  // frequency chunks of a launch
   int kO, ray0;
 };
@@ -544,7 +546,8 @@ struct GatherArgs {
   const RayGeom* geom;
   double* grad;       // [13][N]: kappa, propmat[6], emis[6]
   size_t N;
-  int nx, ny, nz, np;
+  int nx, ny, np;
+  int nz;             // of the geometry table (layer_geom)
   int kO, kM, kP;
   int ray0, nrb, nchunk;
   const T* kappa;     // the coefficients (MODE 1: the Bezier partials depend on them)

@@ -70,13 +70,47 @@ struct RayGeom {
   int fu, fv;
 };
 
+// Rays [ray0, ray0 + nray) on nl layers, `stride` of them apart from one ray to the next.
 struct GeomArgs {
-  const double* z;    // device
-  int nz, nx, ny;     // nz = 0: no geometry
+  const double* z;    // device: heights of the layers' nl + 1 planes
+  int ray0, nray, nl, stride;
+  int nx, ny;
   double inv_dx, inv_dy;
   double half;        // 0 (bilinear) or 0.5 (9-point)
   RayGeom* geom;
 };
+
+// Both sides of one ray and layer: entry e of nray * nl.
+__device__ inline void make_geom(const GeomArgs& ga, const double* __restrict__ mu, int nh,
+                                 int nchi, int e) {
+  const int rb = e / ga.nl, r = ga.ray0 + rb, l = e % ga.nl;
+  const double m0 = mu[(r % nh) / nchi], chi = (r % nchi + 0.5) * (2.0 * M_PI / nchi);
+  const double st = sqrt(fmax(0.0, 1.0 - m0 * m0));
+  const double ds = fabs(ga.z[l + 1] - ga.z[l]) * (1.0 / fabs(m0));
+  const double sx = st * cos(chi), sy = st * sin(chi);
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    const double d = side == 0 ? -ds : ds;
+    double u = d * sx * ga.inv_dx, v = d * sy * ga.inv_dy;
+    // to one period first, so the integer shift stays in range
+    u -= ga.nx * floor(u / ga.nx);
+    v -= ga.ny * floor(v / ga.ny);
+    const double fu = floor(u + ga.half), fv = floor(v + ga.half);
+    RayGeom g;
+    g.ds = ds;
+    g.tx = u - fu;
+    g.ty = v - fv;
+    g.fu = (int)fu;
+    g.fv = (int)fv;
+    ga.geom[((size_t)rb * ga.stride + l) * 2 + side] = g;
+  }
+}
+
+__global__ void __launch_bounds__(256)
+    k_geom(const GeomArgs ga, const double* __restrict__ mu, int nh, int nchi) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < ga.nray * ga.nl) make_geom(ga, mu, nh, nchi, e);
+}
 
 constexpr int kMaxFreq = 4096;   // frequencies of a quadrature, at most
 
@@ -93,30 +127,8 @@ __global__ void __launch_bounds__(256)
   __shared__ double norm;
   const int nh = nmu * nchi;
   if (blockIdx.x > 0) {
-    const int nl = ga.nz - 1;
     const int e = (blockIdx.x - 1) * blockDim.x + threadIdx.x;
-    if (e >= 2 * nh * nl) return;
-    const int r = e / nl, l = e % nl;
-    const double m0 = mu[(r % nh) / nchi], chi = (r % nchi + 0.5) * (2.0 * M_PI / nchi);
-    const double st = sqrt(fmax(0.0, 1.0 - m0 * m0));
-    const double ds = fabs(ga.z[l + 1] - ga.z[l]) * (1.0 / fabs(m0));
-    const double sx = st * cos(chi), sy = st * sin(chi);
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-      const double d = side == 0 ? -ds : ds;
-      double u = d * sx * ga.inv_dx, v = d * sy * ga.inv_dy;
-      // to one period first, so the integer shift stays in range
-      u -= ga.nx * floor(u / ga.nx);
-      v -= ga.ny * floor(v / ga.ny);
-      const double fu = floor(u + ga.half), fv = floor(v + ga.half);
-      RayGeom g;
-      g.ds = ds;
-      g.tx = u - fu;
-      g.ty = v - fv;
-      g.fu = (int)fu;
-      g.fv = (int)fv;
-      ga.geom[(size_t)e * 2 + side] = g;
-    }
+    if (e < ga.nray * ga.nl) make_geom(ga, mu, nh, nchi, e);
     return;
   }
   for (int r = threadIdx.x; r < 2 * nh; r += blockDim.x) {
@@ -397,7 +409,8 @@ __device__ inline void setup_point(const T* __restrict__ kappa, const T* __restr
   setup_sources(rc, parabolic, ps);
 }
 
-// Geometry of the layer between planes k and k2 for one ray and side (0: M, 1: P).
+// Geometry of the layer between planes k and k2 for one ray and side (0: M, 1: P), from a
+// table of nz - 1 layers a ray.
 __device__ inline const RayGeom& layer_geom(const RayGeom* __restrict__ geom, int ray, int nz,
                                             int k, int k2, int side) {
   return geom[((size_t)ray * (nz - 1) + (k < k2 ? k : k2)) * 2 + side];
@@ -644,7 +657,8 @@ struct PlaneArgs {
   HemiArgs<T> h[2];
   double* jkq;       // [10][N] or nullptr
   size_t N;
-  int nx, ny, nz, np, nfreq;
+  int nx, ny, np, nfreq;
+  int nz;            // of the geometry table (layer_geom)
   int ntile;         // tiles of blockDim.x nodes in a plane
   int nchunk, fchunk;
   int nstep;         // blocks of the plane step; the J reduction's follow

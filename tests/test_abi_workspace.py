@@ -89,3 +89,26 @@ def test_planes_beyond_one_launch_go_plane_by_plane(prec, n):
                 > porta.workspace_size(hg, prec, porta.WS_SWEEP, opts=porta.options(block=256)))
     assert not pairs(n)
     assert pairs(n // 2)
+
+
+def _noalloc(hg, prec, opts=None):
+    """Status of a no-alloc sweep on a machine without a GPU, which ends for want of a device once
+    the size is accepted."""
+    import torch
+    if torch.cuda.device_count():
+        pytest.skip("would run on the GPU")
+    d = np.zeros(8).ctypes.data
+    f = porta.Fields(d, d, d, 1.0, 1.0)
+    return porta.lib().porta_fs_sweep_noalloc(
+        C.byref(hg.grid), C.byref(hg.quad), C.byref(f), prec, porta.BILINEAR,
+        C.byref(opts) if opts else None, d, 0, d, None)
+
+
+@pytest.mark.parametrize("prec", [porta.F64, porta.F32])
+@pytest.mark.parametrize("dims", [(1, 1, 7600, 5, 16, 1), (1, 1, 200000, 5, 16, 1),
+                                  (3, 2, 30000, 5, 8, 2), (1, 1, 3000, 64, 32, 1)])
+def test_noalloc_takes_long_columns(dims, prec):
+    """The plane states and partial sums of these fit 64 MiB many times over; the rays' geometry
+    on all layers would not."""
+    assert _noalloc(_grid(*dims), prec) == porta.EDEVICE
+    assert porta.workspace_size(_grid(*dims), prec, porta.WS_SWEEP) < 600 << 20
