@@ -239,6 +239,7 @@ struct SweepPlan {
   int rows;        // rays whose states the workspace holds: nrb, or those of both batches
   size_t jrows;    // (ray, chunk) rows of partial sums the workspace holds
   int window;      // layers of the rays' geometry that the workspace holds (0: all, of all rays)
+  bool few;        // first faces: the cut with the fewest chunks (faces_shape)
 };
 constexpr int64_t kShareBlocks = 2048;
 constexpr size_t kShareBytes = size_t(8) << 30;
@@ -313,6 +314,7 @@ SweepPlan plan_rows(const porta_grid* g, const porta_quad* q, int prec, const po
   const int n = P.chunks ? freq_chunks(tiles * rows, q->nfreq) : 1;
   P.jrows = (size_t)rows * n;
   P.window = faces_of(o) ? 0 : geom_window(g, q, nrb);
+  P.few = false;
   // (a pair of launches of both hemispheres: kPairBoth)
   const int64_t jb = (int64_t)jblocks(g->nx * g->ny) * (prec == PORTA_F64 ? 4 : 2);
   P.pair = pair_of(o) && P.window == 0 && (prec == PORTA_F64 || tiles * nrb > kShareBlocks) &&
@@ -329,14 +331,16 @@ SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const p
 
 // The cut of the first-face march for a launch of `rays` rays (porta_faces.hpp): columns,
 // ways and frequencies of a block.  The options' faces_chunk, if given, is the chunk of one
-// way.  fchunk is 0 if it does not fit the LDS.
+// way.  few: as many frequencies in turn as a thread takes at most, however few the rays, so
+// that the partial sums of the chunks take the least memory.  fchunk is 0 if it does not fit the
+// LDS.
 struct FacesShape {
   int lanes, ways, fchunk, nchunk;
 };
 
 template <class T>
 FacesShape faces_shape_t(const porta_grid* g, const porta_quad* q, const porta_options* o,
-                         int rays) {
+                         int rays, bool few) {
   FacesShape S;
   const int nf = q->nfreq;
   S.lanes = (std::max(g->nx, g->ny) + 63) / 64 * 64;
@@ -351,8 +355,8 @@ FacesShape faces_shape_t(const porta_grid* g, const porta_quad* q, const porta_o
   } else {
     // frequencies in turn in one thread: one while their wavefronts fit on the chip
     const int64_t waves = (int64_t)rays * nf * (S.lanes / 64);
-    const int serial = (int)std::min<int64_t>(faces_serial<T>(),
-                                              (waves + faces_waves<T>() - 1) / faces_waves<T>());
+    const int64_t rounds = (waves + faces_waves<T>() - 1) / faces_waves<T>();
+    const int serial = few ? faces_serial<T>() : (int)std::min<int64_t>(faces_serial<T>(), rounds);
     const int ways = std::min({kFacesMaxWays, kFacesThreads / S.lanes, nf});
     if (serial == 1 && ways > 1) {
       S.fchunk = fit(1, ways);   // one frequency per way: as many ways as fit
@@ -371,14 +375,15 @@ FacesShape faces_shape_t(const porta_grid* g, const porta_quad* q, const porta_o
 }
 
 FacesShape faces_shape(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
-                       int rays) {
-  return prec == PORTA_F32 ? faces_shape_t<float>(g, q, o, rays)
-                           : faces_shape_t<double>(g, q, o, rays);
+                       int rays, bool few = false) {
+  return prec == PORTA_F32 ? faces_shape_t<float>(g, q, o, rays, few)
+                           : faces_shape_t<double>(g, q, o, rays, few);
 }
 
-// The cut without sharing and chunks, which needs the least workspace.
+// The cut without sharing and chunks, which needs the least workspace (no more than scratch_need
+// counts, and the geometry).
 SweepPlan least_plan(const porta_grid* g, int nrb) {
-  return {nrb, false, false, false, nrb, (size_t)nrb, std::min(2, g->nz - 1)};
+  return {nrb, false, false, false, nrb, (size_t)nrb, std::min(2, g->nz - 1), true};
 }
 
 // Chunks of a launch of `rays` rays (each chunk has a row of partial sums).
@@ -454,7 +459,7 @@ Layout sweep_layout(const porta_grid* g, const porta_quad* q, int prec, const po
   off = align_up(off + (P.pair ? 4 : 2) * P.jrows * (nstokes(o) + 1) * np * sizeof(double));
   if (faces_of(o)) {
     // per-chunk partial sums of the first-face kernel
-    L.fshape = faces_shape(g, q, prec, o, P.rows);
+    L.fshape = faces_shape(g, q, prec, o, P.rows, P.few);
     L.ck = off;
     off = align_up(off + (size_t)P.rows * L.fshape.nchunk * 5 * np * sizeof(double));
     // the transfer coefficients with x and y exchanged in every plane

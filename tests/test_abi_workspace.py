@@ -112,3 +112,30 @@ def test_noalloc_takes_long_columns(dims, prec):
     on all layers would not."""
     assert _noalloc(_grid(*dims), prec) == porta.EDEVICE
     assert porta.workspace_size(_grid(*dims), prec, porta.WS_SWEEP) < 600 << 20
+
+
+def test_noalloc_takes_what_its_acceptance_rule_takes():
+    """First-face sweeps with many frequencies and few rays on wide planes, whose usual cut holds
+    one frequency a block: the one of 321x64x2 with 68 frequencies needs 62 MiB by the rule and
+    101 MiB in that cut.  Then any sweep: refused by the rule (its message gives the bytes) or
+    not at all."""
+    o = porta.options(ray_batch=1, faces=1)
+    assert _noalloc(_grid(321, 64, 2, 1, 2, 68), porta.F32, o) == porta.EDEVICE
+    rng = random.Random(7)
+    taken = 0
+    for _ in range(600):
+        wide = rng.randint(64, 512)
+        dims = (wide, rng.randint(1, 80), rng.choice([2, 2, 3, 9]), rng.randint(1, 3),
+                rng.randint(1, 6), rng.randint(1, 100))
+        if rng.random() < 0.3:
+            dims = (dims[1], wide) + dims[2:]
+        o = porta.options(ray_batch=rng.randint(0, 3), faces=rng.choice([1, 1, 0]))
+        for prec in (porta.F64, porta.F32):
+            status = _noalloc(_grid(*dims), prec, o)
+            message = porta.lib().porta_last_error().decode()
+            if status == porta.ENOMEM:
+                assert "this sweep needs" in message, (dims, prec, o.ray_batch, message)
+            else:
+                assert status == porta.EDEVICE
+                taken += 1
+    assert taken > 200

@@ -70,3 +70,26 @@ def test_noalloc_sweep_rejects_a_problem_beyond_its_scratch():
     # the same problem fits once its ray batch is small enough
     opts = porta.options(ray_batch=2)
     assert porta.workspace_size(hg, porta.F64, porta.WS_SWEEP, 1, opts) < 64 << 20
+
+
+@pytest.mark.parametrize("prec", [porta.F64, porta.F32])
+def test_noalloc_first_faces_in_the_cut_that_fits(prec):
+    """A first-face sweep whose usual cut, one frequency a block, does not fit the scratch beside
+    the states: the call takes the cut with the fewest chunks, the one that faces_chunk asks for
+    here, and gives its Stokes vectors bit for bit.  Its batches go one hemisphere after the other
+    and not together, so the four additions to a node of J have another order: 6 roundings at most."""
+    dims = (321, 64, 2, 1, 2, 68) if prec == porta.F32 else (321, 112, 2, 1, 2, 16)
+    chunk = 4   # of 4 (FP32) or 5 (FP64: 7, but LDS has room for 5) at most, evened out
+    atm, q = _case(inputs.Config("wide", *dims, True), 5, prec)
+    torch = require_gpu()
+    dt = torch.float64 if prec == porta.F64 else torch.float32
+    hg = porta.HostGrid.from_inputs(atm, q)
+    kappa, prop, emis = to_dev(atm.kappa, dt), to_dev(atm.propmat, dt), to_dev(atm.emis, dt)
+    want = porta.fs_sweep(hg, kappa, prop, emis, atm.i_bottom, atm.w2, prec=prec,
+                          opts=porta.options(ray_batch=1, faces=1, faces_chunk=chunk))
+    got = [torch.full_like(x, 7.0) for x in want]
+    porta.fs_sweep_noalloc(hg, kappa, prop, emis, atm.i_bottom, got[0], got[1], atm.w2, prec=prec,
+                           opts=porta.options(ray_batch=1, faces=1))
+    torch.cuda.synchronize()
+    assert torch.equal(got[1], want[1])
+    assert float((got[0] - want[0]).abs().max()) <= 6 * 2.0**-53 * float(want[0].abs().max())
