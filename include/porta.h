@@ -167,7 +167,8 @@ typedef struct {
   int32_t faces_chunk;      /* with faces = 1: frequencies one block of the first-face
                                kernel carries through a plane (0: chosen by the number of
                                rays, frequencies and columns, and so that the rows fit
-                               64 KiB of LDS); PORTA_EUNSUPPORTED if more than fit */
+                               64 KiB of LDS); PORTA_EUNSUPPORTED if more than fit there
+                               beside the tables of every frequency */
 } porta_options;
 
 typedef enum { PORTA_CONTROL_BESSER = 0, PORTA_CONTROL_PARABOLIC = 1 } porta_control;

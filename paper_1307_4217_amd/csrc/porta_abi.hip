@@ -329,6 +329,18 @@ SweepPlan sweep_plan(const porta_grid* g, const porta_quad* q, int prec, const p
   return plan_rows(g, q, prec, o, nrb, share ? std::min(nrb, up) + std::min(nrb, down) : nrb);
 }
 
+// The most frequencies that a first-face sweep takes in options.faces_chunk, and it needs room for
+// one: those whose rows fit kFacesLds beside the tables of every frequency.  (A block keeps
+// tables of its own chunk only; what the option and the scratch's rule allow does not depend on
+// the cut.)
+size_t faces_fit(const porta_grid* g, const porta_quad* q, int prec) {
+  const int lanes = (std::max(g->nx, g->ny) + 63) / 64 * 64;
+  const size_t base = prec == PORTA_F32 ? faces_col_offset<float>(q->nfreq)
+                                        : faces_col_offset<double>(q->nfreq);
+  const size_t row = (size_t)(lanes + 4 * (lanes / 64)) * 4 * sizeof(double);
+  return kFacesLds > base ? (kFacesLds - base) / row : 0;
+}
+
 // The cut of the first-face march for a launch of `rays` rays (porta_faces.hpp): columns,
 // ways and frequencies of a block.  The options' faces_chunk, if given, is the chunk of one
 // way.  few: as many frequencies in turn as a thread takes at most, however few the rays, so
@@ -504,10 +516,7 @@ size_t scratch_need(const porta_grid* g, const porta_quad* q, int prec, const po
              align_up(sizeof(double) * nf) + align_up(sizeof(int));
   n += 2 * align_up(nrb * nf * np * nstokes(o) * e) + align_up(2 * nrb * 5 * np * sizeof(double));
   if (faces_of(o)) {
-    const size_t lanes = (std::max(g->nx, g->ny) + 63) / 64 * 64, waves = lanes / 64;
-    const size_t base = (nf * (sizeof(double) + e) + 15) & ~(size_t)15;
-    const size_t fit = kFacesLds > base ? (kFacesLds - base) / ((lanes + 4 * waves) * 32) : 0;
-    size_t chunk = std::min<size_t>({prec == PORTA_F32 ? 4u : 7u, fit, nf});
+    size_t chunk = std::min<size_t>({prec == PORTA_F32 ? 4u : 7u, faces_fit(g, q, prec), nf});
     if (o->faces_chunk > 0) chunk = std::min<size_t>(o->faces_chunk, nf);
     chunk = std::max<size_t>(chunk, 1);
     const size_t nchunk = (nf + chunk - 1) / chunk;
@@ -1345,7 +1354,8 @@ int sweep_entry(const porta_grid* grid, const porta_quad* quad, const porta_fiel
                   "faces = 1 is for the bilinear Stokes-vector sweep without checkpoints");
     if (std::max(grid->nx, grid->ny) > kFacesMaxLanes)
       return fail(PORTA_EUNSUPPORTED, "faces = 1 needs nx, ny <= %d", kFacesMaxLanes);
-    if (faces_shape(grid, quad, prec, opts, 1).fchunk < 1)
+    const size_t want = opts->faces_chunk > 0 ? std::min(opts->faces_chunk, quad->nfreq) : 1;
+    if (want > faces_fit(grid, quad, prec))
       return fail(PORTA_EUNSUPPORTED, "faces = 1: the LDS of a block has no room for %s",
                   opts->faces_chunk > 0 ? "faces_chunk frequencies" : "one frequency");
   }

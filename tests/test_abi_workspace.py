@@ -139,3 +139,25 @@ def test_noalloc_takes_what_its_acceptance_rule_takes():
                 assert status == porta.EDEVICE
                 taken += 1
     assert taken > 200
+
+
+def test_first_face_chunks_beyond_the_lds_stay_refused():
+    """The option's limit: the rows of its frequencies in 64 KiB beside the tables of all
+    frequencies (16 bytes each in FP64, 12 in FP32), and room for one frequency without it."""
+    d = np.zeros(8).ctypes.data
+    f = porta.Fields(d, d, d, 1.0, 1.0)
+
+    def status(dims, prec, chunk):
+        hg = _grid(*dims)
+        return porta.lib().porta_fs_sweep(
+            C.byref(hg.grid), C.byref(hg.quad), C.byref(f), prec, porta.BILINEAR,
+            C.byref(porta.options(faces=1, faces_chunk=chunk)), d, 0, d, None, 0, 0, d, 16, None)
+
+    wide = (321, 8, 2, 1, 2, 68)    # (64 KiB - 1088) / (408 rows of 32 bytes) = 4.9 in FP64
+    assert status(wide, porta.F64, 4) == porta.ENOMEM
+    assert status(wide, porta.F64, 5) == porta.EUNSUPPORTED
+    many = (64, 8, 2, 1, 2, 4000)   # 1536 and 17536 bytes left; a row takes 2176
+    for chunk, prec, want in ((0, porta.F64, porta.EUNSUPPORTED), (1, porta.F64, porta.EUNSUPPORTED),
+                              (0, porta.F32, porta.ENOMEM), (8, porta.F32, porta.ENOMEM),
+                              (9, porta.F32, porta.EUNSUPPORTED)):
+        assert status(many, prec, chunk) == want, (chunk, prec)
