@@ -59,6 +59,13 @@ float hm_sources_f32(float tau, float SM, float SO, float cM) {
   return porta::add_sources(porta::source_weights(porta::coefficients(tau)), s, 0.0f);
 }
 
+// f of cell_shift; the rest into t.
+int hm_cell_shift(double u, int n, double half, double* t) {
+  const porta::CellShift s = porta::cell_shift(u, n, half);
+  *t = s.t;
+  return s.f;
+}
+
 double hm_besser_cm(double yM, double yO, double yP, double ratio) {
   return porta::besser_cm(yM, yO, yP, ratio);
 }

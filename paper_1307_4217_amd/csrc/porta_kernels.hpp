@@ -91,17 +91,9 @@ __device__ inline void make_geom(const GeomArgs& ga, const double* __restrict__ 
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
     const double d = side == 0 ? -ds : ds;
-    double u = d * sx * ga.inv_dx, v = d * sy * ga.inv_dy;
-    // to one period first, so the integer shift stays in range
-    u -= ga.nx * floor(u / ga.nx);
-    v -= ga.ny * floor(v / ga.ny);
-    const double fu = floor(u + ga.half), fv = floor(v + ga.half);
-    RayGeom g;
-    g.ds = ds;
-    g.tx = u - fu;
-    g.ty = v - fv;
-    g.fu = (int)fu;
-    g.fv = (int)fv;
+    const CellShift u = cell_shift(d * sx * ga.inv_dx, ga.nx, ga.half);
+    const CellShift v = cell_shift(d * sy * ga.inv_dy, ga.ny, ga.half);
+    const RayGeom g = {ds, u.t, v.t, u.f, v.f};
     ga.geom[((size_t)rb * ga.stride + l) * 2 + side] = g;
   }
 }
@@ -225,15 +217,8 @@ __device__ inline Stencil make_stencil(int i, int j, int nx, int ny, const RayGe
 
 // The same for a displacement (u, v) in cells.
 __device__ inline Stencil make_stencil(int i, int j, int nx, int ny, double u, double v) {
-  u -= nx * floor(u / nx);
-  v -= ny * floor(v / ny);
-  const double fu = floor(u), fv = floor(v);
-  RayGeom g;
-  g.ds = 0.0;
-  g.tx = u - fu;
-  g.ty = v - fv;
-  g.fu = (int)fu;
-  g.fv = (int)fv;
+  const CellShift su = cell_shift(u, nx, 0.0), sv = cell_shift(v, ny, 0.0);
+  const RayGeom g = {0.0, su.t, sv.t, su.f, sv.f};
   return make_stencil(i, j, nx, ny, g);
 }
 
@@ -657,8 +642,9 @@ struct PlaneArgs {
   HemiArgs<T> h[2];
   double* jkq;       // [10][N] or nullptr
   size_t N;
-  int nx, ny, np, nfreq;
+  int nx, ny;
   int nz;            // of the geometry table (layer_geom)
+  int np, nfreq;
   int ntile;         // tiles of blockDim.x nodes in a plane
   int nchunk, fchunk;
   int nstep;         // blocks of the plane step; the J reduction's follow

@@ -46,6 +46,33 @@ __host__ __device__ inline T dot3(T a0, T b0, T a1, T b1, T a2, T b2) {
 }
 
 // ---------------------------------------------------------------------------
+// A displacement of u cells on a periodic axis of n nodes, reduced to one period and split into
+// the node it is taken from (half = 0: the node below it; 1/2: the nearest) and the rest.  f is
+// in [0, n] for every u: also where u is so large that n floor(u / n) is rounded (from 2^53 cells
+// on, rays along the plane or a tiny period) or not finite, when the place has no meaning left
+// but is read all the same.
+// ---------------------------------------------------------------------------
+struct CellShift {
+  int f;
+  double t;
+};
+
+__host__ __device__ inline CellShift cell_shift(double u, int n, double half) {
+  // to one period first, so the integer shift stays in range
+  u -= n * floor(u / n);
+  const double f = floor(u + half);
+  CellShift s;
+  s.t = u - f;
+  if (f >= 0.0 && f <= n) {
+    s.f = (int)f;
+  } else {
+    const int v = fabs(f) < 2147483647.0 ? (int)f % n : 0;
+    s.f = v < 0 ? v + n : v;
+  }
+  return s;
+}
+
+// ---------------------------------------------------------------------------
 // Coefficients of Eq. fsbez (Sect. 3.3):
 //   e = exp(-tau), psi'_M, psi'_O (linear K'I), omega_M, omega_O, omega_C
 //   (quadratic Bezier source function with control point c_M).

@@ -178,3 +178,26 @@ def test_sources_of_steep_and_thick_steps(hm, prec):
                     S = np.array([SM, SO, SM + part * (SO - SM)]).astype(ty)
                     want = sum(c * np.longdouble(v) for c, v in zip(w, S))
                     assert abs(np.longdouble(fn(tau, *S)) - want) <= 44 * ulp * want, (tau, S)
+
+
+@pytest.mark.parametrize("half", [0.0, 0.5])
+def test_cell_shift_stays_on_the_axis(hm, half):
+    """Node offsets in [0, n], which the kernels add to an index and wrap once, for every
+    displacement: within reach, at and around whole periods, beyond 2^53 cells, where the period
+    cannot be taken off exactly, and not finite."""
+    hm.hm_cell_shift.argtypes = [C.c_double, C.c_int, C.c_double, C.POINTER(C.c_double)]
+    t = C.c_double()
+    rng = np.random.default_rng(21)
+    for n in (1, 2, 3, 7, 64, 250, 4093):
+        near = [k * n * (1 + d * 2.0**-52) for k in (-9, -1, 0, 1, 2, 17, 1023) for d in (-1, 0, 1)]
+        far = [s * 10.0**e for s in (-1, 1, -1.7, 1.3) for e in range(14, 308, 7)]
+        inside = (list(rng.uniform(-20 * n, 20 * n, 300)) +
+                  [k + d for k in range(-2, 3) for d in (-0.5, 0.0, 0.5)])
+        for u in near + far + inside + [np.inf, -np.inf, np.nan]:
+            f = hm.hm_cell_shift(u, n, half, C.byref(t))
+            assert 0 <= f <= n, (u, n, f)
+            if abs(u) < 1e6:
+                # the place itself, up to the rounding of the reduced displacement
+                off = (f + t.value - u) / n
+                assert abs(off - round(off)) * n <= 4e-16 * (abs(u) + n), (u, n, f, t.value)
+                assert -half <= t.value <= 1 - half
