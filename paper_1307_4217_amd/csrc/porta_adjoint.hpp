@@ -42,8 +42,9 @@ struct AdjArgs {
                        // (partials of one node, ray and chunk of frequencies, formed in FP64,
                        // stored in the sweep precision; the gather sums them in FP64)
   size_t N;
-  int nx, ny, np, nfreq;
+  int nx, ny;
   int nz;              // of the geometry table (layer_geom)
+  int np, nfreq;
   int ntile;           // tiles of blockDim.x nodes in a plane
   int nchunk, fchunk;  // frequency chunks, as in the sweep's plane step
   int kO, kM, kP;
@@ -122,8 +123,9 @@ struct TGatherArgs {
   const T* lam_next;   // adjoint of I_M at the nodes of plane kO + 1, same layout
   T* out;              // adjoint of I at the nodes of plane kO, same layout
   const RayGeom* geom;
-  int nx, ny, np, nfreq;
+  int nx, ny;
   int nz;              // of the geometry table (layer_geom)
+  int np, nfreq;
   int nchunk, fchunk;  // frequency chunks of a launch
   int kO, ray0;
 };
@@ -546,8 +548,9 @@ struct GatherArgs {
   const RayGeom* geom;
   double* grad;       // [13][N]: kappa, propmat[6], emis[6]
   size_t N;
-  int nx, ny, np;
+  int nx, ny;
   int nz;             // of the geometry table (layer_geom)
+  int np;
   int kO, kM, kP;
   int ray0, nrb, nchunk;
   const T* kappa;     // the coefficients (MODE 1: the Bezier partials depend on them)
@@ -584,7 +587,7 @@ __global__ void __launch_bounds__(256) k_adjoint_gather(const GatherArgs<T> a) {
     }
   } else if (q < a.np) {
     const int j = q / a.nx, i = q - j * a.nx;
-#pragma unroll(MODE == 0 ? 2 : 1)
+#pragma unroll MODE == 0 ? 2 : 1
     for (int rb = g; rb < a.nrb; rb += G) {
       // M upwind, P downwind, as in the sweep
       const RayGeom& gl = layer_geom(a.geom, a.ray0 + rb, a.nz, a.kO, atM ? a.kM : a.kP, !atM);
