@@ -34,7 +34,7 @@ VALU_PEAK_TLANE = 256 * 4 * 16 * 2.4e9 / 1e12   # unpacked FP32 VALU, lane instr
 # kernels whose rocprofv3 VALU-busy figure shows them bound by the vector ALU rather than
 # by HBM (the 9-point Bezier sweep, 78% busy at 3.2 TB/s; two planes per launch, 85% busy
 # at 4.0 TB/s, counted per plane); the others are reported against HBM
-ALU_BOUND_KERNELS = ("k_sweep_plane<float, 1>", "k_sweep_pair<float>")
+ALU_BOUND_KERNELS = ("k_sweep_plane<float, 1>", "k_sweep_pair<float>", "k_sweep_pair<double>")
 PROFILES = os.path.join(ROOT, "profiles")
 
 
@@ -111,6 +111,53 @@ def sweep_launch_bytes(cfg, nrb, elem, nst=4, pair=False, kept=False):
     updates = nrb * cfg.nfreq * np_
     states = (1.5 if kept else 1.0) if pair else 2.0
     return updates * states * nst * elem + 3 * np_ * 13 * elem + np_ * 10 * 8 * 2, updates
+
+
+def two_planes(sweep, opts):
+    """Whether the library cuts the sweep call into launches of two planes: the call is refused
+    for want of workspace with the bytes that its own cut needs, which hold the partial sums of
+    two planes more than those of the call plane by plane (block=256).  sweep(opts, workspace)
+    makes the call."""
+    import re
+
+    import torch
+    from paper_1307_4217_amd import porta
+    short = torch.empty(16, dtype=torch.uint8)
+
+    def need(o):
+        try:
+            sweep(o, short)
+        except porta.PortaError as e:
+            if e.status != porta.ENOMEM:
+                raise
+            return int(re.search(r"than the (\d+) required", str(e)).group(1))
+        raise RuntimeError("a sweep in 16 bytes of workspace was not refused")
+
+    if opts.block > 0:
+        return False
+    planes = porta.Options.from_buffer_copy(bytes(opts))
+    planes.block = 256
+    return need(opts) > need(planes)
+
+
+def sweep_roofline(kernel, launch_bytes, launch_ms, counters):
+    """The sweep kernel's rate per plane: against HBM, or, where its arithmetic bounds it, the
+    VALU instructions of a launch (committed counters) against the VALU issue peak, with the
+    HBM rate beside it."""
+    gbs = launch_bytes / (launch_ms * 1e-3) / 1e9
+    hbm = {"achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+           "frac": round(gbs / HBM_PEAK_GBS, 4)}
+    c = counters or {}
+    r = {"bound": "hbm", **hbm, "traffic": c.get("traffic_bytes_per_launch"), "kernel": kernel,
+         "valu_busy_pct": c.get("valu_busy_pct"), "launch_ms": round(launch_ms, 4),
+         "bytes_per_launch": launch_bytes}
+    if kernel in ALU_BOUND_KERNELS:
+        insts = c.get("sq_insts_valu_per_dispatch")
+        lane = None if insts is None else insts * 64 / (launch_ms * 1e-3) / 1e12
+        r.update({"bound": "alu", "achieved": None if lane is None else round(lane, 2),
+                  "peak": VALU_PEAK_TLANE, "unit": "T VALU lane-instructions/s",
+                  "frac": None if lane is None else round(lane / VALU_PEAK_TLANE, 4), "hbm": hbm})
+    return r
 
 
 def adjoint_launch_bytes(cfg, nrb, elem):
@@ -503,46 +550,38 @@ def main():
     adj_updates = per_ray_freq * (cfg.nrays // 2) * cfg.nfreq if adj else 0
     value = (fwd_updates + adj_updates) * args.steps / wall
 
-    # every plane of the sweep in one step, by batch: its rays and algorithmic bytes.  At the
-    # default block size the bilinear Stokes sweep takes two planes in a launch; the figures
-    # are per plane.
+    # every plane of the sweep in one step, by batch: its rays, whether its call takes two planes
+    # in a launch (the figures are per plane), and its algorithmic bytes
+    def call_pairs(p, o, ks=(kappa, prop, emis)):
+        return two_planes(lambda opt, w: porta.fs_sweep(
+            hg, *ks, atm.i_bottom, atm.w2, prec=p, interp=interp, jkq=jkq, i_top=itop, opts=opt,
+            workspace=w), o)
+
     if inter:
         shapes = inter.launch_ray_counts()
+        pairs = [call_pairs(prec, o) for o in inter.range_opts]
+        pairs += [call_pairs(prec, inter.down_opts)] * (len(shapes) - len(pairs))
     else:
         shapes = [min(nrb, nh - r) for r in range(0, nh, nrb)] * 2
-    pair = nst == 4 and not args.faces and interp == porta.BILINEAR and args.block == 0
+        pairs = [call_pairs(prec, opts)] * len(shapes)
     launches = (cfg.nz - 1) * len(shapes)
     kept = len(inter.ranges) if inter else 0   # batches of which every plane is kept
     lbytes = (cfg.nz - 1) * sum(sweep_launch_bytes(cfg, n, elem, nst, pair, i < kept)[0]
-                                for i, n in enumerate(shapes)) / launches
+                                for i, (n, pair) in enumerate(zip(shapes, pairs))) / launches
     lupd = fwd_updates / launches
     launch_ms = sweep_ms / launches
-    achieved = lbytes / (launch_ms * 1e-3) / 1e9
     tname = "float" if elem == 4 else "double"
+    # the kernel of most rays
+    most = sum(n for n, pair in zip(shapes, pairs) if pair) * 2 > sum(shapes)
     kname = (f"k_sweep_plane_i<{tname}>" if nst == 1 else
              f"k_sweep_plane_faces<{tname}>" if args.faces else
-             f"k_sweep_pair<{tname}>" if pair else
+             f"k_sweep_pair<{tname}>" if most else
              f"k_sweep_plane<{tname}, {1 if interp == porta.BEZIER2D else 0}>")
     workload = counter_workload(cfg, args.prec, schedule, nrb,
                                 inter.range_rays if inter else 0)
     counters = (measured_counters(kname, workload) if args.block in (0, 256)
                 and args.xcd_remap == -1 and args.faces_chunk == 0 else None)
-    traffic = None if counters is None else counters["traffic_bytes_per_launch"]
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": kname,
-                "valu_busy_pct": None if counters is None else counters.get("valu_busy_pct"),
-                "launch_ms": round(launch_ms, 4), "bytes_per_launch": lbytes,
-                "updates_per_launch": lupd}
-    if kname in ALU_BOUND_KERNELS:
-        # measured VALU-bound: the rate against the VALU issue peak, HBM beside it
-        insts = None if counters is None else counters.get("sq_insts_valu_per_dispatch")
-        lane = None if insts is None else insts * 64 / (launch_ms * 1e-3) / 1e12
-        roofline.update({"bound": "alu", "achieved": None if lane is None else round(lane, 2),
-                         "peak": VALU_PEAK_TLANE, "unit": "T VALU lane-instructions/s",
-                         "frac": None if lane is None else round(lane / VALU_PEAK_TLANE, 4),
-                         "hbm": {"achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4)}})
+    roofline = {**sweep_roofline(kname, lbytes, launch_ms, counters), "updates_per_launch": lupd}
     if adj:
         # the adjoint kernel beside it: its launches carry the ray ranges (or adjoint
         # batches); the calls also hold the gathers of the partials, so this is a floor
@@ -628,26 +667,21 @@ def main():
         extra["fp64_sweep_ms"] = round(ms64, 2)
         extra["fp64_sweep_updates_per_s"] = fwd_updates / (ms64 * 1e-3)
         extra["fp32_over_fp64_rate"] = round(ms64 / sweep_ms, 3)
-        # the FP64 sweep kernel against HBM: its launches (ray batches of `nrb`), their
+        # the FP64 sweep kernel: its launches (ray batches of `nrb`), their
         # algorithmic bytes and, where committed, its counters
         shapes64 = [min(nrb, nh - r) for r in range(0, nh, nrb)] * 2
         n64 = (cfg.nz - 1) * len(shapes64)
-        b64 = (cfg.nz - 1) * sum(sweep_launch_bytes(cfg, n, 8, nst, pair)[0]
+        pair64 = call_pairs(porta.F64, opts, (k64, p64, e64))
+        b64 = (cfg.nz - 1) * sum(sweep_launch_bytes(cfg, n, 8, nst, pair64)[0]
                                  for n in shapes64) / n64
-        a64 = b64 / (ms64 / n64 * 1e-3) / 1e9
         k64name = ("k_sweep_plane_i<double>" if nst == 1 else
                    "k_sweep_plane_faces<double>" if args.faces else
-                   "k_sweep_pair<double>" if pair else
+                   "k_sweep_pair<double>" if pair64 else
                    f"k_sweep_plane<double, {1 if interp == porta.BEZIER2D else 0}>")
         c64 = (measured_counters(k64name, counter_workload(cfg, "f64", "shared", nrb, 0))
                if args.block in (0, 256) and args.xcd_remap == -1 and args.faces_chunk == 0
                else None)
-        extra["fp64_roofline"] = {
-            "bound": "hbm", "kernel": k64name, "achieved": round(a64, 1), "peak": HBM_PEAK_GBS,
-            "unit": "GB/s", "frac": round(a64 / HBM_PEAK_GBS, 4),
-            "traffic": None if c64 is None else c64["traffic_bytes_per_launch"],
-            "valu_busy_pct": None if c64 is None else c64.get("valu_busy_pct"),
-            "launch_ms": round(ms64 / n64, 4), "bytes_per_launch": b64}
+        extra["fp64_roofline"] = sweep_roofline(k64name, b64, ms64 / n64, c64)
         log(f"FP64 sweep {ms64:.1f} ms")
         if adj:
             # One FP64 step of the same schedule: the upward rays in ranges of 4 (every

@@ -127,7 +127,10 @@ typedef struct {
 /* Optional tuning; pass NULL for defaults. */
 typedef struct {
   int32_t ray_batch;        /* rays swept together (0: all of the call's rays in a hemisphere) */
-  int32_t block;            /* threads per block of the sweep kernel (0: 256) */
+  int32_t block;            /* threads per block of the sweep kernel: 64, 128, 192 or 256;
+                               plane by plane.  0 (default): 256, fewer on planes of fewer
+                               nodes, and two planes per launch where that is estimated
+                               to be faster (bilinear Stokes sweeps) */
   int32_t xcd_remap;        /* R > 0: each XCD takes R consecutive tiles per round;
                                0: hardware order; -1: default (8) */
   int32_t control;          /* control point of the source function along a ray:

@@ -255,11 +255,11 @@ bool pair_of(const porta_options* o) {
 // is not spread over as many wavefronts, its tiles have a rim, and its blocks are twice as
 // large.  Times in us: rounds of the chip, times the frequencies and a set-up in units of them,
 // times the time of one.  Measured (rows of both hemispheres where they share launches), pairs
-// and planes, a sweep: FP64 128x128x33, 40 rays, 2, 7, 12 frequencies 6.2 and 4.4, 8.5 and
-// 7.6, 10.5 and 10.4 ms; 256x256x17, 41 frequencies 43.1 and 53.9; shared, 64x64x49, 5, 31, 101
-// frequencies 2.8 and 2.6, 7.0 and 8.1, 18.8 and 24.2; 37x30x45, 80 rays, 31 frequencies
-// (9 tiles for 1110 nodes) 5.4 and 5.0.  FP32 256x256, 40 rays, 9 and 41 frequencies, 33 and 17
-// planes 19.5 and 16.2, 21.6 and 22.5; 256x256x128, 101 frequencies 738 and 845.
+// and planes, a sweep: FP64 128x128x33, 40 rays, 2, 7, 12 frequencies 6.3 and 4.4, 8.5 and
+// 7.6, 10.7 and 10.4 ms; 256x256x17, 41 frequencies 44.1 and 54.0; shared, 64x64x49, 5, 31, 101
+// frequencies 2.8 and 2.5, 7.1 and 8.0, 19.3 and 24.1; 37x30x45, 80 rays, 31 frequencies
+// (9 tiles for 1110 nodes) 5.5 and 5.0.  FP32 256x256, 40 rays, 9 and 41 frequencies, 33 and 17
+// planes 19.3 and 16.2, 21.7 and 22.5; 256x256x128, 101 frequencies 738 and 845.
 bool pair_faster(const porta_grid* g, int prec, int64_t tiles, int64_t rows, int nfreq, int n) {
   const bool f64 = prec == PORTA_F64;
   // the tables of the frequencies and the tiles within 64 KiB of LDS
@@ -492,8 +492,10 @@ size_t sweep_bytes(const porta_grid* g, const porta_quad* q, int prec, const por
   const int nrb = sweep_batch(g, q, o);
   const int rows = std::max(nrb, 2 * std::min(nrb, share_batch(g, q, prec, o)));
   size_t n = 0;
-  for (int r = 1; r <= rows; ++r)
-    n = std::max(n, sweep_layout(g, q, prec, o, plan_rows(g, q, prec, o, std::min(r, nrb), r)).total);
+  for (int r = 1; r <= rows; ++r) {
+    const SweepPlan P = plan_rows(g, q, prec, o, std::min(r, nrb), r);
+    n = std::max(n, sweep_layout(g, q, prec, o, P).total);
+  }
   return n;
 }
 
@@ -1096,8 +1098,8 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
 // ---------------------------------------------------------------------------
 template <class T>
 int forward_plane(const porta_grid* g, const porta_quad* q, const porta_fields* f,
-                  const porta_options* o, int interp, char* ws, const Layout& L, Geometry& geo, int k,
-                  const T* prev, T* next, int ray0, int nrb, int block, hipStream_t st) {
+                  const porta_options* o, int interp, char* ws, const Layout& L, Geometry& geo,
+                  int k, const T* prev, T* next, int ray0, int nrb, int block, hipStream_t st) {
   const int rc = geo.need(ray0, nrb, k, 1, st);
   if (rc) return rc;
   PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L, geo);
@@ -1380,9 +1382,11 @@ int sweep_entry(const porta_grid* grid, const porta_quad* quad, const porta_fiel
     // the cut that fits: the usual one, the plain one, or that with fewer rays in turn, whose
     // window of the rays' geometry takes what is left
     if (L.total > kScratchBytes) {
-      plan = least_plan(grid, plan.nrb);
-      for (; (L = sweep_layout(grid, quad, prec, opts, plan)).total > kScratchBytes && plan.nrb > 1;)
-        plan = least_plan(grid, plan.nrb - 1);
+      int nrb = plan.nrb;
+      do {
+        plan = least_plan(grid, nrb);
+        L = sweep_layout(grid, quad, prec, opts, plan);
+      } while (L.total > kScratchBytes && --nrb > 0);
       if (L.total > kScratchBytes)
         return fail(PORTA_ENOMEM, "this sweep does not fit the static scratch of %zu bytes",
                     kScratchBytes);

@@ -536,10 +536,11 @@ __host__ __device__ inline void kprime_apply(const T e[3], const T r[3], const T
 // in the components perpendicular to r.  (Formed so, and with K' applied to its result, a
 // solve was off by 82 ulp of |x| on average at r = 100 and 770 at r = 1000; this form by 1.1,
 // StokesOp by 0.8, at any r.)  A frequency needs one reciprocal (LorentzFreq) instead of two,
-// shared by the system and its transpose: a Jacobi step on 128x128x96, 80 rays, 41 frequencies
-// takes 4.7 ms less with it than with StokesOp (134.3 and 139.0).  (FP32 stays with StokesOp in the sweep,
-// whose J, accumulated in FP64, would change by the FP32 rounding, 1e-9 of its value, and in
-// the adjoint, which forms the state of the sweep again and takes the same time either way.)
+// shared by the system and its transpose: a Jacobi step on 128x128x96, 160 rays, 41 frequencies
+// takes 4.7 ms less with it than with StokesOp (134.3 and 139.0).  (FP32 stays with StokesOp in
+// the sweep, whose J, accumulated in FP64, would change by the FP32 rounding, 1e-9 of its value,
+// and in the adjoint, which forms the state of the sweep again: 2% at 256x256, 16 rays, where
+// its VALU is 95% busy, no difference at 64x64 and 128x128.)
 template <class T>
 struct LorentzOp {
   T e[3], r[3], X[3];

@@ -90,8 +90,8 @@ struct PairLds {
 };
 
 // Bounded by its arithmetic and LDS reads at 4 wavefronts per SIMD in FP32, 2 in FP64 (the
-// registers of a node's set-up).  A sweep of 256x256x128, 80 rays, 101 frequencies in FP32 takes
-// 738 ms, plane by plane 845; Jacobi steps on 128x128x96, 80 rays, FP64, 131.7 ms and 162.3.
+// registers of a node's set-up).  A sweep of 256x256x128, 160 rays, 101 frequencies in FP32 takes
+// 738 ms, plane by plane 845; one of 128x128x96, 160 rays, 41 frequencies in FP64 133.6 and 161.8.
 template <class T>
 __global__ void __launch_bounds__(kPairThreads)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2, sizeof(T) == 4 ? 4 : 2)))
