@@ -302,6 +302,15 @@ int share_batch(const porta_grid* g, const porta_quad* q, int prec, const porta_
   return (int)std::min<size_t>(kShareBlocks / plane_tiles(g, o), kShareBytes / (4 * state));
 }
 
+// Whether the reduction of J of an FP64 sweep is launches of its own, of kJWideNodes nodes a block
+// (a group of the rays in a wavefront, its constants by scalar loads): the kernels of the plane
+// steps leave it two wavefronts per SIMD, and large planes take several rounds of the chip
+// without it.  Sweeps of 9 planes and 3 frequencies on its own and within the plane steps: 4 rays
+// 160x160 0.34, 0.33 ms; 200x200 0.42, 0.48; 256x256 0.58, 0.74; 400x400 1.39, 1.94; 40 rays
+// 128x128 1.35, 1.25; 160x160 2.02, 1.98; 200x200 2.96, 3.11; 256x256 4.57, 4.99.
+constexpr int kJWide = 36864, kJWideNodes = 64;
+bool jwide(int prec, int np) { return prec == PORTA_F64 && np >= kJWide; }
+
 // The cut for launches of `rows` rays, `nrb` of them in a hemisphere.
 SweepPlan plan_rows(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
                     int nrb, int rows) {
@@ -316,7 +325,8 @@ SweepPlan plan_rows(const porta_grid* g, const porta_quad* q, int prec, const po
   P.window = faces_of(o) ? 0 : geom_window(g, q, nrb);
   P.few = false;
   // (a pair of launches of both hemispheres: kPairBoth)
-  const int64_t jb = (int64_t)jblocks(g->nx * g->ny) * (prec == PORTA_F64 ? 4 : 2);
+  const int np = g->nx * g->ny;
+  const int64_t jb = jwide(prec, np) ? 0 : (int64_t)jblocks(np) * (prec == PORTA_F64 ? 4 : 2);
   P.pair = pair_of(o) && P.window == 0 && (prec == PORTA_F64 || tiles * nrb > kShareBlocks) &&
            fits_launch((int64_t)pair_tiles(g->nx, g->ny) * rows + jb, kPairThreads) &&
            pair_faster(g, prec, tiles, rows, q->nfreq, n);
@@ -712,15 +722,18 @@ int launch_jreduce(double* jkq, const double* jpart, const RayConsts* rays, int 
                    int nchunk, int ns, int np, size_t N, size_t plane_off, double ibound,
                    hipStream_t st) {
   const JJob J = {jpart, rays + ray0, nrb, nchunk, ibound, plane_off};
-  const dim3 blk(256);
-  const size_t lds = jlds_bytes(256, sizeof(T));
-  constexpr int most = int(0xffffffffLL / 256);   // fits_launch
-  for (int first = 0, all = jblocks(np); first < all; first += most) {
-    const dim3 grid(std::min(all - first, most));
-    if (ns == 1)
-      hipLaunchKernelGGL((k_jreduce<1, T>), grid, blk, lds, st, J, jkq, np, N, first);
-    else
-      hipLaunchKernelGGL((k_jreduce<4, T>), grid, blk, lds, st, J, jkq, np, N, first);
+  auto go = [&](auto* kernel, int nodes) {
+    constexpr int most = int(0xffffffffLL / 256);   // fits_launch
+    for (int first = 0, all = jblocks(np, nodes); first < all; first += most)
+      hipLaunchKernelGGL(kernel, dim3(std::min(all - first, most)), dim3(256),
+                         jlds_bytes(256, sizeof(T)), st, J, jkq, np, N, first);
+  };
+  if (sizeof(T) == 8 && np >= kJWide) {
+    if (ns == 1) go(k_jreduce<1, double, kJWideNodes>, kJWideNodes);
+    else go(k_jreduce<4, double, kJWideNodes>, kJWideNodes);
+  } else {
+    if (ns == 1) go(k_jreduce<1, T, kJNodes>, kJNodes);
+    else go(k_jreduce<4, T, kJNodes>, kJNodes);
   }
   return check_launch("jreduce");
 }
@@ -946,6 +959,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
   if (faces_of(o))
     return sweep_faces_impl<T>(g, q, f, o, jkq, itop, ws, P, L, st);
   double* const jbase = reinterpret_cast<double*>(ws + L.jpart);
+  const bool wide = jwide(sizeof(T) == 8 ? PORTA_F64 : PORTA_F32, np);
   const size_t jslot = P.jrows * (ns + 1) * np;   // partial sums of one plane
   int up_lo, up_hi;
   hemi_range(q, o, 0, up_lo, up_hi);
@@ -966,9 +980,10 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
     // states and partial sums of the downward rays follow those of the upward ones
     const size_t soff[2] = {0, (size_t)nr[0] * q->nfreq * np * ns};
     const size_t joff[2] = {0, (size_t)nr[0] * a.nchunk * (ns + 1) * np};
-    // the reduction of J rides on the plane steps (planes of 2^27 nodes: launches of its own,
-    // too many threads for one)
-    const bool fused = jkq && fits_launch((int64_t)a.nstep + 2 * jblocks(np), block);
+    // the reduction of J rides on the plane steps where it pays (and FP32 planes of 2^27 nodes
+    // would have too many threads for a launch)
+    const bool fused =
+        jkq && !wide && fits_launch((int64_t)a.nstep + 2 * jblocks(np), block);
     a.njb = fused ? 2 * jblocks(np) : 0;
     auto reduce = [&](int m, const double* part, int k) -> int {
       if (nr[m] == 0) return PORTA_OK;
@@ -1032,8 +1047,20 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
       A.jp[at[m]][0] = {nullptr, (size_t)kb[m] * np};
       A.njprev[at[m]] = 1;
     }
+    const bool fused = jkq && !wide;
+    auto reduce = [&]() -> int {
+      for (int m = m0; m < m1; ++m)
+        for (int c = 0; c < A.njprev[at[m]]; ++c) {
+          const JPrev& j = A.jp[at[m]][c];
+          const int rc = launch_jreduce<T>(jkq, j.part, rays, m * nh + r0[m], nr[m], 1, ns, np, N,
+                                           j.off, (double)ibound[m], st);
+          if (rc) return rc;
+        }
+      return PORTA_OK;
+    };
     const T* prev[2] = {nullptr, nullptr};
     int step = 1, launch = 0, e;
+    if (jkq && !fused && (e = reduce())) return e;
     if (nz % 2 == 0) {
       for (int m = m0; m < m1; ++m) {
         const int k = kb[m] + up[m];
@@ -1045,19 +1072,20 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
         prev[m] = next;
       }
       set_chunks(a, 1, nr[0] + nr[1]);
-      a.njb = jkq ? 2 * jblocks(np) : 0;
+      a.njb = fused ? 2 * jblocks(np) : 0;
       if ((e = launch_plane<T>(a, ns, interp, block, st))) return e;
+      if (jkq && !fused && (e = reduce())) return e;
       step = 2;
       launch = 1;
     }
     A.ntx = (g->nx + kPairX - 1) / kPairX;
     a.ntile = pair_tiles(g->nx, g->ny);
     a.nstep = a.ntile * (nr[0] + nr[1]);
-    a.njb = jkq ? (kPairBoth<T> ? 4 : 2) * jblocks(np) : 0;
+    a.njb = fused ? (kPairBoth<T> ? 4 : 2) * jblocks(np) : 0;
     a.fchunk = a.nfreq;
     a.nchunk = 1;
     const size_t lds = std::max((size_t)a.nfreq * (sizeof(double) + sizeof(T)),
-                                jkq ? jlds_bytes(kPairGroup, sizeof(T)) : 0);
+                                fused ? jlds_bytes(kPairGroup, sizeof(T)) : 0);
     for (; step < nz; step += 2, ++launch) {
       const int slot = (launch & 1) * 2;
       a.jsame = 0;
@@ -1080,12 +1108,9 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
         A.njprev[at[m]] = 2;
         prev[m] = next[m];
       }
+      if (jkq && !fused && (e = reduce())) return e;
     }
-    for (int m = m0; m < m1 && jkq; ++m)
-      for (int c = 0; c < A.njprev[at[m]]; ++c)
-        if ((e = launch_jreduce<T>(jkq, A.jp[at[m]][c].part, rays, m * nh + r0[m], nr[m], 1, ns, np, N,
-                                   A.jp[at[m]][c].off, (double)ibound[m], st)))
-          return e;
+    if (fused) return reduce();   // the last launch's planes
     return PORTA_OK;
   };
   if (P.pair && interp == PORTA_INTERP_BILINEAR)

@@ -437,7 +437,7 @@ struct HemiArgs {
 // ---------------------------------------------------------------------------
 constexpr int kJNodes = 16;   // consecutive nodes of a block: one 128-byte line of doubles
 constexpr int kJCoefs = 37;   // of a ray: weight and proj[9][4]
-inline int jblocks(int np) { return (np - 1) / kJNodes + 1; }
+inline int jblocks(int np, int nodes = kJNodes) { return (np - 1) / nodes + 1; }
 // LDS for `threads` threads: a slab of threads / kJNodes rays, or ten sums of every thread
 inline size_t jlds_bytes(int threads, size_t elem) {
   return (size_t)(threads / kJNodes) * (elem == 4 ? 5 * kJNodes + kJCoefs : 10 * kJNodes) *
@@ -546,16 +546,20 @@ __device__ inline void jreduce_ordered(const JJob& J, double* __restrict__ jkq, 
 
 // Group g of the threads, (group, node), adds rays g, g + G, ..., and the groups are added
 // through LDS: no barrier between the loads of one ray and the next's, and the projections on
-// all the threads.
-template <int NS>
+// all the threads.  W: nodes of the block.
+template <int NS, int W>
 __device__ inline void jreduce_groups(const JJob& J, double* __restrict__ jkq, size_t N, int np,
                                       int node0, double* lds, int threads) {
   constexpr int NV = NS + 1;
-  const int G = threads / kJNodes;
-  const int g = threadIdx.x / kJNodes, n = threadIdx.x % kJNodes, p = node0 + n;
+  const int G = threads / W;
+  // (a group of whole wavefronts: the same ray for all lanes, its constants by scalar loads)
+  const int g = W < 64 ? (int)threadIdx.x / W
+                       : __builtin_amdgcn_readfirstlane((int)threadIdx.x / W);
+  const int n = threadIdx.x % W, p = node0 + n;
   const bool works = (int)threadIdx.x < threads;
   double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   if (works && p < np) {
+#pragma unroll W < 64 ? 1 : 2
     for (int rb = g; rb < J.nrb; rb += G) {
       double v[NV];
 #pragma unroll
@@ -585,35 +589,35 @@ __device__ inline void jreduce_groups(const JJob& J, double* __restrict__ jkq, s
   }
   if (works) {
 #pragma unroll
-    for (int c = 0; c < 10; ++c) lds[(c * G + g) * kJNodes + n] = acc[c];
+    for (int c = 0; c < 10; ++c) lds[(c * G + g) * W + n] = acc[c];
   }
   __syncthreads();
   if (!works) return;
-  for (int e = threadIdx.x; e < 10 * kJNodes; e += threads) {
-    const int c = e / kJNodes, q = node0 + e % kJNodes;
+  for (int e = threadIdx.x; e < 10 * W; e += threads) {
+    const int c = e / W, q = node0 + e % W;
     double sum = 0.0;
-    for (int k = 0; k < G; ++k) sum += lds[(c * G + k) * kJNodes + e % kJNodes];
+    for (int k = 0; k < G; ++k) sum += lds[(c * G + k) * W + e % W];
     if (q < np) jkq[c * N + J.off + q] += sum;
   }
 }
 
 // Every thread of the block calls it; the first `threads` of them work.  T: precision of the
-// sweep.
-template <int NS, class T>
+// sweep; W: nodes of the block (FP32: kJNodes).
+template <int NS, class T, int W = kJNodes>
 __device__ inline void jreduce_block(const JJob& J, double* __restrict__ jkq, size_t N, int np,
                                      int node0, double* lds, int threads) {
   if constexpr (sizeof(T) == 4)
     jreduce_ordered<NS>(J, jkq, N, np, node0, lds, threads);
   else
-    jreduce_groups<NS>(J, jkq, N, np, node0, lds, threads);
+    jreduce_groups<NS, W>(J, jkq, N, np, node0, lds, threads);
 }
 
-// first: the first block's place among the plane's jblocks.
-template <int NS, class T>
+// first: the first block's place among the plane's blocks of W nodes.
+template <int NS, class T, int W>
 __global__ void __launch_bounds__(256)
     k_jreduce(const JJob J, double* __restrict__ jkq, int np, size_t N, int first) {
   extern __shared__ double s_tab[];
-  jreduce_block<NS, T>(J, jkq, N, np, (first + (int)blockIdx.x) * kJNodes, s_tab, blockDim.x);
+  jreduce_block<NS, T, W>(J, jkq, N, np, (first + (int)blockIdx.x) * W, s_tab, blockDim.x);
 }
 
 // ---------------------------------------------------------------------------

@@ -78,17 +78,18 @@ def test_sharing_is_bounded():
         assert full <= n * state + (9 << 30), n
 
 
-@pytest.mark.parametrize("prec,n", [(porta.F64, 5800), (porta.F32, 8200)])
-def test_planes_beyond_one_launch_go_plane_by_plane(prec, n):
-    """A launch holds fewer than 2^32 threads; a two-plane launch of these planes, with its
-    blocks for J (512 threads for 16 nodes, of four planes or two), would not.  The partial
-    sums of two planes more show where pairs are chosen."""
-    def pairs(n):
+def test_planes_beyond_one_launch_go_plane_by_plane():
+    """A launch holds fewer than 2^32 threads; a two-plane FP32 launch of these planes, with its
+    blocks for J (512 threads for 16 nodes of two planes), would not.  (FP64 planes of that size
+    have J reduced by launches of its own.)  The partial sums of two planes more show where pairs
+    are chosen."""
+    def pairs(n, prec):
         hg = _grid(n, n, 3, 1, 1, 60)
         return (porta.workspace_size(hg, prec, porta.WS_SWEEP)
                 > porta.workspace_size(hg, prec, porta.WS_SWEEP, opts=porta.options(block=256)))
-    assert not pairs(n)
-    assert pairs(n // 2)
+    assert not pairs(8200, porta.F32)
+    assert pairs(4100, porta.F32)
+    assert pairs(8200, porta.F64)
 
 
 def _noalloc(hg, prec, opts=None):
