@@ -1144,12 +1144,21 @@ int forward_plane(const porta_grid* g, const porta_quad* q, const porta_fields* 
 // the bilinear mode 22.0 and 29.3 us at 64x64 nodes, 9.5 and 10.2 us at 37x30, and in the
 // 9-point mode, where a ray costs far more, 37.5 and 23.7 us at 24x24.  Bilinear planes of
 // one node per thread from 24576 nodes: 16 rays in FP32 take 24 and 39 us at 192x176 with and
-// without, 21 and 20 at 128x128.
+// without, 21 and 20 at 128x128.  9-point planes so with few rays, which leave groups of rays
+// idle: adjoints of 8 planes, 4 frequencies, with and without, FP64 128x128, 1 and 2 rays 0.77 and
+// 1.07 ms, 0.91 and 0.97; 200x200, 1, 2 and 4 rays 0.79 and 1.28, 1.15 and 1.59, 1.91 and 2.20;
+// 300x300, 12 rays 11.6 and 12.1, 16 rays alike; FP32 200x200, 1, 2 and 4 rays 0.68 and 1.05, 0.93
+// and 1.22, 1.54 and 1.58; 8 rays 0.92 to 0.98 times as fast.
 template <class T>
 void launch_gather(const GatherArgs<T>& b, bool bez, hipStream_t st) {
-  const dim3 blk(256);
+  const dim3 blk(256), one((b.np + 255) / 256, 4);
   if (!bez && b.nchunk == 1 && b.np >= kCus * 96) {
-    hipLaunchKernelGGL(k_adjoint_gather_wide<T>, dim3((b.np + 255) / 256, 4), blk, 0, st, b);
+    hipLaunchKernelGGL((k_adjoint_gather_wide<T, 0>), one, blk, 0, st, b);
+    return;
+  }
+  if (bez && (b.nrb <= 2 ? b.np >= kCus * 64
+                         : b.nrb <= (sizeof(T) == 8 ? 12 : 4) && b.np >= kCus * 144)) {
+    hipLaunchKernelGGL((k_adjoint_gather_wide<T, 1>), one, blk, 0, st, b);
     return;
   }
   const bool wide = b.np >= kCus * (bez ? 16 : 4);

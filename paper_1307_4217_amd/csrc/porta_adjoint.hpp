@@ -558,6 +558,15 @@ struct GatherArgs {
   const T* emis;
 };
 
+// The coefficient of component c: at M kappa, propmat, emis; at P kappa and emis.
+template <class T>
+__device__ inline const T* gather_field(const GatherArgs<T>& a, bool atM, int c) {
+  return c == 0   ? a.kappa
+         : !atM   ? a.emis + (size_t)(c - 1) * a.N
+         : c < 7  ? a.prop + (size_t)(c - 1) * a.N
+                  : a.emis + (size_t)(c - 7) * a.N;
+}
+
 // A block takes W nodes and, in blockIdx.y, one of the 33 components (13 at O, 13 at M, 7 at
 // P): its threads are (ray group, node), group g gathers rays g, g + G, ..., and the groups
 // are added in order through LDS: the loop over rays is a chain of latencies, which with
@@ -614,12 +623,7 @@ __global__ void __launch_bounds__(256) k_adjoint_gather(const GatherArgs<T> a) {
           prow[d] = wrapi(j - gl.fv + d - 1, a.ny) * a.nx;
           pcol[d] = wrapi(i - gl.fu + d - 1, a.nx);
         }
-        // at M: kappa, propmat, emis; at P: kappa and emis
-        const T* fld = c == 0 ? a.kappa
-                       : !atM ? a.emis + (size_t)(c - 1) * a.N
-                       : c < 7 ? a.prop + (size_t)(c - 1) * a.N
-                               : a.emis + (size_t)(c - 7) * a.N;
-        const T* fb = fld + (size_t)(atM ? a.kM : a.kP) * np;
+        const T* fb = gather_field(a, atM, c) + (size_t)(atM ? a.kM : a.kP) * np;
         double out[1] = {0.0};
         bez9_adjoint_gather<double, 1>(
             wx, wy,
@@ -647,22 +651,24 @@ __global__ void __launch_bounds__(256) k_adjoint_gather(const GatherArgs<T> a) {
   if (q < a.np) a.grad[row * a.N + plane + q] += acc;
 }
 
-// The bilinear gather of planes that fill the chip with one thread per node, each ray in one
-// chunk: a thread takes every ray and a group of components (blockIdx.y: the 13 at O, the 13
-// at M in two halves, the 7 at P), so that a stencil is built once for its components, all
-// its loads are issued together and the next ray's geometry is there.  With one component a
-// thread and planes 256x256, 16 rays 75 us in FP32 and 112 in FP64, so 40 and 90.
-template <class T>
+// The gather of planes that fill the chip with one thread per node: a thread takes every ray and a
+// group of components (blockIdx.y: the 13 at O, the 13 at M in two halves, the 7 at P), so that
+// a stencil is built once for its components.  Bilinear (each ray in one chunk): all loads of a ray
+// are issued together and the next ray's geometry is there.  With one component a thread and
+// planes 256x256, 16 rays 75 us in FP32 and 112 in FP64, so 40 and 90.  (launch_gather has the
+// figures of the 9-point mode.)
+template <class T, int MODE>
 __global__ void __launch_bounds__(256) k_adjoint_gather_wide(const GatherArgs<T> a) {
   const int q = blockIdx.x * 256 + threadIdx.x, part = blockIdx.y;
   if (q >= a.np || (part == 3 && a.kP < 0)) return;
   const size_t np = (size_t)a.np;
+  const int nchunk = MODE == 0 ? 1 : a.nchunk;
   if (part == 0) {
     double acc[13];
 #pragma unroll
     for (int c = 0; c < 13; ++c) acc[c] = 0.0;
-    for (int rb = 0; rb < a.nrb; ++rb) {
-      const T* go = a.g_o + (size_t)rb * 13 * np + q;
+    for (int e = 0; e < a.nrb * nchunk; ++e) {
+      const T* go = a.g_o + (size_t)e * 13 * np + q;
 #pragma unroll
       for (int c = 0; c < 13; ++c) acc[c] += go[c * np];
     }
@@ -677,22 +683,61 @@ __global__ void __launch_bounds__(256) k_adjoint_gather_wide(const GatherArgs<T>
   const int j = q / a.nx, i = q - j * a.nx;
   double acc[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   RayGeom next = layer_geom(a.geom, a.ray0, a.nz, a.kO, k, !atM);
-  for (int rb = 0; rb < a.nrb; ++rb) {
-    const Stencil t = make_tstencil(i, j, a.nx, a.ny, next);
-    next = layer_geom(a.geom, a.ray0 + min(rb + 1, a.nrb - 1), a.nz, a.kO, k, !atM);
-    const T* gb = g + (size_t)rb * ncomp * np;
-    T v[7][4];
+  if constexpr (MODE == 0) {
+    for (int rb = 0; rb < a.nrb; ++rb) {
+      const Stencil t = make_tstencil(i, j, a.nx, a.ny, next);
+      next = layer_geom(a.geom, a.ray0 + min(rb + 1, a.nrb - 1), a.nz, a.kO, k, !atM);
+      const T* gb = g + (size_t)rb * ncomp * np;
+      T v[7][4];
 #pragma unroll
-    for (int c = 0; c < 7; ++c) {
-      const T* h = gb + (c < nc ? c : 0) * np;
-      v[c][0] = h[t.i00];
-      v[c][1] = h[t.i10];
-      v[c][2] = h[t.i01];
-      v[c][3] = h[t.i11];
+      for (int c = 0; c < 7; ++c) {
+        const T* h = gb + (c < nc ? c : 0) * np;
+        v[c][0] = h[t.i00];
+        v[c][1] = h[t.i10];
+        v[c][2] = h[t.i01];
+        v[c][3] = h[t.i11];
+      }
+#pragma unroll
+      for (int c = 0; c < 7; ++c)
+        acc[c] += t.w00 * v[c][0] + t.w10 * v[c][1] + t.w01 * v[c][2] + t.w11 * v[c][3];
     }
+  } else {
+    int rowb[5], coli[5];
 #pragma unroll
-    for (int c = 0; c < 7; ++c)
-      acc[c] += t.w00 * v[c][0] + t.w10 * v[c][1] + t.w01 * v[c][2] + t.w11 * v[c][3];
+    for (int d = 0; d < 5; ++d) {
+      rowb[d] = wrapi(j + d - 2, a.ny) * a.nx;
+      coli[d] = wrapi(i + d - 2, a.nx);
+    }
+    for (int rb = 0; rb < a.nrb; ++rb) {
+      const RayGeom gl = next;
+      next = layer_geom(a.geom, a.ray0 + min(rb + 1, a.nrb - 1), a.nz, a.kO, k, !atM);
+      const BezW<double> wx = bez_weights(gl.tx), wy = bez_weights(gl.ty);
+      int prow[3], pcol[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        prow[d] = wrapi(j - gl.fv + d - 1, a.ny) * a.nx;
+        pcol[d] = wrapi(i - gl.fu + d - 1, a.nx);
+      }
+      const T* gb = g + (size_t)rb * nchunk * ncomp * np;
+#pragma unroll 1
+      for (int c = 0; c < nc; ++c) {
+        const T* fb = gather_field(a, atM, c0 + c) + (size_t)k * np;
+        const T* h = gb + c * np;
+        double out[1] = {0.0};
+        bez9_adjoint_gather<double, 1>(
+            wx, wy,
+            [&](int r, int cc, double v[1]) { v[0] = (double)fb[rowb[r + 2] + coli[cc + 2]]; },
+            [&](int r, int cc, double w[1]) {
+              const T* p = h + prow[r + 1] + pcol[cc + 1];
+              w[0] = (double)p[0];
+              for (int m = 1; m < nchunk; ++m) w[0] += (double)p[(size_t)m * ncomp * np];
+            },
+            out);
+#pragma unroll
+        for (int d = 0; d < 7; ++d)   // (a register array takes no run-time index)
+          if (d == c) acc[d] += out[0];
+      }
+    }
   }
 #pragma unroll
   for (int c = 0; c < 7; ++c) {
