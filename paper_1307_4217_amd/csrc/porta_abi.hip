@@ -307,8 +307,9 @@ int share_batch(const porta_grid* g, const porta_quad* q, int prec, const porta_
 // steps leave it two wavefronts per SIMD, and large planes take several rounds of the chip
 // without it.  Sweeps of 9 planes and 3 frequencies on its own and within the plane steps: 4 rays
 // 160x160 0.34, 0.33 ms; 200x200 0.42, 0.48; 256x256 0.58, 0.74; 400x400 1.39, 1.94; 40 rays
-// 128x128 1.35, 1.25; 160x160 2.02, 1.98; 200x200 2.96, 3.11; 256x256 4.57, 4.99.
-constexpr int kJWide = 36864, kJWideNodes = 64;
+// 128x128 1.35, 1.25; 160x160 2.02, 1.98; 200x200 2.96, 3.11; 256x256 4.57, 4.99; 10 frequencies
+// 128x240, 4, 8, 16 and 40 rays 0.55, 0.55; 0.90, 1.02; 1.69, 1.82; 4.13, 4.31.
+constexpr int kJWide = 30720, kJWideNodes = 64;
 bool jwide(int prec, int np) { return prec == PORTA_F64 && np >= kJWide; }
 
 // The cut for launches of `rows` rays, `nrb` of them in a hemisphere.
