@@ -302,15 +302,22 @@ int share_batch(const porta_grid* g, const porta_quad* q, int prec, const porta_
   return (int)std::min<size_t>(kShareBlocks / plane_tiles(g, o), kShareBytes / (4 * state));
 }
 
-// Whether the reduction of J of an FP64 sweep is launches of its own, of kJWideNodes nodes a block
-// (a group of the rays in a wavefront, its constants by scalar loads): the kernels of the plane
-// steps leave it two wavefronts per SIMD, and large planes take several rounds of the chip
-// without it.  Sweeps of 9 planes and 3 frequencies on its own and within the plane steps: 4 rays
-// 160x160 0.34, 0.33 ms; 200x200 0.42, 0.48; 256x256 0.58, 0.74; 400x400 1.39, 1.94; 40 rays
-// 128x128 1.35, 1.25; 160x160 2.02, 1.98; 200x200 2.96, 3.11; 256x256 4.57, 4.99; 10 frequencies
-// 128x240, 4, 8, 16 and 40 rays 0.55, 0.55; 0.90, 1.02; 1.69, 1.82; 4.13, 4.31.
+// Whether the reduction of J is launches of its own, kJWideNodes nodes a block (FP64: a group of
+// the rays in a wavefront, its constants by scalar loads; FP32, in order: a node a thread): the
+// kernels of the plane steps leave it two wavefronts per SIMD, and large planes take several
+// rounds of the chip without it.  Sweeps of 9 planes on its own and within the plane steps: FP64,
+// 3 frequencies, 4 rays 160x160 0.34, 0.33 ms; 200x200 0.42, 0.48; 256x256 0.58, 0.74; 400x400
+// 1.39, 1.94; 40 rays 128x128 1.35, 1.25; 160x160 2.02, 1.98; 200x200 2.96, 3.11; 256x256 4.57,
+// 4.99; 10 frequencies 128x240, 4, 8, 16 and 40 rays 0.55, 0.55; 0.90, 1.02; 1.69, 1.82; 4.13, 4.31.
+// FP32, 4 frequencies, 2, 4 and 16 rays 200x200 0.25, 0.24; 0.39, 0.31; 1.10, 0.82; 256x256 0.30,
+// 0.36; 0.47, 0.46; 1.40, 1.24; 300x300 0.37, 0.47; 0.60, 0.63; 1.87, 1.78; 400x400 0.56, 0.84; 0.97,
+// 1.18; 2.96, 3.22; 1000x1024 3.10, 5.99; 5.22, 7.88; 18.1, 21.1; 3 rays 256x256 0.37, 0.41; 6 rays
+// 300x300 0.84, 0.86.
 constexpr int kJWide = 30720, kJWideNodes = 64;
-bool jwide(int prec, int np) { return prec == PORTA_F64 && np >= kJWide; }
+bool jwide(int prec, int np, int nrb) {
+  if (prec == PORTA_F64) return np >= kJWide;
+  return np >= (nrb <= 3 ? 65536 : nrb <= 6 ? 81920 : 131072);
+}
 
 // The cut for launches of `rows` rays, `nrb` of them in a hemisphere.
 SweepPlan plan_rows(const porta_grid* g, const porta_quad* q, int prec, const porta_options* o,
@@ -327,7 +334,7 @@ SweepPlan plan_rows(const porta_grid* g, const porta_quad* q, int prec, const po
   P.few = false;
   // (a pair of launches of both hemispheres: kPairBoth)
   const int np = g->nx * g->ny;
-  const int64_t jb = jwide(prec, np) ? 0 : (int64_t)jblocks(np) * (prec == PORTA_F64 ? 4 : 2);
+  const int64_t jb = jwide(prec, np, nrb) ? 0 : (int64_t)jblocks(np) * (prec == PORTA_F64 ? 4 : 2);
   P.pair = pair_of(o) && P.window == 0 && (prec == PORTA_F64 || tiles * nrb > kShareBlocks) &&
            fits_launch((int64_t)pair_tiles(g->nx, g->ny) * rows + jb, kPairThreads) &&
            pair_faster(g, prec, tiles, rows, q->nfreq, n);
@@ -723,18 +730,19 @@ int launch_jreduce(double* jkq, const double* jpart, const RayConsts* rays, int 
                    int nchunk, int ns, int np, size_t N, size_t plane_off, double ibound,
                    hipStream_t st) {
   const JJob J = {jpart, rays + ray0, nrb, nchunk, ibound, plane_off};
-  auto go = [&](auto* kernel, int nodes) {
+  auto go = [&](auto* kernel, int nodes, int threads) {
     constexpr int most = int(0xffffffffLL / 256);   // fits_launch
     for (int first = 0, all = jblocks(np, nodes); first < all; first += most)
-      hipLaunchKernelGGL(kernel, dim3(std::min(all - first, most)), dim3(256),
-                         jlds_bytes(256, sizeof(T)), st, J, jkq, np, N, first);
+      hipLaunchKernelGGL(kernel, dim3(std::min(all - first, most)), dim3(threads),
+                         jlds_bytes(threads, sizeof(T)), st, J, jkq, np, N, first);
   };
-  if (sizeof(T) == 8 && np >= kJWide) {
-    if (ns == 1) go(k_jreduce<1, double, kJWideNodes>, kJWideNodes);
-    else go(k_jreduce<4, double, kJWideNodes>, kJWideNodes);
+  if (jwide(sizeof(T) == 8 ? PORTA_F64 : PORTA_F32, np, nrb)) {
+    const int threads = sizeof(T) == 8 ? 256 : kJWideNodes;
+    if (ns == 1) go(k_jreduce<1, T, kJWideNodes>, kJWideNodes, threads);
+    else go(k_jreduce<4, T, kJWideNodes>, kJWideNodes, threads);
   } else {
-    if (ns == 1) go(k_jreduce<1, T, kJNodes>, kJNodes);
-    else go(k_jreduce<4, T, kJNodes>, kJNodes);
+    if (ns == 1) go(k_jreduce<1, T, kJNodes>, kJNodes, 256);
+    else go(k_jreduce<4, T, kJNodes>, kJNodes, 256);
   }
   return check_launch("jreduce");
 }
@@ -960,7 +968,9 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
   if (faces_of(o))
     return sweep_faces_impl<T>(g, q, f, o, jkq, itop, ws, P, L, st);
   double* const jbase = reinterpret_cast<double*>(ws + L.jpart);
-  const bool wide = jwide(sizeof(T) == 8 ? PORTA_F64 : PORTA_F32, np);
+  auto wide = [&](const int nr[2]) {
+    return jwide(sizeof(T) == 8 ? PORTA_F64 : PORTA_F32, np, std::max(nr[0], nr[1]));
+  };
   const size_t jslot = P.jrows * (ns + 1) * np;   // partial sums of one plane
   int up_lo, up_hi;
   hemi_range(q, o, 0, up_lo, up_hi);
@@ -984,7 +994,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
     // the reduction of J rides on the plane steps where it pays (and FP32 planes of 2^27 nodes
     // would have too many threads for a launch)
     const bool fused =
-        jkq && !wide && fits_launch((int64_t)a.nstep + 2 * jblocks(np), block);
+        jkq && !wide(nr) && fits_launch((int64_t)a.nstep + 2 * jblocks(np), block);
     a.njb = fused ? 2 * jblocks(np) : 0;
     auto reduce = [&](int m, const double* part, int k) -> int {
       if (nr[m] == 0) return PORTA_OK;
@@ -1048,7 +1058,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
       A.jp[at[m]][0] = {nullptr, (size_t)kb[m] * np};
       A.njprev[at[m]] = 1;
     }
-    const bool fused = jkq && !wide;
+    const bool fused = jkq && !wide(nr);
     auto reduce = [&]() -> int {
       for (int m = m0; m < m1; ++m)
         for (int c = 0; c < A.njprev[at[m]]; ++c) {

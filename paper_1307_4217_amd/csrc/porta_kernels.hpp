@@ -430,6 +430,7 @@ struct HemiArgs {
 //   some of them by 6e-8.  The threads, as (ray of a slab, node), load the slab's partial sums
 //   and the rays' coefficients into LDS, and then, as (component, node), add its rays in
 //   order, while the next slab's loads are under way.
+//   Planes that have launches for it: a node a thread (jreduce_serial).
 // (FP64 in the second split: 16x16x32 and 80 rays, 537 us a sweep instead of 459; 64x64x49
 // multigrid cycles 54.6 ms instead of 54.0.)
 // On the boundary plane the Stokes vector is (ibound, 0, 0, 0) at every frequency.  NS: Stokes
@@ -601,13 +602,54 @@ __device__ inline void jreduce_groups(const JJob& J, double* __restrict__ jkq, s
   }
 }
 
+// Thread per node: few rays in order, on planes whose nodes fill the chip.  The sums of
+// jreduce_ordered, operation by operation.
+template <int NS>
+__device__ inline void jreduce_serial(const JJob& J, double* __restrict__ jkq, size_t N, int np,
+                                      int p) {
+  constexpr int NV = NS + 1;
+  if (p >= np) return;
+  double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 4
+  for (int rb = 0; rb < J.nrb; ++rb) {
+    double v[NV];
+#pragma unroll
+    for (int s = 0; s < NV; ++s) v[s] = 0.0;
+    if (!J.part) {
+      v[0] = J.ibound;
+    } else {
+      const double* jp = J.part + (size_t)rb * NV * np + p;   // one chunk
+#pragma unroll
+      for (int s = 0; s < NV; ++s) v[s] = jp[s * (size_t)np];
+    }
+    const RayConsts& rc = J.rays[rb];
+    const double w = rc.weight;
+#pragma unroll
+    for (int c = 0; c < 9; ++c) {
+      double x;
+      if constexpr (NS == 4) {
+        x = dot3(rc.proj[c][1], v[1], rc.proj[c][0], v[0], rc.proj[c][2], v[2]);
+        x = fma_t(rc.proj[c][3], v[3], x);
+      } else {
+        x = rc.proj[c][0] * v[0];
+      }
+      acc[c] = fma_t(w, x, acc[c]);
+    }
+    acc[9] = fma_t(w, v[NS], acc[9]);
+  }
+#pragma unroll
+  for (int c = 0; c < 10; ++c) jkq[c * N + J.off + p] += acc[c];
+}
+
 // Every thread of the block calls it; the first `threads` of them work.  T: precision of the
-// sweep; W: nodes of the block (FP32: kJNodes).
+// sweep; W: nodes of the block (FP32: kJNodes, or a node a thread).
 template <int NS, class T, int W = kJNodes>
 __device__ inline void jreduce_block(const JJob& J, double* __restrict__ jkq, size_t N, int np,
                                      int node0, double* lds, int threads) {
-  if constexpr (sizeof(T) == 4)
+  if constexpr (sizeof(T) == 4 && W == kJNodes)
     jreduce_ordered<NS>(J, jkq, N, np, node0, lds, threads);
+  else if constexpr (sizeof(T) == 4)
+    jreduce_serial<NS>(J, jkq, N, np, node0 + (int)threadIdx.x);
   else
     jreduce_groups<NS, W>(J, jkq, N, np, node0, lds, threads);
 }
