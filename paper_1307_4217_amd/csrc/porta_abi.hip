@@ -991,8 +991,7 @@ int sweep_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f, 
     // states and partial sums of the downward rays follow those of the upward ones
     const size_t soff[2] = {0, (size_t)nr[0] * q->nfreq * np * ns};
     const size_t joff[2] = {0, (size_t)nr[0] * a.nchunk * (ns + 1) * np};
-    // the reduction of J rides on the plane steps where it pays (and FP32 planes of 2^27 nodes
-    // would have too many threads for a launch)
+    // the reduction of J rides on the plane steps where it pays
     const bool fused =
         jkq && !wide(nr) && fits_launch((int64_t)a.nstep + 2 * jblocks(np), block);
     a.njb = fused ? 2 * jblocks(np) : 0;

@@ -79,17 +79,17 @@ def test_sharing_is_bounded():
 
 
 def test_planes_beyond_one_launch_go_plane_by_plane():
-    """A launch holds fewer than 2^32 threads; a two-plane FP32 launch of these planes, with its
-    blocks for J (512 threads for 16 nodes of two planes), would not.  (FP64 planes of that size
-    have J reduced by launches of its own.)  The partial sums of two planes more show where pairs
-    are chosen."""
-    def pairs(n, prec):
-        hg = _grid(n, n, 3, 1, 1, 60)
+    """A launch holds fewer than 2^32 threads (J of planes of that size is reduced by launches of its
+    own).  The partial sums of two planes more show where pairs are chosen."""
+    def pairs(n, prec, nmu=1, nchi=1):
+        hg = _grid(n, n, 3, nmu, nchi, 60)
         return (porta.workspace_size(hg, prec, porta.WS_SWEEP)
                 > porta.workspace_size(hg, prec, porta.WS_SWEEP, opts=porta.options(block=256)))
-    assert not pairs(8200, porta.F32)
-    assert pairs(4100, porta.F32)
-    assert pairs(8200, porta.F64)
+    for prec in (porta.F32, porta.F64):
+        assert not pairs(46000, prec)
+        assert not pairs(16000, prec, 2, 8)
+        assert pairs(8200, prec)
+        assert pairs(16000, prec)
 
 
 def _noalloc(hg, prec, opts=None):
