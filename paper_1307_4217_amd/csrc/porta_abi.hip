@@ -206,22 +206,40 @@ int64_t plane_tiles(const porta_grid* g, const porta_options* o) {
 // 22.5, 16.5, 15.8, 19.1, 18.3 us; FP32 32x32, 24 rays (96 blocks), 41 frequencies: 25.4,
 // 17.3, 19.2, 18.6, 19.5; FP64 32x32, 80 rays (320 blocks): 43.2, 43.0, 45.9, 51.7, 61.1;
 // FP64 64x64, 80 rays (1280 blocks): 213, 231, 250, 279, 319.
-int freq_chunks(int64_t blocks, int nfreq) {
+// least: the part of the time of one chunk, 1/least, that chunks have to save (0: any).
+int freq_chunks(int64_t blocks, int nfreq, int64_t least = 0) {
   constexpr int64_t kSetup = 6, kMaxChunks = 32;
   int best = 1;
-  int64_t cost = 0;
+  int64_t cost = 0, one = 0;
   for (int n = 1; n <= std::min<int64_t>(nfreq, kMaxChunks); ++n) {
     // no n from here on costs less than its share of the chip, without the rounding up
     if (n > 1 && (kSetup * n + nfreq) * blocks >= cost * kCus) break;
     const int64_t per = (nfreq + n - 1) / n;
     if (n > 1 && per == (nfreq + n - 2) / (n - 1)) continue;   // no shorter chunk than n - 1
     const int64_t c = (kSetup + per) * ((blocks * n + kCus - 1) / kCus);
+    if (n == 1) one = c;
     if (n == 1 || c < cost) {
       best = n;
       cost = c;
     }
   }
-  return best;
+  return least > 0 && (one - cost) * least < one ? 1 : best;
+}
+
+// Chunks of the launches of an adjoint, whose partials the gather reads chunk by chunk.  They have
+// to save 1/8 unless they stay long and, in FP32 and the 9-point mode, a chunk's blocks have CUs
+// to themselves.  Adjoints of 9 planes with chunks by the cost alone and so: bilinear FP32
+// 101x71, 4 rays, 3 frequencies 0.281, 0.260 ms; 236x307, 3 rays, 50 frequencies 2.41, 2.14; FP64
+// 206x205, 1 ray, 24 frequencies 0.827, 0.751; 9-point FP32 142x156, 4 rays, 17 frequencies 2.11,
+// 1.76; 190x263, 2 rays, 111 frequencies 7.23, 6.30; FP64 131x137, 6 rays, 69 frequencies 9.92,
+// 9.19.  Those that stay by the cost alone, with chunks and without: bilinear FP64 121x183, 12 rays,
+// 113 frequencies 12.2, 12.8; 162x136, 6 rays, 40 frequencies 2.80, 2.94; FP32 48x62, 12 rays, 29
+// frequencies 0.43, 0.48; 9-point FP32 60x70, 12 rays, 127 frequencies 5.82, 6.26.
+template <class T>
+int adjoint_chunks(int64_t blocks, int nfreq, int interp) {
+  const bool bil = interp == PORTA_INTERP_BILINEAR;
+  const bool any = nfreq >= (bil ? 25 : 80) && (blocks < kCus || (bil && sizeof(T) == 8));
+  return freq_chunks(blocks, nfreq, any ? 0 : 8);
 }
 
 // The cut of a sweep: whether the two hemispheres' batches share launches, and the
@@ -1138,7 +1156,7 @@ int forward_plane(const porta_grid* g, const porta_quad* q, const porta_fields* 
   const int rc = geo.need(ray0, nrb, k, 1, st);
   if (rc) return rc;
   PlaneArgs<T> a = plane_args<T>(g, q, f, o, ws, L, geo);
-  set_chunks(a, freq_chunks((int64_t)a.ntile * nrb, q->nfreq), nrb);
+  set_chunks(a, adjoint_chunks<T>((int64_t)a.ntile * nrb, q->nfreq, interp), nrb);
   HemiArgs<T>& h = a.h[0];
   set_plane(h, g, k, 1);
   h.iprev = prev;
@@ -1220,7 +1238,7 @@ int adjoint_impl(const porta_grid* g, const porta_quad* q, const porta_fields* f
   for (r0 = up_lo; r0 < up_hi; r0 += nrb_max) {
     const int nrb = std::min(nrb_max, up_hi - r0);
     // the workspace has room for the chunks of a full batch
-    const int want = std::min(freq_chunks((int64_t)ntile * nrb, q->nfreq),
+    const int want = std::min(adjoint_chunks<T>((int64_t)ntile * nrb, q->nfreq, interp),
                               nrb_max * freq_chunks((int64_t)ntile * nrb_max, q->nfreq) / nrb);
     const int fchunk = (q->nfreq + want - 1) / want, nchunk = (q->nfreq + fchunk - 1) / fchunk;
     const dim3 agrid((unsigned)(ntile * nrb * nchunk));
